@@ -78,7 +78,9 @@ enum { RINR_FIT_KERNEL_FP32 = 0,        /* rinr_fit_kernel_family: fp32 operands
                                            three terms per product, fp32 accumulate (~22 significant bits per product)       */
 
 /* Device state for fitting n_images models of one architecture to H x W targets (Eq. 1): parameters, Adam moments, keep
- * flags, per-image losses (3 * 4 + 1 bytes per parameter).  All images share the architecture; each has its own parameters.
+ * flags, per-image losses (3 * 4 + 1 bytes per parameter), and, where the images are too few to fill the GPU one by one,
+ * partial gradients of several workgroups per image (at most 4 bytes per parameter for 8 workgroups per compute-unit slot).
+ * All images share the architecture; each has its own parameters.
  * Two families of kernels compute the same step.  The split-precision ones (the default where they are built for the
  * shape) keep the weights of all layers in one CU's LDS as fp16 hi/lo planes and the pre-activations of 16 pixels per
  * wavefront in registers: widest hidden layer <= 32: 12 linear layers, <= 48: 10, <= 64: 6.  The fp32 ones keep fp32 weights
@@ -111,7 +113,8 @@ int rinr_fit_reset_optimizer(rinr_fit *fit);
 int rinr_fit_get_params(const rinr_fit *fit, float *params, void *stream);
 
 /* n_steps full-batch steps (every pixel of every image each step) on `stream`: one kernel per
- * step, one workgroup per image, nothing allocated, no synchronisation.  targets: device,
+ * step, one workgroup per image (few images: several per image and a second, small kernel that adds their gradients up
+ * in a fixed order), nothing allocated, no synchronisation.  targets: device,
  * float[n_images][3][H][W], 4-byte aligned, values on the 0..1 scale of the decoded image. */
 int rinr_fit_steps(rinr_fit *fit, const float *targets, int32_t n_steps, const rinr_fit_opts *opts, void *stream);
 

@@ -127,8 +127,9 @@ __global__ __launch_bounds__(Shape<WP>::NTHREADS, (Shape<WP>::NW <= 4 && ML <= 4
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, n = lane & 15, g = lane >> 4;
-    const size_t img = blockIdx.x;
-    float *P = a.params + img * a.n_params;
+    const FitShare share = fit_share(a, (a.HW + kPC - 1) / kPC);
+    const size_t img = share.img;
+    const float *P = a.params + img * a.n_params;
     const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
     const float neg1 = a.neg1;
     const int L0 = a.L;
@@ -203,8 +204,7 @@ __global__ __launch_bounds__(Shape<WP>::NTHREADS, (Shape<WP>::NW <= 4 && ML <= 4
     float loss_part = 0.0f;
 
     const int pc = wave * 16 + n;                                  // this lane's pixel within the chunk
-    const uint32_t nchunks = (a.HW + kPC - 1) / kPC;
-    for (uint32_t c = 0; c < nchunks; ++c) {
+    for (uint32_t c = share.c0; c < share.c1; ++c) {
         int L = a.L;
         asm volatile("" : "+s"(L));       // read afresh per chunk: keeps the unrolled layers' conditions out of long-lived lane masks
         uint32_t p = c * kPC + (uint32_t)pc;
@@ -402,14 +402,10 @@ __global__ __launch_bounds__(Shape<WP>::NTHREADS, (Shape<WP>::NW <= 4 && ML <= 4
     if (tid == 0) {
         float s = 0.0f;
         for (int w = 0; w < kWaves; ++w) s += red[w];
-        a.loss[img] = a.loss_scale * s;
-        if (a.emag && !a.grad_out) a.emag[img] = sqrtf(s / (3.0f * (float)a.HW));
+        fit_put_loss(a, share, s);
     }
 
-    // ---- every gradient entry is in exactly one lane: Adam in place (or hand the gradient out)
-    float *M = a.m + img * a.n_params, *V = a.v + img * a.n_params;
-    const uint8_t *K = a.keep ? a.keep + img * a.n_params : nullptr;
-    float *G = a.grad_out ? a.grad_out + img * a.n_params : nullptr;
+    // ---- every gradient entry is in exactly one lane: Adam in place, or the entry handed out
 #pragma unroll
     for (int lg = ML - 1; lg >= 0; lg -= PL) {
         int rot = 0;
@@ -432,21 +428,7 @@ __global__ __launch_bounds__(Shape<WP>::NTHREADS, (Shape<WP>::NW <= 4 && ML <= 4
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
                             const int at = param_index<WP>(a, l, ot * 16 + 4 * g + v, it * 16 + n);
-                            if (at >= 0) {
-                                const bool kept = !K || K[at];
-                                const float gr = kept ? acc[l][s][v] * gs : 0.0f;
-                                if (G) {
-                                    G[at] = gr;
-                                } else if (kept) {
-                                    const float mm = a.b1 * M[at] + (1.0f - a.b1) * gr;
-                                    const float vv = a.b2 * V[at] + (1.0f - a.b2) * gr * gr;
-                                    M[at] = mm;
-                                    V[at] = vv;
-                                    P[at] -= a.lr * (mm * a.c1inv) / (sqrtf(vv * a.c2inv) + a.eps);
-                                } else {
-                                    P[at] = 0.0f;
-                                }
-                            }
+                            if (at >= 0) fit_put_grad(a, share, at, acc[l][s][v] * gs);
                         }
                     }
                 }

@@ -84,6 +84,35 @@ def test_loss_and_gradient(name, masked, family):
 
 
 @pytest.mark.parametrize("family", list(FAMILIES))
+@pytest.mark.parametrize("widths,n,H,W", [([2, 15, 15, 3], 40000, 7, 9), ([2, 40, 40, 3], 4200, 9, 15), ([2, 30, 3], 20000, 5, 26)])
+def test_many_images_and_few_agree_with_the_oracle(widths, n, H, W, family):
+    """With many images a workgroup takes a whole image and updates it itself; with few, workgroups share an image's pixels
+    and a second launch adds their gradients up.  The same image through both: gradient against the oracle, one Adam step."""
+    import torch
+    few = 3
+    p0 = synth.init_params(3, widths, few)
+    tgt, tgt_d = targets_of(5, few, H, W)
+    got = {}
+    for m in (few, n):
+        f = rinr_fit.Fit(widths, m, H, W, fp32=FAMILIES[family])
+        f.set_params(np.tile(p0, ((m + few - 1) // few, 1))[:m])
+        t = tgt_d.repeat((m + few - 1) // few, 1, 1, 1)[:m].contiguous()
+        loss, grad = f.loss_grad(t)
+        f.steps(t, 1, 5e-4)
+        got[m] = loss[-few:], grad[-few:], f.get_params()[-few:], f.last_loss()[-few:]
+        f.close()
+    order = [(n - few + i) % few for i in range(few)]                 # which image the last slots of the big batch hold
+    for i in range(few):
+        want_loss, want_g = fo.loss_grad(widths, p0[order[i]].astype(np.float64), tgt[order[i]], None)
+        for m, k in ((few, order[i]), (n, i)):
+            loss, grad, params, last = got[m]
+            assert abs(loss[k] - want_loss) <= 2e-5 * want_loss and last[k] == loss[k]
+            assert np.abs(grad[k] - want_g).max() <= 2e-5 * np.abs(want_g).max()
+            clear = np.abs(grad[k]) > 1e-4 * np.abs(grad[k]).max()    # the first Adam step is lr in the gradient's direction
+            np.testing.assert_allclose((p0[order[i]] - params[k])[clear], 5e-4 * np.sign(want_g[clear]), rtol=1e-3, atol=1e-7)
+
+
+@pytest.mark.parametrize("family", list(FAMILIES))
 @pytest.mark.parametrize("name", ["cifar 3x15 @32x32", "mini-imagenet 10x40 ragged", "tapered"])
 def test_adam_steps_follow_the_oracle(name, family):
     widths, H, W = ARCHS[name]
