@@ -115,6 +115,7 @@ struct FitArgs {
     int32_t splits;               // workgroups per image
     int64_t n_params;
     uint32_t HW, W;
+    uint32_t wmagic, wshift;      // p / W == umulhi(p, wmagic) >> wshift for p < 2^31; wmagic == 0 means W == 1
     float inv2W, inv2H, lo, span, w0rev;        // w0rev = w0 / 2pi
     float loss_scale;
     float neg1;                   // -1, as data: keeps x - float(half) a single mixed-precision fma in the split kernels
@@ -485,30 +486,29 @@ int lds_floats(int wq, int L) {
 
 
 // ---- the split-precision kernels (rinr_fit16.hip.h): built per hidden width rounded up to a multiple of 16 and per depth bucket
-constexpr int fit16_depth_lo(int wp) { return wp == 16 ? 4 : 6; }
-constexpr int fit16_depth_hi(int wp) { return wp <= 32 ? kMaxL : (wp == 48 ? 10 : 6); }
-// Plane sets: two layers per pair of barriers where LDS holds two sets of pixel planes (padded widths 16 and 32), else one.
-template <int WP, int PL> fit_fn kernel16_of(int L) {
-    if (L <= fit16_depth_lo(WP)) return fit16::fit16_step_kernel<WP, fit16_depth_lo(WP), PL>;
-    return fit16::fit16_step_kernel<WP, fit16_depth_hi(WP), PL>;
+constexpr int fit16_depth(int wp) { return wp <= 32 ? kMaxL : (wp == 48 ? 10 : 6); }
+// 16-pixel tiles a wavefront takes at a time: one where that leaves registers for a second wavefront per SIMD and two do not,
+// else two where the registers hold them (a lone wavefront has only its own two tiles to fill the gaps between dependent instructions).
+constexpr int fit16_tiles(int wp, int ml) {
+    const int one = fit16::fit16_waves_per_simd(wp, ml, 1), two = fit16::fit16_waves_per_simd(wp, ml, 2);
+    return (one > 1 && two == 1) || fit16::fit16_registers(wp, ml, 2) > 512 ? 1 : 2;
 }
-fit_fn kernel16_for(int wp, int L, int pl) {
-    switch (wp) {
-        case 16: return pl == 2 ? kernel16_of<16, 2>(L) : kernel16_of<16, 1>(L);
-        case 32: return pl == 2 ? kernel16_of<32, 2>(L) : kernel16_of<32, 1>(L);
-        case 48: return kernel16_of<48, 1>(L);
-        default: return kernel16_of<64, 1>(L);
-    }
+struct Fit16 { fit_fn fn; uint32_t lds; int pixels; };      // kernel, LDS bytes, pixels a workgroup takes at a time
+template <int WP, int ML> Fit16 kernel16(int L) {
+    constexpr int nt = fit16_tiles(WP, ML);
+    return Fit16{fit16::fit16_step_kernel<WP, ML, nt>, fit16::Shape<WP>::total(L), fit16::kThreads / 4 * nt};
 }
-// LDS bytes of a model of L linear layers at padded width wp with pl plane sets, or 0 if no split kernel is built that deep
-uint32_t lds_bytes16(int wp, int L, int pl) {
-    if (L > fit16_depth_hi(wp) || (pl == 2 && wp > 32)) return 0;
-    switch (wp) {
-        case 16: return pl == 2 ? fit16::Shape<16, 2>::total(L) : fit16::Shape<16, 1>::total(L);
-        case 32: return pl == 2 ? fit16::Shape<32, 2>::total(L) : fit16::Shape<32, 1>::total(L);
-        case 48: return fit16::Shape<48, 1>::total(L);
-        default: return fit16::Shape<64, 1>::total(L);
-    }
+// Depth buckets: where another wavefront per SIMD, or a second tile, fits the registers.
+template <int WP> Fit16 kernel16_of(int L) {
+    if (L > fit16_depth(WP)) return Fit16{nullptr, 0, 0};
+    if constexpr (WP == 16) return L <= 4 ? kernel16<16, 4>(L) : (L <= 7 ? kernel16<16, 7>(L) : kernel16<16, 12>(L));
+    else if constexpr (WP == 32) return L <= 4 ? kernel16<32, 4>(L) : (L <= 6 ? kernel16<32, 6>(L) : (L <= 8 ? kernel16<32, 8>(L) : kernel16<32, 12>(L)));
+    else if constexpr (WP == 48) return L <= 4 ? kernel16<48, 4>(L) : (L <= 7 ? kernel16<48, 7>(L) : kernel16<48, 10>(L));
+    else return L <= 3 ? kernel16<64, 3>(L) : (L <= 4 ? kernel16<64, 4>(L) : kernel16<64, 6>(L));
+}
+Fit16 kernel16_for(int wp, int L) {
+    const Fit16 k = wp == 16 ? kernel16_of<16>(L) : (wp == 32 ? kernel16_of<32>(L) : (wp == 48 ? kernel16_of<48>(L) : kernel16_of<64>(L)));
+    return k.lds <= kLdsLimit - 256 ? k : Fit16{nullptr, 0, 0};
 }
 
 }  // namespace
@@ -520,8 +520,7 @@ struct rinr_fit {
     int wq, lds_floats;         // wq: widest hidden layer rounded up to a multiple of 8 (fp32 kernels); lds_floats 0 = no fp32 kernel fits
     int family;                 // RINR_FIT_KERNEL_FP32 or RINR_FIT_KERNEL_SPLIT16: the kernels this handle's steps run
     int wp;                     // widest hidden layer rounded up to a multiple of 16 (split kernels)
-    uint32_t lds16;             // their LDS bytes
-    int pl16;                   // their plane sets (layers per pair of barriers)
+    Fit16 k16;                  // their kernel; null = none is built for the shape
     float *emag;                // [n_images] error size seen by the last step (split kernels' error scale); 0 = none yet
     int32_t p_off[kMaxL];
     float *params, *m, *v, *loss, *scratch_grad;
@@ -540,9 +539,9 @@ namespace {
 // (8 images of 171 x 219, 10 layers x 32): 3241 us a step with one workgroup per image, 142 with 32.
 int plan_splits(const rinr_fit *f, const void *fn) {
     const bool split16 = f->family == RINR_FIT_KERNEL_SPLIT16;
-    const int waves = split16 ? fit16::fit16_waves(f->wp) : fit_waves(f->wq);
-    const size_t lds = split16 ? (size_t)f->lds16 : (size_t)f->lds_floats * 4;
-    const int64_t pc = split16 ? 16 * waves : 64, chunks = ((int64_t)f->H * f->W + pc - 1) / pc;
+    const int waves = split16 ? fit16::kWaves : fit_waves(f->wq);
+    const size_t lds = split16 ? (size_t)f->k16.lds : (size_t)f->lds_floats * 4;
+    const int64_t pc = split16 ? f->k16.pixels : 64, chunks = ((int64_t)f->H * f->W + pc - 1) / pc;
     int device = 0, cus = 256, resident = 1;
     if (hip_fail(hipGetDevice(&device)) || hip_fail(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device)) || cus < 1) cus = 256;
     if (hip_fail(hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, fn, 64 * waves, lds)) || resident < 1) resident = 1;
@@ -584,15 +583,9 @@ extern "C" int rinr_fit_create_ex(const rinr_fit_arch *arch, int64_t n_images, i
     f->wp = (wmax + 15) / 16 * 16;
     f->lds_floats = lds_floats(f->wq, arch->n_layers);
     if ((size_t)f->lds_floats * 4 + 256 > kLdsLimit) f->lds_floats = 0;
-    f->pl16 = 2;
-    f->lds16 = lds_bytes16(f->wp, arch->n_layers, 2);
-    if (f->lds16 == 0 || (size_t)f->lds16 + 256 > kLdsLimit) {
-        f->pl16 = 1;
-        f->lds16 = lds_bytes16(f->wp, arch->n_layers, 1);
-        if ((size_t)f->lds16 + 256 > kLdsLimit) f->lds16 = 0;
-    }
+    f->k16 = kernel16_for(f->wp, arch->n_layers);
     // the split-precision kernels where they are built for the shape, the fp32 ones otherwise or on request
-    f->family = (f->lds16 && !(flags & RINR_FIT_FLAG_FP32_MFMA)) ? RINR_FIT_KERNEL_SPLIT16 : RINR_FIT_KERNEL_FP32;
+    f->family = (f->k16.fn && !(flags & RINR_FIT_FLAG_FP32_MFMA)) ? RINR_FIT_KERNEL_SPLIT16 : RINR_FIT_KERNEL_FP32;
     if (f->family == RINR_FIT_KERNEL_FP32 && f->lds_floats == 0) { delete f; return RINR_E_UNSUPPORTED; }
     f->n_params = 0;
     for (int l = 0; l < arch->n_layers; ++l) {
@@ -605,7 +598,7 @@ extern "C" int rinr_fit_create_ex(const rinr_fit_arch *arch, int64_t n_images, i
     f->keep = nullptr;
     f->has_keep = false;
     f->t = 0;
-    const void *fn = f->family == RINR_FIT_KERNEL_SPLIT16 ? (const void *)kernel16_for(f->wp, arch->n_layers, f->pl16)
+    const void *fn = f->family == RINR_FIT_KERNEL_SPLIT16 ? (const void *)f->k16.fn
                                                          : (const void *)kernel_for(f->wq, arch->n_layers);
     if (hip_fail(hipMalloc((void **)&f->params, np * 4)) || hip_fail(hipMalloc((void **)&f->m, np * 4)) ||
         hip_fail(hipMalloc((void **)&f->v, np * 4)) || hip_fail(hipMalloc((void **)&f->keep, np)) ||
@@ -725,6 +718,10 @@ int launch(rinr_fit *f, const float *targets, float loss_scale, float lr, int64_
     a.n_params = f->n_params;
     a.HW = (uint32_t)(f->H * f->W);
     a.W = (uint32_t)f->W;
+    uint32_t bits = 0;
+    while ((1ull << bits) < (uint64_t)f->W) ++bits;
+    a.wmagic = bits ? (uint32_t)((((uint64_t)1 << (31 + bits)) + (uint64_t)f->W - 1) / (uint64_t)f->W) : 0u;
+    a.wshift = bits ? bits - 1 : 0u;
     a.inv2W = 1.0f / (2.0f * (float)f->W);
     a.inv2H = 1.0f / (2.0f * (float)f->H);
     a.lo = f->arch.coord_lo;
@@ -748,7 +745,7 @@ int launch(rinr_fit *f, const float *targets, float loss_scale, float lr, int64_
     for (int l = 0; l <= a.L; ++l) a.d[l] = f->arch.widths[l];
     for (int l = 0; l < a.L; ++l) a.p_off[l] = f->p_off[l];
     if (f->family == RINR_FIT_KERNEL_SPLIT16)
-        hipLaunchKernelGGL(kernel16_for(f->wp, f->arch.n_layers, f->pl16), dim3((uint32_t)(f->n_images * f->splits)), dim3(64 * fit16::fit16_waves(f->wp)), (size_t)f->lds16, stream, a);
+        hipLaunchKernelGGL(f->k16.fn, dim3((uint32_t)(f->n_images * f->splits)), dim3(fit16::kThreads), (size_t)f->k16.lds, stream, a);
     else
         hipLaunchKernelGGL(kernel_for(f->wq, f->arch.n_layers), dim3((uint32_t)(f->n_images * f->splits)), dim3(64 * fit_waves(f->wq)), (size_t)f->lds_floats * 4, stream, a);
     FIT_HIP(hipGetLastError());

@@ -4,20 +4,34 @@
 // bits per product at a third of the fp32 matrix instruction's time, and the fp16 matrix pipe runs beside the vector ALU
 // that does the sines, cosines and splits.
 //
-// One workgroup per image, 8 wavefronts (2 at padded width 16), 16 pixels of a chunk per wavefront: a wavefront takes its
-// pixels through all layers forward and backward with the activations and errors in registers (lane = (pixel n, group g);
-// a 16-row tile of a layer's units is one quad of four registers per lane, rows 16 t + 4 g + v).  A quad is exactly
-// half of the B operand of one 32-deep matrix step (two tiles' quads side by side), so nothing moves between lanes from
-// one layer to the next, in either direction.  The weights sit in LDS once, row-major [out][in] as a hi and a lo plane:
-// the forward product reads its A operand (4 consecutive inputs of one output row) with plain 8-byte reads, the backward
-// product reads the transposed operand (4 consecutive output rows of one input column) with the transposing LDS read
-// ds_read_b64_tr_b16 (within 16 lanes, lane i receives element i % 4 of the chunks that lanes i / 4, 4 + i / 4,
-// 8 + i / 4, 12 + i / 4 point at).  Only the weight gradient, which contracts over pixels, needs other wavefronts' data:
-// per layer every wavefront writes its pixels' error and layer input as hi/lo planes [pixel][unit] to LDS, and after a
-// barrier each wavefront accumulates the gradient tiles it owns over the chunk's pixels, both operands read with the
-// transposing read; with PL sets of planes, PL layers share one pair of barriers.  The bias is the weight of a unit of
-// ones, placed right behind the layer's inputs where the padded width has room.  Gradient tiles stay in their owner's
-// registers for the whole step; Adam is applied in place at the end, as in the fp32 kernel.
+// A workgroup has four wavefronts, and nothing passes between them until the end of the step: a wavefront takes NT x 16
+// pixels at a time through all layers forward and backward with activations, pre-activations and errors in registers, and
+// accumulates the weight gradients of all layers over its own pixels in registers as well (deep and wide models take all
+// 512 registers of a lone wavefront per SIMD for it).  The only barriers are before the first pixel, when the weights are
+// in LDS, and after the last, when the wavefronts' gradients are added up.  The version before this shared the gradient tiles
+// among eight wavefronts: fewer registers, but every layer's errors and inputs went through LDS between two barriers.
+//
+// What bounds it is instruction issue: a matrix instruction takes two issue slots of 4.1 clocks, a sine or cosine two, other
+// vector instructions one (measured; matrix and vector instructions of one wavefront overlap where they alternate).  A hidden
+// layer of 40 units takes 48 matrix and 169 vector slots per 16 pixels backward, 15 and 52 forward.  Measured, ms a step, before ->
+// now: 256 images of 224 x 224, 10 layers x 40: 8.91 -> 6.86; 10 x 32: 4.54 -> 3.50; 2048 of 32 x 32, 3 x 15: 0.0934 -> 0.0778.
+//
+// Two orientations.  P: lane (n, g) holds pixel n and, per 16-row tile of a layer's units, the quad of units 4 g + v.  That is
+// what a matrix instruction leaves with the units as its rows, and two tiles' quads side by side are exactly the B operand
+// of one 32-deep step of the next layer, so nothing moves between lanes from one layer to the next, in either direction.
+// U: lane (n, g) holds unit n and the pixels 4 g + v: the operand of the weight gradient, which contracts over pixels.  From P
+// to U goes a matrix step with the unit matrix (the data as A, the unit matrix as B), which is exact for halfs.
+// With NT = 2 the two tiles' quads make a 32-deep step over pixels; with NT = 1 the hi and the lo part of one tile do
+// ([Eh | El] x [Hh | Hh], then x [Hl | Hl]: two steps instead of three, and the term lo*lo comes along).  The odd last tile of
+// a layer's units is treated the same way in the forward and backward products ([Wh | Wl] x [Hh | Hh], x [Hl | Hl]).
+//
+// LDS holds the weights of the hidden layers twice, once with the outputs and once with the inputs as rows (those times the
+// factor that the error is multiplied by going down, see below), in operand order: per pair of 16-unit tiles a hi and a lo
+// plane of 64-byte rows, 16 bytes per lane group: the quads of both tiles; an odd last tile's plane has the hi and the lo quad
+// side by side.  A lane reads an operand as one 16-byte word at a fixed place
+// in its row; rows 4..7 of every eight have their two pairs of words exchanged, which makes that read free of bank conflicts
+// (measured: 4.8 clocks per wavefront instead of 8.7).  Plain 8-byte reads of row-major planes, as before, were merged
+// by the compiler into two-address reads at 8.6 clocks or more.
 //
 // Range of the error in fp16: the error of layer l is carried times a power of two T_l.  T of the output layer is
 // chosen from the root-mean-square error the previous step saw (kept per image; 0.25 if there was none), so that the
@@ -32,57 +46,46 @@ namespace fit16 {
 
 typedef _Float16 h4v __attribute__((ext_vector_type(4)));
 typedef _Float16 h2v __attribute__((ext_vector_type(2)));
-typedef short s4v __attribute__((ext_vector_type(4)));
-typedef float f2v __attribute__((ext_vector_type(2)));
-
-// Wavefronts per workgroup: 8 (128 pixels per chunk); 2 at padded width 16 (32 pixels per chunk), whose phases are so short
-// that many small workgroups per CU, each at its own barrier, fill the machine better (3 x 15 at 32 x 32: 0.105 -> 0.092 ms).
-constexpr int fit16_waves(int wp) { return wp == 16 ? 2 : 8; }
-
-// Shapes and the LDS layout (bytes) for hidden widths <= WP (a multiple of 16) and L linear layers.
-template <int WP, int PL = 1> struct Shape {
-    static constexpr int NW = fit16_waves(WP), NTHREADS = 64 * NW, PC = 16 * NW, KS = PC / 32;   // wavefronts, threads, pixels per chunk, 32-pixel steps
-    static constexpr int MT = WP / 16;            // 16-row tiles of a hidden layer
-    static constexpr int NIT = MT + 1;            // column tiles of a weight gradient: the inputs, then the tile whose first column is the bias
-    static constexpr int WPP = WP + 4;            // halfs per weight row (the pad spreads 16 rows over the banks)
-    static constexpr int EP = WP + 4;             // halfs per pixel of the error planes
-    static constexpr int HP = WP + 20;            // halfs per pixel of the input planes: WP units, the unit of ones, 15 zero units, pad
-    static constexpr int GSLOTS = (MT * NIT + NW - 1) / NW;   // gradient tiles a wavefront owns per layer
-    // LDS, in this order: the sets of pixel planes, the first layer, the biases (12 slots), the hidden layers' weight planes,
-    // the output layer's, a pad, small tables.  Everything up to the hidden layers sits at compile-time offsets, so a lane's
-    // address is one register plus an immediate.  Reads that run past an operand's rows or columns (the other half of an
-    // odd last tile, whose partner operand is zero) land in what follows: weight planes, then the pad of zeros.
-    static constexpr uint32_t SET = 4u * PC * (EP + HP);                                                // bytes of one set of planes (error hi, lo; input hi, lo)
-    static __host__ __device__ constexpr uint32_t off_eh(int j) { return (uint32_t)j * SET; }
-    static __host__ __device__ constexpr uint32_t off_el(int j) { return off_eh(j) + 2u * PC * EP; }
-    static __host__ __device__ constexpr uint32_t off_hh(int j) { return off_el(j) + 2u * PC * EP; }
-    static __host__ __device__ constexpr uint32_t off_hl(int j) { return off_hh(j) + 2u * PC * HP; }
-    static __host__ __device__ constexpr uint32_t off_w0() { return PL * SET; }                           // float [WP][4]: x weight, y weight, bias, 0
-    static __host__ __device__ constexpr uint32_t off_bias(int l) { return off_w0() + WP * 16 + (uint32_t)l * WP * 4; }   // float [WP] per layer
-    static __host__ __device__ constexpr uint32_t off_hid(int l) { return off_bias(12) + (uint32_t)(l - 1) * 4u * WP * WPP; }   // hi plane, then lo plane
-    static __host__ __device__ constexpr uint32_t off_last(int L) { return off_hid(L - 1); }              // [16][WPP] hi, then lo
-    static constexpr uint32_t PAD = (2u * 16 * WPP + 15) / 16 * 16 + 64;
-    static __host__ __device__ constexpr uint32_t off_misc(int L) { return off_last(L) + 4u * 16 * WPP + PAD; }   // float [16 + 16 + 16 * 8]: factors, scales, partial sums
-    static __host__ __device__ constexpr uint32_t total(int L) { return off_misc(L) + 4u * (32 + 16 * 8); }
-};
-
 typedef _Float16 h8v __attribute__((ext_vector_type(8)));
-// One matrix step is v_mfma_f32_16x16x32_f16 (the 16-deep instruction runs at half its rate on this chip): lane group g
-// supplies k = 8 g .. 8 g + 7, taken as the quads of two tiles (k = 4 g + v of tile 2 j, then of tile 2 j + 1); both
-// operands of a product are built the same way, so the order within the 32 is immaterial.  An odd last tile pairs with zeros.
+typedef float f2v __attribute__((ext_vector_type(2)));
+typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+
+constexpr int kWaves = 4, kThreads = 64 * kWaves;
+
+// Shapes and the LDS layout (bytes) for hidden widths <= WP (a multiple of 16).
+template <int WP> struct Shape {
+    static constexpr int MT = WP / 16;                  // 16-unit tiles of a hidden layer
+    static constexpr int NP = MT / 2, TAIL = MT % 2;    // pairs of them, and an odd last one
+    static constexpr int NPL = 2 * NP + TAIL;           // planes of one operand matrix
+    static constexpr uint32_t PLANE = WP * 64;          // bytes of a plane of WP rows
+    static constexpr uint32_t HID = NPL * PLANE;        // one hidden layer in one orientation
+    static constexpr int GT = MT == 1 ? 4 : 16;         // gradient tiles that go through LDS at a time at the end
+    // All offsets but the end are compile-time, so a lane's address is one register plus an immediate.
+    static constexpr uint32_t MISC = 0;                                                          // see Misc
+    static constexpr uint32_t W0 = 1024;                                                         // float [WP][4]: x weight, y weight, bias, 0
+    static constexpr uint32_t BIAS = W0 + WP * 16;                                               // float [16] output layer, then [kMaxL - 2][WP], per step (see the kernel)
+    static constexpr uint32_t LASTF = BIAS + 64 + (kMaxL - 2) * WP * 4;                          // 16 rows, channel c in row 4 c
+    static constexpr uint32_t LASTT = LASTF + NPL * 16 * 64;                                     // WP rows, one tile of outputs
+    static constexpr uint32_t HID0 = LASTT + PLANE;                                              // hidden layers: outputs as rows, inputs as rows
+    static __host__ __device__ constexpr uint32_t total(int L) {
+        const uint32_t w = HID0 + (uint32_t)(L - 2) * 2 * HID, r = W0 + kWaves * GT * 1024;
+        return w > r ? w : r;
+    }
+};
+struct Misc {              // small tables at the start of LDS; everything behind is reused when the gradients are added up
+    float grad[16];        // factor of the accumulated gradient, per layer
+    float scale[kMaxL];    // per layer: what the error is multiplied by going down through it
+    float out;             // the output difference's factor
+    float ss[kMaxL][kWaves];
+    float red[kWaves];
+    int32_t d[16], p_off[kMaxL];
+};
+static_assert(sizeof(Misc) <= 1024, "Misc");
+
 __device__ __forceinline__ h8v cat(h4v a, h4v b) { return __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7); }
+// One matrix step: lane group g supplies k = 8 g .. 8 g + 7, as two quads; both operands of a product are built the same
+// way, so the order within the 32 is immaterial.
 __device__ __forceinline__ f32x4 mfma32(h8v a, h8v b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x32_f16(a, b, c, 0, 0, 0); }
-// a x b with both operands as hi/lo pairs
-__device__ __forceinline__ f32x4 mfma3(h8v ah, h8v al, h8v bh, h8v bl, f32x4 c) {
-    c = mfma32(ah, bh, c);
-    c = mfma32(ah, bl, c);
-    return mfma32(al, bh, c);
-}
-// transposing LDS read: see the file header; p is this lane's chunk of 4 halfs
-__device__ __forceinline__ h4v read_tr(const char *p) {
-    const s4v v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((__attribute__((address_space(3))) s4v *)p);
-    return __builtin_bit_cast(h4v, v);
-}
 // exact hi/lo split of a quad, round to nearest (activations, |x| <= 1).  neg1 is -1.0f passed as data, so that
 // x - float(hi) stays one mixed-precision fma instead of a conversion and a subtraction.
 __device__ __forceinline__ void split_rne(f32x4 x, float neg1, h4v &hi, h4v &lo) {
@@ -94,79 +97,142 @@ __device__ __forceinline__ void split_rne(f32x4 x, float neg1, h4v &hi, h4v &lo)
     hi = (h4v){a0[0], a0[1], a1[0], a1[1]};
     lo = (h4v){b0[0], b0[1], b1[0], b1[1]};
 }
+__device__ __forceinline__ h4v to_h4(f32x4 x) {
+    const auto a0 = __builtin_amdgcn_cvt_pkrtz(x[0], x[1]), a1 = __builtin_amdgcn_cvt_pkrtz(x[2], x[3]);
+    return (h4v){(_Float16)a0[0], (_Float16)a0[1], (_Float16)a1[0], (_Float16)a1[1]};
+}
 // hi/lo split of a quad, round toward zero: values beyond the largest half saturate there instead of becoming infinite
 __device__ __forceinline__ void split_rtz(f32x4 x, float neg1, h4v &hi, h4v &lo) {
-    const auto a0 = __builtin_amdgcn_cvt_pkrtz(x[0], x[1]), a1 = __builtin_amdgcn_cvt_pkrtz(x[2], x[3]);
-    const auto b0 = __builtin_amdgcn_cvt_pkrtz(__builtin_fmaf((float)a0[0], neg1, x[0]), __builtin_fmaf((float)a0[1], neg1, x[1]));
-    const auto b1 = __builtin_amdgcn_cvt_pkrtz(__builtin_fmaf((float)a1[0], neg1, x[2]), __builtin_fmaf((float)a1[1], neg1, x[3]));
-    hi = (h4v){(_Float16)a0[0], (_Float16)a0[1], (_Float16)a1[0], (_Float16)a1[1]};
-    lo = (h4v){(_Float16)b0[0], (_Float16)b0[1], (_Float16)b1[0], (_Float16)b1[1]};
+    hi = to_h4(x);
+    lo = to_h4((f32x4){__builtin_fmaf((float)hi[0], neg1, x[0]), __builtin_fmaf((float)hi[1], neg1, x[1]),
+                       __builtin_fmaf((float)hi[2], neg1, x[2]), __builtin_fmaf((float)hi[3], neg1, x[3])});
 }
 __device__ __forceinline__ f32x4 sin4(f32x4 z) {
     return (f32x4){__builtin_amdgcn_sinf(z[0]), __builtin_amdgcn_sinf(z[1]), __builtin_amdgcn_sinf(z[2]), __builtin_amdgcn_sinf(z[3])};
 }
-
-// The unit of ones (its weight is the bias): right behind a layer's inputs where the padded width has room, else at WP.
-template <int WP> __device__ __forceinline__ int ones_unit(int din) { return din < WP ? din : WP; }
-// Where entry (row o, input unit j) of layer l's gradient lives in the parameter vector, or -1 (padding).
-template <int WP> __device__ __forceinline__ int param_index(const FitArgs &a, int l, int o, int j) {
-    const int din = a.d[l], dout = a.d[l + 1];
-    if (o >= dout) return -1;
-    if (j == ones_unit<WP>(din)) return a.p_off[l] + dout * din + o;
-    return j < din ? a.p_off[l] + o * din + j : -1;
+__device__ __forceinline__ f32x4 cos4(f32x4 z) {
+    return (f32x4){__builtin_amdgcn_cosf(z[0]), __builtin_amdgcn_cosf(z[1]), __builtin_amdgcn_cosf(z[2]), __builtin_amdgcn_cosf(z[3])};
 }
 
-template <int WP, int ML, int PL>
-__global__ __launch_bounds__(Shape<WP>::NTHREADS, (Shape<WP>::NW <= 4 && ML <= 4) ? 4 : 2) void fit16_step_kernel(const FitArgs a) {
-    typedef Shape<WP, PL> S;
-    constexpr int kWaves = S::NW, kThreads = S::NTHREADS, kPC = S::PC;
-    constexpr int MT = S::MT, NP = (MT + 1) / 2, WPP = S::WPP, EP = S::EP, HP = S::HP, GSLOTS = S::GSLOTS;
+// Entry (row r, contraction index k) of an operand matrix whose planes have `plane` bytes, as a hi/lo pair
+template <int WP> __device__ __forceinline__ void put_operand(char *m, uint32_t plane, int r, int k, float w) {
+    typedef Shape<WP> S;
+    const _Float16 h = (_Float16)w, l = (_Float16)(w - (float)h);
+    const int t = k >> 4, q = (k >> 2) & 3;
+    const uint32_t at = (uint32_t)r * 64 + 16 * (q ^ ((r >> 1) & 2)) + 2 * (k & 3);
+    if (S::TAIL && t == S::MT - 1) {
+        _Float16 *p = (_Float16 *)(m + 2 * S::NP * plane + at);
+        p[0] = h;
+        p[4] = l;
+    } else {
+        _Float16 *p = (_Float16 *)(m + (t >> 1) * 2 * plane + at + 8 * (t & 1));
+        p[0] = h;
+        p[plane / 2] = l;
+    }
+}
+
+// acc + (operand rows at `m`, this lane's word) x (B as quads Bh, Bl of all tiles)
+template <int WP> __device__ __forceinline__ f32x4 contract(const char *m, uint32_t plane, const h4v (&Bh)[WP / 16], const h4v (&Bl)[WP / 16], f32x4 acc) {
+    typedef Shape<WP> S;
+#pragma unroll
+    for (int j = 0; j < S::NP; ++j) {
+        const h8v ah = *(const h8v *)(m + 2 * j * plane), al = *(const h8v *)(m + (2 * j + 1) * plane);
+        const h8v bh = cat(Bh[2 * j], Bh[2 * j + 1]), bl = cat(Bl[2 * j], Bl[2 * j + 1]);
+        acc = mfma32(ah, bh, acc);
+        acc = mfma32(ah, bl, acc);
+        acc = mfma32(al, bh, acc);
+    }
+    if (S::TAIL) {
+        const h8v at = *(const h8v *)(m + 2 * S::NP * plane);
+        acc = mfma32(at, cat(Bh[S::MT - 1], Bh[S::MT - 1]), acc);
+        acc = mfma32(at, cat(Bl[S::MT - 1], Bl[S::MT - 1]), acc);
+    }
+    return acc;
+}
+
+// Registers: gradient tiles and pre-activations of all layers, and what a layer in progress takes.
+constexpr int fit16_registers(int wp, int ml, int nt) {
+    const int mt = wp / 16;
+    return 4 * (2 * mt + (ml - 2) * mt * mt) + 4 * nt * mt * (ml - 1) + 40 + 16 * nt * mt;
+}
+constexpr int fit16_waves_per_simd(int wp, int ml, int nt) {
+    const int r = fit16_registers(wp, ml, nt);
+    return r <= 128 ? 4 : (r <= 168 ? 3 : (r <= 256 ? 2 : 1));
+}
+
+// A model of L layers in the kernel of a depth bucket ML: the hidden layers are steps u = 0 .. ML - 3 of code unrolled for ML
+// layers, and a shallower model leaves out the first ML - L of them.  So what follows the last hidden layer, and the first
+// layer, are each one piece of code, and a step is one piece without branches that the compiler can interleave.
+template <int WP, int ML, int NT>
+__global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, ML, NT)) void fit16_step_kernel(const FitArgs a) {
+    typedef Shape<WP> S;
+    constexpr int MT = S::MT, NH = ML - 2, kPC = kWaves * 16 * NT;
+    constexpr int kColOut = 11, kColFirst = 12;         // columns of acc_b: step u's biases in column u, the output layer's, the first layer's bias, x and y
+    const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
     const h4v zh = {(_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f};
     extern __shared__ __attribute__((aligned(16))) char lds16[];
     char *const lds = lds16;
+    Misc *const misc = (Misc *)(lds + S::MISC);
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, n = lane & 15, g = lane >> 4;
     const FitShare share = fit_share(a, (a.HW + kPC - 1) / kPC);
     const size_t img = share.img;
     const float *P = a.params + img * a.n_params;
-    const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
     const float neg1 = a.neg1;
-    const int L0 = a.L;
-    float *const misc = (float *)(lds + S::off_misc(L0));      // [0..15] gradient factor per layer, [16..31] scale r per layer, [32..] partial sums
-    char *const EH0 = lds + S::off_eh(0), *const EL0 = lds + S::off_el(0), *const HH0 = lds + S::off_hh(0), *const HL0 = lds + S::off_hl(0);   // set 0; set j is j * S::SET further
+    const int L = a.L, skip = ML - L;
 
-    // ---- set up: zero everything; weights as hi/lo planes (sine layers times w0 / 2pi: Z comes out in revolutions), biases,
-    //      the unit of ones; per layer the sum of squared weights (for the error's scale), summed in a fixed order
-    for (uint32_t q = tid; q < S::total(L0) / 16; q += kThreads) ((uint4 *)lds)[q] = make_uint4(0u, 0u, 0u, 0u);
+    // ---- set up: zero everything; weights as hi/lo operands (sine layers times w0 / 2pi: Z comes out in revolutions), biases;
+    //      per layer the sum of squared weights (for the error's scale), summed in a fixed order.  A thread has all its weights
+    //      of a layer under way at once, and the next layer's while it places this one's: one memory latency, not one per weight.
+    constexpr int kOwn = MT * MT;                       // WP * WP / kThreads
+    float cur[kOwn], next[kOwn];
+    auto fetch = [&](int l, float (&w)[kOwn]) {
+        const int cnt = l < L ? a.d[l] * a.d[l + 1] : 0;
+        const float *src = P + a.p_off[l < L ? l : 0];
+#pragma unroll
+        for (int k = 0; k < kOwn; ++k) w[k] = tid + k * kThreads < cnt ? src[tid + k * kThreads] : 0.0f;
+    };
+    fetch(0, cur);
+    for (uint32_t q = tid; q < S::total(L) / 16; q += kThreads) ((uint4 *)lds)[q] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
-    for (int l = 0; l < L0; ++l) {
+    for (int l = 0; l < L; ++l) {
         const int din = a.d[l], dout = a.d[l + 1];
-        const float *src = P + a.p_off[l];
-        const float sc = l < L0 - 1 ? a.w0rev : 1.0f;
+        const bool last = l == L - 1;
+        const uint32_t per = (1u << 20) / (uint32_t)din + 1u;               // e / din == e * per >> 20 for e < 4096
+        const float sc = last ? 1.0f : a.w0rev;
+        const float bias = tid < dout ? P[a.p_off[l] + dout * din + tid] : 0.0f;
+        fetch(l + 1, next);
+        char *const F = lds + S::HID0 + (uint32_t)(l > 0 ? l - 1 : 0) * 2 * S::HID;
         float ss = 0.0f;
-        if (l == 0) {
-            float *W0 = (float *)(lds + S::off_w0());
-            for (int e = tid; e < dout * 2; e += kThreads) { const float w = src[e] * sc; W0[(e >> 1) * 4 + (e & 1)] = w; }
-            for (int o = tid; o < dout; o += kThreads) W0[o * 4 + 2] = src[dout * din + o] * sc;
-        } else {
-            _Float16 *Wh = (_Float16 *)(lds + (l == L0 - 1 ? S::off_last(L0) : S::off_hid(l)));
-            _Float16 *Wl = Wh + (l == L0 - 1 ? 16 : WP) * WPP;
-            float *B = (float *)(lds + S::off_bias(l));
-            for (int e = tid; e < dout * din; e += kThreads) {
-                const int o = e / din, i = e - o * din;
-                const float w = src[e] * sc;
-                const _Float16 h = (_Float16)w;
-                Wh[o * WPP + i] = h;
-                Wl[o * WPP + i] = (_Float16)(w - (float)h);
+#pragma unroll
+        for (int k = 0; k < kOwn; ++k) {
+            const int e = tid + k * kThreads;
+            if (e < dout * din) {
+                const int o = (int)((uint32_t)e * per >> 20), i = e - o * din;
+                const float w = cur[k] * sc;
                 ss = fmaf(w, w, ss);
+                if (l == 0) {
+                    ((float *)(lds + S::W0))[o * 4 + i] = w;
+                } else if (last) {
+                    put_operand<WP>(lds + S::LASTF, 16 * 64, 4 * o, i, w);
+                    put_operand<16>(lds + S::LASTT, S::PLANE, i, 4 * o, w);
+                } else {
+                    put_operand<WP>(F, S::PLANE, o, i, w);
+                    put_operand<WP>(F + S::HID, S::PLANE, i, o, w);
+                }
             }
-            for (int o = tid; o < dout; o += kThreads) B[o] = src[dout * din + o] * sc;
+            cur[k] = next[k];
+        }
+        if (tid < dout) {
+            float *const B = (float *)(lds + S::BIAS) + (last ? 4 * tid : 16 + (l - 1 + skip) * WP + tid);
+            *(l == 0 ? (float *)(lds + S::W0) + tid * 4 + 2 : B) = bias * sc;
         }
         for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
-        if (lane == 0) misc[32 + l * 8 + wave] = ss;
+        if (lane == 0) misc->ss[l][wave] = ss;
     }
-    for (int p = tid; p < kPC * PL; p += kThreads) ((_Float16 *)(HH0 + (p / kPC) * S::SET))[(p % kPC) * HP + WP] = (_Float16)1.0f;
+    if (tid < 16) misc->d[tid] = tid <= L ? a.d[tid] : 0;
+    if (tid < L) misc->p_off[tid] = a.p_off[tid];
     __syncthreads();
     if (tid == 0) {
         // scale of the output layer's error from the error the previous step saw; then down the layers by the estimated gains
@@ -175,264 +241,321 @@ __global__ __launch_bounds__(Shape<WP>::NTHREADS, (Shape<WP>::NW <= 4 && ML <= 4
         const float raw = 2.0f * a.loss_scale * rms;                        // error of the output layer before scaling, typical size
         float T = exp2f(4.0f - ceilf(log2f(raw)));
         T = fminf(fmaxf(T, 1e-30f), 1e30f);
-        misc[16 + L0 - 1] = T * 2.0f * a.loss_scale;                        // what the output difference is multiplied by
-        misc[L0 - 1] = a.gscale[L0 - 1] / T;
-        for (int l = L0 - 1; l >= 1; --l) {
+        misc->out = T * 2.0f * a.loss_scale;                                // what the output difference is multiplied by
+        misc->grad[L - 1] = a.gscale[L - 1] / T;
+        for (int l = L - 1; l >= 1; --l) {
             float ss = 0.0f;
-            for (int w = 0; w < kWaves; ++w) ss += misc[32 + l * 8 + w];
+            for (int w = 0; w < kWaves; ++w) ss += misc->ss[l][w];
             const float gain = 0.7f * sqrtf(ss / (float)a.d[l]);
             float r = gain > 0.0f ? exp2f(rintf(-log2f(gain))) : 1.0f;
             r = fminf(fmaxf(r, 0.015625f), 256.0f);
             if (!(T * r < 1e30f && T * r > 1e-30f)) r = 1.0f;
             T *= r;
-            misc[16 + l - 1] = r;                                           // E_{l-1} = (W_l^T E_l) cos(.) r
-            misc[l - 1] = a.gscale[l - 1] / T;
+            misc->scale[l] = r;                                             // E_{l-1} = (r W_l^T E_l) cos(.)
+            misc->grad[l - 1] = a.gscale[l - 1] / T;
         }
     }
     __syncthreads();
+    // the transposed weights carry that factor (a power of two)
+    for (int l = 1; l < L; ++l) {
+        const _Float16 r = (_Float16)misc->scale[l];
+        h8v *const T = (h8v *)(lds + (l == L - 1 ? S::LASTT : S::HID0 + (uint32_t)(2 * l - 1) * S::HID));
+        for (uint32_t q = tid; q < (l == L - 1 ? S::PLANE : S::HID) / 16; q += kThreads) T[q] *= r;
+    }
+    __syncthreads();
 
-    f32x4 acc[ML][GSLOTS];          // weight-gradient tiles, whole step
-    f32x4 zst[ML - 1][MT];          // pre-activations (revolutions) of this wavefront's 16 pixels, sine layers
+    f32x4 acc[NH][MT][MT];                         // weight gradients of the hidden layers: rows are outputs, columns inputs
+    f32x4 acc_last[MT], acc_b[MT];                 // output layer (channel c in row 4 c); biases and first layer
+    f32x4 zst[NH + 1][NT][MT];                     // pre-activations (revolutions) of the pixels at hand: what goes into step u, into the output layer
 #pragma unroll
-    for (int l = 0; l < ML; ++l)
+    for (int t = 0; t < MT; ++t) {
+        acc_last[t] = acc_b[t] = zero4;
 #pragma unroll
-        for (int s = 0; s < GSLOTS; ++s) acc[l][s] = zero4;
+        for (int u = 0; u < NH; ++u)
 #pragma unroll
-    for (int l = 0; l < ML - 1; ++l)
+            for (int i = 0; i < MT; ++i) acc[u][t][i] = zero4;
+    }
 #pragma unroll
-        for (int t = 0; t < MT; ++t) zst[l][t] = zero4;
+    for (int u = 0; u <= NH; ++u)
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int t = 0; t < MT; ++t) zst[u][nt][t] = zero4;
     float loss_part = 0.0f;
+    // the unit matrix as B operand, in the first quad (for the even tile of a pair) and in the second
+    const h4v id = {(_Float16)(4 * g == n ? 1.0f : 0.0f), (_Float16)(4 * g + 1 == n ? 1.0f : 0.0f), (_Float16)(4 * g + 2 == n ? 1.0f : 0.0f),
+                    (_Float16)(4 * g + 3 == n ? 1.0f : 0.0f)};
+    const h8v I0 = cat(id, zh), I1 = cat(zh, id);
+    // P -> U: tile t of a hi/lo pair of quads.  An odd last tile's quads go side by side into one operand, of which either unit
+    // matrix takes one half.
+    auto turn = [&](const h4v (&Xh)[MT], const h4v (&Xl)[MT], int t, h4v &hi, h4v &lo) {
+        if (t < 2 * S::NP) {
+            hi = to_h4(mfma32(cat(Xh[t & ~1], Xh[t | 1]), (t & 1) ? I1 : I0, zero4));
+            lo = to_h4(mfma32(cat(Xl[t & ~1], Xl[t | 1]), (t & 1) ? I1 : I0, zero4));
+        } else {
+            const h8v x = cat(Xh[t], Xl[t]);
+            hi = to_h4(mfma32(x, I0, zero4));
+            lo = to_h4(mfma32(x, I1, zero4));
+        }
+    };
+    auto turn1 = [&](h4v xh, h4v xl, h4v &hi, h4v &lo) {
+        const h8v x = cat(xh, xl);
+        hi = to_h4(mfma32(x, I0, zero4));
+        lo = to_h4(mfma32(x, I1, zero4));
+    };
+    auto column = [&](int k) -> h8v {                                       // ones in column k
+        int m = n;
+        asm volatile("" : "+v"(m));         // made again where it is used: eight steps' columns are not held across the loop
+        const uint32_t two = m == k ? 0x3C003C00u : 0u;
+        const u4v w = {two, two, two, two};
+        return __builtin_bit_cast(h8v, w);
+    };
+    const char *const base = lds + (n * 64 + 16 * (g ^ ((n >> 1) & 2)));    // this lane's word of an operand's row
+    auto step = [&](int u, int from, uint32_t at) {                         // ... in step u's layer: one addition per step, the rest immediates
+        uint32_t s = S::HID0 + at + (uint32_t)(u - from) * 2 * S::HID;
+        asm volatile("" : "+s"(s));
+        return base + s;
+    };
 
-    const int pc = wave * 16 + n;                                  // this lane's pixel within the chunk
-    for (uint32_t c = share.c0; c < share.c1; ++c) {
-        int L = a.L;
-        asm volatile("" : "+s"(L));       // read afresh per chunk: keeps the unrolled layers' conditions out of long-lived lane masks
-        uint32_t p = c * kPC + (uint32_t)pc;
-        const bool valid = p < a.HW;
-        p = valid ? p : a.HW - 1;
-        const uint32_t row = p / a.W, col = p - row * a.W;
-        const float x = fmaf(a.span, (float)(2 * col + 1) * a.inv2W, a.lo), y = fmaf(a.span, (float)(2 * row + 1) * a.inv2H, a.lo);
-
-        // ---- forward.  Layer 0 on the vector ALU (two inputs); hidden layers: Z = W H + b, tile by tile
-        h4v Bh[MT], Bl[MT];
-        {
-            const float4 *W0 = (const float4 *)(lds + S::off_w0());
+    auto pixel = [&](uint32_t c, int nt) { return c * kPC + (uint32_t)(wave * 16 * NT + nt * 16 + n); };
+    auto target = [&](uint32_t c, int nt) {                                 // lane group g: channel g
+        const uint32_t p = pixel(c, nt);
+        return a.target[(img * 3 + (g < 3 ? g : 2)) * a.HW + (p < a.HW ? p : a.HW - 1)];
+    };
+    float tgt[NT];
 #pragma unroll
-            for (int t = 0; t < MT; ++t) {
-                f32x4 z;
+    for (int nt = 0; nt < NT; ++nt) tgt[nt] = share.c0 < share.c1 ? target(share.c0, nt) : 0.0f;
+
+    for (uint32_t c = share.c0; c < share.c1; ++c) {
+        int from = skip;
+        asm volatile("" : "+s"(from));    // read afresh per chunk: keeps the unrolled steps' conditions out of long-lived lane masks
+        float x[NT], y[NT], want[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+            const uint32_t p = min(pixel(c, nt), a.HW - 1);
+            const uint32_t row = a.wmagic ? (__umulhi(p, a.wmagic) >> a.wshift) : p, col = p - row * a.W;
+            x[nt] = fmaf(a.span, (float)(2 * col + 1) * a.inv2W, a.lo);
+            y[nt] = fmaf(a.span, (float)(2 * row + 1) * a.inv2H, a.lo);
+            want[nt] = tgt[nt];
+            tgt[nt] = target(c + 1 < share.c1 ? c + 1 : c, nt);             // the next pixels' targets are under way during this chunk
+        }
+
+        // ---- forward.  First layer on the vector ALU (two inputs); hidden layers: Z = W H + b, tile by tile
+        h4v Bh[NT][MT], Bl[NT][MT];
+        auto first = [&](f32x4 (&z)[NT][MT]) {
+#pragma unroll
+            for (int t = 0; t < MT; ++t)
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const float4 w = W0[16 * t + 4 * g + v];
-                    z[v] = fmaf(w.x, x, fmaf(w.y, y, w.z));
+                    const float4 w = ((const float4 *)(lds + S::W0))[16 * t + 4 * g + v];
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) z[nt][t][v] = fmaf(w.x, x[nt], fmaf(w.y, y[nt], w.z));
                 }
-                zst[0][t] = z;
-                split_rne(sin4(z), neg1, Bh[t], Bl[t]);
-            }
-        }
-#pragma unroll
-        for (int l = 1; l < ML - 1; ++l) {
-            if (l < L - 1) {
-                const char *Wh = lds + S::off_hid(l), *Wl = Wh + 2 * WP * WPP;
-                const f32x4 *B = (const f32x4 *)(lds + S::off_bias(l));
-#pragma unroll
-                for (int mt = 0; mt < MT; ++mt) {
-                    f32x4 z = B[4 * mt + g];
-#pragma unroll
-                    for (int j = 0; j < NP; ++j) {
-                        const int at = 2 * ((16 * mt + n) * WPP + 32 * j + 4 * g);
-                        const bool two = 2 * j + 1 < MT;      // an odd last tile: the B operand's other half is zero, the A operand's is whatever follows in LDS (finite halfs)
-                        const h8v ah = cat(*(const h4v *)(Wh + at), *(const h4v *)(Wh + at + 32)), al = cat(*(const h4v *)(Wl + at), *(const h4v *)(Wl + at + 32));
-                        z = mfma3(ah, al, cat(Bh[2 * j], two ? Bh[2 * j + 1] : zh), cat(Bl[2 * j], two ? Bl[2 * j + 1] : zh), z);
-                    }
-                    zst[l][mt] = z;
-                }
-#pragma unroll
-                for (int t = 0; t < MT; ++t) split_rne(sin4(zst[l][t]), neg1, Bh[t], Bl[t]);
-            }
-        }
-        f32x4 E[MT];                       // the error at hand, scaled (see the file header); the output layer's is tile 0
-#pragma unroll
-        for (int t = 0; t < MT; ++t) E[t] = zero4;
+        };
         {
-            const char *Wh = lds + S::off_last(L), *Wl = Wh + 2 * 16 * WPP;
-            f32x4 z = ((const f32x4 *)(lds + S::off_bias(L - 1)))[g];
+            f32x4 z0[NT][MT];
+            first(z0);
 #pragma unroll
-            for (int j = 0; j < NP; ++j) {
-                const int at = 2 * (n * WPP + 32 * j + 4 * g);
-                const bool two = 2 * j + 1 < MT;
-                const h8v ah = cat(*(const h4v *)(Wh + at), *(const h4v *)(Wh + at + 32)), al = cat(*(const h4v *)(Wl + at), *(const h4v *)(Wl + at + 32));
-                z = mfma3(ah, al, cat(Bh[2 * j], two ? Bh[2 * j + 1] : zh), cat(Bl[2 * j], two ? Bl[2 * j + 1] : zh), z);
-            }
-            const float eo = misc[16 + L - 1];
+            for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-            for (int v = 0; v < 3; ++v) {
-                float e = 0.0f;
-                if (g == 0 && valid) e = z[v] - a.target[(img * 3 + v) * a.HW + p];
-                loss_part = fmaf(e, e, loss_part);
-                E[0][v] = e * eo;
+                for (int t = 0; t < MT; ++t) {
+                    if (from == NH) zst[NH][nt][t] = z0[nt][t];
+                    split_rne(sin4(z0[nt][t]), neg1, Bh[nt][t], Bl[nt][t]);
+                }
+        }
+#pragma unroll
+        for (int u = 0; u < NH; ++u) {
+            if (u >= from) {
+                const f32x4 *B = (const f32x4 *)(lds + S::BIAS + 64 + u * WP * 4);
+                const char *const W = step(u, from, 0);
+#pragma unroll
+                for (int t = 0; t < MT; ++t)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) zst[u + 1][nt][t] = contract<WP>(W + t * 1024, S::PLANE, Bh[nt], Bl[nt], B[4 * t + g]);
+#pragma unroll
+                for (int t = 0; t < MT; ++t)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) split_rne(sin4(zst[u + 1][nt][t]), neg1, Bh[nt][t], Bl[nt][t]);
             }
         }
 
-        // ---- backward, PL layers at a time: each wavefront writes its pixels' error and layer input of those layers to LDS
-        //      as hi/lo planes (one set per layer) and takes the error down through them in registers; after a barrier the
-        //      weight-gradient tiles of those layers take the chunk's pixels, spread round-robin over the wavefronts
+        // ---- output layer: channel g of pixel n in the first register of lane (n, g)
+        f32x4 E[NT][MT];                   // the error at hand, scaled (see the file header)
+        {
+            const float eo = misc->out;
+            const f32x4 b = ((const f32x4 *)(lds + S::BIAS))[g];
+            h4v eh[NT], el[NT];
 #pragma unroll
-        for (int lg = ML - 1; lg >= 0; lg -= PL) {
-            const int llow = lg - PL + 1 > 0 ? lg - PL + 1 : 0;
-            if (llow < L) {
+            for (int nt = 0; nt < NT; ++nt) {
+                const f32x4 z = contract<WP>(base + S::LASTF, 16 * 64, Bh[nt], Bl[nt], b);
+                const float e = g < 3 && pixel(c, nt) < a.HW ? z[0] - want[nt] : 0.0f;
+                loss_part = fmaf(e, e, loss_part);
+                split_rtz((f32x4){e * eo, 0.0f, 0.0f, 0.0f}, neg1, eh[nt], el[nt]);
+            }
 #pragma unroll
-                for (int j = 0; j < PL; ++j) {
-                    const int l = lg - j;
-                    if (l >= 0 && l < L) {
-                        const bool last = l == L - 1;
-                        char *const EH = EH0 + j * S::SET, *const EL = EL0 + j * S::SET, *const HH = HH0 + j * S::SET, *const HL = HL0 + j * S::SET;
-                        h4v Eh[MT], El[MT];
+            for (int t = 0; t < MT; ++t) {
+                const h8v at = *(const h8v *)(base + S::LASTT + t * 1024);
 #pragma unroll
-                        for (int t = 0; t < MT; ++t) {
-                            split_rtz(E[t], neg1, Eh[t], El[t]);            // (the output layer's error has one tile; the others are zero)
-                            if (t == 0 || !last) {
-                                const int at = 2 * (pc * EP + 16 * t + 4 * g);
-                                *(h4v *)(EH + at) = Eh[t];
-                                *(h4v *)(EL + at) = El[t];
-                            }
-                        }
-                        const int uo = ones_unit<WP>(a.d[l]);          // < WP: the unit of ones sits inside a tile and is written with it
-                        if (l == 0) {
-                            if (g == 0) {
-                                h4v hi, lo;
-                                split_rne((f32x4){x, y, 1.0f, 0.0f}, neg1, hi, lo);
-                                *(h4v *)(HH + 2 * (pc * HP)) = hi;
-                                *(h4v *)(HL + 2 * (pc * HP)) = lo;
-                            }
-                        } else {
-                            // E_{l-1} = (W_l^T E_l) cos(2 pi z_{l-1}) r: the transposed operand straight from the row-major planes
-                            const char *Wh = lds + (last ? S::off_last(L) : S::off_hid(l)), *Wl = Wh + 2 * (last ? 16 : WP) * WPP;
-                            const float r = misc[16 + l - 1];
-                            const int e4 = n >> 2, q4 = n & 3;
-                            f32x4 gacc[MT];
+                for (int nt = 0; nt < NT; ++nt) E[nt][t] = mfma32(at, cat(el[nt], el[nt]), mfma32(at, cat(eh[nt], eh[nt]), zero4));
+            }
+            h8v A0, A1;
+            h4v uh[NT], ul[NT];
 #pragma unroll
-                            for (int it = 0; it < MT; ++it) {
-                                gacc[it] = zero4;
+            for (int nt = 0; nt < NT; ++nt) turn1(eh[nt], el[nt], uh[nt], ul[nt]);
+            A0 = cat(uh[0], NT == 2 ? uh[NT - 1] : ul[0]);
+            A1 = cat(ul[0], ul[NT - 1]);
+            const h8v ones = column(kColOut);
+            acc_b[0] = mfma32(A0, ones, acc_b[0]);
+            if (NT == 2) acc_b[0] = mfma32(A1, ones, acc_b[0]);
 #pragma unroll
-                                for (int jp = 0; jp < NP; ++jp) {
-                                    if (jp == 0 || !last) {
-                                        const int at = 2 * ((32 * jp + 4 * g + e4) * WPP + 16 * it + 4 * q4);
-                                        const bool two = 2 * jp + 1 < MT;     // rows past the layer's own: whatever follows in LDS, times an error of zero
-                                        const h8v ah = cat(read_tr(Wh + at), read_tr(Wh + at + 32 * WPP)), al = cat(read_tr(Wl + at), read_tr(Wl + at + 32 * WPP));
-                                        gacc[it] = mfma3(ah, al, cat(Eh[2 * jp], two ? Eh[2 * jp + 1] : zh), cat(El[2 * jp], two ? El[2 * jp + 1] : zh), gacc[it]);
-                                    }
-                                }
-                            }
-                            // the layer's input again (sine of the kept pre-activations) for the weight gradient, while the matrix steps run
+            for (int i = 0; i < MT; ++i) {
 #pragma unroll
-                            for (int t = 0; t < MT; ++t) {
-                                h4v hi, lo;
-                                split_rne(sin4(zst[l - 1][t]), neg1, hi, lo);
-                                const int at = 2 * (pc * HP + 16 * t + 4 * g);
-                                *(h4v *)(HH + at) = hi;
-                                *(h4v *)(HL + at) = lo;
-                            }
-                            // the unit of ones inside a tile: the padded unit there was written as 0 by the lane that owns it; that lane
-                            // makes it 1 (same lane, later store: program order)
-                            if (uo < WP && 4 * g == (uo & 12)) ((_Float16 *)HH)[pc * HP + uo] = (_Float16)1.0f;
+                for (int nt = 0; nt < NT; ++nt) turn(Bh[nt], Bl[nt], i, uh[nt], ul[nt]);
+                const h8v b0 = cat(uh[0], uh[NT - 1]), b1 = cat(ul[0], ul[NT - 1]);
+                acc_last[i] = mfma32(A0, b0, acc_last[i]);
+                acc_last[i] = mfma32(A0, b1, acc_last[i]);
+                if (NT == 2) acc_last[i] = mfma32(A1, b0, acc_last[i]);
+            }
 #pragma unroll
-                            for (int it = 0; it < MT; ++it) {
-                                const f32x4 z = zst[l - 1][it];
-                                const f32x4 c = {__builtin_amdgcn_cosf(z[0]), __builtin_amdgcn_cosf(z[1]), __builtin_amdgcn_cosf(z[2]), __builtin_amdgcn_cosf(z[3])};
-                                E[it] = gacc[it] * (c * r);
-                            }
-                        }
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int t = 0; t < MT; ++t) E[nt][t] *= cos4(zst[NH][nt][t]);
+        }
+
+        // ---- backward: the error goes down through the hidden layers, each layer's weight gradient takes these pixels
+        h8v A0[MT], A1[MT];                // the error turned: NT = 2: hi, lo; NT = 1: [hi | lo], unused
+        auto turn_error = [&](const h4v (&Eh)[NT][MT], const h4v (&El)[NT][MT]) {
+#pragma unroll
+            for (int t = 0; t < MT; ++t) {
+                h4v uh[NT], ul[NT];
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) turn(Eh[nt], El[nt], t, uh[nt], ul[nt]);
+                A0[t] = cat(uh[0], NT == 2 ? uh[NT - 1] : ul[0]);
+                A1[t] = cat(ul[0], ul[NT - 1]);
+            }
+        };
+#pragma unroll
+        for (int u = NH - 1; u >= 0; --u) {
+            if (u >= from) {
+                h4v Eh[NT][MT], El[NT][MT], Hh[NT][MT], Hl[NT][MT];
+                const char *const W = step(u, from, S::HID);
+                if (u == from) first(zst[u]);              // not kept from the forward pass: cheaper to form again than to hold
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int t = 0; t < MT; ++t) split_rtz(E[nt][t], neg1, Eh[nt][t], El[nt][t]);
+                f32x4 down[NT][MT];
+#pragma unroll
+                for (int t = 0; t < MT; ++t)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) down[nt][t] = contract<WP>(W + t * 1024, S::PLANE, Eh[nt], El[nt], zero4);
+                turn_error(Eh, El);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int t = 0; t < MT; ++t) split_rne(sin4(zst[u][nt][t]), neg1, Hh[nt][t], Hl[nt][t]);
+                const h8v ones = column(u);
+#pragma unroll
+                for (int t = 0; t < MT; ++t) {
+                    acc_b[t] = mfma32(A0[t], ones, acc_b[t]);
+                    if (NT == 2) acc_b[t] = mfma32(A1[t], ones, acc_b[t]);
+                }
+#pragma unroll
+                for (int i = 0; i < MT; ++i) {
+                    h4v uh[NT], ul[NT];
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) turn(Hh[nt], Hl[nt], i, uh[nt], ul[nt]);
+                    const h8v b0 = cat(uh[0], uh[NT - 1]), b1 = cat(ul[0], ul[NT - 1]);
+#pragma unroll
+                    for (int t = 0; t < MT; ++t) {
+                        acc[u][t][i] = mfma32(A0[t], b0, acc[u][t][i]);
+                        acc[u][t][i] = mfma32(A0[t], b1, acc[u][t][i]);
+                        if (NT == 2) acc[u][t][i] = mfma32(A1[t], b0, acc[u][t][i]);
                     }
                 }
-                __syncthreads();
-                int rot = 0;
+                // E_{l-1} = (r W_l^T E_l) cos(2 pi z_{l-1})
 #pragma unroll
-                for (int j = 0; j < PL; ++j) {
-                    const int l = lg - j;
-                    if (l >= 0 && l < L) {
-                        // dW_l += E_l H_l^T over the chunk's pixels: tile (rows ot, columns it), 32 pixels per matrix step
-                        {
-                            const bool last = l == L - 1;
-                            const int uo = ones_unit<WP>(a.d[l]);
-                            const char *const EH = EH0 + j * S::SET, *const EL = EL0 + j * S::SET, *const HH = HH0 + j * S::SET, *const HL = HL0 + j * S::SET;
-                            int nit = uo / 16 + 1;                           // column tiles up to the one with the unit of ones
-                            asm volatile("" : "+s"(nit));                  // a scalar, derived again per chunk: not a set of per-layer values held across the loop
-                            const int ntasks = (last ? 1 : MT) * nit;
-                            const int e4 = n >> 2, q4 = n & 3;
-                            // the group's layers start their round-robin over the wavefronts where the layer before stopped
-                            const int wv = (wave + kWaves - rot % kWaves) % kWaves;
-                            rot += ntasks;
+                for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                            for (int s = 0; s < GSLOTS; ++s) {
-                                const int task = wv + s * kWaves;
-                                if (task < ntasks) {
-                                    int ot = 0;
+                    for (int t = 0; t < MT; ++t) E[nt][t] = down[nt][t] * cos4(zst[u][nt][t]);
+            }
+        }
+        // ---- first layer: its input's columns are one, x, y
+        {
+            h4v Eh[NT][MT], El[NT][MT], h[NT], lo[NT];
 #pragma unroll
-                                    for (int q = 1; q < MT; ++q) ot += task >= q * nit ? 1 : 0;
-                                    const int it = task - ot * nit;
-                                    f32x4 d0 = zero4, d1 = zero4, d2 = zero4;        // one chain per term: the matrix steps of a tile do not wait for each other
+            for (int nt = 0; nt < NT; ++nt) {
 #pragma unroll
-                                    for (int k = 0; k < kPC / 32; ++k) {
-                                        const int px = 32 * k + 4 * g + e4;
-                                        const int ea = 2 * (px * EP + 16 * ot + 4 * q4), ha = 2 * (px * HP + 16 * it + 4 * q4);
-                                        const h8v eh = cat(read_tr(EH + ea), read_tr(EH + ea + 32 * EP)), el = cat(read_tr(EL + ea), read_tr(EL + ea + 32 * EP));
-                                        const h8v hh = cat(read_tr(HH + ha), read_tr(HH + ha + 32 * HP)), hl = cat(read_tr(HL + ha), read_tr(HL + ha + 32 * HP));
-                                        d0 = mfma32(eh, hh, d0);
-                                        d1 = mfma32(eh, hl, d1);
-                                        d2 = mfma32(el, hh, d2);
-                                    }
-                                    const f32x4 d = acc[l][s] + (d0 + (d1 + d2));
-                                    acc[l][s] = d;
-                                }
-                            }
-                        }
-                    }
-                }
-                __syncthreads();
+                for (int t = 0; t < MT; ++t) split_rtz(E[nt][t], neg1, Eh[nt][t], El[nt][t]);
+                h4v xh, xl;
+                split_rne((f32x4){1.0f, x[nt], y[nt], 0.0f}, neg1, xh, xl);
+                turn1(g == kColFirst / 4 ? xh : zh, g == kColFirst / 4 ? xl : zh, h[nt], lo[nt]);
+            }
+            turn_error(Eh, El);
+            const h8v b0 = cat(h[0], h[NT - 1]), b1 = cat(lo[0], lo[NT - 1]);
+#pragma unroll
+            for (int t = 0; t < MT; ++t) {
+                acc_b[t] = mfma32(A0[t], b0, acc_b[t]);
+                acc_b[t] = mfma32(A0[t], b1, acc_b[t]);
+                if (NT == 2) acc_b[t] = mfma32(A1[t], b0, acc_b[t]);
             }
         }
     }
-    const int L = a.L;
 
     // ---- loss of this step's parameters, and the error's size for the next step's scale
-    __shared__ float red[8];
     for (int off = 32; off > 0; off >>= 1) loss_part += __shfl_xor(loss_part, off, 64);
-    if (lane == 0) red[wave] = loss_part;
+    if (lane == 0) misc->red[wave] = loss_part;
     __syncthreads();
     if (tid == 0) {
         float s = 0.0f;
-        for (int w = 0; w < kWaves; ++w) s += red[w];
+        for (int w = 0; w < kWaves; ++w) s += misc->red[w];
         fit_put_loss(a, share, s);
     }
 
-    // ---- every gradient entry is in exactly one lane: Adam in place, or the entry handed out
+    // ---- the wavefronts' gradients are added up, GT tiles at a time through LDS (in a fixed order), and each entry handed out
+    f32x4 *const R = (f32x4 *)(lds + S::W0);
+    constexpr int kTiles = 2 * MT + NH * MT * MT;
+    const int first_hid = 2 * MT + skip * MT * MT;      // tiles of the steps that the model leaves out are not there
 #pragma unroll
-    for (int lg = ML - 1; lg >= 0; lg -= PL) {
-        int rot = 0;
+    for (int b0 = 0; b0 < kTiles; b0 += S::GT) {
+        if (b0 < 2 * MT || b0 + S::GT > first_hid) {
 #pragma unroll
-        for (int j = 0; j < PL; ++j) {
-            const int l = lg - j;
-            if (l >= 0 && l < L) {
-                const int nit = ones_unit<WP>(a.d[l]) / 16 + 1, ntasks = (l == L - 1 ? 1 : MT) * nit;
-                const int wv = (wave + kWaves - rot % kWaves) % kWaves;        // the same owner as in the loop above
-                rot += ntasks;
-                const float gs = misc[l];
+            for (int q = 0; q < S::GT; ++q) {
+                const int at = b0 + q, h = at - 2 * MT;
+                if (at < kTiles)
+                    R[(wave * S::GT + q) * 64 + lane] = at < MT ? acc_b[at] : (at < 2 * MT ? acc_last[at - MT] : acc[h / (MT * MT)][h / MT % MT][h % MT]);
+            }
+            __syncthreads();
+            for (int q = wave; q < S::GT && b0 + q < kTiles; q += kWaves) {
+                const int at = b0 + q, h = at - 2 * MT;
+                if (h >= 0 && at < first_hid) continue;
+                f32x4 s = R[q * 64 + lane];
 #pragma unroll
-                for (int s = 0; s < GSLOTS; ++s) {
-                    const int task = wv + s * kWaves;
-                    if (task < ntasks) {
-                        int ot = 0;
+                for (int w = 1; w < kWaves; ++w) s += R[(w * S::GT + q) * 64 + lane];
+                // layer, row tile, and which column of its matrix this lane's column is (din: the bias, -1: none)
+                int l = L - 1, ot = 0, col;
+                if (at < MT) {
+                    ot = at;
+                    l = n < NH ? n - skip + 1 : (n == kColOut ? L - 1 : 0);
+                    col = n < NH ? (n >= skip ? misc->d[l] : -1) : (n == kColOut ? misc->d[l] : (n >= kColFirst && n < kColFirst + 3 ? (n + 2 - kColFirst) % 3 : -1));
+                    if (col < 0) l = 0;
+                } else if (at < 2 * MT) {
+                    col = (at - MT) * 16 + n;
+                } else {
+                    l = h / (MT * MT) - skip + 1;
+                    ot = h / MT % MT;
+                    col = h % MT * 16 + n;
+                }
+                const int din = misc->d[l], dout = misc->d[l + 1], off = misc->p_off[l];
+                if (at >= MT && col >= din) col = -1;
+                const float gs = misc->grad[l];
 #pragma unroll
-                        for (int q = 1; q < MT; ++q) ot += task >= q * nit ? 1 : 0;
-                        const int it = task - ot * nit;
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) {
-                            const int at = param_index<WP>(a, l, ot * 16 + 4 * g + v, it * 16 + n);
-                            if (at >= 0) fit_put_grad(a, share, at, acc[l][s][v] * gs);
-                        }
-                    }
+                for (int v = 0; v < 4; ++v) {
+                    const int row = ot * 16 + 4 * g + v, o = l == L - 1 ? (ot == 0 && v == 0 ? g : dout) : row;
+                    if (col >= 0 && o < dout) fit_put_grad(a, share, off + (col == din ? dout * din + o : o * din + col), s[v] * gs);
                 }
             }
+            __syncthreads();
         }
     }
 }

@@ -83,6 +83,24 @@ def test_loss_and_gradient(name, masked, family):
     f.close()
 
 
+@pytest.mark.parametrize("width,L", [(16, 2), (16, 4), (15, 5), (16, 7), (16, 8), (12, 12), (31, 4), (32, 5), (32, 6), (17, 7), (32, 8), (29, 9),
+                                     (32, 12), (47, 4), (33, 5), (48, 7), (48, 8), (48, 10), (64, 2), (64, 3), (49, 4), (64, 5), (64, 6)])
+def test_split_kernels_at_the_edges_of_their_depth_buckets(width, L):
+    """Every depth bucket at its deepest model and at the first one past the bucket before it, gradient against the oracle."""
+    widths, H, W, n = [2] + [width] * (L - 1) + [3], 9, 15, 2
+    p0 = synth.init_params(41, widths, n)
+    tgt, tgt_d = targets_of(43, n, H, W)
+    f = rinr_fit.Fit(widths, n, H, W)
+    assert f.kernel_family == rinr_fit.KERNEL_SPLIT16
+    f.set_params(p0)
+    loss, grad = f.loss_grad(tgt_d)
+    f.close()
+    for i in range(n):
+        want_loss, want_g = fo.loss_grad(widths, p0[i].astype(np.float64), tgt[i], None)
+        assert abs(loss[i] - want_loss) <= 2e-5 * want_loss
+        assert np.abs(grad[i] - want_g).max() <= 2e-5 * np.abs(want_g).max()
+
+
 @pytest.mark.parametrize("family", list(FAMILIES))
 @pytest.mark.parametrize("widths,n,H,W", [([2, 15, 15, 3], 40000, 7, 9), ([2, 40, 40, 3], 4200, 9, 15), ([2, 30, 3], 20000, 5, 26)])
 def test_many_images_and_few_agree_with_the_oracle(widths, n, H, W, family):
