@@ -282,9 +282,11 @@ extern "C" int rinr_store_open_ex(const void *device_blob, const void *host_blob
     for (const IndexEntry &e : s->index) {
         const uint32_t c = e.width == 0 ? 1u : (e.width + 15u) >> 4;
         for (int z = 0; z < kSizes; ++z) {
-            if (resident_fits(s->fit_form[z], c, e.n_layers, e.nbytes, (uint32_t)tile_rows, budget)) {
+            if (resident_fits(s->fit_form[z], c, e.n_layers, e.nbytes, (uint32_t)tile_rows, budget - 16u)) {
                 ++s->n_res[z][c];
-                s->res_lds[z][c] = std::max(s->res_lds[z][c], resident_bytes(s->fit_form[z], c, e.n_layers, (uint32_t)tile_rows) + e.nbytes);
+                // with the packed record staged behind the expanded weights where the budget holds both, and the tile counter
+                const uint32_t need = resident_bytes(s->fit_form[z], c, e.n_layers, (uint32_t)tile_rows) + 16u;
+                s->res_lds[z][c] = std::max(s->res_lds[z][c], need + e.nbytes <= budget ? need + e.nbytes : need);
             } else {
                 ++s->n_str[z][c];
                 s->str_layers[z][c] = std::max<uint32_t>(s->str_layers[z][c], e.n_layers);
@@ -415,7 +417,7 @@ extern "C" int rinr_decode_batch_ex(rinr_store *s, const int64_t *image_ids, int
     a.normalize = (opts->flags & RINR_FLAG_NORMALIZE) ? 1u : 0u;
     a.tile_rows_wide = (uint32_t)s->tile_rows_wide;
     a.vec_store = (HW % 4 == 0 && ((uintptr_t)a.out_f32 & 15) == 0 && ((uintptr_t)a.out_u8 & 3) == 0) ? 1u : 0u;
-    a.lds_budget = s->lds_budget;
+    a.lds_budget = s->lds_budget - 16u;      // what a model may take: the tile counter sits behind it
     for (int c = 0; c < 3; ++c) {
         a.ns[c] = a.normalize ? opts->norm_scale[c] : 1.0f;
         a.nb[c] = a.normalize ? opts->norm_shift[c] : 0.0f;

@@ -92,109 +92,144 @@ template <int TM, int WP> struct Layout {
 };
 
 // ---- expand + dequantise (Sec. IV-A mask, Sec. IV-B codes) -----------------------------
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t x, int lane) {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const uint32_t y = __shfl_up(x, d, 64);
-        if (lane >= d) x += y;
-    }
+// Inclusive sum over the lanes of each row of 16, by data-parallel moves (a register move each, no LDS).
+__device__ __forceinline__ uint32_t row_incl_sum(uint32_t x) {
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x111, 0xf, 0xf, true);     // row_shr 1, 2, 4, 8; lanes shifted in count 0
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x112, 0xf, 0xf, true);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x114, 0xf, 0xf, true);
+    x += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x118, 0xf, 0xf, true);
     return x;
+}
+__device__ __forceinline__ uint32_t lane_value(uint32_t x, int l) { return (uint32_t)__builtin_amdgcn_readlane((int)x, l); }
+__device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
+    const uint32_t r = row_incl_sum(x);
+    return lane_value(r, 15) + lane_value(r, 31) + lane_value(r, 47) + lane_value(r, 63);
 }
 
 __device__ __forceinline__ uint32_t take_code(const uint32_t *cs, uint32_t rank, uint32_t cb) {
-    const uint32_t bit = rank * cb;
+    const uint32_t bit = __umul24(rank, cb);
     const uint32_t w = bit >> 5, sh = bit & 31;
     const uint64_t two = (uint64_t)cs[w] | ((uint64_t)cs[w + 1] << 32);
     const uint32_t m = cb == 32 ? 0xFFFFFFFFu : ((1u << cb) - 1u);
     return (uint32_t)(two >> sh) & m;
 }
 
-__device__ __forceinline__ uint32_t wave_sum(uint32_t x) {
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) x += __shfl_xor(x, d, 64);
-    return x;
-}
-
-// The weights of a model are cut into blocks of 64 consecutive flat indices, layer after layer, and the workgroup's
-// wavefronts share the blocks of the layers at hand (the whole model, or one group of its layers) evenly: wavefront w
-// of nw takes blocks [B w / nw, B (w + 1) / nw) of the B blocks counted over those layers, so a wavefront touches one
-// or two layers whatever the depth and the widths.
-struct ExpandShare {
-    uint32_t g0, g1;      // this wavefront's range of blocks, counted over all layers
-    uint32_t base;        // blocks of the layers before the one at hand (advanced by expand_layer)
+// A layer's weights are taken in passes of a wavefront: a power of two of lanes (at least n_in) per row of the matrix, as many rows
+// as that leaves room for (one of 33..64 inputs, four of 9..16), one weight per lane.  A lane's column is then the same in
+// every pass, so where its weight goes is one multiply-add per pass and not a division and a walk through the layout (per
+// 64 weights about 30 vector instructions instead of 60).  The workgroup's wavefronts share the passes of the layers at hand (the whole model, or
+// one group [l0, l1) of its layers) evenly: wavefront w of nw takes passes [B w / nw, B (w + 1) / nw) of the B passes counted over
+// those layers, so a wavefront touches one or two layers whatever the depth and the widths.
+// Every wavefront holds the layer records in its lanes, lane l the record of layer l (16 at most), so what a layer is takes a
+// lane read, not a chain of memory reads, and sums over the layers are a few register moves.
+struct LaneLayers {
+    uint32_t io, kind, mask_off, code_off, bias_off;    // LayerRec: n_in | n_out << 16, bits | has_mask << 8, offsets
+    float scale;
+    int32_t zp;
+    uint32_t passes, upto;                              // passes of the layer (0 outside the group), of the group's layers up to and with it
+    uint32_t g0, g1;                                    // this wavefront's range of passes
 };
-__device__ __forceinline__ ExpandShare expand_share(const uint32_t *rec, int l0, int l1, int wave, int nwaves) {
-    uint32_t total = 0;
-    for (int l = l0; l < l1; ++l) {
-        const LayerRec *r = (const LayerRec *)(rec + l * (sizeof(LayerRec) / 4));
-        total += ((uint32_t)r->n_in * r->n_out + 63) >> 6;
-    }
-    ExpandShare s;
-    s.g0 = total * (uint32_t)wave / (uint32_t)nwaves;
-    s.g1 = total * (uint32_t)(wave + 1) / (uint32_t)nwaves;
-    s.base = 0;
-    return s;
+
+__device__ __forceinline__ uint32_t row_bits(uint32_t n_in) { return n_in > 1u ? 32u - (uint32_t)__clz(n_in - 1u) : 0u; }   // 2^that lanes per row
+
+// HIDDEN: passes of a hidden layer where they are of another kind (0: as above)
+template <int HIDDEN = 0>
+__device__ __forceinline__ LaneLayers lane_layers(const uint8_t *record, int L, int l0, int l1, int lane, int wave, int nwaves) {
+    LaneLayers t;
+    const int l = lane < L ? lane : L - 1;
+    const uint4 a = ((const uint4 *)record)[2 * l], b = ((const uint4 *)record)[2 * l + 1];
+    t.io = a.x; t.kind = a.y; t.scale = __uint_as_float(a.z); t.zp = (int32_t)a.w;
+    t.mask_off = b.y; t.code_off = b.z; t.bias_off = b.w;
+    const uint32_t rows = 64u >> row_bits(a.x & 0xFFFFu);
+    t.passes = lane >= l0 && lane < l1 ? (HIDDEN && lane > 0 && lane < L - 1 ? (uint32_t)HIDDEN : ((a.x >> 16) + rows - 1u) / rows) : 0u;
+    t.upto = row_incl_sum(t.passes);
+    const uint32_t total = lane_value(t.upto, 15);
+    t.g0 = total * (uint32_t)wave / (uint32_t)nwaves;
+    t.g1 = total * (uint32_t)(wave + 1) / (uint32_t)nwaves;
+    return t;
 }
 
-// This wavefront's part of one layer, one weight per lane.  `rec` is the model record (words; the staged copy in LDS,
+// This wavefront's part of one layer.  `rec` is the model record (words; the staged copy in LDS,
 // or the record itself in global memory).  Over the workgroup, put(o, i, w, q) receives every KEPT weight of the true
 // n_out x n_in matrix exactly once: w the fp32 value and q the integer code - zp of a coded layer (0 for fp32 layers);
 // pruned weights are not reported (the caller's area starts out as zeros); putb(o, b) receives every bias (from the
-// wavefront that holds the layer's first block).  A kept weight's code is found by its rank among the kept ones: the
-// count before the wavefront's first block by one reduction over the mask words, then, per block of 64 weights, the
-// block's keep bits as one 64-bit lane mask (a ballot), the lane's rank by a masked bit count, and the running count in
-// a scalar register.
-template <class PutW, class PutB>
-__device__ __forceinline__ void expand_layer(const uint32_t *rec, const LayerRec &r, int lane, ExpandShare &sh, PutW put, PutB putb) {
-    const uint32_t n_in = r.n_in, cnt = (uint32_t)r.n_in * r.n_out;
-    const uint32_t nwords = (cnt + 31) >> 5, nblocks = (cnt + 63) >> 6;
-    const uint32_t first = sh.base, last = sh.base + nblocks;
-    sh.base = last;
-    if (sh.g1 <= first || sh.g0 >= last) return;
-    const uint32_t b0 = sh.g0 > first ? sh.g0 - first : 0u, b1 = (sh.g1 < last ? sh.g1 : last) - first;
-    const uint32_t *mw = rec + (r.mask_off >> 2);
-    const uint32_t *cs = rec + (r.code_off >> 2);
-    const uint32_t cb = r.bits ? r.bits : 32u;
-    const uint32_t magic = n_in > 1 ? 0xFFFFFFFFu / n_in + 1u : 0u;     // ceil(2^32 / n_in): k / n_in == umulhi(k, magic) for k < 2^16
-    const bool has_mask = r.has_mask != 0;
-    uint32_t running = 0;
-    if (b0) {
+// wavefront that holds the layer's first pass).  A kept weight's code is found by its rank among the kept ones: the
+// count before the wavefront's first pass by one reduction over the mask words, then, per pass, the keep bits as one 64-bit
+// lane mask (a ballot), the lane's rank by a masked bit count, and the running count in a scalar register.  The reads of U
+// passes are in flight together.
+template <int U, class PutW, class PutB>
+__device__ __forceinline__ void expand_layer(const uint32_t *rec, const LaneLayers &t, int l, int lane, PutW put, PutB putb) {
+    const uint32_t last = lane_value(t.upto, l), first = last - lane_value(t.passes, l);
+    if (t.g1 <= first || t.g0 >= last) return;
+    const uint32_t io = lane_value(t.io, l), kind = lane_value(t.kind, l), n_in = io & 0xFFFFu, n_out = io >> 16;
+    const bool has_mask = (kind >> 8 & 0xFFu) != 0, coded = (kind & 0xFFu) != 0;
+    const uint32_t cb = coded ? kind & 0xFFu : 32u;
+    const float scale = __uint_as_float(lane_value(__float_as_uint(t.scale), l));
+    const int32_t zp = (int32_t)lane_value((uint32_t)t.zp, l);
+    const uint32_t *mw = rec + (lane_value(t.mask_off, l) >> 2);
+    const uint32_t *cs = rec + (lane_value(t.code_off, l) >> 2);
+    const uint32_t p0 = t.g0 > first ? t.g0 - first : 0u, p1 = (t.g1 < last ? t.g1 : last) - first;
+    const uint32_t lg = row_bits(n_in), rows = 64u >> lg;
+    const uint32_t i = (uint32_t)lane & ((1u << lg) - 1u);
+    uint32_t o = p0 * rows + ((uint32_t)lane >> lg), k = o * n_in + i;         // row and flat index of the lane's weight
+    const uint32_t k0 = p0 * rows * n_in;                                   // weights before the wavefront's first pass
+    uint32_t running = k0;
+    if (has_mask && p0) {
+        uint32_t part = 0;
+        for (uint32_t wi = lane; wi <= k0 >> 5; wi += 64) part += __popc(mw[wi] & (wi == k0 >> 5 ? (1u << (k0 & 31u)) - 1u : 0xFFFFFFFFu));
+        running = wave_sum(part);
+    }
+    // Straight-line: lanes without a weight read a word or a code that is there (the mask's last word, the first code) and drop it,
+    // since a branch around a read costs more than the read.  With no code kept in U passes there may be none at all: skipped.
+    const uint32_t lane_rows = i < n_in ? n_out : 0u;                       // o < lane_rows: the lane has a weight
+    const uint32_t last_word = (n_in * n_out - 1u) >> 5;
+    for (uint32_t p = p0; p < p1; p += U) {
+        uint32_t word[U], rank[U], code[U];
+        bool kept[U];
+        const uint32_t before = running;
         if (has_mask) {
-            uint32_t part = 0;
-            for (uint32_t wi = lane; wi < 2 * b0; wi += 64) part += __popc(wi < nwords ? mw[wi] : 0u);
-            running = (uint32_t)__builtin_amdgcn_readfirstlane((int)wave_sum(part));
+#pragma unroll
+            for (int j = 0; j < U; ++j) word[j] = mw[min((k + j * rows * n_in) >> 5, last_word)];
         } else {
-            running = b0 << 6;          // dense: every weight before the block is kept (b0 < nblocks, so all of them exist)
+#pragma unroll
+            for (int j = 0; j < U; ++j) word[j] = 0xFFFFFFFFu;
         }
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            const uint32_t end = p + j < p1 ? lane_rows : 0u;
+            kept[j] = o + j * rows < end && (word[j] >> ((k + j * rows * n_in) & 31u) & 1u);
+            const uint64_t keep64 = __ballot(kept[j]);
+            rank[j] = __builtin_amdgcn_mbcnt_hi((uint32_t)(keep64 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)keep64, running));
+            running += (uint32_t)__popcll(keep64);
+            rank[j] = kept[j] ? rank[j] : 0u;
+        }
+        if (running != before) {
+            if (cb == 8u) {
+#pragma unroll
+                for (int j = 0; j < U; ++j) code[j] = ((const uint8_t *)cs)[rank[j]];
+            } else if (cb == 32u) {
+#pragma unroll
+                for (int j = 0; j < U; ++j) code[j] = cs[rank[j]];
+            } else if (cb == 16u) {
+#pragma unroll
+                for (int j = 0; j < U; ++j) code[j] = ((const uint16_t *)cs)[rank[j]];
+            } else {
+#pragma unroll
+                for (int j = 0; j < U; ++j) code[j] = take_code(cs, rank[j], cb);
+            }
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                const int32_t q = coded ? (int32_t)code[j] - zp : 0;
+                const float w = coded ? scale * (float)q : __uint_as_float(code[j]);
+                if (kept[j]) put((int)(o + j * rows), (int)i, w, q);
+            }
+        }
+        o += U * rows;
+        k += U * rows * n_in;
     }
-    for (uint32_t b = b0; b < b1; ++b) {
-        const uint32_t k = (b << 6) + (uint32_t)lane;
-        bool kept = k < cnt;
-        if (has_mask) {
-            const uint32_t wi = k >> 5;
-            const uint32_t word = wi < nwords ? mw[wi] : 0u;      // bits past the layer's end are zero in a valid record
-            kept = (word >> ((uint32_t)lane & 31u)) & 1u;
-        }
-        const uint64_t keep64 = __ballot(kept);
-        const uint32_t rank = __builtin_amdgcn_mbcnt_hi((uint32_t)(keep64 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)keep64, running));
-        running += (uint32_t)__popcll(keep64);
-        if (kept) {
-            uint32_t code;
-            if (cb == 8u) code = ((const uint8_t *)cs)[rank];
-            else if (cb == 32u) code = cs[rank];
-            else if (cb == 16u) code = ((const uint16_t *)cs)[rank];
-            else code = take_code(cs, rank, cb);
-            const uint32_t o = n_in == 1 ? k : __umulhi(k, magic), i = k - o * n_in;
-            float val;
-            int32_t q = 0;
-            if (r.bits) { q = (int32_t)code - r.zp; val = r.scale * (float)q; }
-            else val = __uint_as_float(code);
-            put((int)o, (int)i, val, q);
-        }
-    }
-    if (b0 == 0) {
-        const float *bias = (const float *)(rec + (r.bias_off >> 2));
-        for (uint32_t o = (uint32_t)lane; o < r.n_out; o += 64u) putb((int)o, bias[o]);
+    if (p0 == 0) {
+        const float *bias = (const float *)(rec + (lane_value(t.bias_off, l) >> 2));
+        for (uint32_t b = (uint32_t)lane; b < n_out; b += 64u) putb((int)b, bias[b]);
     }
 }
 
@@ -202,26 +237,24 @@ __device__ __forceinline__ void expand_layer(const uint32_t *rec, const LayerRec
 // weights and biases of the sine layers (w0 / 2pi, so that the pre-activation is in
 // revolutions); the output layer is never scaled.  Ends with a workgroup barrier.
 template <int TM, int WP>
-__device__ __forceinline__ void expand_model(float *lds, const uint32_t *rec, int L, float pre, int tid, int nthreads) {
+__device__ __forceinline__ void expand_model(float *lds, const uint32_t *rec, const LaneLayers &t, int L, float pre, int tid, int nthreads) {
     typedef Layout<TM, WP> LY;
     const int total = LY::total(L);
     for (int q = tid; q < total; q += nthreads) lds[q] = 0.0f;
     __syncthreads();
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, nwaves = nthreads >> 6;
-    ExpandShare sh = expand_share(rec, 0, L, wave, nwaves);
+    const int lane = tid & 63;
     for (int l = 0; l < L; ++l) {
-        const LayerRec r = *(const LayerRec *)(rec + l * (sizeof(LayerRec) / 4));
         if (l == L - 1) {
             float *w = lds + LY::off_out(L), *b = lds + LY::off_outb(L);
-            expand_layer(rec, r, lane, sh, [=](int o, int i, float v, int) { w[LY::idx_out(o, i)] = v; },
+            expand_layer<1>(rec, t, l, lane, [=](int o, int i, float v, int) { w[LY::idx_out(o, i)] = v; },
                          [=](int o, float v) { b[o] = v; });
         } else if (l == 0) {
             float *w = lds + LY::off_first(), *b = lds + LY::off_bias(0);
-            expand_layer(rec, r, lane, sh, [=](int o, int i, float v, int) { w[LY::idx_first(o, i)] = v * pre; },
+            expand_layer<1>(rec, t, l, lane, [=](int o, int i, float v, int) { w[LY::idx_first(o, i)] = v * pre; },
                          [=](int o, float v) { b[LY::idx_bias(o)] = v * pre; });
         } else {
             float *w = lds + LY::off_hidden(L, l), *b = lds + LY::off_bias(l);
-            expand_layer(rec, r, lane, sh, [=](int o, int i, float v, int) { w[LY::idx_hidden(o, i)] = v * pre; },
+            expand_layer<1>(rec, t, l, lane, [=](int o, int i, float v, int) { w[LY::idx_hidden(o, i)] = v * pre; },
                          [=](int o, float v) { b[LY::idx_bias(o)] = v * pre; });
         }
     }
@@ -230,7 +263,11 @@ __device__ __forceinline__ void expand_model(float *lds, const uint32_t *rec, in
 
 // ---- which models are decoded from a resident copy -----------------------------------------------
 // A model is resident when its expanded weights and the staged copy of its packed record fit the LDS of one
-// workgroup together; the host (launch sizes) and the kernels (which workgroups a launch serves) use this one rule.
+// workgroup together.  In the split-precision kernels' two-block form, whose records are as large as what they expand to (fp32
+// or 16-bit hidden layers: 64 units stop fitting at 7 layers instead of 11), the expanded weights alone have to fit, and are
+// expanded from the record in global memory where the launch has no room to stage it (64 images of 224 x 224, 7 layers x 64
+// of fp32 weights: streamed 2070 us, resident 338).  The host (launch sizes) and the kernels (which workgroups a launch
+// serves) use this one rule.
 constexpr uint32_t kLdsLimit = 160 * 1024;   // LDS per workgroup on gfx950
 enum { kFitFp32 = 0,        // fp32 kernels: 4 bytes per padded weight
        kFitXdlOne = 1,      // split-precision kernels, one fp16 block per hidden layer (2..8-bit layers, or fp16 weights)
@@ -250,7 +287,7 @@ __host__ __device__ inline uint32_t resident_bytes(uint32_t form, uint32_t cls, 
 }
 __host__ __device__ inline bool resident_fits(uint32_t form, uint32_t cls, uint32_t L, uint32_t rec_bytes, uint32_t tile_rows_wide,
                                               uint32_t budget) {
-    return (uint64_t)resident_bytes(form, cls, L, tile_rows_wide) + rec_bytes <= budget;
+    return (uint64_t)resident_bytes(form, cls, L, tile_rows_wide) + (form == kFitXdlTwo ? 0u : rec_bytes) <= budget;
 }
 
 // ---- decode kernel ---------------------------------------------------------------------------
@@ -268,7 +305,7 @@ struct DecodeArgs {
     float pre;                    // w0 / (2 pi)
     uint32_t chunks;              // workgroups per slot
     uint32_t tiles_per_chunk;     // 64-pixel tiles per workgroup
-    uint32_t lds_bytes;           // dynamic LDS of this launch; a resident model's packed record is staged at its end
+    uint32_t lds_bytes;           // dynamic LDS of this launch; a resident model's packed record is staged at its end if both fit
     uint32_t cls;                 // width class this launch serves (padded width / 16); 0 = every class
     uint32_t stream_mode;         // 0: every model of the store is decoded from a resident expanded copy;
                                   // 1: this launch skips the models too deep for that; 2: this launch decodes only those,
@@ -528,17 +565,17 @@ __device__ __forceinline__ void decode_body(const DecodeArgs &a, const Work &w, 
     const IndexEntry e = w.e;
     const int L = e.n_layers;
 
-    // ---- stage the packed record at the end of the workgroup's LDS, expand it at the start
-    uint32_t *stage = (uint32_t *)((char *)lds + (a.lds_bytes - e.nbytes));
+    // ---- the packed record at the end of the workgroup's LDS, expanded at the start
+    const uint8_t *record = a.blob + e.off;
+    const uint32_t room = a.lds_bytes - 16u;                     // behind it: the tile counter
     {
-        const uint4 *src = (const uint4 *)(a.blob + e.off);
-        uint4 *dst = (uint4 *)stage;
-        for (uint32_t q = tid; q < (e.nbytes >> 4); q += nthreads) dst[q] = src[q];
+        const LaneLayers t = lane_layers(record, L, 0, L, tid & 63, __builtin_amdgcn_readfirstlane(tid >> 6), nthreads >> 6);
+        uint32_t *stage = (uint32_t *)((char *)lds + (room - e.nbytes));
+        for (uint32_t q = tid; q < (e.nbytes >> 4); q += nthreads) ((uint4 *)stage)[q] = ((const uint4 *)record)[q];
+        expand_model<TM, WP>(lds, stage, t, L, a.pre, tid, nthreads);   // zero-fill barrier orders the staging too
     }
-    expand_model<TM, WP>(lds, stage, L, a.pre, tid, nthreads);   // zero-fill barrier orders the staging too
-    // Tiles are handed out through a counter in LDS (the first word of the staging area, dead by
-    // now): wavefronts sharing a SIMD do not progress at the same rate.
-    uint32_t *next_tile = stage;
+    // Tiles are handed out through a counter in LDS: wavefronts sharing a SIMD do not progress at the same rate.
+    uint32_t *next_tile = (uint32_t *)((char *)lds + room);
     if (tid == 0) *next_tile = tile0 + (nthreads >> 6);
     __syncthreads();
 
@@ -568,18 +605,17 @@ __device__ __forceinline__ void decode_body(const DecodeArgs &a, const Work &w, 
 // One layer into a slot of the streamed layout: the layer's weights in the resident layout's order at the slot's
 // start, its bias tile HIDDEN floats in (the first and the output layer use less of the slot).
 template <int TM, int WP>
-__device__ __forceinline__ void expand_slot(float *wb, const uint32_t *rec, int L, int l, float pre, int lane, ExpandShare &sh) {
+__device__ __forceinline__ void expand_slot(float *wb, const uint32_t *rec, const LaneLayers &t, int L, int l, float pre, int lane) {
     typedef Layout<TM, WP> LY;
-    const LayerRec r = *(const LayerRec *)(rec + l * (sizeof(LayerRec) / 4));
     float *bb = wb + LY::HIDDEN;
     if (l == L - 1)
-        expand_layer(rec, r, lane, sh, [=](int o, int i, float v, int) { wb[LY::idx_out(o, i)] = v; },
+        expand_layer<1>(rec, t, l, lane, [=](int o, int i, float v, int) { wb[LY::idx_out(o, i)] = v; },
                      [=](int o, float v) { bb[o] = v; });
     else if (l == 0)
-        expand_layer(rec, r, lane, sh, [=](int o, int i, float v, int) { wb[LY::idx_first(o, i)] = v * pre; },
+        expand_layer<1>(rec, t, l, lane, [=](int o, int i, float v, int) { wb[LY::idx_first(o, i)] = v * pre; },
                      [=](int o, float v) { bb[LY::idx_bias(o)] = v * pre; });
     else
-        expand_layer(rec, r, lane, sh, [=](int o, int i, float v, int) { wb[LY::idx_hidden(o, i)] = v * pre; },
+        expand_layer<1>(rec, t, l, lane, [=](int o, int i, float v, int) { wb[LY::idx_hidden(o, i)] = v * pre; },
                      [=](int o, float v) { bb[LY::idx_bias(o)] = v * pre; });
 }
 
@@ -615,8 +651,8 @@ __device__ __forceinline__ void decode_stream_body(const DecodeArgs &a, const Wo
             __syncthreads();                                           // every wavefront is done with the previous group
             for (int q = tid; q < (l1 - l0) * SLOT; q += nthreads) lds[q] = 0.0f;
             __syncthreads();
-            ExpandShare sh = expand_share(rec, l0, l1, wave, nwaves);
-            for (int l = l0; l < l1; ++l) expand_slot<TM, WP>(lds + (l - l0) * SLOT, rec, L, l, pre, lane, sh);
+            const LaneLayers t = lane_layers((const uint8_t *)rec, L, l0, l1, lane, wave, nwaves);
+            for (int l = l0; l < l1; ++l) expand_slot<TM, WP>(lds + (l - l0) * SLOT, rec, t, L, l, pre, lane);
             __syncthreads();
             if (!active) continue;
             for (int l = l0; l < l1; ++l) {
@@ -685,8 +721,8 @@ __global__ __launch_bounds__(256) void dequant_debug_kernel(const uint8_t *blob,
     const uint32_t *rec = (const uint32_t *)(blob + e.off);
     for (int q = tid; q < SLOT; q += nthreads) lds[q] = 0.0f;
     __syncthreads();
-    ExpandShare sh = expand_share(rec, layer, layer + 1, wave, nwaves);
-    expand_slot<TM, WP>(lds, rec, L, layer, 1.0f, lane, sh);
+    const LaneLayers t = lane_layers((const uint8_t *)rec, L, layer, layer + 1, lane, wave, nwaves);
+    expand_slot<TM, WP>(lds, rec, t, L, layer, 1.0f, lane);
     __syncthreads();
     const LayerRec r = *(const LayerRec *)(rec + layer * (sizeof(LayerRec) / 4));
     const int n_in = r.n_in, cnt = r.n_in * r.n_out;

@@ -73,7 +73,8 @@ template <int TM, int WP> struct XLayout {
     static constexpr int NQ = WP / (4 * G);        // quads per lane over the layer's rows
     static constexpr int KJ = NQ / 2;              // full k-steps (8 halfs per lane) of a hidden layer
     static constexpr int K16 = NQ % 2;             // plus one half-depth step for an odd last quad (TM = 16 only)
-    static constexpr int TABLE = 16 * 16;          // bytes: one XLayer per linear layer, 16 at most
+    static constexpr int SELECT = 16 * 16;         // bytes: one XLayer per linear layer, 16 at most; then the 16 byte selectors of expand_hidden
+    static constexpr int TABLE = SELECT + 16 * 4;
     static constexpr int HID = WP * WP * 2;        // bytes of one hidden operand block
     static constexpr int FIRST = G * MT * 64 * 16; // bytes: [pixel tile q][mt][lane][8 halfs], hi and lo in one k-step; variant q has the
                                                    // weights in lane group q's k-slots only, so that group q's coordinates alone count
@@ -117,15 +118,15 @@ template <int TM, int WP> struct XLayout {
 __host__ __device__ inline uint32_t xdl_model_bytes(int cls, int n_layers, int n_int, int n_raw) {
     const uint32_t tm = (uint32_t)xdl_tile_rows(cls), wp = 16u * cls, g = 64u / tm, nq = wp / (4u * g);
     const uint32_t out = (nq / 2) * 1024u + (nq % 2) * 512u;
-    return 16u * 16u + ((uint32_t)(n_layers - 1) * wp + tm) * 4u + g * (wp / tm) * 1024u +
+    return 16u * 16u + 16u * 4u + ((uint32_t)(n_layers - 1) * wp + tm) * 4u + g * (wp / tm) * 1024u +
            wp * wp * 2u * (uint32_t)(n_int + 2 * n_raw) + 2u * out;
 }
 
 // Builds the operand blocks of layers [l0, l1) in LDS and their XLayer entries tab[l].  `rec` is the model record:
-// the staged copy in LDS, or the record itself in global memory.
+// the staged copy in LDS, or the record itself in global memory; `t` its layer records in the lanes.
 //   SLOTTED == false (resident model, l0 = 0, l1 = L): table, all bias tiles, then the blocks back to back.
 //   SLOTTED == true  (streamed model): table, then one fixed-size slot per layer of the group: bias tile, blocks.
-// zero_bytes from the start of LDS are cleared first (padding rows and columns, pruned weights).  Ends with a barrier.
+// Ends with a barrier.
 template <int TM, int WP> struct XSlot {
     typedef XLayout<TM, WP> LY;
     static constexpr int BLOCKS = 2 * LY::HID > LY::FIRST ? (2 * LY::HID > 2 * LY::OUT ? 2 * LY::HID : 2 * LY::OUT)
@@ -134,46 +135,182 @@ template <int TM, int WP> struct XSlot {
     static constexpr int BYTES = BIAS + BLOCKS;
 };
 
-template <int TM, int WP, bool W16, bool SLOTTED>
-__device__ __forceinline__ void xdl_expand_layers(char *lds, const uint32_t *rec, int L, int l0, int l1, float pre, int tid,
-                                                  int nthreads, uint32_t zero_bytes) {
+// This wavefront's part of a hidden layer, four consecutive inputs of one output per lane: exactly one 8-byte word of the operand block,
+// written whole, pruned weights and the padding up to WP x WP included, so nothing has to be cleared first.  A lane has a nibble
+// of the mask; the ranks of all lanes' first kept weights come from the counts' three bits (ballots and masked bit counts), and
+// the codes of a lane's kept weights follow each other, so two words of the stream hold them.  For 2..8-bit codes the four bytes
+// go to their places by one byte permute, whose selector is a table's (pruned: the zero point), and to halfs by another:
+// 1024 + code is a half with the code as its low byte, and subtracting 1024 + zp is exact.
+// About 35 vector instructions for up to 256 weights, where one weight per lane took 30 for up to 64 (10 layers x 40: from the
+// workgroup's start to the end of this phase 25 -> 14.5 thousand clocks).
+template <int TM, int WP> struct XExpand {
+    static constexpr int LANES = WP <= 16 ? 4 : (WP <= 32 ? 8 : 16), ROWS = 64 / LANES;      // lanes per row, rows per pass
+    static constexpr int PASSES = WP / ROWS;
+};
+// Byte selector of a nibble of keep bits: byte b is the rank of weight b among the kept ones, or 4 (the zero point) if pruned.
+__device__ __forceinline__ uint32_t nibble_selector(uint32_t bits) {
+    uint32_t s = 0;
+#pragma unroll
+    for (int b = 0; b < 4; ++b) s |= ((bits >> b & 1u) ? (uint32_t)__popc(bits & ((1u << b) - 1u)) : 4u) << (8 * b);
+    return s;
+}
+template <int TM, int WP, bool W16, int KIND, int U>
+__device__ __forceinline__ void expand_hidden(const uint32_t *rec, const LaneLayers &t, int l, int lane, char *lds, char *hi, char *lo, float *bt,
+                                              float bias_factor, bool whole, float pre) {
     typedef XLayout<TM, WP> LY;
-    XLayer *tab = (XLayer *)lds;
-    for (uint32_t q = tid; q < (zero_bytes >> 4); q += nthreads) ((uint4 *)lds)[q] = make_uint4(0u, 0u, 0u, 0u);   // zero_bytes is a multiple of 16
-    __syncthreads();
-    if (tid == 0) {
-        uint32_t bias = LY::TABLE;
-        uint32_t cur = LY::TABLE + (uint32_t)(L - 1) * WP * 4u + LY::OUTB;
-        for (int l = l0; l < l1; ++l) {
-            const LayerRec r = *(const LayerRec *)(rec + l * (sizeof(LayerRec) / 4));
-            if (SLOTTED) {
-                bias = LY::TABLE + (uint32_t)(l - l0) * XSlot<TM, WP>::BYTES;
-                cur = bias + XSlot<TM, WP>::BIAS;
+    typedef XExpand<TM, WP> X;
+    const uint32_t last = lane_value(t.upto, l), first = last - lane_value(t.passes, l);
+    if (t.g1 <= first || t.g0 >= last) return;
+    const uint32_t io = lane_value(t.io, l), kind = lane_value(t.kind, l), n_in = io & 0xFFFFu, n_out = io >> 16;
+    const bool has_mask = (kind >> 8 & 0xFFu) != 0, coded = (kind & 0xFFu) != 0;
+    const uint32_t cb = coded ? kind & 0xFFu : 32u;
+    const float scale = __uint_as_float(lane_value(__float_as_uint(t.scale), l));
+    const int32_t zp = (int32_t)lane_value((uint32_t)t.zp, l);
+    const uint32_t *mw = rec + (lane_value(t.mask_off, l) >> 2);
+    const uint32_t *cs = rec + (lane_value(t.code_off, l) >> 2);
+    const uint32_t p0 = t.g0 > first ? t.g0 - first : 0u, p1 = (t.g1 < last ? t.g1 : last) - first;
+    const uint32_t i = 4u * ((uint32_t)lane % X::LANES);
+    const uint32_t real = i >= n_in ? 0u : (n_in - i >= 4u ? 15u : (1u << (n_in - i)) - 1u);    // the lane's inputs that exist
+    const uint32_t last_word = (n_in * n_out - 1u) >> 5;
+    const uint32_t *select = (const uint32_t *)(lds + LY::SELECT);
+    const uint32_t zp4 = (uint32_t)zp * 0x01010101u;
+    const h2v less = {(_Float16)(float)(-1024 - zp), (_Float16)(float)(-1024 - zp)};
+    const uint32_t k0 = min(p0 * X::ROWS, n_out) * n_in;                        // weights before the wavefront's first pass
+    uint32_t running = k0;
+    if (has_mask && p0) {
+        uint32_t part = 0;
+        for (uint32_t wi = lane; wi <= min(k0 >> 5, last_word); wi += 64) part += __popc(mw[wi] & (wi == k0 >> 5 ? (1u << (k0 & 31u)) - 1u : 0xFFFFFFFFu));
+        running = wave_sum(part);
+    }
+    for (uint32_t p = p0; p < p1; p += U) {
+        uint32_t o[U], bits[U], rank[U];
+        const uint32_t before = running;
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            o[j] = (p + j) * X::ROWS + (uint32_t)lane / X::LANES;
+            bits[j] = 15u;
+            if (has_mask) {
+                const uint32_t k = __umul24(o[j], n_in) + i, w = min(k >> 5, last_word);
+                bits[j] = __builtin_amdgcn_alignbit(mw[min(w + 1u, last_word)], mw[w], k & 31u);
             }
-            XLayer e;
-            e.off_bias = bias;
-            bias += l < L - 1 ? WP * 4 : LY::OUTB;
-            e.scale = 1.0f;
-            e.off_hi = cur;
-            e.off_lo = 0;
-            if (l == 0) cur += LY::FIRST;
-            else if (l == L - 1) { e.off_lo = cur + LY::OUT; cur += 2 * LY::OUT; }
-            else if (W16) cur += LY::HID;
-            else if (xdl_int_layer(r.bits, r.scale * pre)) { e.scale = r.scale * pre; cur += LY::HID; }
-            else { e.off_lo = cur + LY::HID; cur += 2 * LY::HID; }
-            tab[l] = e;
+        }
+#pragma unroll
+        for (int j = 0; j < U; ++j) {
+            bits[j] &= o[j] < n_out ? real : 0u;
+            const uint32_t c = (uint32_t)__popc(bits[j]);
+            const uint64_t c0 = __ballot(c & 1u), c1 = __ballot(c & 2u), c2 = __ballot(c & 4u);
+            const uint32_t r1 = __builtin_amdgcn_mbcnt_hi((uint32_t)(c1 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)c1, 0u));
+            const uint32_t r2 = __builtin_amdgcn_mbcnt_hi((uint32_t)(c2 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)c2, 0u));
+            rank[j] = __builtin_amdgcn_mbcnt_hi((uint32_t)(c0 >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)c0, running)) + 2u * r1 + 4u * r2;
+            rank[j] = bits[j] ? rank[j] : 0u;               // a lane without weights reads the first code and drops it
+            running += (uint32_t)(__popcll(c0) + 2 * __popcll(c1) + 4 * __popcll(c2));
+        }
+        const bool some = running != before;                // no code kept: there may be none to read
+        if (KIND == kHiddenAllInt || (KIND == kHiddenMixed && whole)) {
+            uint32_t x[U], sel[U];
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                sel[j] = select[bits[j]];
+                x[j] = 0u;
+            }
+            if (some) {
+#pragma unroll
+                for (int j = 0; j < U; ++j) {
+                    const uint32_t bit = __umul24(rank[j], cb);
+                    x[j] = __builtin_amdgcn_alignbit(cs[(bit >> 5) + 1u], cs[bit >> 5], bit & 31u);
+                }
+                if (cb != 8u) {
+                    const uint32_t m = (1u << cb) - 1u;
+#pragma unroll
+                    for (int j = 0; j < U; ++j)
+                        x[j] = (x[j] & m) | (x[j] >> cb & m) << 8 | (x[j] >> 2u * cb & m) << 16 | (x[j] >> 3u * cb & m) << 24;
+                }
+            }
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                const uint32_t y = __builtin_amdgcn_perm(zp4, x[j], sel[j]);
+                const h2v h01 = __builtin_bit_cast(h2v, __builtin_amdgcn_perm(0x64646464u, y, 0x04010400u)) + less;
+                const h2v h23 = __builtin_bit_cast(h2v, __builtin_amdgcn_perm(0x64646464u, y, 0x04030402u)) + less;
+                if ((int)i < WP && p + j < p1) *(h4v *)(hi + 2 * LY::idx_hidden((int)o[j], (int)i)) = (h4v){h01[0], h01[1], h23[0], h23[1]};
+            }
+        } else {
+#pragma unroll
+            for (int j = 0; j < U; ++j) {
+                h4v wh, wl;
+#pragma unroll
+                for (int b = 0; b < 4; ++b) {
+                    const bool kept = bits[j] >> b & 1u;
+                    const uint32_t rk = kept ? rank[j] + (uint32_t)__popc(bits[j] & ((1u << b) - 1u)) : 0u;
+                    uint32_t code = 0u;
+                    if (some) {
+                        if (cb == 32u) code = cs[rk];
+                        else if (cb == 16u) code = ((const uint16_t *)cs)[rk];
+                        else if (W16 || KIND == kHiddenMixed || KIND == kHiddenAllRaw) code = take_code(cs, rk, cb);
+                    }
+                    const float v = coded ? scale * (float)((int32_t)code - zp) : __uint_as_float(code);
+                    const float w = kept ? v * pre : 0.0f;
+                    wh[b] = (_Float16)w;
+                    wl[b] = (_Float16)(w - (float)wh[b]);
+                }
+                if ((int)i < WP && p + j < p1) {
+                    *(h4v *)(hi + 2 * LY::idx_hidden((int)o[j], (int)i)) = wh;
+                    if (!W16) *(h4v *)(lo + 2 * LY::idx_hidden((int)o[j], (int)i)) = wl;
+                }
+            }
         }
     }
+    if (p0 == 0) {
+        const float *bias = (const float *)(rec + (lane_value(t.bias_off, l) >> 2));
+        if ((uint32_t)lane < n_out) bt[LY::idx_bias(lane)] = bias[lane] * pre * bias_factor;
+    }
+}
+
+// KIND says which kinds of hidden layer there can be (kHidden...), U how many passes of a hidden layer a wavefront has under way.
+template <int TM, int WP, bool W16, bool SLOTTED, int KIND, int U>
+__device__ __forceinline__ void xdl_expand_layers(char *lds, const uint32_t *rec, const LaneLayers &t, int L, int l0, int l1, float pre, int tid,
+                                                  int nthreads) {
+    typedef XLayout<TM, WP> LY;
+    const int lane = tid & 63;
+    // lane l: layer l's entry; the offsets are sums over the lanes
+    XLayer mine;
+    {
+        const bool last = lane == L - 1, in_group = lane >= l0 && lane < l1;
+        const bool whole = !W16 && lane > 0 && !last && xdl_int_layer(t.kind & 0xFFu, t.scale * pre);
+        const uint32_t one = lane == 0 ? LY::FIRST : (last ? LY::OUT : LY::HID), size = (last || (lane > 0 && !W16 && !whole)) ? 2 * one : one;
+        const uint32_t upto = row_incl_sum(lane < L ? size : 0u);
+        mine.off_bias = LY::TABLE + (SLOTTED ? (uint32_t)(lane - l0) * XSlot<TM, WP>::BYTES : (uint32_t)lane * WP * 4u);
+        mine.off_hi = SLOTTED ? mine.off_bias + XSlot<TM, WP>::BIAS : LY::TABLE + (uint32_t)(L - 1) * WP * 4u + LY::OUTB + upto - size;
+        mine.off_lo = size == one ? 0u : mine.off_hi + one;
+        mine.scale = whole ? t.scale * pre : 1.0f;
+        if (tid < 16) {
+            if (in_group) ((XLayer *)lds)[lane] = mine;
+            ((uint32_t *)(lds + LY::SELECT))[lane] = nibble_selector((uint32_t)lane);
+        }
+    }
+    // cleared: the biases, the first layer's and the output layer's blocks (the hidden layers' are written whole)
+    auto clear = [&](uint32_t from, uint32_t to) {
+        for (uint32_t q = (from >> 4) + tid; q < (to >> 4); q += nthreads) ((uint4 *)lds)[q] = make_uint4(0u, 0u, 0u, 0u);
+    };
+    if (SLOTTED) {
+        for (int l = l0; l < l1; ++l) {
+            const uint32_t at = LY::TABLE + (uint32_t)(l - l0) * XSlot<TM, WP>::BYTES;
+            clear(at, at + (l == 0 || l == L - 1 ? XSlot<TM, WP>::BYTES : XSlot<TM, WP>::BIAS));
+        }
+    } else {
+        const uint32_t out = lane_value(mine.off_hi, L - 1);
+        clear(LY::TABLE, lane_value(mine.off_hi, 0) + LY::FIRST);
+        clear(out, out + 2 * LY::OUT);
+    }
     __syncthreads();
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, nwaves = nthreads >> 6;
-    ExpandShare sh = expand_share(rec, l0, l1, wave, nwaves);
-    for (int l = l0; l < l1; ++l) {
-        const LayerRec r = *(const LayerRec *)(rec + l * (sizeof(LayerRec) / 4));
-        const XLayer e = tab[l];
-        _Float16 *hi = (_Float16 *)(lds + e.off_hi), *lo = (_Float16 *)(lds + e.off_lo);
-        float *bt = (float *)(lds + e.off_bias);
+    // only the layers that have passes of this wavefront (from the lanes: those whose passes end behind its first, and begin before its end)
+    const uint64_t at = __ballot(t.passes != 0u && t.upto > t.g0 && t.upto - t.passes < t.g1) & 0xFFFFull;
+    const int la = at ? __ffsll((unsigned long long)at) - 1 : 0, lb = at ? la + __popcll(at) : 0;
+    for (int l = la; l < lb; ++l) {
+        const uint32_t off_lo = lane_value(mine.off_lo, l);
+        _Float16 *hi = (_Float16 *)(lds + lane_value(mine.off_hi, l)), *lo = (_Float16 *)(lds + off_lo);
+        float *bt = (float *)(lds + lane_value(mine.off_bias, l));
         if (l == L - 1) {
-            expand_layer(rec, r, lane, sh,
+            expand_layer<1>(rec, t, l, lane,
                          [=](int o, int i, float v, int) {
                              const _Float16 h = (_Float16)v;
                              hi[LY::idx_out(o, i)] = h;
@@ -181,7 +318,7 @@ __device__ __forceinline__ void xdl_expand_layers(char *lds, const uint32_t *rec
                          },
                          [=](int o, float v) { bt[LY::idx_bias(4 * o)] = v; });
         } else if (l == 0) {
-            expand_layer(rec, r, lane, sh,
+            expand_layer<1>(rec, t, l, lane,
                          [=](int o, int i, float v, int) {
                              const float w = v * pre;
                              const _Float16 h = (_Float16)w, lw = (_Float16)(w - (float)h);
@@ -192,22 +329,10 @@ __device__ __forceinline__ void xdl_expand_layers(char *lds, const uint32_t *rec
                              }
                          },
                          [=](int o, float v) { bt[LY::idx_bias(o)] = v * pre; });
-        } else if (W16) {
-            expand_layer(rec, r, lane, sh, [=](int o, int i, float v, int) { hi[LY::idx_hidden(o, i)] = (_Float16)(v * pre); },
-                         [=](int o, float v) { bt[LY::idx_bias(o)] = v * pre; });
-        } else if (e.off_lo == 0) {
-            const float inv = 1.0f / e.scale;
-            expand_layer(rec, r, lane, sh, [=](int o, int i, float, int q) { hi[LY::idx_hidden(o, i)] = (_Float16)(float)q; },
-                         [=](int o, float v) { bt[LY::idx_bias(o)] = v * pre * inv; });
         } else {
-            expand_layer(rec, r, lane, sh,
-                         [=](int o, int i, float v, int) {
-                             const float w = v * pre;
-                             const _Float16 h = (_Float16)w;
-                             hi[LY::idx_hidden(o, i)] = h;
-                             lo[LY::idx_hidden(o, i)] = (_Float16)(w - (float)h);
-                         },
-                         [=](int o, float v) { bt[LY::idx_bias(o)] = v * pre; });
+            const bool whole = !W16 && off_lo == 0;
+            const float s = whole ? __uint_as_float(lane_value(__float_as_uint(mine.scale), l)) : 1.0f;
+            expand_hidden<TM, WP, W16, KIND, U>(rec, t, l, lane, lds, (char *)hi, (char *)lo, bt, whole ? 1.0f / s : 1.0f, whole, pre);
         }
     }
     __syncthreads();
@@ -544,19 +669,23 @@ __device__ __forceinline__ void xdl_body(const DecodeArgs &a, const Work &w, flo
     const int L = e.n_layers;
 
     // the packed record is staged at the end of the workgroup's LDS, the operand blocks are built at the start
-    uint32_t *stage = (uint32_t *)(lds + (a.lds_bytes - e.nbytes));
-    {
-        const uint4 *src = (const uint4 *)(a.blob + e.off);
-        uint4 *dst = (uint4 *)stage;
-        for (uint32_t q = tid; q < (e.nbytes >> 4); q += nthreads) dst[q] = src[q];
-    }
-    // Tiles are handed out through a counter in LDS (it reuses the first word of the staging area,
-    // which is dead once the model is expanded): the SIMD arbiter favours its older wavefront, so
+    const uint8_t *record = a.blob + e.off;
+    const uint32_t room = a.lds_bytes - 16u;                     // behind it: the tile counter
+    // Tiles are handed out through a counter in LDS: the SIMD arbiter favours its older wavefront, so
     // with a fixed split the favoured waves would finish early and leave the others running alone.
-    xdl_expand_layers<TM, WP, W16, false>(lds, stage, L, 0, L, a.pre, tid, nthreads, a.lds_bytes - e.nbytes);
-    uint32_t *next_tile = stage;
+    uint32_t *next_tile = (uint32_t *)(lds + room);
     if (tid == 0) *next_tile = tile0 + (nthreads >> 6);
-    __syncthreads();
+    {
+        const LaneLayers t = lane_layers<XExpand<TM, WP>::PASSES>(record, L, 0, L, tid & 63, __builtin_amdgcn_readfirstlane(tid >> 6), nthreads >> 6);
+        const uint32_t need = resident_bytes(a.fit_form, w.cls, L, 0);
+        if (MODE == kHiddenAllInt || W16 || need + e.nbytes <= room) {     // (in one-block form a model fits with its record)
+            uint32_t *stage = (uint32_t *)(lds + (room - e.nbytes));
+            for (uint32_t q = tid; q < (e.nbytes >> 4); q += nthreads) ((uint4 *)stage)[q] = ((const uint4 *)record)[q];
+            xdl_expand_layers<TM, WP, W16, false, MODE, (WP <= 32 ? 1 : 2)>(lds, stage, t, L, 0, L, a.pre, tid, nthreads);
+        } else {
+            xdl_expand_layers<TM, WP, W16, false, MODE, 1>(lds, (const uint32_t *)record, t, L, 0, L, a.pre, tid, nthreads);
+        }
+    }
 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const XLayer *tab = (const XLayer *)lds;
@@ -642,8 +771,8 @@ __device__ __forceinline__ void xdl_stream_body(const DecodeArgs &a, const Work 
         for (int l0 = 0; l0 < L; l0 += K) {
             const int l1 = l0 + K < L ? l0 + K : L;
             __syncthreads();                                           // every wavefront is done with the previous group
-            xdl_expand_layers<TM, WP, W16, true>(lds, rec, L, l0, l1, a.pre, tid, nthreads,
-                                                 LY::TABLE + (uint32_t)(l1 - l0) * XSlot<TM, WP>::BYTES);
+            const LaneLayers t = lane_layers<XExpand<TM, WP>::PASSES>((const uint8_t *)rec, L, l0, l1, lane, wave, nwaves);
+            xdl_expand_layers<TM, WP, W16, true, kHiddenMixed, 1>(lds, rec, t, L, l0, l1, a.pre, tid, nthreads);
             if (!active) continue;
             for (int l = l0; l < l1; ++l) {
                 const XLayer el = uniform_layer(tab[l]);
@@ -710,7 +839,8 @@ __global__ __launch_bounds__(256) void xdl_debug_kernel(const uint8_t *blob, int
     const int L = e.n_layers;
     const uint32_t *rec = (const uint32_t *)(blob + e.off);
     // one layer at a time in the slotted layout, straight from global memory: any depth fits
-    xdl_expand_layers<TM, WP, W16, true>(lds, rec, L, layer, layer + 1, 1.0f, tid, nthreads, lds_bytes);
+    const LaneLayers t = lane_layers<XExpand<TM, WP>::PASSES>((const uint8_t *)rec, L, layer, layer + 1, tid & 63, __builtin_amdgcn_readfirstlane(tid >> 6), nthreads >> 6);
+    xdl_expand_layers<TM, WP, W16, true, kHiddenMixed, 1>(lds, rec, t, L, layer, layer + 1, 1.0f, tid, nthreads);
     const XLayer el = ((const XLayer *)lds)[layer];
     const LayerRec r = *(const LayerRec *)(rec + layer * (sizeof(LayerRec) / 4));
     const _Float16 *hi = (const _Float16 *)(lds + el.off_hi), *lo = (const _Float16 *)(lds + el.off_lo);

@@ -423,6 +423,18 @@ def test_streamed_decode_equals_resident_decode_bit_for_bit(torch):
     assert e.value.code == rinr.E_ARG
 
 
+@pytest.mark.parametrize("width,sines,bits", [(64, 7, [0] * 8), (64, 7, [0, 16, 16, 16, 16, 16, 16, 0]), (48, 9, [0] * 10), (61, 6, [0, 0, 16, 8, 6, 0, 0])])
+def test_models_whose_record_does_not_fit_beside_their_weights(torch, width, sines, bits):
+    """Such a record is expanded from global memory into on-chip weights that still fit: resident, and as accurate as any."""
+    ms = synth.make_models(30 + width, np.arange(5), width, sines, bits, 0.7)
+    st = rinr.Store(rinr.pack(ms))
+    sel = np.array([0, 4, 1, 2, 3, 3, 0], np.uint32)
+    got = st.decode_batch_ex(ids_dev(torch, sel), 37, 29, rinr.OUT_F32, rinr.FLAG_NO_CLAMP).cpu().numpy()
+    assert not st.last_launch_info()["streamed"] and st.status() == 0
+    assert np.abs(got - oracle.decode(ms, sel, 37, 29, clamp=False)).max() <= TIGHT
+    st.close()
+
+
 @pytest.mark.parametrize("width", [12, 32, 40, 48, 64])
 def test_every_term_of_the_output_layer_arrives(torch, width):
     """A model whose first and hidden layers have zero weights: the last sine layer's outputs are the constants
