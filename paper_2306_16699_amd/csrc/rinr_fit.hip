@@ -485,7 +485,7 @@ int lds_floats(int wq, int L) {
 }
 
 
-// ---- the split-precision kernels (rinr_fit16.hip.h): built per hidden width rounded up to a multiple of 16 and per depth bucket
+// ---- the split-precision kernels (rinr_fit16.hip.h): built per hidden width rounded up to a multiple of 16 and per depth
 constexpr int fit16_depth(int wp) { return wp <= 32 ? kMaxL : (wp == 48 ? 10 : 6); }
 // 16-pixel tiles a wavefront takes at a time: one where that leaves registers for a second wavefront per SIMD and two do not,
 // else two where the registers hold them (a lone wavefront has only its own two tiles to fill the gaps between dependent instructions).
@@ -494,17 +494,13 @@ constexpr int fit16_tiles(int wp, int ml) {
     return (one > 1 && two == 1) || fit16::fit16_registers(wp, ml, 2) > 512 ? 1 : 2;
 }
 struct Fit16 { fit_fn fn; uint32_t lds; int pixels; };      // kernel, LDS bytes, pixels a workgroup takes at a time
-template <int WP, int ML> Fit16 kernel16(int L) {
-    constexpr int nt = fit16_tiles(WP, ML);
-    return Fit16{fit16::fit16_step_kernel<WP, ML, nt>, fit16::Shape<WP>::total(L), fit16::kThreads / 4 * nt};
-}
-// Depth buckets: where another wavefront per SIMD, or a second tile, fits the registers.
-template <int WP> Fit16 kernel16_of(int L) {
-    if (L > fit16_depth(WP)) return Fit16{nullptr, 0, 0};
-    if constexpr (WP == 16) return L <= 4 ? kernel16<16, 4>(L) : (L <= 7 ? kernel16<16, 7>(L) : kernel16<16, 12>(L));
-    else if constexpr (WP == 32) return L <= 4 ? kernel16<32, 4>(L) : (L <= 6 ? kernel16<32, 6>(L) : (L <= 8 ? kernel16<32, 8>(L) : kernel16<32, 12>(L)));
-    else if constexpr (WP == 48) return L <= 4 ? kernel16<48, 4>(L) : (L <= 7 ? kernel16<48, 7>(L) : kernel16<48, 10>(L));
-    else return L <= 3 ? kernel16<64, 3>(L) : (L <= 4 ? kernel16<64, 4>(L) : kernel16<64, 6>(L));
+template <int WP, int L = 2> Fit16 kernel16_of(int n) {
+    if constexpr (L > fit16_depth(WP)) {
+        return Fit16{nullptr, 0, 0};
+    } else {
+        constexpr int nt = fit16_tiles(WP, L);
+        return n == L ? Fit16{fit16::fit16_step_kernel<WP, L, nt>, fit16::Shape<WP>::total(L), fit16::kThreads / 4 * nt} : kernel16_of<WP, L + 1>(n);
+    }
 }
 Fit16 kernel16_for(int wp, int L) {
     const Fit16 k = wp == 16 ? kernel16_of<16>(L) : (wp == 32 ? kernel16_of<32>(L) : (wp == 48 ? kernel16_of<48>(L) : kernel16_of<64>(L)));

@@ -13,8 +13,10 @@
 //
 // What bounds it is instruction issue: a matrix instruction takes two issue slots of 4.1 clocks, a sine or cosine two, other
 // vector instructions one (measured; matrix and vector instructions of one wavefront overlap where they alternate).  A hidden
-// layer of 40 units takes 48 matrix and 169 vector slots per 16 pixels backward, 15 and 52 forward.  Measured, ms a step, before ->
-// now: 256 images of 224 x 224, 10 layers x 40: 8.91 -> 6.86; 10 x 32: 4.54 -> 3.50; 2048 of 32 x 32, 3 x 15: 0.0934 -> 0.0778.
+// layer of 40 units takes 48 matrix and 169 vector slots per 16 pixels backward, 15 and 52 forward.  At 10 layers x 40 the matrix
+// unit is busy 48 % of the time and vector issue 42 %, but only a quarter of the matrix time has vector instructions beside it.
+// Measured, ms a step, gradient tiles shared -> a wavefront's own -> layers interleaved (see the kernel): 256 images of 224 x 224,
+// 10 layers x 40: 8.91 -> 6.83 -> 6.29; 10 x 32: 4.54 -> 3.50 -> 3.00; 2048 of 32 x 32, 3 x 15: 0.0934 -> 0.0738 -> 0.0675.
 //
 // Two orientations.  P: lane (n, g) holds pixel n and, per 16-row tile of a layer's units, the quad of units 4 g + v.  That is
 // what a matrix instruction leaves with the units as its rows, and two tiles' quads side by side are exactly the B operand
@@ -131,24 +133,30 @@ template <int WP> __device__ __forceinline__ void put_operand(char *m, uint32_t 
     }
 }
 
-// acc + (operand rows at `m`, this lane's word) x (B as quads Bh, Bl of all tiles)
-template <int WP> __device__ __forceinline__ f32x4 contract(const char *m, uint32_t plane, const h4v (&Bh)[WP / 16], const h4v (&Bl)[WP / 16], f32x4 acc) {
+// The operand words of R row tiles of a matrix, all planes: this lane's word of each row tile is at `m` + 1024 t
+template <int WP, int R> struct Words {
     typedef Shape<WP> S;
+    h8v w[S::NPL][R];
+    __device__ __forceinline__ void load(const char *m, uint32_t plane) {
 #pragma unroll
-    for (int j = 0; j < S::NP; ++j) {
-        const h8v ah = *(const h8v *)(m + 2 * j * plane), al = *(const h8v *)(m + (2 * j + 1) * plane);
-        const h8v bh = cat(Bh[2 * j], Bh[2 * j + 1]), bl = cat(Bl[2 * j], Bl[2 * j + 1]);
-        acc = mfma32(ah, bh, acc);
-        acc = mfma32(ah, bl, acc);
-        acc = mfma32(al, bh, acc);
+        for (int p = 0; p < S::NPL; ++p)
+#pragma unroll
+            for (int t = 0; t < R; ++t) w[p][t] = *(const h8v *)(m + p * plane + t * 1024);
     }
-    if (S::TAIL) {
-        const h8v at = *(const h8v *)(m + 2 * S::NP * plane);
-        acc = mfma32(at, cat(Bh[S::MT - 1], Bh[S::MT - 1]), acc);
-        acc = mfma32(at, cat(Bl[S::MT - 1], Bl[S::MT - 1]), acc);
+    // acc += rows x B, contraction block k: a pair of tiles (three terms) or an odd last tile (two); the row tiles take turns, so
+    // that a matrix step does not wait for the one before it
+    template <int NT> __device__ __forceinline__ void block(int k, const h4v (&Bh)[NT][S::MT], const h4v (&Bl)[NT][S::MT], f32x4 (&acc)[NT][R]) const {
+        const bool tail = k == S::NP;
+        const int p = 2 * k, b0 = 2 * k, b1 = tail ? b0 : b0 + 1;
+#pragma unroll
+        for (int term = 0; term < (tail ? 2 : 3); ++term)
+#pragma unroll
+            for (int t = 0; t < R; ++t)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+                    acc[nt][t] = mfma32(w[term == 2 ? p + 1 : p][t], term == 1 ? cat(Bl[nt][b0], Bl[nt][b1]) : cat(Bh[nt][b0], Bh[nt][b1]), acc[nt][t]);
     }
-    return acc;
-}
+};
 
 // Registers: gradient tiles and pre-activations of all layers, and what a layer in progress takes.
 constexpr int fit16_registers(int wp, int ml, int nt) {
@@ -157,16 +165,31 @@ constexpr int fit16_registers(int wp, int ml, int nt) {
 }
 constexpr int fit16_waves_per_simd(int wp, int ml, int nt) {
     const int r = fit16_registers(wp, ml, nt);
-    return r <= 128 ? 4 : (r <= 168 ? 3 : (r <= 256 ? 2 : 1));
+    return r <= 128 ? 4 : (r <= 156 ? 3 : (r <= 256 ? 2 : 1));     // a third wavefront at 160 (8 x 16) or 168 (3 x 32) spills: 243 against 232 us, 150 against 144
 }
 
-// A model of L layers in the kernel of a depth bucket ML: the hidden layers are steps u = 0 .. ML - 3 of code unrolled for ML
-// layers, and a shallower model leaves out the first ML - L of them.  So what follows the last hidden layer, and the first
-// layer, are each one piece of code, and a step is one piece without branches that the compiler can interleave.
-template <int WP, int ML, int NT>
-__global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, ML, NT)) void fit16_step_kernel(const FitArgs a) {
+// Ends a basic block between two layers: `stop` is 0, which the compiler cannot see.  A whole chunk as one block has its
+// registers assigned badly (10 layers x 40: 78 to 219 spilled; with these edges none), and code moves across too far.
+// A kernel that takes more than 256 registers must not spill: the compiler's pass that puts matrix results into the upper half
+// then loses reloads of parts of a quad (seen in the assembly of a 7 x 48 kernel whose gradients were wrong in that quad).
+#define FIT16_EDGE                         \
+    do {                                   \
+        asm volatile("" : "+s"(stop));     \
+        if (stop) return;                  \
+    } while (0)
+
+// One kernel per depth L: the hidden layers are steps u = 0 .. L - 3 of unrolled code without conditions, so that what one
+// layer's end and the next one's start have to do runs side by side.  Forward, a piece of code between two edges takes the last
+// block of a layer's contraction (its odd last tile, or last pair of tiles), the sines and splits of its tiles as they come
+// out, and the next layer's other blocks, whose operand words it has loaded first; the row tiles take turns at the matrix
+// unit.  With a layer a piece of its own, as before, a layer's matrix steps waited for each other and for every load, and its
+// sines came after them.  Measured, ms a step, before -> now: 256 images of 224 x 224, 10 layers x 40: 6.83 -> 6.29; 512 of
+// 224 x 224, 10 x 32: 6.98 -> 6.00; 512 of 96 x 96, 5 x 24: 0.532 -> 0.457; 64 of 128 x 128, 6 x 64: 0.500 -> 0.450.  Forcing one
+// matrix step per two to four vector instructions backward (scheduling groups) was slower: 7.8 ms at 10 x 40.
+template <int WP, int L, int NT>
+__global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, L, NT)) void fit16_step_kernel(const FitArgs a) {
     typedef Shape<WP> S;
-    constexpr int MT = S::MT, NH = ML - 2, kPC = kWaves * 16 * NT;
+    constexpr int MT = S::MT, NH = L - 2, kPC = kWaves * 16 * NT;
     constexpr int kColOut = 11, kColFirst = 12;         // columns of acc_b: step u's biases in column u, the output layer's, the first layer's bias, x and y
     const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
     const h4v zh = {(_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f};
@@ -180,7 +203,6 @@ __global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, ML, NT)) void fi
     const size_t img = share.img;
     const float *P = a.params + img * a.n_params;
     const float neg1 = a.neg1;
-    const int L = a.L, skip = ML - L;
 
     // ---- set up: zero everything; weights as hi/lo operands (sine layers times w0 / 2pi: Z comes out in revolutions), biases;
     //      per layer the sum of squared weights (for the error's scale), summed in a fixed order.  A thread has all its weights
@@ -225,7 +247,7 @@ __global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, ML, NT)) void fi
             cur[k] = next[k];
         }
         if (tid < dout) {
-            float *const B = (float *)(lds + S::BIAS) + (last ? 4 * tid : 16 + (l - 1 + skip) * WP + tid);
+            float *const B = (float *)(lds + S::BIAS) + (last ? 4 * tid : 16 + (l - 1) * WP + tid);
             *(l == 0 ? (float *)(lds + S::W0) + tid * 4 + 2 : B) = bias * sc;
         }
         for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
@@ -264,7 +286,7 @@ __global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, ML, NT)) void fi
     }
     __syncthreads();
 
-    f32x4 acc[NH][MT][MT];                         // weight gradients of the hidden layers: rows are outputs, columns inputs
+    f32x4 acc[NH > 0 ? NH : 1][MT][MT];                         // weight gradients of the hidden layers: rows are outputs, columns inputs
     f32x4 acc_last[MT], acc_b[MT];                 // output layer (channel c in row 4 c); biases and first layer
     f32x4 zst[NH + 1][NT][MT];                     // pre-activations (revolutions) of the pixels at hand: what goes into step u, into the output layer
 #pragma unroll
@@ -303,17 +325,17 @@ __global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, ML, NT)) void fi
         hi = to_h4(mfma32(x, I0, zero4));
         lo = to_h4(mfma32(x, I1, zero4));
     };
-    auto column = [&](int k) -> h8v {                                       // ones in column k
+    auto column = [&](int k, uint32_t c) -> h8v {                           // ones in column k
         int m = n;
-        asm volatile("" : "+v"(m));         // made again where it is used: eight steps' columns are not held across the loop
+        asm("" : "+v"(m) : "s"(c));         // made again where it is used: eight steps' columns are not held across the loop
         const uint32_t two = m == k ? 0x3C003C00u : 0u;
         const u4v w = {two, two, two, two};
         return __builtin_bit_cast(h8v, w);
     };
     const char *const base = lds + (n * 64 + 16 * (g ^ ((n >> 1) & 2)));    // this lane's word of an operand's row
-    auto step = [&](int u, int from, uint32_t at) {                         // ... in step u's layer: one addition per step, the rest immediates
-        uint32_t s = S::HID0 + at + (uint32_t)(u - from) * 2 * S::HID;
-        asm volatile("" : "+s"(s));
+    auto step = [&](int u, uint32_t c, uint32_t at) {                       // ... in step u's layer: one addition per step, the rest immediates
+        uint32_t s = S::HID0 + at + (uint32_t)u * 2 * S::HID;
+        asm("" : "+s"(s) : "s"(c));        // formed per chunk: not held across the loop in a register per layer
         return base + s;
     };
 
@@ -327,8 +349,7 @@ __global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, ML, NT)) void fi
     for (int nt = 0; nt < NT; ++nt) tgt[nt] = share.c0 < share.c1 ? target(share.c0, nt) : 0.0f;
 
     for (uint32_t c = share.c0; c < share.c1; ++c) {
-        int from = skip;
-        asm volatile("" : "+s"(from));    // read afresh per chunk: keeps the unrolled steps' conditions out of long-lived lane masks
+        int stop = 0;                      // see FIT16_EDGE
         float x[NT], y[NT], want[NT];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
@@ -340,7 +361,7 @@ __global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, ML, NT)) void fi
             tgt[nt] = target(c + 1 < share.c1 ? c + 1 : c, nt);             // the next pixels' targets are under way during this chunk
         }
 
-        // ---- forward.  First layer on the vector ALU (two inputs); hidden layers: Z = W H + b, tile by tile
+        // ---- forward.  First layer on the vector ALU (two inputs); hidden layers: Z = W H + b
         h4v Bh[NT][MT], Bl[NT][MT];
         auto first = [&](f32x4 (&z)[NT][MT]) {
 #pragma unroll
@@ -352,43 +373,85 @@ __global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, ML, NT)) void fi
                     for (int nt = 0; nt < NT; ++nt) z[nt][t][v] = fmaf(w.x, x[nt], fmaf(w.y, y[nt], w.z));
                 }
         };
+        Words<WP, MT> W;
+        Words<WP, 1> WL;
+        f32x4 zo[NT][1];                   // output layer: channel g of pixel n in the first register of lane (n, g)
+        // What the contraction into step u's layer, or the output layer, starts from: its operand words, and the biases
+        auto begin = [&](int u) {
+            if (u < NH) {
+                const f32x4 *B = (const f32x4 *)(lds + S::BIAS + 64 + u * WP * 4);
+                W.load(step(u, c, 0), S::PLANE);
+#pragma unroll
+                for (int t = 0; t < MT; ++t)
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) zst[u + 1][nt][t] = B[4 * t + g];
+            } else {
+                WL.load(base + S::LASTF, 16 * 64);
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) zo[nt][0] = ((const f32x4 *)(lds + S::BIAS))[g];
+            }
+        };
+        constexpr int kBlocks = S::NP + S::TAIL;
+        auto blocks = [&](int u, int k0, int k1) {
+#pragma unroll
+            for (int k = k0; k < k1; ++k) {
+                if (u < NH) W.template block<NT>(k, Bh, Bl, zst[u + 1]);
+                else WL.template block<NT>(k, Bh, Bl, zo);
+            }
+        };
         {
             f32x4 z0[NT][MT];
             first(z0);
+            begin(0);
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
                 for (int t = 0; t < MT; ++t) {
-                    if (from == NH) zst[NH][nt][t] = z0[nt][t];
+                    if (NH == 0) zst[NH][nt][t] = z0[nt][t];
                     split_rne(sin4(z0[nt][t]), neg1, Bh[nt][t], Bl[nt][t]);
                 }
+            blocks(0, 0, kBlocks - 1);
         }
 #pragma unroll
         for (int u = 0; u < NH; ++u) {
-            if (u >= from) {
-                const f32x4 *B = (const f32x4 *)(lds + S::BIAS + 64 + u * WP * 4);
-                const char *const W = step(u, from, 0);
+            FIT16_EDGE;
+            blocks(u, kBlocks - 1, kBlocks);
+            begin(u + 1);
 #pragma unroll
-                for (int t = 0; t < MT; ++t)
+            for (int t = 0; t < MT; ++t)
 #pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) zst[u + 1][nt][t] = contract<WP>(W + t * 1024, S::PLANE, Bh[nt], Bl[nt], B[4 * t + g]);
-#pragma unroll
-                for (int t = 0; t < MT; ++t)
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) split_rne(sin4(zst[u + 1][nt][t]), neg1, Bh[nt][t], Bl[nt][t]);
-            }
+                for (int nt = 0; nt < NT; ++nt) split_rne(sin4(zst[u + 1][nt][t]), neg1, Bh[nt][t], Bl[nt][t]);
+            blocks(u + 1, 0, kBlocks - 1);
         }
+        FIT16_EDGE;
+        blocks(NH, kBlocks - 1, kBlocks);
 
-        // ---- output layer: channel g of pixel n in the first register of lane (n, g)
+        // ---- output layer
         f32x4 E[NT][MT];                   // the error at hand, scaled (see the file header)
+        h4v Eh[NT][MT], El[NT][MT];
+        // Its split belongs to the end of the layer that leaves it, beside that layer's weight gradient (10 layers x 32: 6.08 ->
+        // 6.00 ms a step); where registers are scarce, to the start of the next; and where they are scarcest (10 x 40), the
+        // contraction comes before the turning: nothing may be spilled there (see FIT16_EDGE), and the faster order, 6.08 ms
+        // against 6.29, spills 20.
+        constexpr bool kLate = fit16_registers(WP, L, NT) > 480, kScarce = fit16_registers(WP, L, NT) > 500;
+        auto leave = [&](int nt, int t, f32x4 e) {
+            E[nt][t] = e;
+            if (!kLate) split_rtz(e, neg1, Eh[nt][t], El[nt][t]);
+        };
+        auto take = [&] {
+            if (kLate)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                    for (int t = 0; t < MT; ++t) split_rtz(E[nt][t], neg1, Eh[nt][t], El[nt][t]);
+        };
         {
+            FIT16_EDGE;
             const float eo = misc->out;
-            const f32x4 b = ((const f32x4 *)(lds + S::BIAS))[g];
             h4v eh[NT], el[NT];
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
-                const f32x4 z = contract<WP>(base + S::LASTF, 16 * 64, Bh[nt], Bl[nt], b);
-                const float e = g < 3 && pixel(c, nt) < a.HW ? z[0] - want[nt] : 0.0f;
+                const float e = g < 3 && pixel(c, nt) < a.HW ? zo[nt][0][0] - want[nt] : 0.0f;
                 loss_part = fmaf(e, e, loss_part);
                 split_rtz((f32x4){e * eo, 0.0f, 0.0f, 0.0f}, neg1, eh[nt], el[nt]);
             }
@@ -404,7 +467,7 @@ __global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, ML, NT)) void fi
             for (int nt = 0; nt < NT; ++nt) turn1(eh[nt], el[nt], uh[nt], ul[nt]);
             A0 = cat(uh[0], NT == 2 ? uh[NT - 1] : ul[0]);
             A1 = cat(ul[0], ul[NT - 1]);
-            const h8v ones = column(kColOut);
+            const h8v ones = column(kColOut, c);
             acc_b[0] = mfma32(A0, ones, acc_b[0]);
             if (NT == 2) acc_b[0] = mfma32(A1, ones, acc_b[0]);
 #pragma unroll
@@ -419,7 +482,7 @@ __global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, ML, NT)) void fi
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                for (int t = 0; t < MT; ++t) E[nt][t] *= cos4(zst[NH][nt][t]);
+                for (int t = 0; t < MT; ++t) leave(nt, t, E[nt][t] * cos4(zst[NH][nt][t]));
         }
 
         // ---- backward: the error goes down through the hidden layers, each layer's weight gradient takes these pixels
@@ -436,57 +499,67 @@ __global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, ML, NT)) void fi
         };
 #pragma unroll
         for (int u = NH - 1; u >= 0; --u) {
-            if (u >= from) {
-                h4v Eh[NT][MT], El[NT][MT], Hh[NT][MT], Hl[NT][MT];
-                const char *const W = step(u, from, S::HID);
-                if (u == from) first(zst[u]);              // not kept from the forward pass: cheaper to form again than to hold
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                    for (int t = 0; t < MT; ++t) split_rtz(E[nt][t], neg1, Eh[nt][t], El[nt][t]);
-                f32x4 down[NT][MT];
-#pragma unroll
-                for (int t = 0; t < MT; ++t)
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) down[nt][t] = contract<WP>(W + t * 1024, S::PLANE, Eh[nt], El[nt], zero4);
-                turn_error(Eh, El);
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                    for (int t = 0; t < MT; ++t) split_rne(sin4(zst[u][nt][t]), neg1, Hh[nt][t], Hl[nt][t]);
-                const h8v ones = column(u);
+            if (u == 0) {                              // not kept from the forward pass: cheaper to form again than to hold
+                FIT16_EDGE;
+                first(zst[0]);
+            }
+            h4v Hh[NT][MT], Hl[NT][MT];
+            FIT16_EDGE;
+            take();
+            f32x4 down[NT][MT];
+            auto contract = [&] {
 #pragma unroll
                 for (int t = 0; t < MT; ++t) {
-                    acc_b[t] = mfma32(A0[t], ones, acc_b[t]);
-                    if (NT == 2) acc_b[t] = mfma32(A1[t], ones, acc_b[t]);
+                    Words<WP, 1> V;
+                    V.load(step(u, c, S::HID + t * 1024), S::PLANE);
+                    f32x4 d[NT][1];
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) d[nt][0] = zero4;
+#pragma unroll
+                    for (int k = 0; k < kBlocks; ++k) V.template block<NT>(k, Eh, El, d);
+#pragma unroll
+                    for (int nt = 0; nt < NT; ++nt) down[nt][t] = d[nt][0];
                 }
+            };
+            if (kScarce) contract();
+            turn_error(Eh, El);
 #pragma unroll
-                for (int i = 0; i < MT; ++i) {
-                    h4v uh[NT], ul[NT];
+            for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) turn(Hh[nt], Hl[nt], i, uh[nt], ul[nt]);
-                    const h8v b0 = cat(uh[0], uh[NT - 1]), b1 = cat(ul[0], ul[NT - 1]);
+                for (int t = 0; t < MT; ++t) split_rne(sin4(zst[u][nt][t]), neg1, Hh[nt][t], Hl[nt][t]);
+            if (!kScarce) contract();
+            const h8v ones = column(u, c);
 #pragma unroll
-                    for (int t = 0; t < MT; ++t) {
-                        acc[u][t][i] = mfma32(A0[t], b0, acc[u][t][i]);
-                        acc[u][t][i] = mfma32(A0[t], b1, acc[u][t][i]);
-                        if (NT == 2) acc[u][t][i] = mfma32(A1[t], b0, acc[u][t][i]);
-                    }
-                }
-                // E_{l-1} = (r W_l^T E_l) cos(2 pi z_{l-1})
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-                    for (int t = 0; t < MT; ++t) E[nt][t] = down[nt][t] * cos4(zst[u][nt][t]);
+            for (int t = 0; t < MT; ++t) {
+                acc_b[t] = mfma32(A0[t], ones, acc_b[t]);
+                if (NT == 2) acc_b[t] = mfma32(A1[t], ones, acc_b[t]);
             }
+#pragma unroll
+            for (int i = 0; i < MT; ++i) {
+                h4v uh[NT], ul[NT];
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) turn(Hh[nt], Hl[nt], i, uh[nt], ul[nt]);
+                const h8v b0 = cat(uh[0], uh[NT - 1]), b1 = cat(ul[0], ul[NT - 1]);
+#pragma unroll
+                for (int t = 0; t < MT; ++t) {
+                    acc[u][t][i] = mfma32(A0[t], b0, acc[u][t][i]);
+                    acc[u][t][i] = mfma32(A0[t], b1, acc[u][t][i]);
+                    if (NT == 2) acc[u][t][i] = mfma32(A1[t], b0, acc[u][t][i]);
+                }
+            }
+            // E_{l-1} = (r W_l^T E_l) cos(2 pi z_{l-1})
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+                for (int t = 0; t < MT; ++t) leave(nt, t, down[nt][t] * cos4(zst[u][nt][t]));
         }
         // ---- first layer: its input's columns are one, x, y
         {
-            h4v Eh[NT][MT], El[NT][MT], h[NT], lo[NT];
+            FIT16_EDGE;
+            h4v h[NT], lo[NT];
+            take();
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt) {
-#pragma unroll
-                for (int t = 0; t < MT; ++t) split_rtz(E[nt][t], neg1, Eh[nt][t], El[nt][t]);
                 h4v xh, xl;
                 split_rne((f32x4){1.0f, x[nt], y[nt], 0.0f}, neg1, xh, xl);
                 turn1(g == kColFirst / 4 ? xh : zh, g == kColFirst / 4 ? xl : zh, h[nt], lo[nt]);
@@ -515,10 +588,9 @@ __global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, ML, NT)) void fi
     // ---- the wavefronts' gradients are added up, GT tiles at a time through LDS (in a fixed order), and each entry handed out
     f32x4 *const R = (f32x4 *)(lds + S::W0);
     constexpr int kTiles = 2 * MT + NH * MT * MT;
-    const int first_hid = 2 * MT + skip * MT * MT;      // tiles of the steps that the model leaves out are not there
 #pragma unroll
     for (int b0 = 0; b0 < kTiles; b0 += S::GT) {
-        if (b0 < 2 * MT || b0 + S::GT > first_hid) {
+        {
 #pragma unroll
             for (int q = 0; q < S::GT; ++q) {
                 const int at = b0 + q, h = at - 2 * MT;
@@ -528,7 +600,6 @@ __global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, ML, NT)) void fi
             __syncthreads();
             for (int q = wave; q < S::GT && b0 + q < kTiles; q += kWaves) {
                 const int at = b0 + q, h = at - 2 * MT;
-                if (h >= 0 && at < first_hid) continue;
                 f32x4 s = R[q * 64 + lane];
 #pragma unroll
                 for (int w = 1; w < kWaves; ++w) s += R[(w * S::GT + q) * 64 + lane];
@@ -536,13 +607,13 @@ __global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, ML, NT)) void fi
                 int l = L - 1, ot = 0, col;
                 if (at < MT) {
                     ot = at;
-                    l = n < NH ? n - skip + 1 : (n == kColOut ? L - 1 : 0);
-                    col = n < NH ? (n >= skip ? misc->d[l] : -1) : (n == kColOut ? misc->d[l] : (n >= kColFirst && n < kColFirst + 3 ? (n + 2 - kColFirst) % 3 : -1));
+                    l = n < NH ? n + 1 : (n == kColOut ? L - 1 : 0);
+                    col = n < NH ? misc->d[l] : (n == kColOut ? misc->d[l] : (n >= kColFirst && n < kColFirst + 3 ? (n + 2 - kColFirst) % 3 : -1));
                     if (col < 0) l = 0;
                 } else if (at < 2 * MT) {
                     col = (at - MT) * 16 + n;
                 } else {
-                    l = h / (MT * MT) - skip + 1;
+                    l = h / (MT * MT) + 1;
                     ot = h / MT % MT;
                     col = h % MT * 16 + n;
                 }

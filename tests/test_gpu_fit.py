@@ -101,6 +101,12 @@ def test_split_kernels_at_the_edges_of_their_depth_buckets(width, L):
         assert np.abs(grad[i] - want_g).max() <= 2e-5 * np.abs(want_g).max()
 
 
+@pytest.mark.parametrize("width,L", [(9, 3), (16, 6), (14, 9), (16, 10), (13, 11), (18, 2), (32, 3), (25, 10), (32, 11), (40, 2), (48, 3), (41, 6), (40, 9)])
+def test_split_kernels_at_the_other_depths(width, L):
+    """The depths between: there is a kernel for each."""
+    test_split_kernels_at_the_edges_of_their_depth_buckets(width, L)
+
+
 @pytest.mark.parametrize("family", list(FAMILIES))
 @pytest.mark.parametrize("widths,n,H,W", [([2, 15, 15, 3], 40000, 7, 9), ([2, 40, 40, 3], 4200, 9, 15), ([2, 30, 3], 20000, 5, 26)])
 def test_many_images_and_few_agree_with_the_oracle(widths, n, H, W, family):

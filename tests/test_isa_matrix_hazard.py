@@ -129,3 +129,20 @@ def test_fit_kernels_use_one_matrix_opcode_per_accumulator(tmp_path):
         assert scan_kernel(body) is None
         seen += 1
     assert seen >= 10, seen
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not found")
+def test_fit_kernels_beyond_256_registers_do_not_spill(tmp_path):
+    """The compiler loses reloads of parts of a matrix result that it spilled in such a kernel (wrong gradients, seen in
+    the assembly), so none may spill.  Compiled with the flags of the build."""
+    from paper_2306_16699_amd import build
+    out = tmp_path / "rinr_fit.s"
+    cmd = ["hipcc", *build.HIP_FLAGS, *build.SOURCES["rinr_fit.hip"], "--cuda-device-only", "-S", "-o", str(out), FIT_SRC]
+    subprocess.run(cmd, check=True, stdout=subprocess.DEVNULL, stderr=subprocess.PIPE)
+    big, spilled = 0, []
+    for name, regs, spills in re.findall(r"\.name:\s+(\S*step_kernel\S*).*?\.vgpr_count:\s+(\d+).*?\.vgpr_spill_count:\s+(\d+)", out.read_text(), re.S):
+        if int(regs) > 256:
+            big += 1
+            if int(spills):
+                spilled.append((name, regs, spills))
+    assert big >= 8 and not spilled, (big, spilled)
