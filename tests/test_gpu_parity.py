@@ -599,3 +599,15 @@ def test_zz_report_worst_errors():
              rinr.FLAG_FP16_ALL: "fp16 weights and activations where granted", rinr.FLAG_FP16_ACT | UNCHECKED: "fp16 activations forced",
              rinr.FLAG_FP16_ALL | UNCHECKED: "fp16 weights and activations forced"}
     print("largest unclamped max-abs error per mode:", {names[m]: f"{e:.2e}" for m, e in WORST.items()})
+
+
+@pytest.mark.parametrize("n,H,W,width", [(1, 224, 224, 40), (2, 64, 64, 16), (1, 5, 3, 32), (33, 100, 101, 64), (300, 64, 65, 24), (129, 32, 32, 15)])
+def test_the_launch_plan_does_not_change_the_bytes(torch, n, H, W, width):
+    """Few slots take small workgroups, and slots of one cost are split so that whole rounds fill the machine."""
+    models = synth.make_models(5, np.arange(7), width, 3, [0, 8, 8, 0], 0.6)
+    st = rinr.Store(rinr.pack(models))
+    ids = torch.arange(n, device="cuda") % 7
+    got = st.decode_batch(ids, H, W)
+    want = st.decode_batch_ex(ids, H, W, threads=512, blocks_per_cu=1)
+    assert torch.equal(got, want)
+    st.close()
