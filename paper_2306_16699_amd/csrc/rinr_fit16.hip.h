@@ -28,7 +28,7 @@
 // a layer's units is treated the same way in the forward and backward products ([Wh | Wl] x [Hh | Hh], x [Hl | Hl]).
 //
 // LDS holds the weights of the hidden layers twice, once with the outputs and once with the inputs as rows (those times the
-// factor that the error is multiplied by going down, see below), in operand order: per pair of 16-unit tiles a hi and a lo
+// factor that the error is multiplied by going down, where it is above 1, see below), in operand order: per pair of 16-unit tiles a hi and a lo
 // plane of 64-byte rows, 16 bytes per lane group: the quads of both tiles; an odd last tile's plane has the hi and the lo quad
 // side by side.  A lane reads an operand as one 16-byte word at a fixed place
 // in its row; rows 4..7 of every eight have their two pairs of words exchanged, which makes that read free of bank conflicts
@@ -42,6 +42,11 @@
 // which keeps the scaled error's magnitude level through deep models.  The split of the error rounds toward zero, which
 // saturates at the largest half instead of producing infinities; 1 / T_l goes into the factor that the accumulated
 // gradient is multiplied by at the end.
+// A layer's factor above 1 (the usual case) is in its transposed weights: times a power of two both halves stay exact.  Below 1
+// (an estimated gain above 1.4) the low half would go into fp16's subnormals, 1.1e-7 of the weights' size instead of 4.6e-8
+// (64 units, factor 1/64), so such a factor multiplies the cosine in fp32.  One more multiply per unit costs every model
+// 2 to 6 % (10 layers x 40: 6.26 -> 6.65 ms a step); so the code over the pixels is there twice, and a model takes the form with the
+// multiply only if one of its factors is below 1.  The other form's times stay (10 x 40: 6.27 -> 6.24 ms, 3 x 15: 0.0677 -> 0.0679).
 #pragma once
 
 namespace fit16 {
@@ -78,6 +83,7 @@ struct Misc {              // small tables at the start of LDS; everything behin
     float grad[16];        // factor of the accumulated gradient, per layer
     float scale[kMaxL];    // per layer: what the error is multiplied by going down through it
     float out;             // the output difference's factor
+    int32_t below;         // a factor in `scale` is below 1
     float ss[kMaxL][kWaves];
     float red[kWaves];
     int32_t d[16], p_off[kMaxL];
@@ -178,31 +184,14 @@ constexpr int fit16_waves_per_simd(int wp, int ml, int nt) {
         if (stop) return;                  \
     } while (0)
 
-// One kernel per depth L: the hidden layers are steps u = 0 .. L - 3 of unrolled code without conditions, so that what one
-// layer's end and the next one's start have to do runs side by side.  Forward, a piece of code between two edges takes the last
-// block of a layer's contraction (its odd last tile, or last pair of tiles), the sines and splits of its tiles as they come
-// out, and the next layer's other blocks, whose operand words it has loaded first; the row tiles take turns at the matrix
-// unit.  With a layer a piece of its own, as before, a layer's matrix steps waited for each other and for every load, and its
-// sines came after them.  Measured, ms a step, before -> now: 256 images of 224 x 224, 10 layers x 40: 6.83 -> 6.29; 512 of
-// 224 x 224, 10 x 32: 6.98 -> 6.00; 512 of 96 x 96, 5 x 24: 0.532 -> 0.457; 64 of 128 x 128, 6 x 64: 0.500 -> 0.450.  Forcing one
-// matrix step per two to four vector instructions backward (scheduling groups) was slower: 7.8 ms at 10 x 40.
-template <int WP, int L, int NT>
-__global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, L, NT)) void fit16_step_kernel(const FitArgs a) {
+// Weights and tables of image `img` into LDS.  Returns whether some layer's factor of the error is below 1 (the same in every lane).
+template <int WP, int L> __device__ __forceinline__ bool fit16_set_up(const FitArgs &a, char *lds, size_t img, int wave) {
     typedef Shape<WP> S;
-    constexpr int MT = S::MT, NH = L - 2, kPC = kWaves * 16 * NT;
-    constexpr int kColOut = 11, kColFirst = 12;         // columns of acc_b: step u's biases in column u, the output layer's, the first layer's bias, x and y
-    const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
-    const h4v zh = {(_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f};
-    extern __shared__ __attribute__((aligned(16))) char lds16[];
-    char *const lds = lds16;
+    constexpr int MT = S::MT;
     Misc *const misc = (Misc *)(lds + S::MISC);
     const int tid = threadIdx.x;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int lane = tid & 63, n = lane & 15, g = lane >> 4;
-    const FitShare share = fit_share(a, (a.HW + kPC - 1) / kPC);
-    const size_t img = share.img;
+    const int lane = tid & 63;
     const float *P = a.params + img * a.n_params;
-    const float neg1 = a.neg1;
 
     // ---- set up: zero everything; weights as hi/lo operands (sine layers times w0 / 2pi: Z comes out in revolutions), biases;
     //      per layer the sum of squared weights (for the error's scale), summed in a fixed order.  A thread has all its weights
@@ -265,6 +254,7 @@ __global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, L, NT)) void fit
         T = fminf(fmaxf(T, 1e-30f), 1e30f);
         misc->out = T * 2.0f * a.loss_scale;                                // what the output difference is multiplied by
         misc->grad[L - 1] = a.gscale[L - 1] / T;
+        bool below = false;
         for (int l = L - 1; l >= 1; --l) {
             float ss = 0.0f;
             for (int w = 0; w < kWaves; ++w) ss += misc->ss[l][w];
@@ -273,18 +263,44 @@ __global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, L, NT)) void fit
             r = fminf(fmaxf(r, 0.015625f), 256.0f);
             if (!(T * r < 1e30f && T * r > 1e-30f)) r = 1.0f;
             T *= r;
-            misc->scale[l] = r;                                             // E_{l-1} = (r W_l^T E_l) cos(.)
+            misc->scale[l] = r;                                             // E_{l-1} = r (W_l^T E_l) cos(.)
+            below |= r < 1.0f;
             misc->grad[l - 1] = a.gscale[l - 1] / T;
         }
+        misc->below = below;
     }
     __syncthreads();
-    // the transposed weights carry that factor (a power of two)
+    const bool below = __builtin_amdgcn_readfirstlane(misc->below) != 0;
+    // the transposed weights carry that factor where it is above 1
     for (int l = 1; l < L; ++l) {
-        const _Float16 r = (_Float16)misc->scale[l];
+        const _Float16 r = (_Float16)fmaxf(misc->scale[l], 1.0f);
         h8v *const T = (h8v *)(lds + (l == L - 1 ? S::LASTT : S::HID0 + (uint32_t)(2 * l - 1) * S::HID));
         for (uint32_t q = tid; q < (l == L - 1 ? S::PLANE : S::HID) / 16; q += kThreads) T[q] *= r;
     }
     __syncthreads();
+
+    return below;
+}
+
+// One kernel per depth L: the hidden layers are steps u = 0 .. L - 3 of unrolled code without conditions, so that what one
+// layer's end and the next one's start have to do runs side by side.  Forward, a piece of code between two edges takes the last
+// block of a layer's contraction (its odd last tile, or last pair of tiles), the sines and splits of its tiles as they come
+// out, and the next layer's other blocks, whose operand words it has loaded first; the row tiles take turns at the matrix
+// unit.  With a layer a piece of its own, as before, a layer's matrix steps waited for each other and for every load, and its
+// sines came after them.  Measured, ms a step, before -> now: 256 images of 224 x 224, 10 layers x 40: 6.83 -> 6.29; 512 of
+// 224 x 224, 10 x 32: 6.98 -> 6.00; 512 of 96 x 96, 5 x 24: 0.532 -> 0.457; 64 of 128 x 128, 6 x 64: 0.500 -> 0.450.  Forcing one
+// matrix step per two to four vector instructions backward (scheduling groups) was slower: 7.8 ms at 10 x 40.
+// kBelow: some layer's factor of the error is below 1 and is applied here, on the cosine (see the file header).
+template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fit16_pixels(const FitArgs &a, char *lds, const FitShare &share, int wave) {
+    typedef Shape<WP> S;
+    constexpr int MT = S::MT, NH = L - 2, kPC = kWaves * 16 * NT;
+    constexpr int kColOut = 11, kColFirst = 12;         // columns of acc_b: step u's biases in column u, the output layer's, the first layer's bias, x and y
+    const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
+    const h4v zh = {(_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f};
+    Misc *const misc = (Misc *)(lds + S::MISC);
+    const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
+    const size_t img = share.img;
+    const float neg1 = a.neg1;
 
     f32x4 acc[NH > 0 ? NH : 1][MT][MT];                         // weight gradients of the hidden layers: rows are outputs, columns inputs
     f32x4 acc_last[MT], acc_b[MT];                 // output layer (channel c in row 4 c); biases and first layer
@@ -430,10 +446,11 @@ __global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, L, NT)) void fit
         f32x4 E[NT][MT];                   // the error at hand, scaled (see the file header)
         h4v Eh[NT][MT], El[NT][MT];
         // Its split belongs to the end of the layer that leaves it, beside that layer's weight gradient (10 layers x 32: 6.08 ->
-        // 6.00 ms a step); where registers are scarce, to the start of the next; and where they are scarcest (10 x 40), the
-        // contraction comes before the turning: nothing may be spilled there (see FIT16_EDGE), and the faster order, 6.08 ms
-        // against 6.29, spills 20.
-        constexpr bool kLate = fit16_registers(WP, L, NT) > 480, kScarce = fit16_registers(WP, L, NT) > 500;
+        // 6.00 ms a step); where registers are scarce, to the start of the next; and where they are scarcest (one kernel: padded width
+        // 48, 10 layers), the contraction comes before the turning: nothing may be spilled there (see FIT16_EDGE), and the
+        // faster order, 6.08 ms against 6.29, spills 20.  So it does in the rarer of the two forms, at every shape.
+        constexpr bool kLate = fit16_registers(WP, L, NT) > 480, kScarce = kBelow || fit16_registers(WP, L, NT) > 500;
+        auto slope = [&](f32x4 z, int l) { return kBelow ? cos4(z) * fminf(misc->scale[l], 1.0f) : cos4(z); };
         auto leave = [&](int nt, int t, f32x4 e) {
             E[nt][t] = e;
             if (!kLate) split_rtz(e, neg1, Eh[nt][t], El[nt][t]);
@@ -482,7 +499,7 @@ __global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, L, NT)) void fit
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                for (int t = 0; t < MT; ++t) leave(nt, t, E[nt][t] * cos4(zst[NH][nt][t]));
+                for (int t = 0; t < MT; ++t) leave(nt, t, E[nt][t] * slope(zst[NH][nt][t], L - 1));
         }
 
         // ---- backward: the error goes down through the hidden layers, each layer's weight gradient takes these pixels
@@ -547,11 +564,11 @@ __global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, L, NT)) void fit
                     if (NT == 2) acc[u][t][i] = mfma32(A1[t], b0, acc[u][t][i]);
                 }
             }
-            // E_{l-1} = (r W_l^T E_l) cos(2 pi z_{l-1})
+            // E_{l-1} = r (W_l^T E_l) cos(2 pi z_{l-1})
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                for (int t = 0; t < MT; ++t) leave(nt, t, down[nt][t] * cos4(zst[u][nt][t]));
+                for (int t = 0; t < MT; ++t) leave(nt, t, down[nt][t] * slope(zst[u][nt][t], u + 1));
         }
         // ---- first layer: its input's columns are one, x, y
         {
@@ -629,6 +646,16 @@ __global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, L, NT)) void fit
             __syncthreads();
         }
     }
+}
+
+template <int WP, int L, int NT>
+__global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, L, NT)) void fit16_step_kernel(const FitArgs a) {
+    extern __shared__ __attribute__((aligned(16))) char lds16[];
+    const uint32_t pixels = kWaves * 16 * NT;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const FitShare share = fit_share(a, (a.HW + pixels - 1) / pixels);
+    if (!fit16_set_up<WP, L>(a, lds16, share.img, wave)) fit16_pixels<WP, L, NT, false>(a, lds16, share, wave);
+    else fit16_pixels<WP, L, NT, true>(a, lds16, share, wave);
 }
 
 }  // namespace fit16

@@ -202,6 +202,39 @@ def test_split_kernels_carry_the_error_at_any_size():
     f.close()
 
 
+@pytest.mark.parametrize("family", list(FAMILIES))
+@pytest.mark.parametrize("width,L", [(16, 3), (15, 7), (16, 8), (24, 4), (32, 12), (40, 3), (48, 7), (40, 10), (64, 4), (64, 6)])
+def test_large_weights_lose_nothing_on_the_way_down(width, L, family):
+    """A layer that multiplies the error by far more than one: its small weights arrive with all their bits.  With zero weights
+    below it every pre-activation is 0 and every cosine 1, and one unit alone gets an error from above, a power of two, so
+    the bias gradient of each unit is one weight times a power of two."""
+    H = W = 4
+    widths = [2] + [width] * (L - 1) + [3]
+    rng = np.random.default_rng(width + L)
+    small = rng.uniform(0.02, 0.2, (2, width)) * rng.choice([-1.0, 1.0], (2, width))
+    p0 = np.zeros((2, fo.n_params(widths)), np.float32)
+    mats = [rinr_fit.split_params(widths, p) for p in p0]
+    mats[0][L - 1][0][0] = small[0]                           # image 0: the output layer, channel 0
+    mats[0][L - 1][0][1:] = 40.0                              # (channels 1 and 2 set the layer's size and see no error)
+    mats[1][L - 2][0][:] = 40.0                               # image 1: the last hidden layer, unit 2
+    mats[1][L - 2][0][2] = small[1]
+    mats[1][L - 1][0][0, 2] = 1.0
+    tgt = np.zeros((2, 3, H, W), np.float32)
+    tgt[:, 0] = -8.0                                          # the output is 0: an error of 8 in channel 0
+    import torch
+    f = rinr_fit.Fit(widths, 2, H, W, fp32=FAMILIES[family])
+    f.set_params(p0)
+    _, grad = f.loss_grad(torch.from_numpy(tgt).cuda(), loss_scale=2.0 ** -10)
+    f.close()
+    for i, l in ((0, L - 2), (1, L - 3)):
+        _, want = fo.loss_grad(widths, p0[i].astype(np.float64), tgt[i], None, loss_scale=2.0 ** -10)
+        got, want = rinr_fit.split_params(widths, grad[i])[l][1], rinr_fit.split_params(widths, want)[l][1]
+        # split of the weight 2^-23 of itself or 2^-25; split of the error, toward zero twice, 2^-20 of itself or 2^-24 (it is 0.3 or
+        # more); sum over 16 equal terms and six factors in fp32
+        bound = (2.0 ** -23 + 2.0 ** -25 / 0.02 + 2.0 ** -20 + 2.0 ** -24 / 0.3 + 21 * 2.0 ** -24) * np.abs(want)
+        assert want.all() and np.all(np.abs(got - want) <= bound), (i, np.max(np.abs(got / want - 1.0)))
+
+
 @pytest.mark.parametrize("widths,H,W,steps,lr,tol", [([2, 15, 15, 3], 32, 32, 600, 2e-3, 2e-3),
                                                      ([2] + [32] * 4 + [3], 40, 56, 400, 1e-3, 2e-2),
                                                      ([2] + [40] * 9 + [3], 48, 48, 400, 5e-4, 0.5)],
