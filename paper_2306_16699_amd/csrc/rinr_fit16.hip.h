@@ -169,9 +169,15 @@ constexpr int fit16_registers(int wp, int ml, int nt) {
     const int mt = wp / 16;
     return 4 * (2 * mt + (ml - 2) * mt * mt) + 4 * nt * mt * (ml - 1) + 40 + 16 * nt * mt;
 }
+// Wavefronts per SIMD a kernel is compiled for: as many as its estimate leaves without a spill, but for one shape, which spills
+// at three and is the better for it.  Measured, us a step, spilled -> as chosen:
+//   four instead of three, 48 x 48, width 16, 2048 images: 4 layers 198 -> 189, 5 layers 249 -> 241; 6144 images: 561 -> 555, 692 -> 691;
+//     against it only where four make whole rounds (1024 images of 64 x 64, width 15): 175 -> 180, 219 -> 227
+//   two instead of three: 8 layers x 16: 243 -> 232; 3 x 32: 150 -> 144
+//   three (spills 24) instead of two at 7 layers x 16, 48 x 48: 6144 images 1063 -> 1001; against it 1024 of 64 x 64: 319 -> 328
 constexpr int fit16_waves_per_simd(int wp, int ml, int nt) {
     const int r = fit16_registers(wp, ml, nt);
-    return r <= 128 ? 4 : (r <= 156 ? 3 : (r <= 256 ? 2 : 1));     // a third wavefront at 160 (8 x 16) or 168 (3 x 32) spills: 243 against 232 us, 150 against 144
+    return r <= 100 ? 4 : (r <= 156 ? 3 : (r <= 256 ? 2 : 1));
 }
 
 // Ends a basic block between two layers: `stop` is 0, which the compiler cannot see.  A whole chunk as one block has its
