@@ -79,7 +79,8 @@ enum { RINR_FIT_KERNEL_FP32 = 0,        /* rinr_fit_kernel_family: fp32 operands
 
 /* Device state for fitting n_images models of one architecture to H x W targets (Eq. 1): parameters, Adam moments, keep
  * flags, per-image losses (3 * 4 + 1 bytes per parameter), and, where the images are too few to fill the GPU one by one,
- * partial gradients of several workgroups per image (at most 4 bytes per parameter for 8 workgroups per compute-unit slot).
+ * partial gradients of several workgroups per image (at most 4 bytes per parameter for 8 workgroups per compute-unit slot;
+ * without the memory for them an image is one workgroup's, which is slower).
  * All images share the architecture; each has its own parameters.
  * Two families of kernels compute the same step.  The split-precision ones (the default where they are built for the
  * shape) keep the weights of all layers in one CU's LDS as fp16 hi/lo planes and the pre-activations of 16 pixels per

@@ -606,9 +606,11 @@ extern "C" int rinr_fit_create_ex(const rinr_fit_arch *arch, int64_t n_images, i
         return RINR_E_HIP;
     }
     f->splits = plan_splits(f, fn);
+    // no memory for the partial gradients: a workgroup takes a whole image, and the refusal is not left for the first launch's check
     if (f->splits > 1 && hip_fail(hipMalloc((void **)&f->part, ni * (size_t)f->splits * (size_t)(f->n_params + 1) * 4))) {
-        rinr_fit_destroy(f);
-        return RINR_E_HIP;
+        f->part = nullptr;
+        f->splits = 1;
+        (void)hipGetLastError();
     }
     *out = f;
     return RINR_OK;

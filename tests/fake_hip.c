@@ -1,0 +1,67 @@
+/* The HIP runtime calls that librinr.so makes, as host stand-ins: allocations come from the heap (those above a limit fail),
+ * kernel launches are only written down.  For tests of the library's host side without a GPU; loaded before librinr.so. */
+#include <stddef.h>
+#include <stdint.h>
+#include <stdlib.h>
+#include <string.h>
+
+typedef struct { uint32_t x, y, z; } dim3;
+enum { OK = 0, OUT_OF_MEMORY = 2, N_LAUNCHES = 1024 };
+
+static int last_error;
+static size_t malloc_limit = SIZE_MAX;
+static int cus = 256, resident = 1;
+static int64_t live;                    /* allocations not freed */
+static int n_launches;
+static uint32_t launches[N_LAUNCHES][4];       /* grid x, y; threads; dynamic LDS */
+
+void fake_set(size_t limit, int n_cus, int n_resident) { malloc_limit = limit; cus = n_cus; resident = n_resident; n_launches = 0; }
+int fake_launches(uint32_t *out) { memcpy(out, launches, (size_t)n_launches * sizeof launches[0]); return n_launches; }
+int64_t fake_live(void) { return live; }
+
+int hipMalloc(void **p, size_t n) {
+    *p = n <= malloc_limit ? calloc(1, n ? n : 1) : NULL;
+    if (!*p) return last_error = OUT_OF_MEMORY;
+    ++live;
+    return OK;
+}
+int hipFree(void *p) { if (p) --live; free(p); return OK; }
+int hipMemset(void *p, int v, size_t n) { memset(p, v, n); return OK; }
+int hipMemcpy(void *d, const void *s, size_t n, int kind) { (void)kind; memcpy(d, s, n); return OK; }
+int hipGetLastError(void) { const int e = last_error; last_error = OK; return e; }      /* reported once, as the runtime does */
+int hipDeviceSynchronize(void) { return OK; }
+int hipStreamSynchronize(void *s) { (void)s; return OK; }
+int hipGetDevice(int *d) { *d = 0; return OK; }
+int hipDeviceGetAttribute(int *v, int attr, int d) { (void)attr; (void)d; *v = cus; return OK; }
+int hipFuncSetAttribute(const void *f, int attr, int v) { (void)f; (void)attr; (void)v; return OK; }
+int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *f, int threads, size_t lds) {
+    (void)f; (void)threads; (void)lds;
+    *n = resident;
+    return OK;
+}
+
+static struct { dim3 grid, block; size_t lds; void *stream; } call;
+int __hipPushCallConfiguration(dim3 grid, dim3 block, size_t lds, void *stream) {
+    call.grid = grid; call.block = block; call.lds = lds; call.stream = stream;
+    return OK;
+}
+int __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, void **stream) {
+    *grid = call.grid; *block = call.block; *lds = call.lds; *stream = call.stream;
+    return OK;
+}
+int hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t lds, void *stream) {
+    (void)f; (void)args; (void)stream;
+    if (n_launches < N_LAUNCHES) {
+        uint32_t *l = launches[n_launches++];
+        l[0] = grid.x; l[1] = grid.y; l[2] = block.x; l[3] = (uint32_t)lds;
+    }
+    return OK;
+}
+void **__hipRegisterFatBinary(const void *data) { static void *h; (void)data; return &h; }
+void __hipUnregisterFatBinary(void **h) { (void)h; }
+void __hipRegisterFunction(void **h, const void *f, char *df, const char *n, unsigned lim, void *a, void *b, void *c, void *d, int *w) {
+    (void)h; (void)f; (void)df; (void)n; (void)lim; (void)a; (void)b; (void)c; (void)d; (void)w;
+}
+void __hipRegisterVar(void **h, void *v, char *hv, char *dv, int ext, size_t size, int constant, int global) {
+    (void)h; (void)v; (void)hv; (void)dv; (void)ext; (void)size; (void)constant; (void)global;
+}
