@@ -532,7 +532,7 @@ namespace {
 // idle (few of them, or a last round that is nearly empty), an image's pixels are shared by several, and a second kernel
 // adds their partial gradients up.  The model: rounds of workgroups x (a share's chunks + what a workgroup costs before its
 // first chunk, about two chunks' time), and for more than one share the second launch (about one chunk more).  Measured
-// (8 images of 171 x 219, 10 layers x 32): 3241 us a step with one workgroup per image, 142 with 32.
+// (8 images of 171 x 219, 10 layers x 32): 3241 us a step with one workgroup per image, 106 with 30 and the kernels of today.
 int plan_splits(const rinr_fit *f, const void *fn) {
     const bool split16 = f->family == RINR_FIT_KERNEL_SPLIT16;
     const int waves = split16 ? fit16::kWaves : fit_waves(f->wq);

@@ -68,5 +68,39 @@ def test_without_memory_for_partial_sums_a_workgroup_takes_a_whole_image(tmp_pat
     assert all(g["live"] == 0 for g in got)
 
 
+# case, the pixels a workgroup takes at a time, workgroups that run side by side on a CU (four wavefronts per SIMD at most), workgroups per image (None: more than one)
+PLANS = {
+    "few photographs": (case(8, 171, 219, 32, 10), 128, 1, 30),              # one round of 256, ten chunks each
+    "one photograph": (case(1, 224, 224, 40, 10), 64, 1, 196),              # four chunks each; shorter shares pay more for their start
+    "one per CU": (case(256, 224, 224, 40, 10), 64, 1, 1),
+    "one more than CUs": (case(257, 224, 224, 40, 10), 64, 1, None),        # a second round for one image would double the step
+    "two full rounds": (case(2048, 32, 32, 15, 3, resident=4), 128, 4, 1),
+    "many": (case(5000, 64, 64, 40, 10), 64, 1, 1),                         # 16 rounds and more: the last one's idle part does not matter
+    "two chunks": (case(2, 16, 16, 32, 10), 128, 1, 1),                     # sharing would cost the second launch what it saves
+    "three chunks": (case(2, 18, 18, 32, 10), 128, 1, 3),                   # no share without pixels
+    "one chunk": (case(3, 5, 7, 16, 3, resident=8), 128, 4, 1),
+    "fp32 kernels": (case(8, 171, 219, 32, 10, fp32=1, resident=2), 64, 2, None),
+    "fp32, one per CU": (case(256, 224, 224, 64, 7, resident=1), 64, 1, 1),
+}
+
+
+def test_workgroups_per_image(tmp_path):
+    got = on_fake_runtime(tmp_path, [c for c, _, _, _ in PLANS.values()])
+    for (name, (c, pixels, side, want)), g in zip(PLANS.items(), got):
+        assert g["rc"] == [0, 0, 0] and g["live"] == 0
+        n, slots, chunks = c["n"], CUS * side, -(-c["H"] * c["W"] // pixels)
+        grid = g["launches"][0][0]
+        s = grid // n
+        assert grid == n * s and 1 <= s <= chunks, (name, s)
+        assert s == want if want else s > 1, (name, s)
+
+        def cost(s):                                # chunk times: rounds of workgroups x (a share and its start), and the second launch
+            return -(-n * s // slots) * (-(-chunks // s) + 2) + (s > 1)
+        assert cost(s) <= cost(1) and all(cost(s) <= cost(t) for t in range(2, min(chunks, 8 * slots // n) + 1) if n < 16 * slots), (name, s)
+        n_params = sum((i + 1) * o for i, o in zip(c["widths"], c["widths"][1:]))
+        second = [[n_params // 64 + 1, n, 256 if s <= 16 else 1024]] if s > 1 else []
+        assert [l[:3] for l in g["launches"][1:]] == second, name
+
+
 if __name__ == "__main__":
     child(sys.argv[1], json.loads(sys.argv[2]))
