@@ -16,6 +16,8 @@ import subprocess
 
 import pytest
 
+from paper_2306_16699_amd import build
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 SRC = os.path.join(ROOT, "paper_2306_16699_amd", "csrc", "rinr_api.hip")
 FIT_SRC = os.path.join(ROOT, "paper_2306_16699_amd", "csrc", "rinr_fit.hip")
@@ -89,13 +91,21 @@ def test_scanner_sees_a_close_pair_and_a_separated_one():
     assert scan_kernel(rewritten) is None                 # the accumulator was reloaded: no dependency on the first
 
 
+def assembly(src, out):
+    """The gfx950 assembly of a source, with the flags of the build."""
+    cmd = ["hipcc", *build.HIP_FLAGS, *build.SOURCES[os.path.basename(src)], "--cuda-device-only", "-S", "-o", str(out), src]
+    subprocess.run(cmd, check=True, stdout=subprocess.DEVNULL, stderr=subprocess.PIPE)
+    return out.read_text()
+
+
+@pytest.fixture(scope="module")
+def fit_asm(tmp_path_factory):
+    return assembly(FIT_SRC, tmp_path_factory.mktemp("isa") / "rinr_fit.s")
+
+
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not found")
 def test_mixed_depth_matrix_steps_stay_apart(tmp_path):
-    out = tmp_path / "rinr_api.s"
-    cmd = ["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-Wno-unused-command-line-argument", "--cuda-device-only", "-S", "-o", str(out), SRC]
-    subprocess.run(cmd, check=True, stdout=subprocess.DEVNULL, stderr=subprocess.PIPE)
-    text = out.read_text()
+    text = assembly(SRC, tmp_path / "rinr_api.s")
     n_kernels = n_pairs = 0
     bad = []
     for name, body in kernels_of(text):
@@ -113,15 +123,11 @@ def test_mixed_depth_matrix_steps_stay_apart(tmp_path):
 
 
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not found")
-def test_fit_kernels_use_one_matrix_opcode_per_accumulator(tmp_path):
+def test_fit_kernels_use_one_matrix_opcode_per_accumulator(fit_asm):
     """The fit kernels avoid the case altogether: each family uses a single matrix instruction (the split-precision ones
     pad an odd last tile with zeros rather than take a half-depth step)."""
-    out = tmp_path / "rinr_fit.s"
-    cmd = ["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-           "-Wno-unused-command-line-argument", "--cuda-device-only", "-S", "-o", str(out), FIT_SRC]
-    subprocess.run(cmd, check=True, stdout=subprocess.DEVNULL, stderr=subprocess.PIPE)
     seen = 0
-    for name, body in kernels_of(out.read_text()):
+    for name, body in kernels_of(fit_asm):
         if "step_kernel" not in name:
             continue
         ops = {m.group(1) for m in map(MFMA.match, body) if m}
@@ -132,15 +138,11 @@ def test_fit_kernels_use_one_matrix_opcode_per_accumulator(tmp_path):
 
 
 @pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not found")
-def test_fit_kernels_beyond_256_registers_do_not_spill(tmp_path):
+def test_fit_kernels_beyond_256_registers_do_not_spill(fit_asm):
     """The compiler loses reloads of parts of a matrix result that it spilled in such a kernel (wrong gradients, seen in
-    the assembly), so none may spill.  Compiled with the flags of the build."""
-    from paper_2306_16699_amd import build
-    out = tmp_path / "rinr_fit.s"
-    cmd = ["hipcc", *build.HIP_FLAGS, *build.SOURCES["rinr_fit.hip"], "--cuda-device-only", "-S", "-o", str(out), FIT_SRC]
-    subprocess.run(cmd, check=True, stdout=subprocess.DEVNULL, stderr=subprocess.PIPE)
+    the assembly), so none may spill."""
     big, spilled = 0, []
-    for name, regs, spills in re.findall(r"\.name:\s+(\S*step_kernel\S*).*?\.vgpr_count:\s+(\d+).*?\.vgpr_spill_count:\s+(\d+)", out.read_text(), re.S):
+    for name, regs, spills in re.findall(r"\.name:\s+(\S*step_kernel\S*).*?\.vgpr_count:\s+(\d+).*?\.vgpr_spill_count:\s+(\d+)", fit_asm, re.S):
         if int(regs) > 256:
             big += 1
             if int(spills):
