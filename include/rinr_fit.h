@@ -117,7 +117,7 @@ int rinr_fit_get_params(const rinr_fit *fit, float *params, void *stream);
  * step, one workgroup per image (few images: several per image and a second, small kernel that adds their gradients up
  * in a fixed order), nothing allocated, no synchronisation.  targets: device,
  * float[n_images][3][H][W], 4-byte aligned, values on the 0..1 scale of the decoded image.
- * Same handle, same inputs: same bits, whichever call order led there.  But how an image's pixels are cut into partial sums
+ * The same calls on handles of one shape give the same bits.  But how an image's pixels are cut into partial sums
  * is chosen when the handle is created, from n_images, H, W, the architecture and the GPU's number of compute units; so the
  * same image fitted alone, in a batch, or on another GPU can differ in the rounding of its gradient (both within the bar of the
  * tests), and after many steps as far as any rounding difference carries.  To reproduce a fit bit for bit, keep all of these. */

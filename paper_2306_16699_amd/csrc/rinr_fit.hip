@@ -220,7 +220,13 @@ __global__ __launch_bounds__(Shape<WQ>::NTHREADS, fit_waves_per_simd(WQ)) void f
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, m = lane & 15, kq = lane >> 4;
-    const FitShare share = fit_share(a, (a.HW + PC - 1) / PC);
+    // fit_share divides on the vector ALU; its results, the same in every lane, are taken out of the vector registers, where they
+    // would stay over the whole kernel: 8 more of the deepest kernels' registers spilled (us a step, 256 images of 128 x 128:
+    // 12 layers x 24 3732 -> 3709, 12 x 32 4597 -> 4562).  The split-precision kernels are not the better for it (10 x 32: 6010 -> 6090).
+    FitShare share = fit_share(a, (a.HW + PC - 1) / PC);
+    share.img = __builtin_amdgcn_readfirstlane((uint32_t)share.img);
+    share.c0 = __builtin_amdgcn_readfirstlane(share.c0);
+    share.c1 = __builtin_amdgcn_readfirstlane(share.c1);
     const size_t img = share.img;
     const float *P = a.params + img * a.n_params;
     const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};

@@ -148,3 +148,13 @@ def test_fit_kernels_beyond_256_registers_do_not_spill(fit_asm):
             if int(spills):
                 spilled.append((name, regs, spills))
     assert big >= 8 and not spilled, (big, spilled)
+
+
+@pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not found")
+def test_fp32_fit_kernels_spill_only_where_they_always_did(fit_asm):
+    """Two depths of 12 layers and 7 x 64 take their register budget with a few spills; what is the same in every lane is not to add to them."""
+    allowed = {(24, 12): 24, (32, 12): 24, (64, 7): 8}
+    seen = {}
+    for wq, ml, spills in re.findall(r"\.name:\s+\S*15fit_step_kernelILi(\d+)ELi(\d+)E\S*.*?\.vgpr_spill_count:\s+(\d+)", fit_asm, re.S):
+        seen[int(wq), int(ml)] = int(spills)
+    assert set(allowed) <= set(seen) and all(s <= allowed.get(k, 0) for k, s in seen.items()), seen
