@@ -117,7 +117,7 @@ def bench_fit(args) -> int:
            "roofline": {"bound": "mfma", "achieved": ach, "peak": peak, "unit": "TFLOP/s",
                         "frac": ach / peak, "traffic": None, "kernel_ms": kern_ms,
                         "flop_per_launch": flops, "executed_over_algorithmic_flop": 3.0 if split else 1.0,
-                        "kernel": ("fit16_step_kernel (fp16 hi+lo operand pairs on MFMA 16x16x16, three terms per product, fp32 accumulate)"
+                        "kernel": ("fit16_step_kernel (fp16 hi+lo operand pairs on MFMA 16x16x32, three terms per product, fp32 accumulate)"
                                    if split else "fit_step_kernel (fp32 MFMA 16x16x4 from LDS)")}}
     if not args.no_cpu_baseline:
         from oracle import fit_oracle

@@ -16,7 +16,7 @@ HIP_FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rd
              "-Wall", "-Wno-unused-command-line-argument"]
 # Sources, the one that takes longest first, with flags of their own.  The fit kernels that run one wavefront per SIMD use all
 # 512 of its registers: matrix results that vector instructions read next go to the directly addressable half, else every
-# one of them is copied there first (10 layers x 40: 17.0 -> 11.6 ms a step when it was introduced).
+# one of them is copied there first, and six kernels spill beyond 256 registers, which must not be (10 layers x 40: 360).
 SOURCES = {"rinr_fit.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form=1"], "rinr_api.hip": [], "rinr_pack.cpp": [], "rinr_bounds.cpp": [],
            "rinr_encode.cpp": []}
 

@@ -14,7 +14,8 @@
 // What bounds it is instruction issue: a matrix instruction takes two issue slots of 4.1 clocks, a sine or cosine two, other
 // vector instructions one (measured; matrix and vector instructions of one wavefront overlap where they alternate).  A hidden
 // layer of 40 units takes 48 matrix and 169 vector slots per 16 pixels backward, 15 and 52 forward.  At 10 layers x 40 the matrix
-// unit is busy 48 % of the time and vector issue 42 %, but only a quarter of the matrix time has vector instructions beside it.
+// unit is busy 46 % of the time and vector issue 53 % (the matrix instructions' included), but only 27 % of the matrix time has
+// vector instructions beside it, and a wavefront waits 24 % of its time for loads and barriers and 15 % to issue.
 // Measured, ms a step, gradient tiles shared -> a wavefront's own -> layers interleaved (see the kernel): 256 images of 224 x 224,
 // 10 layers x 40: 8.91 -> 6.83 -> 6.29; 10 x 32: 4.54 -> 3.50 -> 3.00; 2048 of 32 x 32, 3 x 15: 0.0934 -> 0.0738 -> 0.0675.
 //
