@@ -2,7 +2,7 @@
 // Built and run by tests/test_host_sanitized.py:
 //   g++ -fsanitize=address,undefined -fno-sanitize-recover=undefined  this file
 //       + csrc/rinr_pack.cpp csrc/rinr_bounds.cpp csrc/rinr_encode.cpp  (the library's host side)
-//       + oracle/inr_oracle.c oracle/fit_oracle.c                       (the checkers)
+//       + oracle/inr_oracle.c oracle/fit_oracle.c                       (the oracles)
 // 1. pack -> validate -> unpack round trip on random models in exactly-sized heap buffers
 //    (a read or write one byte outside is an ASan report);
 // 2. seeded mutation fuzz of the blob (byte flips, truncations, edits of header / index / layer-record
