@@ -429,7 +429,6 @@ extern "C" int rinr_decode_batch_ex(rinr_store *s, const int64_t *image_ids, int
     a.span = h.coord_hi - h.coord_lo;
     a.pre = (float)((double)h.w0 / (2.0 * M_PI));
     a.no_clamp = (opts->flags & RINR_FLAG_NO_CLAMP) ? 1u : 0u;
-    a.neg1 = -1.0f;
     a.affine = opts->affine;
     a.normalize = (opts->flags & RINR_FLAG_NORMALIZE) ? 1u : 0u;
     a.tile_rows_wide = (uint32_t)s->tile_rows_wide;

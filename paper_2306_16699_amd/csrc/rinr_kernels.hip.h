@@ -315,7 +315,6 @@ struct DecodeArgs {
     uint32_t lds_budget;          // LDS a workgroup may use (160 KB unless the store was opened with less)
     uint32_t no_clamp;
     uint32_t handle_bad;          // this launch zero-fills and counts out-of-range ids
-    float neg1;                   // -1.0f, passed as data (keeps a subtraction in mixed-precision fma form)
     const float *affine;          // per-slot 2x3 map of the sampling grid, or NULL
     float ns[3], nb[3];           // per-channel scale / shift applied after the clamp when normalize != 0
     uint32_t normalize;

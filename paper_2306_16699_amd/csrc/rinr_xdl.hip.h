@@ -362,17 +362,29 @@ template <> struct XTile<32> {
     static __device__ __forceinline__ acc_t mfma_half(h4v, h4v, acc_t c) { return c; }     // never used: no odd quad at TM = 32
 };
 
-// sine of four accumulator values (one quad), then the exact hi/lo split of the results.
-// neg1 is -1.0f passed as data so that h - float(hi) stays a single mixed-precision fma.
-__device__ __forceinline__ void sine_split(float d0, float d1, float d2, float d3, float scale, float neg1, h4v &hi, h4v &lo) {
+// sine of four accumulator values (one quad), then the exact hi/lo split of the results: hi = fp16(h), lo = fp16(h - hi).
+// The four differences come from one small matrix step, v_mfma_f32_4x4x4_16b_f16, C operand h, B operand hi, A operand minus the
+// unit matrix (`neg_unit`): its 16 blocks are four lanes each, and with that A a lane gets its own C less its own B back.
+// One product per sum and a difference that 32 bits hold: exact, and the outputs are those of the
+// four mixed-precision subtractions (v_fma_mix_f32) that it replaces, byte for byte.  Those took 4.9 clocks each beside matrix work,
+// this step takes about 4.2 (a matrix step delays vector instructions by a clock per operand register of A and B, and has two
+// of each here, against four of each in a 16x16x32 step).  us before -> now: 256 images of 224 x 224, 6 x 64: 986 -> 955; 4096 of
+// 32 x 32, 4 x 32: 109.3 -> 104.0; 64 of 224 x 224, 9 x 40: 283 -> 268; 256 of 160 x 160, 4 x 16: 88.2 -> 83.1, 4 x 64 of fp32 weights: 415 -> 408.
+__device__ __forceinline__ void sine_split(float d0, float d1, float d2, float d3, float scale, h4v neg_unit, h4v &hi, h4v &lo) {
     const f2v p0 = {sin_rev(d0 * scale), sin_rev(d1 * scale)};
     const f2v p1 = {sin_rev(d2 * scale), sin_rev(d3 * scale)};
     const h2v a0 = __builtin_convertvector(p0, h2v), a1 = __builtin_convertvector(p1, h2v);
-    const f2v r0 = {__builtin_fmaf((float)a0[0], neg1, p0[0]), __builtin_fmaf((float)a0[1], neg1, p0[1])};
-    const f2v r1 = {__builtin_fmaf((float)a1[0], neg1, p1[0]), __builtin_fmaf((float)a1[1], neg1, p1[1])};
-    const h2v b0 = __builtin_convertvector(r0, h2v), b1 = __builtin_convertvector(r1, h2v);
     hi = (h4v){a0[0], a0[1], a1[0], a1[1]};
+    const f32x4 r = __builtin_amdgcn_mfma_f32_4x4x4f16(neg_unit, hi, (f32x4){p0[0], p0[1], p1[0], p1[1]}, 0, 0, 0);
+    const f2v r0 = {r[0], r[1]}, r1 = {r[2], r[3]};
+    const h2v b0 = __builtin_convertvector(r0, h2v), b1 = __builtin_convertvector(r1, h2v);
     lo = (h4v){b0[0], b0[1], b1[0], b1[1]};
+}
+// Row l % 4 of minus the unit matrix, the A operand of that step
+__device__ __forceinline__ h4v xdl_neg_unit(int lane) {
+    const _Float16 one = (_Float16)-1.0f, z = (_Float16)0.0f;
+    const int r = lane & 3;
+    return (h4v){r == 0 ? one : z, r == 1 ? one : z, r == 2 ? one : z, r == 3 ? one : z};
 }
 
 // sine of four accumulator values rounded to fp16 (single-term activations)
@@ -400,9 +412,9 @@ template <int TM, int WP> struct XHalf {
     typename XTile<TM>::acc_t D[NTH][LY::MT];      // accumulators
 };
 
-// sine + split of all accumulators of a half: WP/2 activations per lane, 4 VALU instructions each
+// sine + split of all accumulators of a half: WP/2 activations per lane, 3 VALU instructions and a quarter of a small matrix step each
 template <int TM, int WP, bool A16>
-__device__ __forceinline__ void xdl_epilogue(XHalf<TM, WP> &H, float scale, float neg1) {
+__device__ __forceinline__ void xdl_epilogue(XHalf<TM, WP> &H, float scale, h4v neg_unit) {
     typedef XLayout<TM, WP> LY;
     constexpr int QT = LY::RV / 4;                 // quads per tile
 #pragma unroll
@@ -414,7 +426,7 @@ __device__ __forceinline__ void xdl_epilogue(XHalf<TM, WP> &H, float scale, floa
                 const int q = t * QT + qq;         // quad index over the layer's rows
                 h4v hi, lo;
                 if (A16) sine_hi(H.D[nt][t][qq * 4 + 0], H.D[nt][t][qq * 4 + 1], H.D[nt][t][qq * 4 + 2], H.D[nt][t][qq * 4 + 3], scale, hi);
-                else sine_split(H.D[nt][t][qq * 4 + 0], H.D[nt][t][qq * 4 + 1], H.D[nt][t][qq * 4 + 2], H.D[nt][t][qq * 4 + 3], scale, neg1,
+                else sine_split(H.D[nt][t][qq * 4 + 0], H.D[nt][t][qq * 4 + 1], H.D[nt][t][qq * 4 + 2], H.D[nt][t][qq * 4 + 3], scale, neg_unit,
                                 hi, lo);
                 if (q < 2 * LY::KJ) {
 #pragma unroll
@@ -498,12 +510,12 @@ __device__ __forceinline__ void xdl_hidden(XHalf<TM, WP> &H, const char *lds, co
 // together with the sine/split of Y(l-1), then the matrix work of Y(l) with the sine/split of X(l).
 template <int TM, int WP, bool LO, bool A16>
 __device__ __forceinline__ void xdl_layer(XHalf<TM, WP> &X, XHalf<TM, WP> &Y, const char *lds, const XLayer el, int lane, int g,
-                                          float scale_prev, float scale, float neg1) {
+                                          float scale_prev, float scale, h4v neg_unit) {
     xdl_hidden<TM, WP, LO, A16>(X, lds, el, lane, g);
-    xdl_epilogue<TM, WP, A16>(Y, scale_prev, neg1);
+    xdl_epilogue<TM, WP, A16>(Y, scale_prev, neg_unit);
     __builtin_amdgcn_sched_barrier(0);
     xdl_hidden<TM, WP, LO, A16>(Y, lds, el, lane, g);
-    xdl_epilogue<TM, WP, A16>(X, scale, neg1);
+    xdl_epilogue<TM, WP, A16>(X, scale, neg_unit);
 }
 
 // The slot's augmentation map (every lane holds it alike), in scalar registers.
@@ -689,7 +701,7 @@ __device__ __forceinline__ void xdl_body(const DecodeArgs &a, const Work &w, flo
 
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const XLayer *tab = (const XLayer *)lds;
-    const float neg1 = a.neg1;
+    const h4v neg_unit = xdl_neg_unit(tid & 63);
     const XLayer e0 = uniform_layer(tab[0]), eo = uniform_layer(tab[L - 1]);
     const XUniform u = xdl_uniform(a, w.slot);
     // per-channel normalisation constants as values (not as an address chosen per lane)
@@ -702,7 +714,7 @@ __device__ __forceinline__ void xdl_body(const DecodeArgs &a, const Work &w, flo
         asm volatile("" : "+s"(ones));
         int lane = (int)__builtin_amdgcn_mbcnt_hi(ones, __builtin_amdgcn_mbcnt_lo(ones, 0u));
         xdl_first<TM, WP>(X, Y, a, u, lds, e0, tile, lane);
-        xdl_epilogue<TM, WP, A16>(X, 1.0f, neg1);
+        xdl_epilogue<TM, WP, A16>(X, 1.0f, neg_unit);
         // ---- hidden layers, software-pipelined over the two halves:
         //      matrix work of X(l) with the sine/split of Y(l-1), then matrix work of Y(l) with the sine/split of X(l)
         float scale_prev = 1.0f;
@@ -711,7 +723,7 @@ __device__ __forceinline__ void xdl_body(const DecodeArgs &a, const Work &w, flo
             const XLayer el = uniform_layer(tab[1]);
             int ll = lane;
             asm volatile("" : "+v"(ll));
-            xdl_layer<TM, WP, false, A16>(X, Y, lds, el, ll, ll / TM, 1.0f, el.scale, neg1);
+            xdl_layer<TM, WP, false, A16>(X, Y, lds, el, ll, ll / TM, 1.0f, el.scale, neg_unit);
             scale_prev = el.scale;
             l = 2;
         }
@@ -720,16 +732,16 @@ __device__ __forceinline__ void xdl_body(const DecodeArgs &a, const Work &w, flo
             int ll = lane;                       // the lane group is derived from the lane index per layer, not kept
             asm volatile("" : "+v"(ll));
             if constexpr (MODE == kHiddenAllInt) {
-                xdl_layer<TM, WP, false, A16>(X, Y, lds, el, ll, ll / TM, scale_prev, el.scale, neg1);
+                xdl_layer<TM, WP, false, A16>(X, Y, lds, el, ll, ll / TM, scale_prev, el.scale, neg_unit);
             } else if constexpr (MODE == kHiddenAllRaw) {
-                xdl_layer<TM, WP, !W16, A16>(X, Y, lds, el, ll, ll / TM, 1.0f, 1.0f, neg1);
+                xdl_layer<TM, WP, !W16, A16>(X, Y, lds, el, ll, ll / TM, 1.0f, 1.0f, neg_unit);
             } else {
-                if (el.off_lo == 0) xdl_layer<TM, WP, false, A16>(X, Y, lds, el, ll, ll / TM, scale_prev, el.scale, neg1);
-                else xdl_layer<TM, WP, true, A16>(X, Y, lds, el, ll, ll / TM, scale_prev, el.scale, neg1);
+                if (el.off_lo == 0) xdl_layer<TM, WP, false, A16>(X, Y, lds, el, ll, ll / TM, scale_prev, el.scale, neg_unit);
+                else xdl_layer<TM, WP, true, A16>(X, Y, lds, el, ll, ll / TM, scale_prev, el.scale, neg_unit);
             }
             scale_prev = el.scale;
         }
-        xdl_epilogue<TM, WP, A16>(Y, scale_prev, neg1);
+        xdl_epilogue<TM, WP, A16>(Y, scale_prev, neg_unit);
         asm volatile("" : "+s"(ones));           // pixel indices and addresses: derived again rather than kept
         lane = (int)__builtin_amdgcn_mbcnt_hi(ones, __builtin_amdgcn_mbcnt_lo(ones, 0u));
         xdl_output<TM, WP, A16>(X, Y, a, ns0, ns1, ns2, nb0, nb1, nb2, lds, eo, tile, lane, plane0);
@@ -757,7 +769,7 @@ __device__ __forceinline__ void xdl_stream_body(const DecodeArgs &a, const Work 
     const int K = (int)((a.lds_bytes - LY::TABLE) / (uint32_t)XSlot<TM, WP>::BYTES);   // layers per group (>= 1 by the host's launch size)
     const uint32_t *rec = (const uint32_t *)(a.blob + e.off);
     const XLayer *tab = (const XLayer *)lds;
-    const float neg1 = a.neg1;
+    const h4v neg_unit = xdl_neg_unit(tid & 63);
     const XUniform u = xdl_uniform(a, w.slot);
     // per-channel normalisation constants as values (not as an address chosen per lane)
     const float ns0 = uniform_f(a.ns[0]), ns1 = uniform_f(a.ns[1]), ns2 = uniform_f(a.ns[2]);
@@ -778,14 +790,14 @@ __device__ __forceinline__ void xdl_stream_body(const DecodeArgs &a, const Work 
                 const XLayer el = uniform_layer(tab[l]);
                 if (l == 0) {
                     xdl_first<TM, WP>(X, Y, a, u, lds, el, tile, lane);
-                    xdl_epilogue<TM, WP, A16>(X, 1.0f, neg1);
+                    xdl_epilogue<TM, WP, A16>(X, 1.0f, neg_unit);
                 } else if (l < L - 1) {
-                    if (W16) xdl_layer<TM, WP, false, A16>(X, Y, lds, el, lane, lane / TM, 1.0f, 1.0f, neg1);
-                    else if (el.off_lo == 0) xdl_layer<TM, WP, false, A16>(X, Y, lds, el, lane, lane / TM, scale_prev, el.scale, neg1);
-                    else xdl_layer<TM, WP, true, A16>(X, Y, lds, el, lane, lane / TM, scale_prev, el.scale, neg1);
+                    if (W16) xdl_layer<TM, WP, false, A16>(X, Y, lds, el, lane, lane / TM, 1.0f, 1.0f, neg_unit);
+                    else if (el.off_lo == 0) xdl_layer<TM, WP, false, A16>(X, Y, lds, el, lane, lane / TM, scale_prev, el.scale, neg_unit);
+                    else xdl_layer<TM, WP, true, A16>(X, Y, lds, el, lane, lane / TM, scale_prev, el.scale, neg_unit);
                     scale_prev = W16 ? 1.0f : el.scale;
                 } else {
-                    xdl_epilogue<TM, WP, A16>(Y, scale_prev, neg1);
+                    xdl_epilogue<TM, WP, A16>(Y, scale_prev, neg_unit);
                     xdl_output<TM, WP, A16>(X, Y, a, ns0, ns1, ns2, nb0, nb1, nb2, lds, el, tile, lane, w.plane0);
                 }
             }
