@@ -38,28 +38,31 @@ struct ClassImpl {
     decode_fn decode;         // fp32 MFMA kernel
     decode_fn decode_xdl[7];  // split-precision fp16 MFMA kernel, per kind of hidden layers (kHiddenAllInt, AllRaw, Mixed); + 3: fp16 activations; 6: all fp16
     decode_fn stream;         // fp32 MFMA kernel, layers streamed through LDS
-    decode_fn stream_xdl[3];  // split-precision kernel, layers streamed: hi+lo activations, fp16 activations, all fp16
+    decode_fn stream_xdl[4];  // split-precision kernel, layers streamed: hi+lo activations, fp16 activations, all fp16, hi+lo and all layers integer-coded
     debug_fn debug;
-    xdebug_fn xdebug[2];      // split-precision operand export: as stored / fp16 weights
+    xdebug_fn xdebug[3];      // split-precision operand export: as stored / fp16 weights / as stored, all layers integer-coded
     uint32_t slot_bytes;      // fp32 kernels: LDS of one layer in the streamed layout
-    uint32_t xslot_bytes;     // split-precision kernels: LDS of one layer in the streamed layout
+    uint32_t xslot_bytes[2];  // split-precision kernels: LDS of one layer in the streamed layout; all layers integer-coded
     uint32_t xtable_bytes;
 };
 
-template <int TM, int WP> ClassImpl make_impl() {
-    constexpr int CLS = WP / 16, XTM = xdl_tile_rows(CLS);
+// WQ: the class's padded width WP, or 8 less where every model of the class is as narrow
+template <int TM, int WP, int WQ> ClassImpl make_impl() {
+    constexpr int XTM = xdl_tile_rows(WP / 16);
     return ClassImpl{decode_kernel<TM, WP, kThreads>,
-                     {decode_xdl_kernel<CLS, kThreads, kHiddenAllInt>, decode_xdl_kernel<CLS, kThreads, kHiddenAllRaw>,
-                      decode_xdl_kernel<CLS, kThreads, kHiddenMixed>, decode_xdl_kernel<CLS, kThreads, kHiddenAllInt | kAct16>,
-                      decode_xdl_kernel<CLS, kThreads, kHiddenAllRaw | kAct16>, decode_xdl_kernel<CLS, kThreads, kHiddenMixed | kAct16>,
-                      decode_xdl_kernel<CLS, kThreads, kAct16 | kWeight16>},
+                     {decode_xdl_kernel<WQ, kThreads, kHiddenAllInt>, decode_xdl_kernel<WQ, kThreads, kHiddenAllRaw>,
+                      decode_xdl_kernel<WQ, kThreads, kHiddenMixed>, decode_xdl_kernel<WQ, kThreads, kHiddenAllInt | kAct16>,
+                      decode_xdl_kernel<WQ, kThreads, kHiddenAllRaw | kAct16>, decode_xdl_kernel<WQ, kThreads, kHiddenMixed | kAct16>,
+                      decode_xdl_kernel<WQ, kThreads, kAct16 | kWeight16>},
                      decode_stream_kernel<TM, WP>,
-                     {decode_xdl_stream_kernel<CLS, 0>, decode_xdl_stream_kernel<CLS, kAct16>, decode_xdl_stream_kernel<CLS, kAct16 | kWeight16>},
+                     {decode_xdl_stream_kernel<WQ, kHiddenMixed>, decode_xdl_stream_kernel<WQ, kHiddenMixed | kAct16>,
+                      decode_xdl_stream_kernel<WQ, kHiddenMixed | kAct16 | kWeight16>, decode_xdl_stream_kernel<WQ, kHiddenAllInt>},
                      dequant_debug_kernel<TM, WP>,
-                     {xdl_debug_kernel<XTM, WP, false>, xdl_debug_kernel<XTM, WP, true>},
+                     {xdl_debug_kernel<XTM, WQ, kHiddenMixed, false>, xdl_debug_kernel<XTM, WQ, kHiddenMixed, true>,
+                      xdl_debug_kernel<XTM, WQ, kHiddenAllInt, false>},
                      (uint32_t)(Layout<TM, WP>::HIDDEN + WP) * 4u,
-                     (uint32_t)XSlot<XTM, WP>::BYTES,
-                     (uint32_t)XLayout<XTM, WP>::TABLE};
+                     {(uint32_t)XSlot<XLayout<XTM, WQ, false>>::BYTES, (uint32_t)XSlot<XLayout<XTM, WQ, true>>::BYTES},
+                     (uint32_t)XLayout<XTM, WQ, false>::TABLE};
 }
 
 const void *xdl_any_fn(int kind, bool act16 = false, bool all16 = false) {
@@ -78,12 +81,13 @@ const void *xdl_any_fn(int kind, bool act16 = false, bool all16 = false) {
     }
 }
 
-ClassImpl impl_for(uint32_t cls, int tile_rows_wide) {
+template <int TM, int WP> ClassImpl impl_of(bool narrow) { return narrow ? make_impl<TM, WP, WP - 8>() : make_impl<TM, WP, WP>(); }
+ClassImpl impl_for(uint32_t cls, int tile_rows_wide, bool narrow) {
     switch (cls) {
-        case 1: return make_impl<16, 16>();
-        case 2: return tile_rows_wide == 32 ? make_impl<32, 32>() : make_impl<16, 32>();
-        case 3: return make_impl<16, 48>();
-        default: return tile_rows_wide == 32 ? make_impl<32, 64>() : make_impl<16, 64>();
+        case 1: return impl_of<16, 16>(narrow);
+        case 2: return tile_rows_wide == 32 ? impl_of<32, 32>(narrow) : impl_of<16, 32>(narrow);
+        case 3: return impl_of<16, 48>(narrow);
+        default: return tile_rows_wide == 32 ? impl_of<32, 64>(narrow) : impl_of<16, 64>(narrow);
     }
 }
 
@@ -190,6 +194,7 @@ struct rinr_store {
     double class_tile_us_xdl[kMaxClass + 1];
     bool xdl_ok;                              // every operand fits fp16 range after pre-scaling
     int hidden_kind;                          // kHiddenAllInt / AllRaw / Mixed over all hidden layers of all models
+    bool narrow[kMaxClass + 1];               // no model of the class is wider than 8 less than its padded width
     bool even_cost;                           // every model has the same width class and depth: slot order does not matter
     uint32_t fit_form[kSizes];                // resident_fits form per way of sizing
     uint32_t res_lds[kSizes][kMaxClass + 1];  // LDS of a resident launch: largest expanded model + its record, over the models that fit
@@ -238,12 +243,14 @@ extern "C" int rinr_store_open_ex(const void *device_blob, const void *host_blob
     std::memset(s->last_info, 0, sizeof s->last_info);
     s->plan_hw = -1; s->plan_n = -1; s->plan_threads = -1; s->plan_knob = -1;
     s->even_cost = true;
+    for (uint32_t c = 0; c <= kMaxClass; ++c) s->narrow[c] = true;
     {   // mean matrix work per pixel of each class -> time of a 64-pixel tile on one SIMD's MFMA pipe
         double macs[kMaxClass + 1] = {0, 0, 0, 0, 0};
         for (const IndexEntry &e : s->index) {
             const uint32_t c = e.width == 0 ? 1u : (e.width + 15u) >> 4;
             const IndexEntry &f = s->index[0];
             if (e.n_layers != f.n_layers || c != (f.width == 0 ? 1u : (f.width + 15u) >> 4)) s->even_cost = false;
+            if (e.width > 16u * c - 8u) s->narrow[c] = false;
             const double wp = 16.0 * c;
             macs[c] += wp * (4.0 + (e.n_layers - 2) * wp);
         }
@@ -313,12 +320,12 @@ extern "C" int rinr_store_open_ex(const void *device_blob, const void *host_blob
     bool ok = true;
     for (uint32_t c = 1; c <= kMaxClass && ok; ++c) {
         if (!sum.class_count[c]) continue;
-        const ClassImpl im = impl_for(c, s->tile_rows_wide);
+        const ClassImpl im = impl_for(c, s->tile_rows_wide, s->narrow[c]);
         ok = allow_full_lds((const void *)im.decode) && allow_full_lds((const void *)im.stream) &&
              allow_full_lds((const void *)im.debug) && allow_full_lds((const void *)im.xdebug[0]) &&
-             allow_full_lds((const void *)im.xdebug[1]);
+             allow_full_lds((const void *)im.xdebug[1]) && allow_full_lds((const void *)im.xdebug[2]);
         for (int k = 0; k < 7 && ok; ++k) ok = allow_full_lds((const void *)im.decode_xdl[k]);
-        for (int k = 0; k < 3 && ok; ++k) ok = allow_full_lds((const void *)im.stream_xdl[k]);
+        for (int k = 0; k < 4 && ok; ++k) ok = allow_full_lds((const void *)im.stream_xdl[k]);
     }
     ok = ok && allow_full_lds(xdl_any_fn(kHiddenAllInt)) && allow_full_lds(xdl_any_fn(kHiddenAllRaw)) &&
          allow_full_lds(xdl_any_fn(kHiddenMixed)) && allow_full_lds(xdl_any_fn(kHiddenAllInt, true)) &&
@@ -523,7 +530,7 @@ extern "C" int rinr_decode_batch_ex(rinr_store *s, const int64_t *image_ids, int
     } else if (!one_grid) {
         for (uint32_t c = 1; c <= kMaxClass; ++c) {
             if (!s->n_res[z][c]) continue;
-            const ClassImpl im = impl_for(c, s->tile_rows_wide);
+            const ClassImpl im = impl_for(c, s->tile_rows_wide, s->narrow[c]);
             const uint32_t lds_bytes = s->res_lds[z][c];
             if (replan) {
                 int resident = 1;
@@ -558,14 +565,15 @@ extern "C" int rinr_decode_batch_ex(rinr_store *s, const int64_t *image_ids, int
         if ((uint64_t)n * a.chunks > 0x7FFFFFFFull) return RINR_E_SIZE;
         for (uint32_t c = 1; c <= kMaxClass; ++c) {
             if (!s->n_str[z][c]) continue;
-            const ClassImpl im = impl_for(c, s->tile_rows_wide);
-            const uint32_t slot = xdl ? im.xslot_bytes : im.slot_bytes, table = xdl ? im.xtable_bytes : 0u;
+            const ClassImpl im = impl_for(c, s->tile_rows_wide, s->narrow[c]);
+            const bool ints = s->hidden_kind == kHiddenAllInt && !act16;
+            const uint32_t slot = xdl ? im.xslot_bytes[ints] : im.slot_bytes, table = xdl ? im.xtable_bytes : 0u;
             const uint32_t k = std::min<uint32_t>(s->str_layers[z][c], (s->lds_budget - table) / slot);
             const uint32_t lds_bytes = table + k * slot;
             a.cls = c;
             a.lds_bytes = lds_bytes;
             if (int rc = before_launch()) return rc;
-            hipLaunchKernelGGL(xdl ? im.stream_xdl[all16 ? 2 : (act16 ? 1 : 0)] : im.stream, dim3((uint32_t)n * a.chunks),
+            hipLaunchKernelGGL(xdl ? im.stream_xdl[all16 ? 2 : (act16 ? 1 : (ints ? 3 : 0))] : im.stream, dim3((uint32_t)n * a.chunks),
                                dim3((uint32_t)kStreamThreads), lds_bytes, (hipStream_t)stream, a);
             RINR_HIP(hipGetLastError());
             ++launches;
@@ -626,7 +634,7 @@ extern "C" int rinr_debug_dequant(const rinr_store *s, int64_t id, int32_t layer
     if (!s || !device_out) return RINR_E_NULL;
     uint32_t cls = 0;
     if (int rc = debug_target(s, id, layer, &cls)) return rc;
-    const ClassImpl im = impl_for(cls, s->tile_rows_wide);
+    const ClassImpl im = impl_for(cls, s->tile_rows_wide, s->narrow[cls]);
     hipLaunchKernelGGL(im.debug, dim3(1), dim3(256), im.slot_bytes, (hipStream_t)stream, s->blob, id, (int)layer, device_out, bias_out);
     RINR_HIP(hipGetLastError());
     return RINR_OK;
@@ -637,9 +645,10 @@ extern "C" int rinr_debug_dequant_split(const rinr_store *s, int64_t id, int32_t
     if (!s || !hi_out || !lo_out) return RINR_E_NULL;
     uint32_t cls = 0;
     if (int rc = debug_target(s, id, layer, &cls)) return rc;
-    const ClassImpl im = impl_for(cls, s->tile_rows_wide);
-    const uint32_t lds_bytes = im.xtable_bytes + im.xslot_bytes;
-    hipLaunchKernelGGL(im.xdebug[fp16_weights ? 1 : 0], dim3(1), dim3(256), lds_bytes, (hipStream_t)stream, s->blob, id, (int)layer,
+    const ClassImpl im = impl_for(cls, s->tile_rows_wide, s->narrow[cls]);
+    const bool ints = s->hidden_kind == kHiddenAllInt && !fp16_weights;
+    const uint32_t lds_bytes = im.xtable_bytes + im.xslot_bytes[ints];
+    hipLaunchKernelGGL(im.xdebug[fp16_weights ? 1 : (ints ? 2 : 0)], dim3(1), dim3(256), lds_bytes, (hipStream_t)stream, s->blob, id, (int)layer,
                        lds_bytes, hi_out, lo_out, bias_out, scale_out);
     RINR_HIP(hipGetLastError());
     return RINR_OK;

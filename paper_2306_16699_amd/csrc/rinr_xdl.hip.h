@@ -15,8 +15,8 @@
 // all row tiles of the layer) holds rows
 //     TM = 16:  16 Q + 4 g + b            TM = 32:  32 (Q / 4) + 8 (Q % 4) + 4 g + b,   b = 0..3.
 // One MFMA k-step takes 8 halfs per lane = quads 2j and 2j+1 of every lane group, i.e. exactly the
-// activations the lanes already hold, so again nothing crosses lanes between layers.  An odd last quad (padded widths
-// 16 and 48) takes a half-depth step, v_mfma_f32_16x16x16_f16, on the same accumulators.
+// activations the lanes already hold, so again nothing crosses lanes between layers.  An odd last quad takes a step of its own,
+// full-depth, with the hi and the lo parts side by side, or half-depth, v_mfma_f32_16x16x16_f16, on the same accumulators (XLayout::TAIL).
 // Two MFMAs of different depth must not follow each other closely on one accumulator: with a 16x16x16 step issued
 // right behind a 16x16x32 step that writes its C operand (one vector instruction between them, no wait states
 // added by the compiler) the second read the accumulator before the first had written it, and the first step's
@@ -66,60 +66,92 @@ struct XLayer {            // one entry per linear layer, built in LDS by the wo
     uint32_t off_bias;     // byte offset of the fp32 bias tile(s)
 };
 
-template <int TM, int WP> struct XLayout {
+// How the last quad of a layer's rows enters the next layer's contraction where the quads do not pair up, or are not full.
+//   kTailHalf  an odd last quad by half-depth steps, a step per term
+//   kTailFull  an odd last quad by full-depth steps: [hi | lo] of the activations against the weights twice over (and against their
+//              low parts twice over where the layer has them: two steps instead of three)
+//   kTailTwo   an odd last quad of which two rows are real: (h0 h1 l0 l1 | h0 h1 l0 l1) against (W0 W1 W0 W1 | w0 w1 0 0), w the weights' low
+//              parts: one step for all terms, whatever the kind of layer
+enum { kTailNone = 0, kTailHalf = 1, kTailFull = 2, kTailTwo = 3 };
+
+// WQ: the widest hidden layer rounded up to a multiple of 8.  Rows are padded to WP, but what is not computed for the padding is half a
+// tile: where WQ is an odd multiple of 8, a lane holds two real rows of the last 16-row tile (units 16 t + 2 g + b sit in rows 4 g + b,
+// b < 2, and the padding in b = 2, 3), or one quad less of a 32-row tile.  A padded unit would cost a sine and its split like a real one:
+// us a call, width padded to 16 -> to 8: 64 images of 224 x 224, 9 x 40: 269 -> 240; 256 of 160 x 160, 4 sine layers of 8 units: 83.0 -> 64.9, 24:
+// 142.6 -> 122.3, 40: 234 -> 212, 56: 325 -> 313, of fp32 weights 152 -> 137 (24), 279 -> 236 (40).  kTailFull instead of kTailHalf, a step where
+// two half-depth ones and their wait were: 1024 of 64 x 64, 5 x 48: 196 -> 187; 256 of 160 x 160, 4 x 48: 244.6 -> 233.9, 4 x 16: 83.0 -> 81.7.
+// Where activations are single halfs (one term: one step either way) or the layer has a low part, wide odd last quads stay with kTailHalf.
+// INT: every hidden layer of the models served is integer-coded, and activations are hi/lo pairs.
+template <int TM, int WQ_, bool INT> struct XLayout {
+    static constexpr int WQ = WQ_, WP = (WQ + 15) / 16 * 16;
     static constexpr int G = 64 / TM;              // lane groups
     static constexpr int RV = TM * TM / 64;        // accumulator registers per tile
     static constexpr int MT = WP / TM;             // row tiles per layer
-    static constexpr int NQ = WP / (4 * G);        // quads per lane over the layer's rows
-    static constexpr int KJ = NQ / 2;              // full k-steps (8 halfs per lane) of a hidden layer
-    static constexpr int K16 = NQ % 2;             // plus one half-depth step for an odd last quad (TM = 16 only)
+    static constexpr bool HALF = TM == 16 && WQ != WP;   // two real rows per lane in the last tile
+    static constexpr int NQ = TM == 16 ? WP / 16 : WQ / 8;   // quads per lane over the layer's rows
+    static constexpr int KJ = NQ / 2;              // full k-steps (8 halfs per lane) of two quads
+    static constexpr int TAIL = NQ % 2 == 0 ? kTailNone : (HALF ? kTailTwo : (TM == 32 || INT ? kTailFull : kTailHalf));
     static constexpr int SELECT = 16 * 16;         // bytes: one XLayer per linear layer, 16 at most; then the 16 byte selectors of expand_hidden
     static constexpr int TABLE = SELECT + 16 * 4;
-    static constexpr int HID = WP * WP * 2;        // bytes of one hidden operand block
+    static constexpr int TAILB = TAIL == kTailNone ? 0 : (TAIL == kTailHalf ? 512 : 1024);       // bytes of the last quad's step, per row tile
+    static constexpr int HID = KJ * MT * 1024 + MT * TAILB;                                      // bytes of one hidden operand block
+    static constexpr int HIDLO = KJ * MT * 1024 + (TAIL == kTailTwo ? 0 : MT * TAILB);           // ... of the low parts (kTailTwo has them with the others)
     static constexpr int FIRST = G * MT * 64 * 16; // bytes: [pixel tile q][mt][lane][8 halfs], hi and lo in one k-step; variant q has the
                                                    // weights in lane group q's k-slots only, so that group q's coordinates alone count
-    static constexpr int OUT = KJ * 64 * 16 + K16 * 64 * 8;   // bytes: one TM-row tile
+    static constexpr int OUT = KJ * 1024 + TAILB, OUTLO = KJ * 1024 + (TAIL == kTailTwo ? 0 : TAILB);   // bytes: one TM-row tile
     static constexpr int OUTB = TM * 4;            // bytes of the output layer's bias tile
-    static_assert(WP % TM == 0 && (TM == 16 || K16 == 0), "layout");
+    static_assert(WP % TM == 0 && WQ % 8 == 0, "layout");
 
-    // row r of the layer -> (quad, lane group, position in the quad)
+    // unit r of the layer -> (quad, lane group, position in the quad)
     static __device__ __forceinline__ void locate(int r, int &q, int &g, int &b) {
         b = r & 3;
-        if (TM == 16) { q = r >> 4; g = (r >> 2) & 3; }
-        else { q = ((r >> 5) << 2) | ((r >> 3) & 3); g = (r >> 2) & 1; }
+        if (TM == 32) { q = r >> 3; g = (r >> 2) & 1; return; }
+        q = r >> 4; g = (r >> 2) & 3;
+        if (HALF && q == MT - 1) { g = (r >> 1) & 3; b = (r & 1) + ((r & 8) >> 2); }
     }
-    // half index of hidden weight (o, i) inside its block: [k-step][row tile][lane][8]
+    // ... -> row
+    static __device__ __forceinline__ int row(int r) {
+        if (!HALF) return r;
+        int q, g, b;
+        locate(r, q, g, b);
+        return 16 * q + 4 * g + b;
+    }
+    // half index inside an operand block of `mts` row tiles: k-step's row tile mt, lane, input (q, g, b); kTailFull has the weight at + 4 too,
+    // kTailTwo at + 2, and its low part at + 4
+    static __device__ __forceinline__ int idx(int mts, int mt, int m, int q, int g, int b) {
+        if (q < 2 * KJ) return (((q >> 1) * mts + mt) * 64 + g * TM + m) * 8 + (q & 1) * 4 + b;
+        return KJ * mts * 512 + (mt * 64 + g * TM + m) * (TAIL == kTailHalf ? 4 : 8) + b;
+    }
+    static __device__ __forceinline__ bool in_tail(int i) { return TAIL != kTailNone && i >= (TM == 16 ? 32 * KJ : 16 * KJ); }
+    // hidden weight (o, i); i's quad position 0 where four inputs go out together
     static __device__ __forceinline__ int idx_hidden(int o, int i) {
-        const int mt = o / TM, m = o % TM;
+        const int r = row(o);
         int q, g, b;
         locate(i, q, g, b);
-        if (q < 2 * KJ) return (((q >> 1) * MT + mt) * 64 + g * TM + m) * 8 + (q & 1) * 4 + b;
-        return KJ * MT * 512 + (mt * 64 + g * TM + m) * 4 + b;
+        return idx(MT, r / TM, r % TM, q, g, b);
     }
-    static __device__ __forceinline__ int idx_first(int q, int o, int e) { return (((q * MT + o / TM) * 64) + q * TM + (o % TM)) * 8 + e; }
+    static __device__ __forceinline__ int idx_first(int q, int o, int e) { const int r = row(o); return (((q * MT + r / TM) * 64) + q * TM + (r % TM)) * 8 + e; }
     // output channel c sits in row 4c of the single output tile
     static __device__ __forceinline__ int idx_out(int c, int i) {
         int q, g, b;
         locate(i, q, g, b);
-        const int lane = g * TM + 4 * c;
-        if (q < 2 * KJ) return ((q >> 1) * 64 + lane) * 8 + (q & 1) * 4 + b;
-        return KJ * 512 + lane * 4 + b;
+        return idx(1, 0, 4 * c, q, g, b);
     }
-    // bias tiles are accumulator shaped: [row tile][lane group][register]
-    static __device__ __forceinline__ int idx_bias(int o) {
-        int q, g, b;
-        locate(o % TM, q, g, b);
-        return ((o / TM) * G + g) * RV + q * 4 + b;
+    // bias tiles are accumulator shaped: [row tile][lane group][register]; `o` a row for the output layer's tile
+    static __device__ __forceinline__ int idx_bias_row(int r) {
+        const int v = TM == 16 ? r & 3 : ((r >> 3 & 3) << 2) | (r & 3), g = TM == 16 ? (r >> 2) & 3 : (r >> 2) & 1;
+        return ((r / TM) * G + g) * RV + v;
     }
+    static __device__ __forceinline__ int idx_bias(int o) { return idx_bias_row(row(o)); }
 };
 
-// Bytes of LDS the expanded model of width class `cls` needs (without the staging copy of the
-// record).  n_int = hidden layers in integer form, n_raw = hidden layers split hi/lo.
+// Bytes of LDS the expanded model of width class `cls` needs at most (without the staging copy of the
+// record), whatever kernel takes it.  n_int = hidden layers in integer form, n_raw = hidden layers split hi/lo.
 __host__ __device__ inline uint32_t xdl_model_bytes(int cls, int n_layers, int n_int, int n_raw) {
     const uint32_t tm = (uint32_t)xdl_tile_rows(cls), wp = 16u * cls, g = 64u / tm, nq = wp / (4u * g);
-    const uint32_t out = (nq / 2) * 1024u + (nq % 2) * 512u;
+    const uint32_t out = (nq / 2 + nq % 2) * 1024u, one = wp * wp * 2u + (nq % 2) * (wp / tm) * 512u;
     return 16u * 16u + 16u * 4u + ((uint32_t)(n_layers - 1) * wp + tm) * 4u + g * (wp / tm) * 1024u +
-           wp * wp * 2u * (uint32_t)(n_int + 2 * n_raw) + 2u * out;
+           one * (uint32_t)n_int + 2u * wp * wp * 2u * (uint32_t)n_raw + 2u * out;
 }
 
 // Builds the operand blocks of layers [l0, l1) in LDS and their XLayer entries tab[l].  `rec` is the model record:
@@ -127,11 +159,10 @@ __host__ __device__ inline uint32_t xdl_model_bytes(int cls, int n_layers, int n
 //   SLOTTED == false (resident model, l0 = 0, l1 = L): table, all bias tiles, then the blocks back to back.
 //   SLOTTED == true  (streamed model): table, then one fixed-size slot per layer of the group: bias tile, blocks.
 // Ends with a barrier.
-template <int TM, int WP> struct XSlot {
-    typedef XLayout<TM, WP> LY;
-    static constexpr int BLOCKS = 2 * LY::HID > LY::FIRST ? (2 * LY::HID > 2 * LY::OUT ? 2 * LY::HID : 2 * LY::OUT)
-                                                          : (LY::FIRST > 2 * LY::OUT ? LY::FIRST : 2 * LY::OUT);
-    static constexpr int BIAS = WP * 4 > LY::OUTB ? WP * 4 : LY::OUTB;
+template <class LY> struct XSlot {
+    static constexpr int HID = LY::HID + LY::HIDLO, OUT = LY::OUT + LY::OUTLO;
+    static constexpr int BLOCKS = HID > LY::FIRST ? (HID > OUT ? HID : OUT) : (LY::FIRST > OUT ? LY::FIRST : OUT);
+    static constexpr int BIAS = LY::WP * 4 > LY::OUTB ? LY::WP * 4 : LY::OUTB;
     static constexpr int BYTES = BIAS + BLOCKS;
 };
 
@@ -143,7 +174,7 @@ template <int TM, int WP> struct XSlot {
 // 1024 + code is a half with the code as its low byte, and subtracting 1024 + zp is exact.
 // About 35 vector instructions for up to 256 weights, where one weight per lane took 30 for up to 64 (10 layers x 40: from the
 // workgroup's start to the end of this phase 25 -> 14.5 thousand clocks).
-template <int TM, int WP> struct XExpand {
+template <int WP> struct XExpand {
     static constexpr int LANES = WP <= 16 ? 4 : (WP <= 32 ? 8 : 16), ROWS = 64 / LANES;      // lanes per row, rows per pass
     static constexpr int PASSES = WP / ROWS;
 };
@@ -154,11 +185,31 @@ __device__ __forceinline__ uint32_t nibble_selector(uint32_t bits) {
     for (int b = 0; b < 4; ++b) s |= ((bits >> b & 1u) ? (uint32_t)__popc(bits & ((1u << b) - 1u)) : 4u) << (8 * b);
     return s;
 }
-template <int TM, int WP, bool W16, int KIND, int U>
+// Four consecutive inputs of one output into an operand block: one word of it, or, where they are in a last tile with two rows a lane,
+// half of the words of two lane groups.
+template <class LY> __device__ __forceinline__ void put_four(char *block, int o, int i, h4v w, h4v low) {
+    const h4v none = (h4v)((_Float16)0.0f);
+    char *const p = block + 2 * LY::idx_hidden(o, i);
+    if (LY::HALF && i >= 16 * (LY::MT - 1)) {
+        constexpr int NEXT = 16 * 16;                       // bytes to the next lane group's word
+        const h4v w01 = __builtin_shufflevector(w, none, 0, 1, 4, 5), w23 = __builtin_shufflevector(w, none, 2, 3, 4, 5);
+        if (LY::TAIL == kTailTwo) {
+            *(h8v *)p = __builtin_shufflevector(__builtin_shufflevector(w, w, 0, 1, 0, 1), __builtin_shufflevector(low, none, 0, 1, 4, 5), 0, 1, 2, 3, 4, 5, 6, 7);
+            *(h8v *)(p + NEXT) = __builtin_shufflevector(__builtin_shufflevector(w, w, 2, 3, 2, 3), __builtin_shufflevector(low, none, 2, 3, 4, 5), 0, 1, 2, 3, 4, 5, 6, 7);
+        } else {
+            *(h4v *)p = w01;
+            *(h4v *)(p + NEXT) = w23;
+        }
+    } else if (LY::TAIL == kTailFull && LY::in_tail(i)) {
+        *(h8v *)p = __builtin_shufflevector(w, w, 0, 1, 2, 3, 4, 5, 6, 7);
+    } else {
+        *(h4v *)p = w;
+    }
+}
+template <class LY, bool W16, int KIND, int U>
 __device__ __forceinline__ void expand_hidden(const uint32_t *rec, const LaneLayers &t, int l, int lane, char *lds, char *hi, char *lo, float *bt,
                                               float bias_factor, bool whole, float pre) {
-    typedef XLayout<TM, WP> LY;
-    typedef XExpand<TM, WP> X;
+    typedef XExpand<LY::WP> X;
     const uint32_t last = lane_value(t.upto, l), first = last - lane_value(t.passes, l);
     if (t.g1 <= first || t.g0 >= last) return;
     const uint32_t io = lane_value(t.io, l), kind = lane_value(t.kind, l), n_in = io & 0xFFFFu, n_out = io >> 16;
@@ -231,7 +282,7 @@ __device__ __forceinline__ void expand_hidden(const uint32_t *rec, const LaneLay
                 const uint32_t y = __builtin_amdgcn_perm(zp4, x[j], sel[j]);
                 const h2v h01 = __builtin_bit_cast(h2v, __builtin_amdgcn_perm(0x64646464u, y, 0x04010400u)) + less;
                 const h2v h23 = __builtin_bit_cast(h2v, __builtin_amdgcn_perm(0x64646464u, y, 0x04030402u)) + less;
-                if ((int)i < WP && p + j < p1) *(h4v *)(hi + 2 * LY::idx_hidden((int)o[j], (int)i)) = (h4v){h01[0], h01[1], h23[0], h23[1]};
+                if ((int)i < LY::WQ && p + j < p1) put_four<LY>(hi, (int)o[j], (int)i, (h4v){h01[0], h01[1], h23[0], h23[1]}, (h4v)((_Float16)0.0f));
             }
         } else {
 #pragma unroll
@@ -252,9 +303,9 @@ __device__ __forceinline__ void expand_hidden(const uint32_t *rec, const LaneLay
                     wh[b] = (_Float16)w;
                     wl[b] = (_Float16)(w - (float)wh[b]);
                 }
-                if ((int)i < WP && p + j < p1) {
-                    *(h4v *)(hi + 2 * LY::idx_hidden((int)o[j], (int)i)) = wh;
-                    if (!W16) *(h4v *)(lo + 2 * LY::idx_hidden((int)o[j], (int)i)) = wl;
+                if ((int)i < LY::WQ && p + j < p1) {
+                    put_four<LY>(hi, (int)o[j], (int)i, wh, W16 ? (h4v)((_Float16)0.0f) : wl);
+                    if (!W16 && !(LY::TAIL == kTailTwo && LY::in_tail((int)i))) put_four<LY>(lo, (int)o[j], (int)i, wl, wl);
                 }
             }
         }
@@ -266,21 +317,22 @@ __device__ __forceinline__ void expand_hidden(const uint32_t *rec, const LaneLay
 }
 
 // KIND says which kinds of hidden layer there can be (kHidden...), U how many passes of a hidden layer a wavefront has under way.
-template <int TM, int WP, bool W16, bool SLOTTED, int KIND, int U>
+template <class LY, bool W16, bool SLOTTED, int KIND, int U>
 __device__ __forceinline__ void xdl_expand_layers(char *lds, const uint32_t *rec, const LaneLayers &t, int L, int l0, int l1, float pre, int tid,
                                                   int nthreads) {
-    typedef XLayout<TM, WP> LY;
+    constexpr int WP = LY::WP;
     const int lane = tid & 63;
     // lane l: layer l's entry; the offsets are sums over the lanes
     XLayer mine;
     {
         const bool last = lane == L - 1, in_group = lane >= l0 && lane < l1;
         const bool whole = !W16 && lane > 0 && !last && xdl_int_layer(t.kind & 0xFFu, t.scale * pre);
-        const uint32_t one = lane == 0 ? LY::FIRST : (last ? LY::OUT : LY::HID), size = (last || (lane > 0 && !W16 && !whole)) ? 2 * one : one;
+        const uint32_t one = lane == 0 ? LY::FIRST : (last ? LY::OUT : LY::HID), two = last ? LY::OUTLO : (lane > 0 && !W16 && !whole ? LY::HIDLO : 0u);
+        const uint32_t size = one + two;
         const uint32_t upto = row_incl_sum(lane < L ? size : 0u);
-        mine.off_bias = LY::TABLE + (SLOTTED ? (uint32_t)(lane - l0) * XSlot<TM, WP>::BYTES : (uint32_t)lane * WP * 4u);
-        mine.off_hi = SLOTTED ? mine.off_bias + XSlot<TM, WP>::BIAS : LY::TABLE + (uint32_t)(L - 1) * WP * 4u + LY::OUTB + upto - size;
-        mine.off_lo = size == one ? 0u : mine.off_hi + one;
+        mine.off_bias = LY::TABLE + (SLOTTED ? (uint32_t)(lane - l0) * XSlot<LY>::BYTES : (uint32_t)lane * WP * 4u);
+        mine.off_hi = SLOTTED ? mine.off_bias + XSlot<LY>::BIAS : LY::TABLE + (uint32_t)(L - 1) * WP * 4u + LY::OUTB + upto - size;
+        mine.off_lo = last || (lane > 0 && !W16 && !whole) ? mine.off_hi + one : 0u;
         mine.scale = whole ? t.scale * pre : 1.0f;
         if (tid < 16) {
             if (in_group) ((XLayer *)lds)[lane] = mine;
@@ -293,13 +345,13 @@ __device__ __forceinline__ void xdl_expand_layers(char *lds, const uint32_t *rec
     };
     if (SLOTTED) {
         for (int l = l0; l < l1; ++l) {
-            const uint32_t at = LY::TABLE + (uint32_t)(l - l0) * XSlot<TM, WP>::BYTES;
-            clear(at, at + (l == 0 || l == L - 1 ? XSlot<TM, WP>::BYTES : XSlot<TM, WP>::BIAS));
+            const uint32_t at = LY::TABLE + (uint32_t)(l - l0) * XSlot<LY>::BYTES;
+            clear(at, at + (l == 0 || l == L - 1 ? XSlot<LY>::BYTES : XSlot<LY>::BIAS));
         }
     } else {
         const uint32_t out = lane_value(mine.off_hi, L - 1);
         clear(LY::TABLE, lane_value(mine.off_hi, 0) + LY::FIRST);
-        clear(out, out + 2 * LY::OUT);
+        clear(out, out + LY::OUT + LY::OUTLO);
     }
     __syncthreads();
     // only the layers that have passes of this wavefront (from the lanes: those whose passes end behind its first, and begin before its end)
@@ -312,11 +364,21 @@ __device__ __forceinline__ void xdl_expand_layers(char *lds, const uint32_t *rec
         if (l == L - 1) {
             expand_layer<1>(rec, t, l, lane,
                          [=](int o, int i, float v, int) {
-                             const _Float16 h = (_Float16)v;
-                             hi[LY::idx_out(o, i)] = h;
-                             lo[LY::idx_out(o, i)] = (_Float16)(v - (float)h);
+                             const _Float16 h = (_Float16)v, w = (_Float16)(v - (float)h);
+                             const int at = LY::idx_out(o, i);
+                             hi[at] = h;
+                             if (LY::TAIL == kTailTwo && LY::in_tail(i)) {
+                                 hi[at + 2] = h;
+                                 hi[at + 4] = w;
+                             } else {
+                                 lo[at] = w;
+                                 if (LY::TAIL == kTailFull && LY::in_tail(i)) {
+                                     hi[at + 4] = h;
+                                     lo[at + 4] = w;
+                                 }
+                             }
                          },
-                         [=](int o, float v) { bt[LY::idx_bias(4 * o)] = v; });
+                         [=](int o, float v) { bt[LY::idx_bias_row(4 * o)] = v; });
         } else if (l == 0) {
             expand_layer<1>(rec, t, l, lane,
                          [=](int o, int i, float v, int) {
@@ -332,7 +394,7 @@ __device__ __forceinline__ void xdl_expand_layers(char *lds, const uint32_t *rec
         } else {
             const bool whole = !W16 && off_lo == 0;
             const float s = whole ? __uint_as_float(lane_value(__float_as_uint(mine.scale), l)) : 1.0f;
-            expand_hidden<TM, WP, W16, KIND, U>(rec, t, l, lane, lds, (char *)hi, (char *)lo, bt, whole ? 1.0f / s : 1.0f, whole, pre);
+            expand_hidden<LY, W16, KIND, U>(rec, t, l, lane, lds, (char *)hi, (char *)lo, bt, whole ? 1.0f / s : 1.0f, whole, pre);
         }
     }
     __syncthreads();
@@ -403,55 +465,71 @@ template <class Acc> __device__ __forceinline__ void xdl_touch(Acc &acc) { asm v
 __device__ __forceinline__ void xdl_wait_states() { asm volatile("s_nop 15\n\ts_nop 3"); }
 
 // ---- per-wavefront state of one half (32 pixels) of a 64-pixel tile ------------------------------------
-template <int TM, int WP> struct XHalf {
-    typedef XLayout<TM, WP> LY;
+template <int TM, class LY_> struct XHalf {
+    typedef LY_ LY;
     static constexpr int NTH = 32 / TM;            // pixel tiles in a half: two of 16 pixels, or one of 32
     static constexpr int KJA = LY::KJ ? LY::KJ : 1;
     h8v Hh[NTH][KJA], Hl[NTH][KJA];                // activations as fp16 hi / lo, one entry per full k-step
-    h4v Hh4[NTH], Hl4[NTH];                        // ... of the half-depth step (odd last quad)
+    h4v Hh4[NTH], Hl4[NTH];                        // ... of the last quad (kTailHalf)
+    h8v Ht[NTH];                                   // ... or of its full-depth step (kTailFull, kTailTwo)
     typename XTile<TM>::acc_t D[NTH][LY::MT];      // accumulators
 };
 
-// sine + split of all accumulators of a half: WP/2 activations per lane, 3 VALU instructions and a quarter of a small matrix step each
-template <int TM, int WP, bool A16>
-__device__ __forceinline__ void xdl_epilogue(XHalf<TM, WP> &H, float scale, h4v neg_unit) {
-    typedef XLayout<TM, WP> LY;
+// sine + split of all accumulators of a half: WQ/2 activations per lane, 3 VALU instructions and a quarter of a small matrix step each
+template <int TM, class LY, bool A16>
+__device__ __forceinline__ void xdl_epilogue(XHalf<TM, LY> &H, float scale, h4v neg_unit) {
     constexpr int QT = LY::RV / 4;                 // quads per tile
+    constexpr int NTH = XHalf<TM, LY>::NTH;
+    const h4v none = (h4v)((_Float16)0.0f);
 #pragma unroll
-    for (int nt = 0; nt < XHalf<TM, WP>::NTH; ++nt)
+    for (int nt = 0; nt < NTH; ++nt)
 #pragma unroll
-        for (int t = 0; t < LY::MT; ++t)
+        for (int q = 0; q < LY::NQ - (LY::HALF ? 1 : 0); ++q) {
+            const int t = q / QT, v0 = q % QT * 4;
+            h4v hi, lo = none;
+            if (A16) sine_hi(H.D[nt][t][v0], H.D[nt][t][v0 + 1], H.D[nt][t][v0 + 2], H.D[nt][t][v0 + 3], scale, hi);
+            else sine_split(H.D[nt][t][v0], H.D[nt][t][v0 + 1], H.D[nt][t][v0 + 2], H.D[nt][t][v0 + 3], scale, neg_unit, hi, lo);
+            if (q < 2 * LY::KJ) {
 #pragma unroll
-            for (int qq = 0; qq < QT; ++qq) {
-                const int q = t * QT + qq;         // quad index over the layer's rows
-                h4v hi, lo;
-                if (A16) sine_hi(H.D[nt][t][qq * 4 + 0], H.D[nt][t][qq * 4 + 1], H.D[nt][t][qq * 4 + 2], H.D[nt][t][qq * 4 + 3], scale, hi);
-                else sine_split(H.D[nt][t][qq * 4 + 0], H.D[nt][t][qq * 4 + 1], H.D[nt][t][qq * 4 + 2], H.D[nt][t][qq * 4 + 3], scale, neg_unit,
-                                hi, lo);
-                if (q < 2 * LY::KJ) {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        H.Hh[nt][q >> 1][(q & 1) * 4 + v] = hi[v];
-                        if (!A16) H.Hl[nt][q >> 1][(q & 1) * 4 + v] = lo[v];
-                    }
-                } else {
-                    H.Hh4[nt] = hi;
-                    if (!A16) H.Hl4[nt] = lo;
+                for (int v = 0; v < 4; ++v) {
+                    H.Hh[nt][q >> 1][(q & 1) * 4 + v] = hi[v];
+                    if (!A16) H.Hl[nt][q >> 1][(q & 1) * 4 + v] = lo[v];
                 }
+            } else if (LY::TAIL == kTailHalf) {
+                H.Hh4[nt] = hi;
+                if (!A16) H.Hl4[nt] = lo;
+            } else {
+                H.Ht[nt] = __builtin_shufflevector(hi, lo, 0, 1, 2, 3, 4, 5, 6, 7);
             }
+        }
+    if constexpr (LY::HALF) {                      // two rows a lane of the last tile: the two pixel tiles make one quad for the split
+        constexpr int t = LY::MT - 1;
+        h4v hi, lo = none;
+        if (A16) sine_hi(H.D[0][t][0], H.D[0][t][1], H.D[1][t][0], H.D[1][t][1], scale, hi);
+        else sine_split(H.D[0][t][0], H.D[0][t][1], H.D[1][t][0], H.D[1][t][1], scale, neg_unit, hi, lo);
+        if (LY::TAIL == kTailTwo) {
+            H.Ht[0] = __builtin_shufflevector(hi, lo, 0, 1, 4, 5, 0, 1, 4, 5);
+            H.Ht[1] = __builtin_shufflevector(hi, lo, 2, 3, 6, 7, 2, 3, 6, 7);
+        } else {
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int nt = 0; nt < 2; ++nt) {
+                    H.Hh[nt][LY::KJ - 1][4 + v] = v < 2 ? hi[2 * nt + v] : (_Float16)0.0f;
+                    if (!A16) H.Hl[nt][LY::KJ - 1][4 + v] = v < 2 ? lo[2 * nt + v] : (_Float16)0.0f;
+                }
+        }
+    }
 }
 
 // MFMAs of one hidden layer for a half.  LO: the layer has a low weight part (one more term).  A16: no low activation part.
-template <int TM, int WP, bool LO, bool A16>
-__device__ __forceinline__ void xdl_hidden(XHalf<TM, WP> &H, const char *lds, const XLayer el, int lane, int g) {
-    typedef XLayout<TM, WP> LY;
+template <int TM, class LY, bool LO, bool A16>
+__device__ __forceinline__ void xdl_hidden(XHalf<TM, LY> &H, const char *lds, const XLayer el, int lane, int g) {
     typedef XTile<TM> T;
     typedef typename T::acc_t acc_t;
-    constexpr int KJ = LY::KJ, K16 = LY::K16, MT = LY::MT, NTH = XHalf<TM, WP>::NTH;
+    constexpr int KJ = LY::KJ, MT = LY::MT, NTH = XHalf<TM, LY>::NTH;
     const h8v *ah = (const h8v *)(lds + el.off_hi) + lane;
     const h8v *al = (const h8v *)(lds + el.off_lo) + lane;
-    const h4v *ah4 = (const h4v *)(lds + el.off_hi + KJ * MT * 1024) + lane;
-    const h4v *al4 = (const h4v *)(lds + el.off_lo + KJ * MT * 1024) + lane;
     const acc_t *bt = (const acc_t *)(lds + el.off_bias) + g;
 #pragma unroll
     for (int j = 0; j < KJ; ++j)
@@ -473,7 +551,24 @@ __device__ __forceinline__ void xdl_hidden(XHalf<TM, WP> &H, const char *lds, co
                 for (int nt = 0; nt < NTH; ++nt) H.D[nt][mt] = T::mfma(aw, H.Hh[nt][j], H.D[nt][mt]);
             }
         }
-    if (K16) {
+    if constexpr (LY::TAIL == kTailFull || LY::TAIL == kTailTwo) {
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+            const h8v av = ah[(KJ * MT + mt) * 64];
+            acc_t c;
+            if (KJ == 0) c = bt[mt * LY::G];
+#pragma unroll
+            for (int nt = 0; nt < NTH; ++nt) H.D[nt][mt] = T::mfma(av, H.Ht[nt], KJ == 0 ? c : H.D[nt][mt]);
+            if (LO && LY::TAIL == kTailFull) {
+                const h8v aw = al[(KJ * MT + mt) * 64];
+#pragma unroll
+                for (int nt = 0; nt < NTH; ++nt) H.D[nt][mt] = T::mfma(aw, H.Ht[nt], H.D[nt][mt]);
+            }
+        }
+    }
+    if constexpr (LY::TAIL == kTailHalf) {
+        const h4v *ah4 = (const h4v *)(lds + el.off_hi + KJ * MT * 1024) + lane;
+        const h4v *al4 = (const h4v *)(lds + el.off_lo + KJ * MT * 1024) + lane;
         if (KJ) {
 #pragma unroll
             for (int nt = 0; nt < NTH; ++nt)
@@ -508,14 +603,14 @@ __device__ __forceinline__ void xdl_hidden(XHalf<TM, WP> &H, const char *lds, co
 
 // One hidden layer for both halves of a 64-pixel tile, software-pipelined: the matrix work of X(l) is issued
 // together with the sine/split of Y(l-1), then the matrix work of Y(l) with the sine/split of X(l).
-template <int TM, int WP, bool LO, bool A16>
-__device__ __forceinline__ void xdl_layer(XHalf<TM, WP> &X, XHalf<TM, WP> &Y, const char *lds, const XLayer el, int lane, int g,
+template <int TM, class LY, bool LO, bool A16>
+__device__ __forceinline__ void xdl_layer(XHalf<TM, LY> &X, XHalf<TM, LY> &Y, const char *lds, const XLayer el, int lane, int g,
                                           float scale_prev, float scale, h4v neg_unit) {
-    xdl_hidden<TM, WP, LO, A16>(X, lds, el, lane, g);
-    xdl_epilogue<TM, WP, A16>(Y, scale_prev, neg_unit);
+    xdl_hidden<TM, LY, LO, A16>(X, lds, el, lane, g);
+    xdl_epilogue<TM, LY, A16>(Y, scale_prev, neg_unit);
     __builtin_amdgcn_sched_barrier(0);
-    xdl_hidden<TM, WP, LO, A16>(Y, lds, el, lane, g);
-    xdl_epilogue<TM, WP, A16>(X, scale, neg_unit);
+    xdl_hidden<TM, LY, LO, A16>(Y, lds, el, lane, g);
+    xdl_epilogue<TM, LY, A16>(X, scale, neg_unit);
 }
 
 // The slot's augmentation map (every lane holds it alike), in scalar registers.
@@ -539,13 +634,12 @@ __device__ __forceinline__ XUniform xdl_uniform(const DecodeArgs &a, uint32_t sl
 //      Per-lane values that only the first and the last layer use are derived again for every tile
 //      (the empty asm keeps them from being hoisted): held across the hidden layers they would
 //      push the kernel over its register budget.
-template <int TM, int WP>
-__device__ __forceinline__ void xdl_first(XHalf<TM, WP> &X, XHalf<TM, WP> &Y, const DecodeArgs &a, const XUniform &u, const char *lds,
+template <int TM, class LY>
+__device__ __forceinline__ void xdl_first(XHalf<TM, LY> &X, XHalf<TM, LY> &Y, const DecodeArgs &a, const XUniform &u, const char *lds,
                                           const XLayer e0, uint32_t tile, int lane) {
-    typedef XLayout<TM, WP> LY;
     typedef XTile<TM> T;
     typedef typename T::acc_t acc_t;
-    constexpr int MT = LY::MT, G = LY::G, NTH = XHalf<TM, WP>::NTH;
+    constexpr int MT = LY::MT, G = LY::G, NTH = XHalf<TM, LY>::NTH;
     const int g = lane / TM;
     float lo_v = a.lo, af2 = u.af2, af5 = u.af5;        // second uniform operand of an fma: copied to a vector register at the use
     asm volatile("" : "+s"(lo_v), "+s"(af2), "+s"(af5));
@@ -577,19 +671,16 @@ __device__ __forceinline__ void xdl_first(XHalf<TM, WP> &X, XHalf<TM, WP> &Y, co
 // ---- output layer width -> 3: one TM-row tile with channel c in row 4c.  At TM = 16 that is
 //      register 0 of lane group c; at TM = 32 registers 0 (R) and 4 (B) of group 0, register 0 (G) of group 1.
 //      Then clamp, optional normalisation and the NCHW store.
-template <int TM, int WP, bool A16>
-__device__ __forceinline__ void xdl_output(const XHalf<TM, WP> &X, const XHalf<TM, WP> &Y, const DecodeArgs &a, float ns0, float ns1,
+template <int TM, class LY, bool A16>
+__device__ __forceinline__ void xdl_output(const XHalf<TM, LY> &X, const XHalf<TM, LY> &Y, const DecodeArgs &a, float ns0, float ns1,
                                            float ns2, float nb0, float nb1, float nb2, const char *lds, const XLayer eo,
                                            uint32_t tile, int lane, size_t plane0) {
-    typedef XLayout<TM, WP> LY;
     typedef XTile<TM> T;
     typedef typename T::acc_t acc_t;
-    constexpr int KJ = LY::KJ, K16 = LY::K16, NTH = XHalf<TM, WP>::NTH;
+    constexpr int KJ = LY::KJ, NTH = XHalf<TM, LY>::NTH;
     const int go = lane / TM, no = lane % TM;
     const h8v *ah = (const h8v *)(lds + eo.off_hi) + lane;
     const h8v *al = (const h8v *)(lds + eo.off_lo) + lane;
-    const h4v *ah4 = (const h4v *)(lds + eo.off_hi + KJ * 1024) + lane;
-    const h4v *al4 = (const h4v *)(lds + eo.off_lo + KJ * 1024) + lane;
     const acc_t c = ((const acc_t *)(lds + eo.off_bias))[go];
     acc_t O[2 * NTH];
 #pragma unroll
@@ -605,7 +696,20 @@ __device__ __forceinline__ void xdl_output(const XHalf<TM, WP> &X, const XHalf<T
             O[nt] = T::mfma(aw, bh, O[nt]);
         }
     }
-    if (K16) {
+    if constexpr (LY::TAIL == kTailFull || LY::TAIL == kTailTwo) {
+        const h8v av = ah[KJ * 64];
+        h8v aw;
+        if (LY::TAIL == kTailFull) aw = al[KJ * 64];
+#pragma unroll
+        for (int nt = 0; nt < 2 * NTH; ++nt) {
+            const h8v bt = nt < NTH ? X.Ht[nt % NTH] : Y.Ht[nt % NTH];
+            O[nt] = T::mfma(av, bt, O[nt]);
+            if (LY::TAIL == kTailFull) O[nt] = T::mfma(aw, bt, O[nt]);
+        }
+    }
+    if constexpr (LY::TAIL == kTailHalf) {
+        const h4v *ah4 = (const h4v *)(lds + eo.off_hi + KJ * 1024) + lane;
+        const h4v *al4 = (const h4v *)(lds + eo.off_lo + KJ * 1024) + lane;
         if (KJ) {
 #pragma unroll
             for (int nt = 0; nt < 2 * NTH; ++nt) xdl_touch(O[nt]);
@@ -667,12 +771,14 @@ __device__ __forceinline__ void xdl_output(const XHalf<TM, WP> &X, const XHalf<T
 
 // Resident form: the model is expanded once per workgroup; a wavefront takes one 64-pixel tile at a time through all
 // layers.
-template <int TM, int WP, int MODE_>
+template <int TM, int WQ, int MODE_>
 __device__ __forceinline__ void xdl_body(const DecodeArgs &a, const Work &w, float *lds_f) {
     constexpr bool W16 = (MODE_ & kWeight16) != 0;
     constexpr int MODE = W16 ? (int)kHiddenAllRaw : (MODE_ & 3);      // all-fp16: one form for every hidden layer, no scale
     constexpr bool A16 = (MODE_ & kAct16) != 0 || W16;
-    typedef XHalf<TM, WP> Half;
+    typedef XLayout<TM, WQ, MODE_ == kHiddenAllInt> LY;
+    typedef XHalf<TM, LY> Half;
+    constexpr int WP = LY::WP;
     char *lds = (char *)lds_f;
     const int tid = threadIdx.x, nthreads = blockDim.x;
     const uint32_t tile0 = w.tile0, tile1 = w.tile1;
@@ -688,14 +794,14 @@ __device__ __forceinline__ void xdl_body(const DecodeArgs &a, const Work &w, flo
     uint32_t *next_tile = (uint32_t *)(lds + room);
     if (tid == 0) *next_tile = tile0 + (nthreads >> 6);
     {
-        const LaneLayers t = lane_layers<XExpand<TM, WP>::PASSES>(record, L, 0, L, tid & 63, __builtin_amdgcn_readfirstlane(tid >> 6), nthreads >> 6);
+        const LaneLayers t = lane_layers<XExpand<LY::WP>::PASSES>(record, L, 0, L, tid & 63, __builtin_amdgcn_readfirstlane(tid >> 6), nthreads >> 6);
         const uint32_t need = resident_bytes(a.fit_form, w.cls, L, 0);
         if (MODE == kHiddenAllInt || W16 || need + e.nbytes <= room) {     // (in one-block form a model fits with its record)
             uint32_t *stage = (uint32_t *)(lds + (room - e.nbytes));
             for (uint32_t q = tid; q < (e.nbytes >> 4); q += nthreads) ((uint4 *)stage)[q] = ((const uint4 *)record)[q];
-            xdl_expand_layers<TM, WP, W16, false, MODE, (WP <= 32 ? 1 : 2)>(lds, stage, t, L, 0, L, a.pre, tid, nthreads);
+            xdl_expand_layers<LY, W16, false, MODE, (WP <= 32 ? 1 : 2)>(lds, stage, t, L, 0, L, a.pre, tid, nthreads);
         } else {
-            xdl_expand_layers<TM, WP, W16, false, MODE, 1>(lds, (const uint32_t *)record, t, L, 0, L, a.pre, tid, nthreads);
+            xdl_expand_layers<LY, W16, false, MODE, 1>(lds, (const uint32_t *)record, t, L, 0, L, a.pre, tid, nthreads);
         }
     }
 
@@ -713,8 +819,8 @@ __device__ __forceinline__ void xdl_body(const DecodeArgs &a, const Work &w, flo
         uint32_t ones = ~0u;
         asm volatile("" : "+s"(ones));
         int lane = (int)__builtin_amdgcn_mbcnt_hi(ones, __builtin_amdgcn_mbcnt_lo(ones, 0u));
-        xdl_first<TM, WP>(X, Y, a, u, lds, e0, tile, lane);
-        xdl_epilogue<TM, WP, A16>(X, 1.0f, neg_unit);
+        xdl_first<TM, LY>(X, Y, a, u, lds, e0, tile, lane);
+        xdl_epilogue<TM, LY, A16>(X, 1.0f, neg_unit);
         // ---- hidden layers, software-pipelined over the two halves:
         //      matrix work of X(l) with the sine/split of Y(l-1), then matrix work of Y(l) with the sine/split of X(l)
         float scale_prev = 1.0f;
@@ -723,7 +829,7 @@ __device__ __forceinline__ void xdl_body(const DecodeArgs &a, const Work &w, flo
             const XLayer el = uniform_layer(tab[1]);
             int ll = lane;
             asm volatile("" : "+v"(ll));
-            xdl_layer<TM, WP, false, A16>(X, Y, lds, el, ll, ll / TM, 1.0f, el.scale, neg_unit);
+            xdl_layer<TM, LY, false, A16>(X, Y, lds, el, ll, ll / TM, 1.0f, el.scale, neg_unit);
             scale_prev = el.scale;
             l = 2;
         }
@@ -732,19 +838,19 @@ __device__ __forceinline__ void xdl_body(const DecodeArgs &a, const Work &w, flo
             int ll = lane;                       // the lane group is derived from the lane index per layer, not kept
             asm volatile("" : "+v"(ll));
             if constexpr (MODE == kHiddenAllInt) {
-                xdl_layer<TM, WP, false, A16>(X, Y, lds, el, ll, ll / TM, scale_prev, el.scale, neg_unit);
+                xdl_layer<TM, LY, false, A16>(X, Y, lds, el, ll, ll / TM, scale_prev, el.scale, neg_unit);
             } else if constexpr (MODE == kHiddenAllRaw) {
-                xdl_layer<TM, WP, !W16, A16>(X, Y, lds, el, ll, ll / TM, 1.0f, 1.0f, neg_unit);
+                xdl_layer<TM, LY, !W16, A16>(X, Y, lds, el, ll, ll / TM, 1.0f, 1.0f, neg_unit);
             } else {
-                if (el.off_lo == 0) xdl_layer<TM, WP, false, A16>(X, Y, lds, el, ll, ll / TM, scale_prev, el.scale, neg_unit);
-                else xdl_layer<TM, WP, true, A16>(X, Y, lds, el, ll, ll / TM, scale_prev, el.scale, neg_unit);
+                if (el.off_lo == 0) xdl_layer<TM, LY, false, A16>(X, Y, lds, el, ll, ll / TM, scale_prev, el.scale, neg_unit);
+                else xdl_layer<TM, LY, true, A16>(X, Y, lds, el, ll, ll / TM, scale_prev, el.scale, neg_unit);
             }
             scale_prev = el.scale;
         }
-        xdl_epilogue<TM, WP, A16>(Y, scale_prev, neg_unit);
+        xdl_epilogue<TM, LY, A16>(Y, scale_prev, neg_unit);
         asm volatile("" : "+s"(ones));           // pixel indices and addresses: derived again rather than kept
         lane = (int)__builtin_amdgcn_mbcnt_hi(ones, __builtin_amdgcn_mbcnt_lo(ones, 0u));
-        xdl_output<TM, WP, A16>(X, Y, a, ns0, ns1, ns2, nb0, nb1, nb2, lds, eo, tile, lane, plane0);
+        xdl_output<TM, LY, A16>(X, Y, a, ns0, ns1, ns2, nb0, nb1, nb2, lds, eo, tile, lane, plane0);
         uint32_t nt_ = 0;
         if (lane == 0) nt_ = atomicAdd(next_tile, 1u);
         tile = __builtin_amdgcn_readfirstlane(nt_);
@@ -755,18 +861,18 @@ __device__ __forceinline__ void xdl_body(const DecodeArgs &a, const Work &w, flo
 // slots as fit.  Every wavefront keeps one tile in registers (both halves, mid-pipeline: X holds activations, Y
 // accumulators awaiting their sine); for each group the workgroup builds the group's blocks straight from the
 // packed record in global memory, then every wavefront takes its tile through the group's layers.
-template <int TM, int WP, int MODE_>
+template <int TM, int WQ, int MODE_>
 __device__ __forceinline__ void xdl_stream_body(const DecodeArgs &a, const Work &w, float *lds_f) {
     constexpr bool W16 = (MODE_ & kWeight16) != 0;
     constexpr bool A16 = (MODE_ & kAct16) != 0 || W16;
-    typedef XLayout<TM, WP> LY;
-    typedef XHalf<TM, WP> Half;
+    typedef XLayout<TM, WQ, MODE_ == kHiddenAllInt> LY;
+    typedef XHalf<TM, LY> Half;
     char *lds = (char *)lds_f;
     const int tid = threadIdx.x, nthreads = blockDim.x;
     const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), nwaves = nthreads >> 6;
     const IndexEntry e = w.e;
     const int L = e.n_layers;
-    const int K = (int)((a.lds_bytes - LY::TABLE) / (uint32_t)XSlot<TM, WP>::BYTES);   // layers per group (>= 1 by the host's launch size)
+    const int K = (int)((a.lds_bytes - LY::TABLE) / (uint32_t)XSlot<LY>::BYTES);   // layers per group (>= 1 by the host's launch size)
     const uint32_t *rec = (const uint32_t *)(a.blob + e.off);
     const XLayer *tab = (const XLayer *)lds;
     const h4v neg_unit = xdl_neg_unit(tid & 63);
@@ -783,35 +889,37 @@ __device__ __forceinline__ void xdl_stream_body(const DecodeArgs &a, const Work 
         for (int l0 = 0; l0 < L; l0 += K) {
             const int l1 = l0 + K < L ? l0 + K : L;
             __syncthreads();                                           // every wavefront is done with the previous group
-            const LaneLayers t = lane_layers<XExpand<TM, WP>::PASSES>((const uint8_t *)rec, L, l0, l1, lane, wave, nwaves);
-            xdl_expand_layers<TM, WP, W16, true, kHiddenMixed, 1>(lds, rec, t, L, l0, l1, a.pre, tid, nthreads);
+            const LaneLayers t = lane_layers<XExpand<LY::WP>::PASSES>((const uint8_t *)rec, L, l0, l1, lane, wave, nwaves);
+            xdl_expand_layers<LY, W16, true, kHiddenMixed, 1>(lds, rec, t, L, l0, l1, a.pre, tid, nthreads);
             if (!active) continue;
             for (int l = l0; l < l1; ++l) {
                 const XLayer el = uniform_layer(tab[l]);
                 if (l == 0) {
-                    xdl_first<TM, WP>(X, Y, a, u, lds, el, tile, lane);
-                    xdl_epilogue<TM, WP, A16>(X, 1.0f, neg_unit);
+                    xdl_first<TM, LY>(X, Y, a, u, lds, el, tile, lane);
+                    xdl_epilogue<TM, LY, A16>(X, 1.0f, neg_unit);
                 } else if (l < L - 1) {
-                    if (W16) xdl_layer<TM, WP, false, A16>(X, Y, lds, el, lane, lane / TM, 1.0f, 1.0f, neg_unit);
-                    else if (el.off_lo == 0) xdl_layer<TM, WP, false, A16>(X, Y, lds, el, lane, lane / TM, scale_prev, el.scale, neg_unit);
-                    else xdl_layer<TM, WP, true, A16>(X, Y, lds, el, lane, lane / TM, scale_prev, el.scale, neg_unit);
+                    if (W16) xdl_layer<TM, LY, false, A16>(X, Y, lds, el, lane, lane / TM, 1.0f, 1.0f, neg_unit);
+                    else if (el.off_lo == 0) xdl_layer<TM, LY, false, A16>(X, Y, lds, el, lane, lane / TM, scale_prev, el.scale, neg_unit);
+                    else xdl_layer<TM, LY, true, A16>(X, Y, lds, el, lane, lane / TM, scale_prev, el.scale, neg_unit);
                     scale_prev = W16 ? 1.0f : el.scale;
                 } else {
-                    xdl_epilogue<TM, WP, A16>(Y, scale_prev, neg_unit);
-                    xdl_output<TM, WP, A16>(X, Y, a, ns0, ns1, ns2, nb0, nb1, nb2, lds, el, tile, lane, w.plane0);
+                    xdl_epilogue<TM, LY, A16>(Y, scale_prev, neg_unit);
+                    xdl_output<TM, LY, A16>(X, Y, a, ns0, ns1, ns2, nb0, nb1, nb2, lds, el, tile, lane, w.plane0);
                 }
             }
         }
     }
 }
 
-// One width class per launch (a.cls != 0) ...
-template <int CLS, int NTHREADS, int MODE>
+// One width class per launch (a.cls != 0): WQ is the class's padded width, or 8 less where the store has no wider model of the class.
+// (One kernel with both bodies, chosen per model, takes more registers than either, and 2048 ragged images of 32 x 32, decoded class by
+// class, went from 135 to 141 us.) ...
+template <int WQ, int NTHREADS, int MODE>
 __global__ __launch_bounds__(NTHREADS) void decode_xdl_kernel(const DecodeArgs a) {
     extern __shared__ __attribute__((aligned(16))) float lds_f[];
     Work w;
     if (!decode_prologue(a, w)) return;
-    xdl_body<xdl_tile_rows(CLS), 16 * CLS, MODE>(a, w, lds_f);
+    xdl_body<xdl_tile_rows((WQ + 15) / 16), WQ, MODE>(a, w, lds_f);
 }
 
 // ... or every width class in one launch (a.cls == 0)
@@ -820,39 +928,42 @@ __global__ __launch_bounds__(NTHREADS) void decode_xdl_any_kernel(const DecodeAr
     extern __shared__ __attribute__((aligned(16))) float lds_f[];
     Work w;
     if (!decode_prologue(a, w)) return;
-    switch (w.cls) {
-        case 1: xdl_body<xdl_tile_rows(1), 16, MODE>(a, w, lds_f); break;
-        case 2: xdl_body<xdl_tile_rows(2), 32, MODE>(a, w, lds_f); break;
-        case 3: xdl_body<xdl_tile_rows(3), 48, MODE>(a, w, lds_f); break;
-        default: xdl_body<32, 64, MODE>(a, w, lds_f); break;    // 32-row tiles: measured faster here, slower in the one-class kernel;
-                                                                // the layout is smaller than the 16-row one the host sizes LDS for
+    switch ((w.e.width + 7u) >> 3) {
+        case 0: case 1: xdl_body<xdl_tile_rows(1), 8, MODE>(a, w, lds_f); break;
+        case 2: xdl_body<xdl_tile_rows(1), 16, MODE>(a, w, lds_f); break;
+        case 3: xdl_body<xdl_tile_rows(2), 24, MODE>(a, w, lds_f); break;
+        case 4: xdl_body<xdl_tile_rows(2), 32, MODE>(a, w, lds_f); break;
+        case 5: xdl_body<xdl_tile_rows(3), 40, MODE>(a, w, lds_f); break;
+        case 6: xdl_body<xdl_tile_rows(3), 48, MODE>(a, w, lds_f); break;
+        case 7: xdl_body<32, 56, MODE>(a, w, lds_f); break;     // 32-row tiles: measured faster here, slower in the one-class kernel;
+        default: xdl_body<32, 64, MODE>(a, w, lds_f); break;    // the layout is smaller than the 16-row one the host sizes LDS for
     }
 }
 
-// The streamed form: one width class per launch, one wavefront per SIMD.  MODE: 0 (hi+lo activations, any kind of
-// hidden layer), kAct16, or kAct16 | kWeight16.
-template <int CLS, int MODE>
+// The streamed form: one width class per launch, one wavefront per SIMD.  MODE: kHiddenAllInt or kHiddenMixed (hi+lo activations; the
+// resident kernels' layout for such models, so that the bytes are the same), kHiddenMixed | kAct16, or kHiddenMixed | kAct16 | kWeight16.
+template <int WQ, int MODE>
 __global__ __launch_bounds__(kStreamThreads) void decode_xdl_stream_kernel(const DecodeArgs a) {
     extern __shared__ __attribute__((aligned(16))) float lds_f[];
     Work w;
     if (!decode_prologue(a, w)) return;
-    xdl_stream_body<xdl_tile_rows(CLS), 16 * CLS, MODE>(a, w, lds_f);
+    xdl_stream_body<xdl_tile_rows((WQ + 15) / 16), WQ, MODE>(a, w, lds_f);
 }
 
 // ---- debug export of the split-precision operand blocks (see rinr_debug_dequant_split) ----------------------------
-template <int TM, int WP, bool W16>
+template <int TM, int WQ, int KIND, bool W16>
 __global__ __launch_bounds__(256) void xdl_debug_kernel(const uint8_t *blob, int64_t id, int layer, uint32_t lds_bytes,
                                                         float *hi_out, float *lo_out, float *bias_out, float *scale_out) {
-    typedef XLayout<TM, WP> LY;
+    typedef XLayout<TM, WQ, !W16 && KIND == kHiddenAllInt> LY;
     extern __shared__ __attribute__((aligned(16))) float lds_f[];
     char *lds = (char *)lds_f;
-    const int tid = threadIdx.x, nthreads = blockDim.x;
     const IndexEntry e = *(const IndexEntry *)(blob + sizeof(StoreHeader) + (size_t)id * sizeof(IndexEntry));
+    const int tid = threadIdx.x, nthreads = blockDim.x;
     const int L = e.n_layers;
     const uint32_t *rec = (const uint32_t *)(blob + e.off);
     // one layer at a time in the slotted layout, straight from global memory: any depth fits
-    const LaneLayers t = lane_layers<XExpand<TM, WP>::PASSES>((const uint8_t *)rec, L, layer, layer + 1, tid & 63, __builtin_amdgcn_readfirstlane(tid >> 6), nthreads >> 6);
-    xdl_expand_layers<TM, WP, W16, true, kHiddenMixed, 1>(lds, rec, t, L, layer, layer + 1, 1.0f, tid, nthreads);
+    const LaneLayers t = lane_layers<XExpand<LY::WP>::PASSES>((const uint8_t *)rec, L, layer, layer + 1, tid & 63, __builtin_amdgcn_readfirstlane(tid >> 6), nthreads >> 6);
+    xdl_expand_layers<LY, W16, true, kHiddenMixed, 1>(lds, rec, t, L, layer, layer + 1, 1.0f, tid, nthreads);
     const XLayer el = ((const XLayer *)lds)[layer];
     const LayerRec r = *(const LayerRec *)(rec + layer * (sizeof(LayerRec) / 4));
     const _Float16 *hi = (const _Float16 *)(lds + el.off_hi), *lo = (const _Float16 *)(lds + el.off_lo);
@@ -862,10 +973,7 @@ __global__ __launch_bounds__(256) void xdl_debug_kernel(const uint8_t *blob, int
     for (int k = tid; k < cnt; k += nthreads) {
         const int o = k / n_in, i = k - o * n_in;
         float h, l;
-        if (layer == L - 1) {
-            h = (float)hi[LY::idx_out(o, i)];
-            l = (float)lo[LY::idx_out(o, i)];
-        } else if (layer == 0) {
+        if (layer == 0) {
             h = (float)hi[LY::idx_first(0, o, i)];
             l = (float)hi[LY::idx_first(0, o, 4 + i)];
             for (int q = 0; q < LY::G; ++q) {          // every copy must agree
@@ -873,14 +981,18 @@ __global__ __launch_bounds__(256) void xdl_debug_kernel(const uint8_t *blob, int
                 if ((float)hi[LY::idx_first(q, o, 4 + i)] != l) l = nan;
             }
         } else {
-            h = (float)hi[LY::idx_hidden(o, i)];
-            l = el.off_lo ? (float)lo[LY::idx_hidden(o, i)] : 0.0f;
+            const int at = layer == L - 1 ? LY::idx_out(o, i) : LY::idx_hidden(o, i);
+            const bool two = LY::TAIL == kTailTwo && LY::in_tail(i), full = LY::TAIL == kTailFull && LY::in_tail(i);
+            h = (float)hi[at];
+            l = el.off_lo ? (float)(two ? hi[at + 4] : lo[at]) : 0.0f;
+            if ((two && (float)hi[at + 2] != h) || (full && (float)hi[at + 4] != h)) h = nan;
+            if (full && el.off_lo && (float)lo[at + 4] != l) l = nan;
         }
         hi_out[k] = h;
         lo_out[k] = l;
     }
     if (bias_out)
-        for (int o = tid; o < r.n_out; o += nthreads) bias_out[o] = bt[LY::idx_bias(layer == L - 1 ? 4 * o : o)];
+        for (int o = tid; o < r.n_out; o += nthreads) bias_out[o] = bt[layer == L - 1 ? LY::idx_bias_row(4 * o) : LY::idx_bias(o)];
     if (scale_out && tid == 0) *scale_out = el.scale;
 }
 
