@@ -505,7 +505,7 @@ template <int WP, int L = 2> Fit16 kernel16_of(int n) {
         return Fit16{nullptr, 0, 0};
     } else {
         constexpr int nt = fit16_tiles(WP, L);
-        return n == L ? Fit16{fit16::fit16_step_kernel<WP, L, nt>, fit16::Shape<WP>::total(L), fit16::kThreads / 4 * nt} : kernel16_of<WP, L + 1>(n);
+        return n == L ? Fit16{fit16::fit16_step_kernel<WP, L, nt>, fit16::Shape<WP>::total(L, nt), fit16::kThreads / 4 * nt} : kernel16_of<WP, L + 1>(n);
     }
 }
 Fit16 kernel16_for(int wp, int L) {

@@ -60,6 +60,22 @@ typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 
 constexpr int kWaves = 4, kThreads = 64 * kWaves;
 
+// Registers: gradient tiles and pre-activations of all layers, and what a layer in progress takes.
+constexpr int fit16_registers(int wp, int ml, int nt) {
+    const int mt = wp / 16;
+    return 4 * (2 * mt + (ml - 2) * mt * mt) + 4 * nt * mt * (ml - 1) + 40 + 16 * nt * mt;
+}
+// Wavefronts per SIMD a kernel is compiled for: as many as its estimate leaves without a spill, but for one shape, which spills
+// at three and is the better for it.  Measured, us a step, spilled -> as chosen:
+//   four instead of three, 48 x 48, width 16, 2048 images: 4 layers 198 -> 189, 5 layers 249 -> 241; 6144 images: 561 -> 555, 692 -> 691;
+//     against it only where four make whole rounds (1024 images of 64 x 64, width 15): 175 -> 180, 219 -> 227
+//   two instead of three: 8 layers x 16: 243 -> 232; 3 x 32: 150 -> 144
+//   three (spills 24) instead of two at 7 layers x 16, 48 x 48: 6144 images 1063 -> 1001; against it 1024 of 64 x 64: 319 -> 328
+constexpr int fit16_waves_per_simd(int wp, int ml, int nt) {
+    const int r = fit16_registers(wp, ml, nt);
+    return r <= 100 ? 4 : (r <= 156 ? 3 : (r <= 256 ? 2 : 1));
+}
+
 // Shapes and the LDS layout (bytes) for hidden widths <= WP (a multiple of 16).
 template <int WP> struct Shape {
     static constexpr int MT = WP / 16;                  // 16-unit tiles of a hidden layer
@@ -75,8 +91,27 @@ template <int WP> struct Shape {
     static constexpr uint32_t LASTF = BIAS + 64 + (kMaxL - 2) * WP * 4;                          // 16 rows, channel c in row 4 c
     static constexpr uint32_t LASTT = LASTF + NPL * 16 * 64;                                     // WP rows, one tile of outputs
     static constexpr uint32_t HID0 = LASTT + PLANE;                                              // hidden layers: outputs as rows, inputs as rows
-    static __host__ __device__ constexpr uint32_t total(int L) {
-        const uint32_t w = HID0 + (uint32_t)(L - 2) * 2 * HID, r = W0 + kWaves * GT * 1024;
+    static __host__ __device__ constexpr uint32_t weights(int L) { return HID0 + (uint32_t)(L - 2) * 2 * HID; }
+    static constexpr uint32_t INPUT = kWaves * MT * 1024;                                        // one layer's input, hi and lo, per 16 pixels of a wavefront
+    // How many areas of that size fit beside the weights, with as many workgroups on a CU as its registers hold.  In them the inputs of
+    // the first hidden layers stay from the forward pass for the weight gradient, which then takes neither their sines and splits again
+    // nor the steps that turn them, and an error is turned through one more: fewer instructions, and LDS latency instead of
+    // the matrix unit's.  It pays where another wavefront of the SIMD fills that latency.  us a step, before -> now: 2048 of 32 x 32, 3 x 15:
+    // 68.0 -> 64.6; 1024 of 64 x 64, 5 x 15: 227 -> 196, 8 x 15: 360 -> 309; 512 of 96 x 96, 5 x 24: 457 -> 416, 6 x 30: 628 -> 570; 256 of 96 x 96,
+    // 3 x 46: 212 -> 200.  A lone wavefront, which waits for LDS with nothing else to do, gets slower (10 x 32: 6000 -> 6360, all turning
+    // through LDS 7190), and so does an SIMD that loses a wavefront to the areas (8 x 30: 865 -> 1084).  The error turned through LDS as well:
+    // 8 x 15: 325 -> 309, but 3 x 15: 64.7 -> 65.7, 5 x 30: 430 -> 530.  One area of several layers: 8 x 30: 863 -> 869.
+    static __host__ __device__ constexpr int areas(int L, int NT) {
+        const int waves = fit16_waves_per_simd(WP, L, NT), room = (int)kLdsLimit / waves - 256 - (int)weights(L);
+        return waves == 1 || room < 0 ? 0 : room / (int)(NT * INPUT);
+    }
+    static __host__ __device__ constexpr bool turned(int L, int NT) { return WP == 16 && L > 3 && areas(L, NT) > 0; }
+    static __host__ __device__ constexpr int kept(int L, int NT) {
+        const int n = areas(L, NT) - turned(L, NT);
+        return n >= L - 2 ? L - 2 : (n >= 2 ? n : 0);
+    }
+    static __host__ __device__ constexpr uint32_t total(int L, int NT) {
+        const uint32_t w = weights(L) + (kept(L, NT) + turned(L, NT)) * NT * INPUT, r = W0 + kWaves * GT * 1024;
         return w > r ? w : r;
     }
 };
@@ -165,22 +200,6 @@ template <int WP, int R> struct Words {
     }
 };
 
-// Registers: gradient tiles and pre-activations of all layers, and what a layer in progress takes.
-constexpr int fit16_registers(int wp, int ml, int nt) {
-    const int mt = wp / 16;
-    return 4 * (2 * mt + (ml - 2) * mt * mt) + 4 * nt * mt * (ml - 1) + 40 + 16 * nt * mt;
-}
-// Wavefronts per SIMD a kernel is compiled for: as many as its estimate leaves without a spill, but for one shape, which spills
-// at three and is the better for it.  Measured, us a step, spilled -> as chosen:
-//   four instead of three, 48 x 48, width 16, 2048 images: 4 layers 198 -> 189, 5 layers 249 -> 241; 6144 images: 561 -> 555, 692 -> 691;
-//     against it only where four make whole rounds (1024 images of 64 x 64, width 15): 175 -> 180, 219 -> 227
-//   two instead of three: 8 layers x 16: 243 -> 232; 3 x 32: 150 -> 144
-//   three (spills 24) instead of two at 7 layers x 16, 48 x 48: 6144 images 1063 -> 1001; against it 1024 of 64 x 64: 319 -> 328
-constexpr int fit16_waves_per_simd(int wp, int ml, int nt) {
-    const int r = fit16_registers(wp, ml, nt);
-    return r <= 100 ? 4 : (r <= 156 ? 3 : (r <= 256 ? 2 : 1));
-}
-
 // Ends a basic block between two layers: `stop` is 0, which the compiler cannot see.  A whole chunk as one block has its
 // registers assigned badly (10 layers x 40: 78 to 219 spilled; with these edges none), and code moves across too far.
 // A kernel that takes more than 256 registers must not spill: the compiler's pass that puts matrix results into the upper half
@@ -212,7 +231,7 @@ template <int WP, int L> __device__ __forceinline__ bool fit16_set_up(const FitA
         for (int k = 0; k < kOwn; ++k) w[k] = tid + k * kThreads < cnt ? src[tid + k * kThreads] : 0.0f;
     };
     fetch(0, cur);
-    for (uint32_t q = tid; q < S::total(L) / 16; q += kThreads) ((uint4 *)lds)[q] = make_uint4(0u, 0u, 0u, 0u);
+    for (uint32_t q = tid; q < S::weights(L) / 16; q += kThreads) ((uint4 *)lds)[q] = make_uint4(0u, 0u, 0u, 0u);
     __syncthreads();
     for (int l = 0; l < L; ++l) {
         const int din = a.d[l], dout = a.d[l + 1];
@@ -348,6 +367,28 @@ template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fi
         hi = to_h4(mfma32(x, I0, zero4));
         lo = to_h4(mfma32(x, I1, zero4));
     };
+    // P -> U through LDS: a quad is written as it is, 32 bytes of a tile's units to a pixel, and read back by the transposing read, in which
+    // the 16 lanes of a group take four rows of 16 halfs and get a column each; places exchanged in half of the rows, for the banks.
+    constexpr int kKept = S::kept(L, NT);               // steps u < kKept: the input stays in area u
+    constexpr bool kTurned = S::turned(L, NT);          // the error goes through area kKept
+    char *const areas = lds + S::weights(L) + wave * (NT * MT * 1024);
+    char *const put_at = areas + (n * 32 + 8 * (g ^ ((n >> 2) & 2)));
+    const char *const get_at = areas + ((4 * g + (n >> 2)) * 32 + 8 * ((n & 3) ^ (g & 2)));
+    auto put = [&](int area, const h4v (&Xh)[NT][MT], const h4v (&Xl)[NT][MT]) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+            for (int t = 0; t < MT; ++t) {
+                char *const p = put_at + area * (NT * S::INPUT) + (nt * MT + t) * 1024;
+                *(h4v *)p = Xh[nt][t];
+                *(h4v *)(p + 512) = Xl[nt][t];
+            }
+    };
+    auto get = [&](int area, int nt, int t, int part) -> h4v {
+        typedef __fp16 f4v __attribute__((ext_vector_type(4)));
+        const char *const p = get_at + area * (NT * S::INPUT) + (nt * MT + t) * 1024 + part * 512;
+        return __builtin_bit_cast(h4v, __builtin_amdgcn_ds_read_tr16_b64_v4f16((__attribute__((address_space(3))) f4v *)p));
+    };
     auto column = [&](int k, uint32_t c) -> h8v {                           // ones in column k
         int m = n;
         asm("" : "+v"(m) : "s"(c));         // made again where it is used: eight steps' columns are not held across the loop
@@ -433,6 +474,7 @@ template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fi
                     if (NH == 0) zst[NH][nt][t] = z0[nt][t];
                     split_rne(sin4(z0[nt][t]), neg1, Bh[nt][t], Bl[nt][t]);
                 }
+            if (kKept > 0) put(0, Bh, Bl);
             blocks(0, 0, kBlocks - 1);
         }
 #pragma unroll
@@ -444,6 +486,7 @@ template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fi
             for (int t = 0; t < MT; ++t)
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) split_rne(sin4(zst[u + 1][nt][t]), neg1, Bh[nt][t], Bl[nt][t]);
+            if (u + 1 < kKept) put(u + 1, Bh, Bl);
             blocks(u + 1, 0, kBlocks - 1);
         }
         FIT16_EDGE;
@@ -512,11 +555,15 @@ template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fi
         // ---- backward: the error goes down through the hidden layers, each layer's weight gradient takes these pixels
         h8v A0[MT], A1[MT];                // the error turned: NT = 2: hi, lo; NT = 1: [hi | lo], unused
         auto turn_error = [&](const h4v (&Eh)[NT][MT], const h4v (&El)[NT][MT]) {
+            if (kTurned) put(kKept, Eh, El);
 #pragma unroll
             for (int t = 0; t < MT; ++t) {
                 h4v uh[NT], ul[NT];
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) turn(Eh[nt], El[nt], t, uh[nt], ul[nt]);
+                for (int nt = 0; nt < NT; ++nt) {
+                    if (!kTurned) turn(Eh[nt], El[nt], t, uh[nt], ul[nt]);
+                    else { uh[nt] = get(kKept, nt, t, 0); ul[nt] = get(kKept, nt, t, 1); }
+                }
                 A0[t] = cat(uh[0], NT == 2 ? uh[NT - 1] : ul[0]);
                 A1[t] = cat(ul[0], ul[NT - 1]);
             }
@@ -547,10 +594,11 @@ template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fi
             };
             if (kScarce) contract();
             turn_error(Eh, El);
+            if (u >= kKept)
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
+                for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                for (int t = 0; t < MT; ++t) split_rne(sin4(zst[u][nt][t]), neg1, Hh[nt][t], Hl[nt][t]);
+                    for (int t = 0; t < MT; ++t) split_rne(sin4(zst[u][nt][t]), neg1, Hh[nt][t], Hl[nt][t]);
             if (!kScarce) contract();
             const h8v ones = column(u, c);
 #pragma unroll
@@ -562,7 +610,10 @@ template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fi
             for (int i = 0; i < MT; ++i) {
                 h4v uh[NT], ul[NT];
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) turn(Hh[nt], Hl[nt], i, uh[nt], ul[nt]);
+                for (int nt = 0; nt < NT; ++nt) {
+                    if (u >= kKept) turn(Hh[nt], Hl[nt], i, uh[nt], ul[nt]);
+                    else { uh[nt] = get(u, nt, i, 0); ul[nt] = get(u, nt, i, 1); }
+                }
                 const h8v b0 = cat(uh[0], uh[NT - 1]), b1 = cat(ul[0], ul[NT - 1]);
 #pragma unroll
                 for (int t = 0; t < MT; ++t) {
