@@ -48,7 +48,7 @@ struct ClassImpl {
 
 // WQ: the class's padded width WP, or 8 less where every model of the class is as narrow
 template <int TM, int WP, int WQ> ClassImpl make_impl() {
-    constexpr int XTM = xdl_tile_rows(WP / 16);
+    constexpr int XTM = xdl_tile_rows(WQ, kHiddenAllInt);
     return ClassImpl{decode_kernel<TM, WP, kThreads>,
                      {decode_xdl_kernel<WQ, kThreads, kHiddenAllInt>, decode_xdl_kernel<WQ, kThreads, kHiddenAllRaw>,
                       decode_xdl_kernel<WQ, kThreads, kHiddenMixed>, decode_xdl_kernel<WQ, kThreads, kHiddenAllInt | kAct16>,

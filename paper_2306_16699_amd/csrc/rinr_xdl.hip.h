@@ -10,7 +10,7 @@
 //
 // Same structure as the fp32 kernel: workgroup = (slot, range of 64-pixel tiles), model
 // expanded once into LDS, activations register-resident across layers.  Tile = TM rows x TM
-// pixels (TM = 32 at padded width 32, and at 64 in the all-class kernel; else 16), lane = (n = lane % TM, g = lane / TM).
+// pixels (xdl_tile_rows; 32 above 48 units in the all-class kernel), lane = (n = lane % TM, g = lane / TM).
 // A lane's accumulator registers come in quads of four consecutive rows; quad Q (counted over
 // all row tiles of the layer) holds rows
 //     TM = 16:  16 Q + 4 g + b            TM = 32:  32 (Q / 4) + 8 (Q % 4) + 4 g + b,   b = 0..3.
@@ -42,11 +42,6 @@ __host__ __device__ inline bool xdl_int_layer(uint32_t bits, float scale_pre) {
     return bits >= 2 && bits <= 8 && a >= 1e-12f && a <= 1e12f;
 }
 
-// MFMA tile rows the split-precision kernel uses for a width class (padded width = 16 * cls).
-// The 32-row instruction does twice the work per issue slot; at padded width 32 that pays, at 64 the
-// 16-register accumulator tuples cost more in register pressure than the issue slots give back.
-__host__ __device__ constexpr int xdl_tile_rows(int cls) { return cls == 2 ? 32 : 16; }
-
 // What kinds of hidden layer the models served by a launch have (the host knows it from the store): a kernel
 // for one kind runs a layer loop without a branch on the kind.  With the branch inside, the compiler hoists and
 // sinks the two halves' common epilogue code out of the branches, away from the MFMAs it is meant to run under.
@@ -58,6 +53,17 @@ enum { kAct16 = 4 };
 // whether the layer is stored as codes or as fp32, so every hidden layer is one MFMA term and its epilogue is
 // sine + conversion (RINR_FLAG_FP16_ALL): fp16 operands with fp32 accumulation throughout the hidden layers.
 enum { kWeight16 = 8 };
+
+// MFMA tile rows the split-precision kernels use for widths up to WQ (a multiple of 8).  A matrix step delays the vector instructions
+// beside it by a clock per operand register, so a 32-row step, which does twice the work of a 16-row one on as many, delays
+// less; but it takes more energy for it, and these kernels run at the card's power limit (a stream of 32-row steps on random operands runs at
+// 1.73 GHz, of 16-row ones at 1.9, on zeros both at 2.4), and its accumulators are harder to place.  us, 32 -> 16 rows, on two cards: 256 images
+// of 160 x 160, 4 x 32: 154.5 -> 147.7 and 148.6 -> 144.7, of fp32 weights 171 -> 159 and 161 -> 152, the reduced
+// modes (one term, the lightest on the matrix unit) 110 -> 104 and 103.0 -> 103.5, 114 -> 114 and 111.8 -> 113.5; 4 x 64: 349.5 -> 337.5.  At 24 units a 32-row tile has three
+// quads a lane and the odd one's terms take one step, while 16-row ones make a pair of a full and a half-filled tile: 126.9 against 128.2.
+__host__ __device__ constexpr int xdl_tile_rows(int wq, int mode) {
+    return wq == 24 || (wq == 32 && (mode & (kAct16 | kWeight16))) ? 32 : 16;
+}
 
 struct XLayer {            // one entry per linear layer, built in LDS by the workgroup
     uint32_t off_hi;       // byte offset of the fp16 operand block
@@ -84,6 +90,7 @@ enum { kTailNone = 0, kTailHalf = 1, kTailFull = 2, kTailTwo = 3 };
 // INT: every hidden layer of the models served is integer-coded, and activations are hi/lo pairs.
 template <int TM, int WQ_, bool INT> struct XLayout {
     static constexpr int WQ = WQ_, WP = (WQ + 15) / 16 * 16;
+    static constexpr bool INTS = INT;
     static constexpr int G = 64 / TM;              // lane groups
     static constexpr int RV = TM * TM / 64;        // accumulator registers per tile
     static constexpr int MT = WP / TM;             // row tiles per layer
@@ -148,10 +155,15 @@ template <int TM, int WQ_, bool INT> struct XLayout {
 // Bytes of LDS the expanded model of width class `cls` needs at most (without the staging copy of the
 // record), whatever kernel takes it.  n_int = hidden layers in integer form, n_raw = hidden layers split hi/lo.
 __host__ __device__ inline uint32_t xdl_model_bytes(int cls, int n_layers, int n_int, int n_raw) {
-    const uint32_t tm = (uint32_t)xdl_tile_rows(cls), wp = 16u * cls, g = 64u / tm, nq = wp / (4u * g);
-    const uint32_t out = (nq / 2 + nq % 2) * 1024u, one = wp * wp * 2u + (nq % 2) * (wp / tm) * 512u;
-    return 16u * 16u + 16u * 4u + ((uint32_t)(n_layers - 1) * wp + tm) * 4u + g * (wp / tm) * 1024u +
+    const uint32_t wp = 16u * cls, nq = (uint32_t)cls;              // 16-row tiles; layouts of 32-row tiles are smaller
+    const uint32_t out = (nq / 2 + nq % 2) * 1024u, one = wp * wp * 2u + (nq % 2) * nq * 512u;
+    return 16u * 16u + 16u * 4u + ((uint32_t)(n_layers - 1) * wp + 16u) * 4u + 4u * nq * 1024u +
            one * (uint32_t)n_int + 2u * wp * wp * 2u * (uint32_t)n_raw + 2u * out;
+}
+// Whether that holds for layout LY: for the parts every model has, and per hidden layer of either kind
+template <class LY> constexpr bool xdl_within_bound() {
+    constexpr int nq = LY::WP / 16, out = (nq / 2 + nq % 2) * 1024, two = 4 * LY::WP * LY::WP, one = two / 2 + nq % 2 * nq * 512;
+    return LY::OUTB + LY::FIRST + LY::OUT + LY::OUTLO <= 64 + 4 * nq * 1024 + 2 * out && LY::HID <= one && (LY::INTS || LY::HID + LY::HIDLO <= two);
 }
 
 // Builds the operand blocks of layers [l0, l1) in LDS and their XLayer entries tab[l].  `rec` is the model record:
@@ -779,6 +791,7 @@ __device__ __forceinline__ void xdl_body(const DecodeArgs &a, const Work &w, flo
     typedef XLayout<TM, WQ, MODE_ == kHiddenAllInt> LY;
     typedef XHalf<TM, LY> Half;
     constexpr int WP = LY::WP;
+    static_assert(xdl_within_bound<LY>(), "what the host sizes LDS for");
     char *lds = (char *)lds_f;
     const int tid = threadIdx.x, nthreads = blockDim.x;
     const uint32_t tile0 = w.tile0, tile1 = w.tile1;
@@ -919,7 +932,7 @@ __global__ __launch_bounds__(NTHREADS) void decode_xdl_kernel(const DecodeArgs a
     extern __shared__ __attribute__((aligned(16))) float lds_f[];
     Work w;
     if (!decode_prologue(a, w)) return;
-    xdl_body<xdl_tile_rows((WQ + 15) / 16), WQ, MODE>(a, w, lds_f);
+    xdl_body<xdl_tile_rows(WQ, MODE), WQ, MODE>(a, w, lds_f);
 }
 
 // ... or every width class in one launch (a.cls == 0)
@@ -929,12 +942,12 @@ __global__ __launch_bounds__(NTHREADS) void decode_xdl_any_kernel(const DecodeAr
     Work w;
     if (!decode_prologue(a, w)) return;
     switch ((w.e.width + 7u) >> 3) {
-        case 0: case 1: xdl_body<xdl_tile_rows(1), 8, MODE>(a, w, lds_f); break;
-        case 2: xdl_body<xdl_tile_rows(1), 16, MODE>(a, w, lds_f); break;
-        case 3: xdl_body<xdl_tile_rows(2), 24, MODE>(a, w, lds_f); break;
-        case 4: xdl_body<xdl_tile_rows(2), 32, MODE>(a, w, lds_f); break;
-        case 5: xdl_body<xdl_tile_rows(3), 40, MODE>(a, w, lds_f); break;
-        case 6: xdl_body<xdl_tile_rows(3), 48, MODE>(a, w, lds_f); break;
+        case 0: case 1: xdl_body<xdl_tile_rows(8, MODE), 8, MODE>(a, w, lds_f); break;
+        case 2: xdl_body<xdl_tile_rows(16, MODE), 16, MODE>(a, w, lds_f); break;
+        case 3: xdl_body<xdl_tile_rows(24, MODE), 24, MODE>(a, w, lds_f); break;
+        case 4: xdl_body<xdl_tile_rows(32, MODE), 32, MODE>(a, w, lds_f); break;
+        case 5: xdl_body<xdl_tile_rows(40, MODE), 40, MODE>(a, w, lds_f); break;
+        case 6: xdl_body<xdl_tile_rows(48, MODE), 48, MODE>(a, w, lds_f); break;
         case 7: xdl_body<32, 56, MODE>(a, w, lds_f); break;     // 32-row tiles: measured faster here, slower in the one-class kernel;
         default: xdl_body<32, 64, MODE>(a, w, lds_f); break;    // the layout is smaller than the 16-row one the host sizes LDS for
     }
@@ -947,7 +960,7 @@ __global__ __launch_bounds__(kStreamThreads) void decode_xdl_stream_kernel(const
     extern __shared__ __attribute__((aligned(16))) float lds_f[];
     Work w;
     if (!decode_prologue(a, w)) return;
-    xdl_stream_body<xdl_tile_rows((WQ + 15) / 16), WQ, MODE>(a, w, lds_f);
+    xdl_stream_body<xdl_tile_rows(WQ, MODE), WQ, MODE>(a, w, lds_f);
 }
 
 // ---- debug export of the split-precision operand blocks (see rinr_debug_dequant_split) ----------------------------
