@@ -429,6 +429,7 @@ extern "C" int rinr_decode_batch_ex(rinr_store *s, const int64_t *image_ids, int
         while ((1ull << l) < (uint64_t)W) ++l;
         a.wmagic = l ? (uint32_t)((((uint64_t)1 << (31 + l)) + (uint64_t)W - 1) / (uint64_t)W) : 0u;
         a.wshift = l ? l - 1 : 0u;
+        a.wsmall = W < 64 ? (65536u + (uint32_t)W - 1u) / (uint32_t)W : 0u;
     }
     a.inv2W = (float)(1.0 / (2.0 * W));
     a.inv2H = (float)(1.0 / (2.0 * H));

@@ -300,6 +300,7 @@ struct DecodeArgs {
     uint64_t n_models;
     uint32_t HW, W;
     uint32_t wmagic, wshift;      // p / W == umulhi(p, wmagic) >> wshift for p < 2^31; wmagic == 0 means W == 1
+    uint32_t wsmall;              // W < 64: c / W == c * wsmall >> 16 for c < 127; else 0
     float inv2W, inv2H;           // 1/(2W), 1/(2H)
     float lo, span;               // coordinate = lo + span * (2k+1)/(2n)
     float pre;                    // w0 / (2 pi)

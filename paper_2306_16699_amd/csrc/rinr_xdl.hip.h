@@ -536,7 +536,7 @@ __device__ __forceinline__ void xdl_epilogue(XHalf<TM, LY> &H, float scale, h4v 
 
 // MFMAs of one hidden layer for a half.  LO: the layer has a low weight part (one more term).  A16: no low activation part.
 template <int TM, class LY, bool LO, bool A16>
-__device__ __forceinline__ void xdl_hidden(XHalf<TM, LY> &H, const char *lds, const XLayer el, int lane, int g) {
+__device__ __forceinline__ void xdl_hidden(XHalf<TM, LY> &H, const char *lds, const XLayer el, uint32_t lane, uint32_t g) {
     typedef XTile<TM> T;
     typedef typename T::acc_t acc_t;
     constexpr int KJ = LY::KJ, MT = LY::MT, NTH = XHalf<TM, LY>::NTH;
@@ -616,7 +616,7 @@ __device__ __forceinline__ void xdl_hidden(XHalf<TM, LY> &H, const char *lds, co
 // One hidden layer for both halves of a 64-pixel tile, software-pipelined: the matrix work of X(l) is issued
 // together with the sine/split of Y(l-1), then the matrix work of Y(l) with the sine/split of X(l).
 template <int TM, class LY, bool LO, bool A16>
-__device__ __forceinline__ void xdl_layer(XHalf<TM, LY> &X, XHalf<TM, LY> &Y, const char *lds, const XLayer el, int lane, int g,
+__device__ __forceinline__ void xdl_layer(XHalf<TM, LY> &X, XHalf<TM, LY> &Y, const char *lds, const XLayer el, uint32_t lane, uint32_t g,
                                           float scale_prev, float scale, h4v neg_unit) {
     xdl_hidden<TM, LY, LO, A16>(X, lds, el, lane, g);
     xdl_epilogue<TM, LY, A16>(Y, scale_prev, neg_unit);
@@ -648,23 +648,37 @@ __device__ __forceinline__ XUniform xdl_uniform(const DecodeArgs &a, uint32_t sl
 //      push the kernel over its register budget.
 template <int TM, class LY>
 __device__ __forceinline__ void xdl_first(XHalf<TM, LY> &X, XHalf<TM, LY> &Y, const DecodeArgs &a, const XUniform &u, const char *lds,
-                                          const XLayer e0, uint32_t tile, int lane) {
+                                          const XLayer e0, uint32_t tile, uint32_t lane) {
     typedef XTile<TM> T;
     typedef typename T::acc_t acc_t;
     constexpr int MT = LY::MT, G = LY::G, NTH = XHalf<TM, LY>::NTH;
-    const int g = lane / TM;
+    const uint32_t g = lane / TM;
     float lo_v = a.lo, af2 = u.af2, af5 = u.af5;        // second uniform operand of an fma: copied to a vector register at the use
     asm volatile("" : "+s"(lo_v), "+s"(af2), "+s"(af5));
     const h8v *a0 = (const h8v *)(lds + e0.off_hi) + lane;
     const acc_t *bt = (const acc_t *)(lds + e0.off_bias) + g;
     // lane (pixel tile q = lane / TM, column n = lane % TM) feeds pixel n * (64 / TM) + q of the 64: a lane's columns of the
-    // pixel tiles are then consecutive pixels, which the output layer stores as one vector
-    uint32_t p = (tile << 6) + (uint32_t)(lane % TM) * (64 / TM) + (uint32_t)(lane / TM);
-    p = min(p, a.HW - 1);
-    const uint32_t row = a.wmagic ? (__umulhi(p, a.wmagic) >> a.wshift) : p, col = p - row * a.W;
+    // pixel tiles are then consecutive pixels, which the output layer stores as one vector.  The tile's first pixel's row and column are the
+    // scalar unit's; a lane is at most 63 pixels on, which is one row at most, or, where rows are shorter, a small quotient.
+    const uint32_t p0 = tile << 6, row0 = a.wmagic ? (__umulhi(p0, a.wmagic) >> a.wshift) : p0;
+    uint32_t col = p0 - row0 * a.W + min(lane % TM * (64 / TM) + lane / TM, a.HW - 1 - p0), row;
+    if (a.wsmall) {
+        const uint32_t q = __umul24(col, a.wsmall) >> 16;
+        col -= __umul24(q, a.W);
+        row = row0 + q;
+    } else {
+        const bool next = col >= a.W;
+        col -= next ? a.W : 0u;
+        row = row0 + next;
+    }
     const float x0 = fmaf(a.span, (float)(2 * col + 1) * a.inv2W, lo_v);
     const float y0 = fmaf(a.span, (float)(2 * row + 1) * a.inv2H, lo_v);
-    const float x = fmaf(u.af0, x0, fmaf(u.af1, y0, af2)), y = fmaf(u.af3, x0, fmaf(u.af4, y0, af5));
+    float x = x0, y = y0;
+    if (a.affine) {
+        asm volatile("");                               // a branch, not selects
+        x = fmaf(u.af0, x0, fmaf(u.af1, y0, af2));
+        y = fmaf(u.af3, x0, fmaf(u.af4, y0, af5));
+    }
     const _Float16 xh = (_Float16)x, yh = (_Float16)y;
     const _Float16 xl = (_Float16)(x - (float)xh), yl = (_Float16)(y - (float)yh);
     const _Float16 z = (_Float16)0.0f;
@@ -686,11 +700,11 @@ __device__ __forceinline__ void xdl_first(XHalf<TM, LY> &X, XHalf<TM, LY> &Y, co
 template <int TM, class LY, bool A16>
 __device__ __forceinline__ void xdl_output(const XHalf<TM, LY> &X, const XHalf<TM, LY> &Y, const DecodeArgs &a, float ns0, float ns1,
                                            float ns2, float nb0, float nb1, float nb2, const char *lds, const XLayer eo,
-                                           uint32_t tile, int lane, size_t plane0) {
+                                           uint32_t tile, uint32_t lane, uint32_t chan, size_t plane0) {
     typedef XTile<TM> T;
     typedef typename T::acc_t acc_t;
     constexpr int KJ = LY::KJ, NTH = XHalf<TM, LY>::NTH;
-    const int go = lane / TM, no = lane % TM;
+    const uint32_t go = lane / TM, no = lane % TM;
     const h8v *ah = (const h8v *)(lds + eo.off_hi) + lane;
     const h8v *al = (const h8v *)(lds + eo.off_lo) + lane;
     const acc_t c = ((const acc_t *)(lds + eo.off_bias))[go];
@@ -744,16 +758,24 @@ __device__ __forceinline__ void xdl_output(const XHalf<TM, LY> &X, const XHalf<T
     const uint32_t p0 = (tile << 6) + (uint32_t)no * NT;
 #pragma unroll
     for (int k = 0; k < NS; ++k) {
-        const int ch = TM == 16 ? go : (go == 0 ? 2 * k : 1);
+        const uint32_t ch = TM == 16 ? go : (go == 0 ? 2 * k : 1);
         const bool live = TM == 16 ? go < 3 : (go == 0 || k == 0);
         float r[NT];
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
             r[nt] = O[nt][TM == 16 ? 0 : 4 * k];
-            if (!a.no_clamp) r[nt] = fminf(fmaxf(r[nt], 0.0f), 1.0f);
-            if (a.normalize) r[nt] = fmaf(r[nt], ch == 0 ? ns0 : (ch == 1 ? ns1 : ns2), ch == 0 ? nb0 : (ch == 1 ? nb1 : nb2));
         }
-        const uint32_t at = (uint32_t)ch * a.HW + p0;       // within the slot's three planes: 3 HW < 2^32 is checked by the host
+        if (!a.no_clamp) {
+            asm volatile("");                               // branches, not selects
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) r[nt] = fminf(fmaxf(r[nt], 0.0f), 1.0f);
+        }
+        if (a.normalize) {
+            asm volatile("");
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) r[nt] = fmaf(r[nt], ch == 0 ? ns0 : (ch == 1 ? ns1 : ns2), ch == 0 ? nb0 : (ch == 1 ? nb1 : nb2));
+        }
+        const uint32_t at = (TM == 16 ? chan : (k ? 2u * a.HW : chan)) + p0;    // within the slot's three planes: 3 HW < 2^32 is checked by the host
         if (a.vec_store) {                                  // HW is a multiple of 4 and the outputs are aligned: whole vectors
             if (live && p0 < a.HW) {
                 if (a.out_f32) {
@@ -782,7 +804,10 @@ __device__ __forceinline__ void xdl_output(const XHalf<TM, LY> &X, const XHalf<T
 }
 
 // Resident form: the model is expanded once per workgroup; a wavefront takes one 64-pixel tile at a time through all
-// layers.
+// layers.  What a tile costs beside its layers counts at small models (3 x 15: 108 of 188 vector instructions): pixel indices come from
+// the scalar unit and an addition per lane, the augmentation map, the clamp and the normalisation are branches that a launch without
+// them skips, where a layer's blocks are is arithmetic.  us a call, before -> now: 4096 images of 32 x 32, fp16 activations, 2 x 15: 34.3 ->
+// 31.4; 4 x 32: 100.2 -> 96.1; 1024 of 64 x 64, 5 x 48: 180.2 -> 176.3; 256 of 224 x 224, 6 x 64: 914 -> 905; 256 of 160 x 160, 4 x 8: 65.1 -> 58.3.
 template <int TM, int WQ, int MODE_>
 __device__ __forceinline__ void xdl_body(const DecodeArgs &a, const Work &w, float *lds_f) {
     constexpr bool W16 = (MODE_ & kWeight16) != 0;
@@ -827,11 +852,24 @@ __device__ __forceinline__ void xdl_body(const DecodeArgs &a, const Work &w, flo
     const float ns0 = uniform_f(a.ns[0]), ns1 = uniform_f(a.ns[1]), ns2 = uniform_f(a.ns[2]);
     const float nb0 = uniform_f(a.nb[0]), nb1 = uniform_f(a.nb[1]), nb2 = uniform_f(a.nb[2]);
 
+    uint32_t chan = (uint32_t)(tid & 63) / TM * a.HW;            // the first plane this lane stores to
+    asm volatile("" : "+v"(chan));
+    // Where a layer's blocks are: known from its number where all hidden layers are of one kind, else from the table
+    const uint32_t hidden0 = e0.off_hi + LY::FIRST;
+    auto layer = [&](int l) -> XLayer {
+        if (MODE == kHiddenMixed) return uniform_layer(tab[l]);
+        XLayer el;
+        el.off_hi = hidden0 + (uint32_t)(l - 1) * (MODE == kHiddenAllInt || W16 ? LY::HID : LY::HID + LY::HIDLO);
+        el.off_lo = MODE == kHiddenAllInt || W16 ? 0u : el.off_hi + LY::HID;
+        el.scale = MODE == kHiddenAllInt ? uniform_f(tab[l].scale) : 1.0f;
+        el.off_bias = LY::TABLE + (uint32_t)l * WP * 4u;
+        return el;
+    };
     for (uint32_t tile = tile0 + wave; tile < tile1;) {
         Half X, Y;
         uint32_t ones = ~0u;
         asm volatile("" : "+s"(ones));
-        int lane = (int)__builtin_amdgcn_mbcnt_hi(ones, __builtin_amdgcn_mbcnt_lo(ones, 0u));
+        uint32_t lane = __builtin_amdgcn_mbcnt_hi(ones, __builtin_amdgcn_mbcnt_lo(ones, 0u));
         xdl_first<TM, LY>(X, Y, a, u, lds, e0, tile, lane);
         xdl_epilogue<TM, LY, A16>(X, 1.0f, neg_unit);
         // ---- hidden layers, software-pipelined over the two halves:
@@ -839,16 +877,16 @@ __device__ __forceinline__ void xdl_body(const DecodeArgs &a, const Work &w, flo
         float scale_prev = 1.0f;
         int l = 1;
         if (MODE == kHiddenAllInt && L > 2) {      // first hidden layer on its own: the first layer's outputs carry no scale
-            const XLayer el = uniform_layer(tab[1]);
-            int ll = lane;
+            const XLayer el = layer(1);
+            uint32_t ll = lane;
             asm volatile("" : "+v"(ll));
             xdl_layer<TM, LY, false, A16>(X, Y, lds, el, ll, ll / TM, 1.0f, el.scale, neg_unit);
             scale_prev = el.scale;
             l = 2;
         }
         for (; l < L - 1; ++l) {
-            const XLayer el = uniform_layer(tab[l]);
-            int ll = lane;                       // the lane group is derived from the lane index per layer, not kept
+            const XLayer el = layer(l);
+            uint32_t ll = lane;                       // the lane group is derived from the lane index per layer, not kept
             asm volatile("" : "+v"(ll));
             if constexpr (MODE == kHiddenAllInt) {
                 xdl_layer<TM, LY, false, A16>(X, Y, lds, el, ll, ll / TM, scale_prev, el.scale, neg_unit);
@@ -862,8 +900,8 @@ __device__ __forceinline__ void xdl_body(const DecodeArgs &a, const Work &w, flo
         }
         xdl_epilogue<TM, LY, A16>(Y, scale_prev, neg_unit);
         asm volatile("" : "+s"(ones));           // pixel indices and addresses: derived again rather than kept
-        lane = (int)__builtin_amdgcn_mbcnt_hi(ones, __builtin_amdgcn_mbcnt_lo(ones, 0u));
-        xdl_output<TM, LY, A16>(X, Y, a, ns0, ns1, ns2, nb0, nb1, nb2, lds, eo, tile, lane, plane0);
+        lane = __builtin_amdgcn_mbcnt_hi(ones, __builtin_amdgcn_mbcnt_lo(ones, 0u));
+        xdl_output<TM, LY, A16>(X, Y, a, ns0, ns1, ns2, nb0, nb1, nb2, lds, eo, tile, lane, chan, plane0);
         uint32_t nt_ = 0;
         if (lane == 0) nt_ = atomicAdd(next_tile, 1u);
         tile = __builtin_amdgcn_readfirstlane(nt_);
@@ -917,7 +955,7 @@ __device__ __forceinline__ void xdl_stream_body(const DecodeArgs &a, const Work 
                     scale_prev = W16 ? 1.0f : el.scale;
                 } else {
                     xdl_epilogue<TM, LY, A16>(Y, scale_prev, neg_unit);
-                    xdl_output<TM, LY, A16>(X, Y, a, ns0, ns1, ns2, nb0, nb1, nb2, lds, el, tile, lane, w.plane0);
+                    xdl_output<TM, LY, A16>(X, Y, a, ns0, ns1, ns2, nb0, nb1, nb2, lds, el, tile, lane, (uint32_t)lane / TM * a.HW, w.plane0);
                 }
             }
         }

@@ -14,8 +14,8 @@ WIDTHS = (1, 7, 8, 9, 15, 16, 17, 23, 24, 25, 33, 39, 40, 41, 47, 48, 49, 55, 56
 
 
 def models_of(width, kind, sines=4):
-    bits = {"ints": [0, 8, 5, 6, 0], "fp32": [0] * 5, "16 bits": [0, 16, 16, 16, 0], "mixed": [0, 8, 0, 16, 0]}[kind]
-    taper = [width, max(1, width - 1), max(1, width // 2), width]          # the widest first and last, odd inner layers
+    bits = {"ints": [0, 8, 5, 6], "fp32": [0] * 4, "16 bits": [0, 16, 16, 16], "mixed": [0, 8, 0, 16]}[kind][:sines] + [0]
+    taper = ([width, max(1, width - 1)] + [max(1, width // 2), width])[:sines]          # the widest first and last, odd inner layers
     return (synth.make_models(70 + width, np.arange(2), width, sines, bits, 0.6) +
             synth.make_models(71 + width, np.arange(1), width, sines, bits, None, widths=taper))
 
@@ -61,4 +61,16 @@ def test_all_widths_in_one_grid(torch):  # noqa: F811
     got = st.decode_batch_ex(ids_dev(torch, sel), 65, 64, rinr.OUT_F32, rinr.FLAG_NO_CLAMP).cpu().numpy()
     assert st.last_launch_info()["launches"] == 1 and st.status() == 0
     assert np.abs(got - oracle.decode(ms, sel, 65, 64, clamp=False)).max() <= TIGHT
+    st.close()
+
+
+@pytest.mark.parametrize("W", [1, 2, 3, 7, 31, 33, 62, 63, 64, 65, 66, 127, 128, 129, 1000])
+def test_rows_and_columns_of_every_pixel(torch, W):  # noqa: F811
+    """A lane's row and column follow from those of its tile's first pixel: rows shorter than a tile, as long, a little longer."""
+    ms = models_of(16, "fp32", 2) + models_of(24, "ints", 2)
+    st = rinr.Store(rinr.pack(ms))
+    for H in (1, 2, 67):
+        sel = np.array([0, 5, 2, 3])
+        got = st.decode_batch_ex(ids_dev(torch, sel), H, W, rinr.OUT_F32, rinr.FLAG_NO_CLAMP).cpu().numpy()
+        assert np.abs(got - oracle.decode(ms, sel, H, W, clamp=False)).max() <= TIGHT, (H, W)
     st.close()
