@@ -500,16 +500,21 @@ constexpr int fit16_tiles(int wp, int ml) {
     return (one > 1 && two == 1) || fit16::fit16_registers(wp, ml, 2) > 512 ? 1 : 2;
 }
 struct Fit16 { fit_fn fn; uint32_t lds; int pixels; };      // kernel, LDS bytes, pixels a workgroup takes at a time
-template <int WP, int L = 2> Fit16 kernel16_of(int n) {
+template <int WP, bool HALF, int L = 2> Fit16 kernel16_of(int n) {
     if constexpr (L > fit16_depth(WP)) {
         return Fit16{nullptr, 0, 0};
     } else {
         constexpr int nt = fit16_tiles(WP, L);
-        return n == L ? Fit16{fit16::fit16_step_kernel<WP, L, nt>, fit16::Shape<WP>::total(L, nt), fit16::kThreads / 4 * nt} : kernel16_of<WP, L + 1>(n);
+        return n == L ? Fit16{fit16::fit16_step_kernel<WP, HALF, L, nt>, fit16::Shape<WP, HALF>::total(L, nt), fit16::kThreads / 4 * nt} : kernel16_of<WP, HALF, L + 1>(n);
     }
 }
-Fit16 kernel16_for(int wp, int L) {
-    const Fit16 k = wp == 16 ? kernel16_of<16>(L) : (wp == 32 ? kernel16_of<32>(L) : (wp == 48 ? kernel16_of<48>(L) : kernel16_of<64>(L)));
+// width: of the widest hidden layer
+Fit16 kernel16_for(int width, int L) {
+    const int wp = (width + 15) / 16 * 16;
+    const bool half = width <= wp - 8;
+    const Fit16 k = wp == 16 ? (half ? kernel16_of<16, true>(L) : kernel16_of<16, false>(L))
+                  : wp == 32 ? kernel16_of<32, false>(L)
+                  : wp == 48 ? (half ? kernel16_of<48, true>(L) : kernel16_of<48, false>(L)) : kernel16_of<64, false>(L);
     return k.lds <= kLdsLimit - 256 ? k : Fit16{nullptr, 0, 0};
 }
 
@@ -521,7 +526,6 @@ struct rinr_fit {
     int32_t H, W;
     int wq, lds_floats;         // wq: widest hidden layer rounded up to a multiple of 8 (fp32 kernels); lds_floats 0 = no fp32 kernel fits
     int family;                 // RINR_FIT_KERNEL_FP32 or RINR_FIT_KERNEL_SPLIT16: the kernels this handle's steps run
-    int wp;                     // widest hidden layer rounded up to a multiple of 16 (split kernels)
     Fit16 k16;                  // their kernel; null = none is built for the shape
     float *emag;                // [n_images] error size seen by the last step (split kernels' error scale); 0 = none yet
     int32_t p_off[kMaxL];
@@ -582,10 +586,9 @@ extern "C" int rinr_fit_create_ex(const rinr_fit_arch *arch, int64_t n_images, i
     int wmax = 1;
     for (int l = 1; l < arch->n_layers; ++l) wmax = arch->widths[l] > wmax ? arch->widths[l] : wmax;
     f->wq = (wmax + 7) / 8 * 8;
-    f->wp = (wmax + 15) / 16 * 16;
     f->lds_floats = lds_floats(f->wq, arch->n_layers);
     if ((size_t)f->lds_floats * 4 + 256 > kLdsLimit) f->lds_floats = 0;
-    f->k16 = kernel16_for(f->wp, arch->n_layers);
+    f->k16 = kernel16_for(wmax, arch->n_layers);
     // the split-precision kernels where they are built for the shape, the fp32 ones otherwise or on request
     f->family = (f->k16.fn && !(flags & RINR_FIT_FLAG_FP32_MFMA)) ? RINR_FIT_KERNEL_SPLIT16 : RINR_FIT_KERNEL_FP32;
     if (f->family == RINR_FIT_KERNEL_FP32 && f->lds_floats == 0) { delete f; return RINR_E_UNSUPPORTED; }

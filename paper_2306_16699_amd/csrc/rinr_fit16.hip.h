@@ -13,9 +13,9 @@
 //
 // What bounds it is instruction issue: a matrix instruction takes two issue slots of 4.1 clocks, a sine or cosine two, other
 // vector instructions one (measured; matrix and vector instructions of one wavefront overlap where they alternate).  A hidden
-// layer of 40 units takes 48 matrix and 169 vector slots per 16 pixels backward, 15 and 52 forward.  At 10 layers x 40 the matrix
-// unit is busy 46 % of the time and vector issue 53 % (the matrix instructions' included), but only 27 % of the matrix time has
-// vector instructions beside it, and a wavefront waits 24 % of its time for loads and barriers and 15 % to issue.
+// layer of 48 units takes 48 matrix and 169 vector slots per 16 pixels backward, 15 and 52 forward.  At 10 layers x 40, padded to 48, the matrix
+// unit was busy 46 % of the time and vector issue 53 % (the matrix instructions' included), but only 27 % of the matrix time had
+// vector instructions beside it, and a wavefront waited 24 % of its time for loads and barriers and 15 % to issue.
 // Measured, ms a step, gradient tiles shared -> a wavefront's own -> layers interleaved (see the kernel): 256 images of 224 x 224,
 // 10 layers x 40: 8.91 -> 6.83 -> 6.29; 10 x 32: 4.54 -> 3.50 -> 3.00; 2048 of 32 x 32, 3 x 15: 0.0934 -> 0.0738 -> 0.0675.
 //
@@ -23,7 +23,8 @@
 // what a matrix instruction leaves with the units as its rows, and two tiles' quads side by side are exactly the B operand
 // of one 32-deep step of the next layer, so nothing moves between lanes from one layer to the next, in either direction.
 // U: lane (n, g) holds unit n and the pixels 4 g + v: the operand of the weight gradient, which contracts over pixels.  From P
-// to U goes a matrix step with the unit matrix (the data as A, the unit matrix as B), which is exact for halfs.
+// to U goes a matrix step with the unit matrix (the data as A, the unit matrix as B), which is exact for halfs, or, where
+// several wavefronts share a SIMD, a write to LDS and a transposing read (Shape::areas).
 // With NT = 2 the two tiles' quads make a 32-deep step over pixels; with NT = 1 the hi and the lo part of one tile do
 // ([Eh | El] x [Hh | Hh], then x [Hl | Hl]: two steps instead of three, and the term lo*lo comes along).  The odd last tile of
 // a layer's units is treated the same way in the forward and backward products ([Wh | Wl] x [Hh | Hh], x [Hl | Hl]).
@@ -77,10 +78,24 @@ constexpr int fit16_waves_per_simd(int wp, int ml, int nt) {
 }
 
 // Shapes and the LDS layout (bytes) for hidden widths <= WP (a multiple of 16).
-template <int WP> struct Shape {
+// HALF (an odd number of tiles): the widths are at most WP - 8, so half of the last tile is padding.  A lane then holds two real units of it
+// instead of four (units 16 t + 2 g + v sit in rows 4 g + v, v < 2), which takes half the sines, cosines and splits, and the two
+// halfs of both go into one quad (h0 h1 l0 l1).  As an operand that quad twice meets (W0 W1 W0 W1 | w0 w1 0 0), w the weights' low parts: all three terms in one
+// matrix step instead of two.  Turned in one step, its rows are the units' hi and lo parts side by side, and the gradient tile
+// that it makes as either operand takes all terms likewise; the parts' rows and columns are added up at the end of the step.
+// A hidden layer of 40 units takes 52 matrix steps per 16 pixels instead of 63, and 10 sines instead of 12 each way.  us a step, before ->
+// now: 256 images of 224 x 224, 10 x 40: 6230 -> 5120; of 96 x 96, 3 x 40: 190 -> 166, 7 x 40: 709 -> 584; 1024 of 64 x 64, 3 x 8: 114 -> 79, 10 x 8: 394 ->
+// 244.  Against fp64 the gradient is as far off as before (10 x 40: 2.73e-6, 3 x 8: 7.8e-7).
+template <int WP, bool HALF> struct Shape {
     static constexpr int MT = WP / 16;                  // 16-unit tiles of a hidden layer
     static constexpr int NP = MT / 2, TAIL = MT % 2;    // pairs of them, and an odd last one
     static constexpr int NPL = 2 * NP + TAIL;           // planes of one operand matrix
+    static_assert(!HALF || TAIL, "half tiles only where there is an odd one");
+    static __device__ __forceinline__ bool mixed(int t) { return HALF && t == MT - 1; }          // tile t's quads hold hi and lo
+    static __device__ __forceinline__ int row(int unit) {
+        const int j = unit & 15;
+        return mixed(unit >> 4) ? (unit & ~15) + 4 * ((j >> 1) & 3) + (j & 1) + ((j & 8) >> 2) : unit;
+    }
     static constexpr uint32_t PLANE = WP * 64;          // bytes of a plane of WP rows
     static constexpr uint32_t HID = NPL * PLANE;        // one hidden layer in one orientation
     static constexpr int GT = MT == 1 ? 4 : 16;         // gradient tiles that go through LDS at a time at the end
@@ -151,6 +166,19 @@ __device__ __forceinline__ void split_rtz(f32x4 x, float neg1, h4v &hi, h4v &lo)
     lo = to_h4((f32x4){__builtin_fmaf((float)hi[0], neg1, x[0]), __builtin_fmaf((float)hi[1], neg1, x[1]),
                        __builtin_fmaf((float)hi[2], neg1, x[2]), __builtin_fmaf((float)hi[3], neg1, x[3])});
 }
+// the same of two values, both parts in one quad
+__device__ __forceinline__ h4v split2_rne(float x0, float x1, float neg1) {
+    const f2v p = {x0, x1};
+    const h2v a = __builtin_convertvector(p, h2v);
+    const f2v r = {__builtin_fmaf((float)a[0], neg1, x0), __builtin_fmaf((float)a[1], neg1, x1)};
+    const h2v b = __builtin_convertvector(r, h2v);
+    return (h4v){a[0], a[1], b[0], b[1]};
+}
+__device__ __forceinline__ h4v split2_rtz(float x0, float x1, float neg1) {
+    const auto a = __builtin_amdgcn_cvt_pkrtz(x0, x1);
+    const auto b = __builtin_amdgcn_cvt_pkrtz(__builtin_fmaf((float)a[0], neg1, x0), __builtin_fmaf((float)a[1], neg1, x1));
+    return (h4v){(_Float16)a[0], (_Float16)a[1], (_Float16)b[0], (_Float16)b[1]};
+}
 __device__ __forceinline__ f32x4 sin4(f32x4 z) {
     return (f32x4){__builtin_amdgcn_sinf(z[0]), __builtin_amdgcn_sinf(z[1]), __builtin_amdgcn_sinf(z[2]), __builtin_amdgcn_sinf(z[3])};
 }
@@ -158,13 +186,29 @@ __device__ __forceinline__ f32x4 cos4(f32x4 z) {
     return (f32x4){__builtin_amdgcn_cosf(z[0]), __builtin_amdgcn_cosf(z[1]), __builtin_amdgcn_cosf(z[2]), __builtin_amdgcn_cosf(z[3])};
 }
 
+// A quad of tile t: the sines, split; the error, split
+template <class S> __device__ __forceinline__ void sine_split(f32x4 z, int t, float neg1, h4v &hi, h4v &lo) {
+    if (S::mixed(t)) hi = lo = split2_rne(__builtin_amdgcn_sinf(z[0]), __builtin_amdgcn_sinf(z[1]), neg1);
+    else split_rne(sin4(z), neg1, hi, lo);
+}
+template <class S> __device__ __forceinline__ void error_split(f32x4 e, int t, float neg1, h4v &hi, h4v &lo) {
+    if (S::mixed(t)) hi = lo = split2_rtz(e[0], e[1], neg1);
+    else split_rtz(e, neg1, hi, lo);
+}
+
 // Entry (row r, contraction index k) of an operand matrix whose planes have `plane` bytes, as a hi/lo pair
-template <int WP> __device__ __forceinline__ void put_operand(char *m, uint32_t plane, int r, int k, float w) {
-    typedef Shape<WP> S;
+template <int WP, bool HALF> __device__ __forceinline__ void put_operand(char *m, uint32_t plane, int r, int k, float w) {
+    typedef Shape<WP, HALF> S;
     const _Float16 h = (_Float16)w, l = (_Float16)(w - (float)h);
-    const int t = k >> 4, q = (k >> 2) & 3;
+    const int t = k >> 4;
+    if (HALF) k = S::row(k);
+    const int q = (k >> 2) & 3;
     const uint32_t at = (uint32_t)r * 64 + 16 * (q ^ ((r >> 1) & 2)) + 2 * (k & 3);
-    if (S::TAIL && t == S::MT - 1) {
+    if (HALF && t == S::MT - 1) {
+        _Float16 *p = (_Float16 *)(m + 2 * S::NP * plane + at);
+        p[0] = p[2] = h;
+        p[4] = l;
+    } else if (S::TAIL && t == S::MT - 1) {
         _Float16 *p = (_Float16 *)(m + 2 * S::NP * plane + at);
         p[0] = h;
         p[4] = l;
@@ -176,8 +220,8 @@ template <int WP> __device__ __forceinline__ void put_operand(char *m, uint32_t 
 }
 
 // The operand words of R row tiles of a matrix, all planes: this lane's word of each row tile is at `m` + 1024 t
-template <int WP, int R> struct Words {
-    typedef Shape<WP> S;
+template <int WP, bool HALF, int R> struct Words {
+    typedef Shape<WP, HALF> S;
     h8v w[S::NPL][R];
     __device__ __forceinline__ void load(const char *m, uint32_t plane) {
 #pragma unroll
@@ -191,7 +235,7 @@ template <int WP, int R> struct Words {
         const bool tail = k == S::NP;
         const int p = 2 * k, b0 = 2 * k, b1 = tail ? b0 : b0 + 1;
 #pragma unroll
-        for (int term = 0; term < (tail ? 2 : 3); ++term)
+        for (int term = 0; term < (tail ? (HALF ? 1 : 2) : 3); ++term)
 #pragma unroll
             for (int t = 0; t < R; ++t)
 #pragma unroll
@@ -211,8 +255,8 @@ template <int WP, int R> struct Words {
     } while (0)
 
 // Weights and tables of image `img` into LDS.  Returns whether some layer's factor of the error is below 1 (the same in every lane).
-template <int WP, int L> __device__ __forceinline__ bool fit16_set_up(const FitArgs &a, char *lds, size_t img, int wave) {
-    typedef Shape<WP> S;
+template <int WP, bool HALF, int L> __device__ __forceinline__ bool fit16_set_up(const FitArgs &a, char *lds, size_t img, int wave) {
+    typedef Shape<WP, HALF> S;
     constexpr int MT = S::MT;
     Misc *const misc = (Misc *)(lds + S::MISC);
     const int tid = threadIdx.x;
@@ -252,17 +296,17 @@ template <int WP, int L> __device__ __forceinline__ bool fit16_set_up(const FitA
                 if (l == 0) {
                     ((float *)(lds + S::W0))[o * 4 + i] = w;
                 } else if (last) {
-                    put_operand<WP>(lds + S::LASTF, 16 * 64, 4 * o, i, w);
-                    put_operand<16>(lds + S::LASTT, S::PLANE, i, 4 * o, w);
+                    put_operand<WP, HALF>(lds + S::LASTF, 16 * 64, 4 * o, i, w);
+                    put_operand<16, false>(lds + S::LASTT, S::PLANE, S::row(i), 4 * o, w);
                 } else {
-                    put_operand<WP>(F, S::PLANE, o, i, w);
-                    put_operand<WP>(F + S::HID, S::PLANE, i, o, w);
+                    put_operand<WP, HALF>(F, S::PLANE, S::row(o), i, w);
+                    put_operand<WP, HALF>(F + S::HID, S::PLANE, S::row(i), o, w);
                 }
             }
             cur[k] = next[k];
         }
         if (tid < dout) {
-            float *const B = (float *)(lds + S::BIAS) + (last ? 4 * tid : 16 + (l - 1) * WP + tid);
+            float *const B = (float *)(lds + S::BIAS) + (last ? 4 * tid : 16 + (l - 1) * WP + S::row(tid));
             *(l == 0 ? (float *)(lds + S::W0) + tid * 4 + 2 : B) = bias * sc;
         }
         for (int off = 32; off > 0; off >>= 1) ss += __shfl_xor(ss, off, 64);
@@ -317,8 +361,8 @@ template <int WP, int L> __device__ __forceinline__ bool fit16_set_up(const FitA
 // 224 x 224, 10 x 32: 6.98 -> 6.00; 512 of 96 x 96, 5 x 24: 0.532 -> 0.457; 64 of 128 x 128, 6 x 64: 0.500 -> 0.450.  Forcing one
 // matrix step per two to four vector instructions backward (scheduling groups) was slower: 7.8 ms at 10 x 40.
 // kBelow: some layer's factor of the error is below 1 and is applied here, on the cosine (see the file header).
-template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fit16_pixels(const FitArgs &a, char *lds, const FitShare &share, int wave) {
-    typedef Shape<WP> S;
+template <int WP, bool HALF, int L, int NT, bool kBelow> __device__ __forceinline__ void fit16_pixels(const FitArgs &a, char *lds, const FitShare &share, int wave) {
+    typedef Shape<WP, HALF> S;
     constexpr int MT = S::MT, NH = L - 2, kPC = kWaves * 16 * NT;
     constexpr int kColOut = 11, kColFirst = 12;         // columns of acc_b: step u's biases in column u, the output layer's, the first layer's bias, x and y
     const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
@@ -359,7 +403,7 @@ template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fi
         } else {
             const h8v x = cat(Xh[t], Xl[t]);
             hi = to_h4(mfma32(x, I0, zero4));
-            lo = to_h4(mfma32(x, I1, zero4));
+            lo = HALF ? hi : to_h4(mfma32(x, I1, zero4));      // (a half tile's quad holds both)
         }
     };
     auto turn1 = [&](h4v xh, h4v xl, h4v &hi, h4v &lo) {
@@ -381,7 +425,7 @@ template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fi
             for (int t = 0; t < MT; ++t) {
                 char *const p = put_at + area * (NT * S::INPUT) + (nt * MT + t) * 1024;
                 *(h4v *)p = Xh[nt][t];
-                *(h4v *)(p + 512) = Xl[nt][t];
+                if (!S::mixed(t)) *(h4v *)(p + 512) = Xl[nt][t];
             }
     };
     auto get = [&](int area, int nt, int t, int part) -> h4v {
@@ -431,14 +475,14 @@ template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fi
 #pragma unroll
             for (int t = 0; t < MT; ++t)
 #pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    const float4 w = ((const float4 *)(lds + S::W0))[16 * t + 4 * g + v];
+                for (int v = 0; v < (S::mixed(t) ? 2 : 4); ++v) {
+                    const float4 w = ((const float4 *)(lds + S::W0))[16 * t + (S::mixed(t) ? 2 : 4) * g + v];
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt) z[nt][t][v] = fmaf(w.x, x[nt], fmaf(w.y, y[nt], w.z));
                 }
         };
-        Words<WP, MT> W;
-        Words<WP, 1> WL;
+        Words<WP, HALF, MT> W;
+        Words<WP, HALF, 1> WL;
         f32x4 zo[NT][1];                   // output layer: channel g of pixel n in the first register of lane (n, g)
         // What the contraction into step u's layer, or the output layer, starts from: its operand words, and the biases
         auto begin = [&](int u) {
@@ -472,7 +516,7 @@ template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fi
 #pragma unroll
                 for (int t = 0; t < MT; ++t) {
                     if (NH == 0) zst[NH][nt][t] = z0[nt][t];
-                    split_rne(sin4(z0[nt][t]), neg1, Bh[nt][t], Bl[nt][t]);
+                    sine_split<S>(z0[nt][t], t, neg1, Bh[nt][t], Bl[nt][t]);
                 }
             if (kKept > 0) put(0, Bh, Bl);
             blocks(0, 0, kBlocks - 1);
@@ -485,7 +529,7 @@ template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fi
 #pragma unroll
             for (int t = 0; t < MT; ++t)
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) split_rne(sin4(zst[u + 1][nt][t]), neg1, Bh[nt][t], Bl[nt][t]);
+                for (int nt = 0; nt < NT; ++nt) sine_split<S>(zst[u + 1][nt][t], t, neg1, Bh[nt][t], Bl[nt][t]);
             if (u + 1 < kKept) put(u + 1, Bh, Bl);
             blocks(u + 1, 0, kBlocks - 1);
         }
@@ -499,18 +543,31 @@ template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fi
         // 6.00 ms a step); where registers are scarce, to the start of the next; and where they are scarcest (one kernel: padded width
         // 48, 10 layers), the contraction comes before the turning: nothing may be spilled there (see FIT16_EDGE), and the
         // faster order, 6.08 ms against 6.29, spills 20.  So it does in the rarer of the two forms, at every shape.
-        constexpr bool kLate = fit16_registers(WP, L, NT) > 480, kScarce = kBelow || fit16_registers(WP, L, NT) > 500;
+        constexpr bool kLate = fit16_registers(WP, L, NT) > 480, kScarce = kBelow || (!HALF && fit16_registers(WP, L, NT) > 500);
         auto slope = [&](f32x4 z, int l) { return kBelow ? cos4(z) * fminf(misc->scale[l], 1.0f) : cos4(z); };
-        auto leave = [&](int nt, int t, f32x4 e) {
-            E[nt][t] = e;
-            if (!kLate) split_rtz(e, neg1, Eh[nt][t], El[nt][t]);
+        auto leave = [&](int nt, int t, f32x4 e, f32x4 z, int l) {
+            if (HALF) {
+                f32x4 c = zero4;
+                if (S::mixed(t)) {
+                    c[0] = __builtin_amdgcn_cosf(z[0]);
+                    c[1] = __builtin_amdgcn_cosf(z[1]);
+                } else {
+                    c = cos4(z);
+                }
+                if (kBelow) c *= fminf(misc->scale[l], 1.0f);
+#pragma unroll
+                for (int v = 0; v < (S::mixed(t) ? 2 : 4); ++v) E[nt][t][v] = e[v] * c[v];
+            } else {
+                E[nt][t] = e * slope(z, l);
+            }
+            if (!kLate) error_split<S>(E[nt][t], t, neg1, Eh[nt][t], El[nt][t]);
         };
         auto take = [&] {
             if (kLate)
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                    for (int t = 0; t < MT; ++t) split_rtz(E[nt][t], neg1, Eh[nt][t], El[nt][t]);
+                    for (int t = 0; t < MT; ++t) error_split<S>(E[nt][t], t, neg1, Eh[nt][t], El[nt][t]);
         };
         {
             FIT16_EDGE;
@@ -543,13 +600,13 @@ template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fi
                 for (int nt = 0; nt < NT; ++nt) turn(Bh[nt], Bl[nt], i, uh[nt], ul[nt]);
                 const h8v b0 = cat(uh[0], uh[NT - 1]), b1 = cat(ul[0], ul[NT - 1]);
                 acc_last[i] = mfma32(A0, b0, acc_last[i]);
-                acc_last[i] = mfma32(A0, b1, acc_last[i]);
+                if (!S::mixed(i)) acc_last[i] = mfma32(A0, b1, acc_last[i]);
                 if (NT == 2) acc_last[i] = mfma32(A1, b0, acc_last[i]);
             }
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                for (int t = 0; t < MT; ++t) leave(nt, t, E[nt][t] * slope(zst[NH][nt][t], L - 1));
+                for (int t = 0; t < MT; ++t) leave(nt, t, E[nt][t], zst[NH][nt][t], L - 1);
         }
 
         // ---- backward: the error goes down through the hidden layers, each layer's weight gradient takes these pixels
@@ -562,6 +619,7 @@ template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fi
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) {
                     if (!kTurned) turn(Eh[nt], El[nt], t, uh[nt], ul[nt]);
+                    else if (S::mixed(t)) uh[nt] = ul[nt] = get(kKept, nt, t, 0);
                     else { uh[nt] = get(kKept, nt, t, 0); ul[nt] = get(kKept, nt, t, 1); }
                 }
                 A0[t] = cat(uh[0], NT == 2 ? uh[NT - 1] : ul[0]);
@@ -581,7 +639,7 @@ template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fi
             auto contract = [&] {
 #pragma unroll
                 for (int t = 0; t < MT; ++t) {
-                    Words<WP, 1> V;
+                    Words<WP, HALF, 1> V;
                     V.load(step(u, c, S::HID + t * 1024), S::PLANE);
                     f32x4 d[NT][1];
 #pragma unroll
@@ -598,13 +656,13 @@ template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fi
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                    for (int t = 0; t < MT; ++t) split_rne(sin4(zst[u][nt][t]), neg1, Hh[nt][t], Hl[nt][t]);
+                    for (int t = 0; t < MT; ++t) sine_split<S>(zst[u][nt][t], t, neg1, Hh[nt][t], Hl[nt][t]);
             if (!kScarce) contract();
             const h8v ones = column(u, c);
 #pragma unroll
             for (int t = 0; t < MT; ++t) {
                 acc_b[t] = mfma32(A0[t], ones, acc_b[t]);
-                if (NT == 2) acc_b[t] = mfma32(A1[t], ones, acc_b[t]);
+                if (NT == 2 && !S::mixed(t)) acc_b[t] = mfma32(A1[t], ones, acc_b[t]);
             }
 #pragma unroll
             for (int i = 0; i < MT; ++i) {
@@ -612,21 +670,22 @@ template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fi
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) {
                     if (u >= kKept) turn(Hh[nt], Hl[nt], i, uh[nt], ul[nt]);
+                    else if (S::mixed(i)) uh[nt] = ul[nt] = get(u, nt, i, 0);
                     else { uh[nt] = get(u, nt, i, 0); ul[nt] = get(u, nt, i, 1); }
                 }
                 const h8v b0 = cat(uh[0], uh[NT - 1]), b1 = cat(ul[0], ul[NT - 1]);
 #pragma unroll
                 for (int t = 0; t < MT; ++t) {
                     acc[u][t][i] = mfma32(A0[t], b0, acc[u][t][i]);
-                    acc[u][t][i] = mfma32(A0[t], b1, acc[u][t][i]);
-                    if (NT == 2) acc[u][t][i] = mfma32(A1[t], b0, acc[u][t][i]);
+                    if (!S::mixed(i)) acc[u][t][i] = mfma32(A0[t], b1, acc[u][t][i]);
+                    if (NT == 2 && !S::mixed(t)) acc[u][t][i] = mfma32(A1[t], b0, acc[u][t][i]);
                 }
             }
             // E_{l-1} = r (W_l^T E_l) cos(2 pi z_{l-1})
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
-                for (int t = 0; t < MT; ++t) leave(nt, t, down[nt][t] * slope(zst[u][nt][t], u + 1));
+                for (int t = 0; t < MT; ++t) leave(nt, t, down[nt][t], zst[u][nt][t], u + 1);
         }
         // ---- first layer: its input's columns are one, x, y
         {
@@ -645,7 +704,7 @@ template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fi
             for (int t = 0; t < MT; ++t) {
                 acc_b[t] = mfma32(A0[t], b0, acc_b[t]);
                 acc_b[t] = mfma32(A0[t], b1, acc_b[t]);
-                if (NT == 2) acc_b[t] = mfma32(A1[t], b0, acc_b[t]);
+                if (NT == 2 && !S::mixed(t)) acc_b[t] = mfma32(A1[t], b0, acc_b[t]);
             }
         }
     }
@@ -693,11 +752,24 @@ template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fi
                     col = h % MT * 16 + n;
                 }
                 const int din = misc->d[l], dout = misc->d[l + 1], off = misc->p_off[l];
+                float gs = misc->grad[l];
+                // a half tile's hi and lo parts: columns n and n + 2, rows v and v + 2; those rows came in twice where a step has 16 pixels
+                if (HALF && at >= MT && (at < 2 * MT ? at - MT : h % MT) == MT - 1) {
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) s[v] += __shfl_xor(s[v], 2, 64);
+                    col = (n & 2) ? -1 : (MT - 1) * 16 + 2 * (n >> 2) + (n & 1);
+                }
+                const bool half_rows = HALF && (at < MT || at >= 2 * MT) && l < L - 1 && ot == MT - 1;
+                if (half_rows) {
+                    s[0] += s[2];
+                    s[1] += s[3];
+                    gs *= NT == 1 ? 0.5f : 1.0f;
+                }
                 if (at >= MT && col >= din) col = -1;
-                const float gs = misc->grad[l];
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    const int row = ot * 16 + 4 * g + v, o = l == L - 1 ? (ot == 0 && v == 0 ? g : dout) : row;
+                    if (half_rows && v >= 2) continue;
+                    const int row = ot * 16 + (half_rows ? 2 : 4) * g + v, o = l == L - 1 ? (ot == 0 && v == 0 ? g : dout) : row;
                     if (col >= 0 && o < dout) fit_put_grad(a, share, off + (col == din ? dout * din + o : o * din + col), s[v] * gs);
                 }
             }
@@ -706,14 +778,14 @@ template <int WP, int L, int NT, bool kBelow> __device__ __forceinline__ void fi
     }
 }
 
-template <int WP, int L, int NT>
+template <int WP, bool HALF, int L, int NT>
 __global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, L, NT)) void fit16_step_kernel(const FitArgs a) {
     extern __shared__ __attribute__((aligned(16))) char lds16[];
     const uint32_t pixels = kWaves * 16 * NT;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const FitShare share = fit_share(a, (a.HW + pixels - 1) / pixels);
-    if (!fit16_set_up<WP, L>(a, lds16, share.img, wave)) fit16_pixels<WP, L, NT, false>(a, lds16, share, wave);
-    else fit16_pixels<WP, L, NT, true>(a, lds16, share, wave);
+    if (!fit16_set_up<WP, HALF, L>(a, lds16, share.img, wave)) fit16_pixels<WP, HALF, L, NT, false>(a, lds16, share, wave);
+    else fit16_pixels<WP, HALF, L, NT, true>(a, lds16, share, wave);
 }
 
 }  // namespace fit16
