@@ -65,6 +65,13 @@ template <int TM, int WP, int WQ> ClassImpl make_impl() {
                      (uint32_t)XLayout<XTM, WQ, false>::TABLE};
 }
 
+// Streamed layers in a store of several classes: the bodies of the one grid's kernel
+decode_fn xdl_stream_any_fn(bool ints, bool act16, bool all16) {
+    if (all16) return decode_xdl_stream_any_kernel<kHiddenMixed | kAct16 | kWeight16>;
+    if (act16) return decode_xdl_stream_any_kernel<kHiddenMixed | kAct16>;
+    return ints ? decode_xdl_stream_any_kernel<kHiddenAllInt> : decode_xdl_stream_any_kernel<kHiddenMixed>;
+}
+
 const void *xdl_any_fn(int kind, bool act16 = false, bool all16 = false) {
     if (all16) return (const void *)decode_xdl_any_kernel<kThreads, kAct16 | kWeight16>;
     if (act16) {
@@ -111,7 +118,19 @@ double even_slots_us(double n_slots, uint32_t chunks, uint32_t tpc, uint32_t nw,
     const double work = per_cu * (tpc * tile_us / 4.0 + 0.13 * tile_us + 0.3);
     return work / std::max(rate, 0.25) + (0.26 * tile_us + 1.0) * (at_once < 1.5 ? per_cu : 1.0);
 }
-Plan plan_chunks(double n_slots, uint32_t tiles, uint32_t nw, int n_cu, int resident, double tile_us, int blocks_per_cu, bool even) {
+// Slots of unequal cost in the split-precision kernels, heaviest first where `ordered`: while every workgroup has a place at once, the
+// heaviest model's decides, and what shares its CU; else the work there is and a part of the heaviest workgroup for the end.  Against
+// 17 ragged batches of 4 to 4000 images of 16 x 16 to 700 x 700 with up to 32 workgroups per CU it picks the best split or one within 5 %.  With
+// a workgroup per image where the other model left them, 256 images of 160 x 160 took 418 us (now 245), 64 of 300 x 300 373 (205).
+double uneven_slots_us(double n_slots, uint32_t chunks, uint32_t tpc, int n_cu, int resident, double tile_us, double heavy_us, bool ordered) {
+    const double own_us = 1.8, blocks = n_slots * chunks;             // what a workgroup costs its CU beside its tiles
+    const double mean = tpc * tile_us / 4.0 + own_us, heavy = tpc * heavy_us / 4.0 + own_us;
+    if (blocks <= n_cu) return heavy;
+    if (blocks <= (double)n_cu * resident) return ordered ? heavy + mean * (blocks / n_cu - 1.0) : heavy * resident;     // unordered: two heavy ones may meet
+    return mean * blocks / n_cu + (ordered ? 0.15 : 0.6) * heavy;
+}
+enum { kEven = 0, kUneven = 1, kUnevenOrdered = 2, kUnevenFp32 = 3 };       // how a plan's time is reckoned
+Plan plan_chunks(double n_slots, uint32_t tiles, uint32_t nw, int n_cu, int resident, double tile_us, double heavy_us, int blocks_per_cu, int how) {
     const double expand_us = 15.0;
     if (n_slots < 1.0) n_slots = 1.0;
     Plan best{1, ((tiles + nw - 1) / nw) * nw};
@@ -129,9 +148,10 @@ Plan plan_chunks(double n_slots, uint32_t tiles, uint32_t nw, int n_cu, int resi
         if (tpc == last_tpc) { if (tpc <= nw) break; continue; }
         last_tpc = tpc;
         const uint32_t cc = (tiles + tpc - 1) / tpc;
-        if (even) {
-            const double t = even_slots_us(n_slots, cc, tpc, nw, n_cu, resident, tile_us);
-            if (t < best_t * 0.98) { best_t = t; best = Plan{cc, tpc}; }
+        if (how != kUnevenFp32) {
+            const double t = how == kEven ? even_slots_us(n_slots, cc, tpc, nw, n_cu, resident, tile_us)
+                                          : uneven_slots_us(n_slots, cc, tpc, n_cu, resident, tile_us, heavy_us, how == kUnevenOrdered);
+            if (t < best_t * (how == kEven ? 0.98 : 0.99)) { best_t = t; best = Plan{cc, tpc}; }
             if (tpc <= nw) break;
             continue;
         }
@@ -192,6 +212,8 @@ struct rinr_store {
     std::vector<IndexEntry> index;            // host copy of the index (debug export, diagnostics)
     double class_tile_us[kMaxClass + 1];      // modelled time of one 64-pixel tile on one SIMD
     double class_tile_us_xdl[kMaxClass + 1];
+    double heavy_tile_us_xdl;                 // ... of the heaviest model
+    bool two_of_512[3];                       // two workgroups of 512 threads of the all-class kernel fit a CU: default, fp16 activations, all fp16
     bool xdl_ok;                              // every operand fits fp16 range after pre-scaling
     int hidden_kind;                          // kHiddenAllInt / AllRaw / Mixed over all hidden layers of all models
     bool narrow[kMaxClass + 1];               // no model of the class is wider than 8 less than its padded width
@@ -263,7 +285,7 @@ extern "C" int rinr_store_open_ex(const void *device_blob, const void *host_blob
     {   // split-precision kernels: kinds of hidden layer, fp16 range of every operand they would build
         const uint8_t *hb = (const uint8_t *)host_blob;
         const float pre = (float)((double)sum.header.w0 / (2.0 * M_PI));
-        double acts[kMaxClass + 1] = {0, 0, 0, 0, 0};
+        double acts[kMaxClass + 1] = {0, 0, 0, 0, 0}, most = 0.0;
         s->xdl_ok = std::fabs(sum.header.coord_lo) < 60000.0f && std::fabs(sum.header.coord_hi) < 60000.0f;   // coordinates travel as fp16 hi+lo
         int64_t tot_int = 0, tot_raw = 0;
         for (const IndexEntry &e : s->index) {
@@ -286,6 +308,7 @@ extern "C" int rinr_store_open_ex(const void *device_blob, const void *host_blob
                 if (!(wmax * std::fabs(k) < 60000.0f)) s->xdl_ok = false;
             }
             acts[c] += (e.n_layers - 1) * 16.0 * c;
+            most = std::max(most, (e.n_layers - 1) * 16.0 * c);
         }
         s->hidden_kind = tot_raw == 0 ? kHiddenAllInt : (tot_int == 0 ? kHiddenAllRaw : kHiddenMixed);
         for (uint32_t c = 1; c <= kMaxClass; ++c) {
@@ -293,6 +316,7 @@ extern "C" int rinr_store_open_ex(const void *device_blob, const void *host_blob
             const double mean = sum.class_count[c] ? acts[c] / (double)sum.class_count[c] : 0.0;
             s->class_tile_us_xdl[c] = (mean * 20.0 + 600.0) / 2400.0;
         }
+        s->heavy_tile_us_xdl = (most * 20.0 + 600.0) / 2400.0;
         store_error_bounds(host_blob, sum, s->bounds);
     }
     // which models each kernel family decodes from a resident copy, and the LDS that takes
@@ -330,9 +354,18 @@ extern "C" int rinr_store_open_ex(const void *device_blob, const void *host_blob
     ok = ok && allow_full_lds(xdl_any_fn(kHiddenAllInt)) && allow_full_lds(xdl_any_fn(kHiddenAllRaw)) &&
          allow_full_lds(xdl_any_fn(kHiddenMixed)) && allow_full_lds(xdl_any_fn(kHiddenAllInt, true)) &&
          allow_full_lds(xdl_any_fn(kHiddenAllRaw, true)) && allow_full_lds(xdl_any_fn(kHiddenMixed, true)) &&
-         allow_full_lds(xdl_any_fn(0, true, true)) && allow_full_lds((const void *)decode_any_kernel<16, kThreads>) &&
+         allow_full_lds(xdl_any_fn(0, true, true)) && allow_full_lds((const void *)xdl_stream_any_fn(true, false, false)) &&
+         allow_full_lds((const void *)xdl_stream_any_fn(false, false, false)) && allow_full_lds((const void *)xdl_stream_any_fn(false, true, false)) &&
+         allow_full_lds((const void *)xdl_stream_any_fn(false, true, true)) && allow_full_lds((const void *)decode_any_kernel<16, kThreads>) &&
          allow_full_lds((const void *)decode_any_kernel<32, kThreads>);
     if (!ok) { delete s; return RINR_E_HIP; }
+    for (int m = 0; m < 3; ++m) {
+        uint32_t lds_bytes = 16;
+        for (uint32_t c = 1; c <= kMaxClass; ++c) lds_bytes = std::max(lds_bytes, s->res_lds[m == 2 ? kSizeXdl16 : kSizeXdl][c]);
+        int resident = 0;
+        s->two_of_512[m] = !hip_fail(hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, xdl_any_fn(s->hidden_kind, m == 1, m == 2), 512, lds_bytes)) &&
+                           resident >= 2;
+    }
     if (hip_fail(hipGetDevice(&s->device))) { delete s; return RINR_E_HIP; }
     if (int rc = scratch_for_device(s->device, &s->scratch)) { delete s; return rc; }
     hipDeviceProp_t prop;
@@ -459,13 +492,6 @@ extern "C" int rinr_decode_batch_ex(rinr_store *s, const int64_t *image_ids, int
     a.fit_form = s->fit_form[z];
 
     const uint32_t tiles = (uint32_t)((HW + 63) >> 6);
-    // by tiles, and the smaller workgroups where the others would not give half the CUs one (one image of 224 x 224, 9 x 40: 24.4 -> 19.1 us)
-    const uint32_t full = tiles >= 96 ? 768 : (tiles >= 64 ? 512 : 256);
-    const bool few = (int64_t)n * ((tiles + full / 64 - 1) / (full / 64)) * 2 <= s->n_cu;
-    const int threads = opts->launch_threads ? opts->launch_threads : (int)(few ? 256 : full);
-    const uint32_t nw = (uint32_t)threads / 64;
-    const int64_t any_min_tiles = opts->one_grid_min_tiles ? opts->one_grid_min_tiles : 64;
-
     int n_classes = 0;
     uint64_t any_streamed = 0, any_resident = 0;
     for (uint32_t c = 1; c <= kMaxClass; ++c) {
@@ -473,15 +499,24 @@ extern "C" int rinr_decode_batch_ex(rinr_store *s, const int64_t *image_ids, int
         any_streamed += s->n_str[z][c];
         any_resident += s->n_res[z][c];
     }
-    // a store that mixes width classes: one grid whose workgroups run the body of their slot's class, or, for images of
-    // few tiles, one launch per class with that class's LDS size (workgroups of other classes return at once)
-    // (an empty store also takes the one grid: every id is out of range and its slot is zero-filled)
+    // a store that mixes width classes: one grid whose workgroups run the body of their slot's class, in two workgroups of 512 threads a
+    // CU where they fit (us, class by class in workgroups by tiles -> so: 4000 ragged images of 32 x 32 216 -> 187, of 16 x 16 100 -> 88, 500
+    // of 32 x 32 80 -> 38).  The fp32 kernels take images of few tiles class by class, with that class's LDS size (workgroups of other
+    // classes return at once).  An empty store also takes the one grid: every id is out of range and its slot is zero-filled.
+    const int64_t any_min_tiles = opts->one_grid_min_tiles ? opts->one_grid_min_tiles : (xdl ? 1 : 64);
     const bool one_grid = n_classes == 0 || (n_classes > 1 && (int64_t)tiles >= any_min_tiles);
-    const int knob = opts->launch_blocks_per_cu * 16 + family + (one_grid ? 8 : 0);
-    const bool replan = !(s->plan_hw == HW && s->plan_n == n && s->plan_threads == threads && s->plan_knob == knob);
-
     // slots of unequal cost are taken heaviest first when the caller gives the scratch for the order
     const bool order = opts->workspace && !s->even_cost;
+    // threads by tiles, and the smaller workgroups where the others would not give half the CUs one (one image of 224 x 224, 9 x 40: 24.4 -> 19.1 us)
+    const uint32_t full = tiles >= 96 ? 768 : (tiles >= 64 ? 512 : 256);
+    const bool few = (int64_t)n * ((tiles + full / 64 - 1) / (full / 64)) * 2 <= s->n_cu;
+    const bool pairs = one_grid && xdl && s->two_of_512[all16 ? 2 : (act16 ? 1 : 0)];
+    const int threads = opts->launch_threads ? opts->launch_threads : (int)(pairs ? 512 : (few ? 256 : full));
+    const uint32_t nw = (uint32_t)threads / 64;
+    const int how = s->even_cost ? kEven : (!xdl ? kUnevenFp32 : (order ? kUnevenOrdered : kUneven));
+    const int knob = opts->launch_blocks_per_cu * 16 + family + (one_grid ? 8 : 0) + (order ? 4 : 0);
+    const bool replan = !(s->plan_hw == HW && s->plan_n == n && s->plan_threads == threads && s->plan_knob == knob);
+
     if (order) a.order = (const uint32_t *)opts->workspace;
     int launches = 0;
     bool ordered = false;
@@ -513,7 +548,7 @@ extern "C" int rinr_decode_batch_ex(rinr_store *s, const int64_t *image_ids, int
             int resident = 1;
             if (hip_fail(hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, fn, threads, lds_bytes)) || resident < 1)
                 resident = 1;
-            s->plan[0] = plan_chunks((double)n, tiles, nw, s->n_cu, resident, tile_us, opts->launch_blocks_per_cu, false);
+            s->plan[0] = plan_chunks((double)n, tiles, nw, s->n_cu, resident, tile_us, s->heavy_tile_us_xdl, opts->launch_blocks_per_cu, how == kEven ? kUnevenFp32 : how);
         }
         const Plan pl = s->plan[0];
         if ((uint64_t)n * pl.chunks > 0x7FFFFFFFull) return RINR_E_SIZE;
@@ -539,7 +574,7 @@ extern "C" int rinr_decode_batch_ex(rinr_store *s, const int64_t *image_ids, int
                                                                           threads, lds_bytes)) || resident < 1)
                     resident = 1;
                 s->plan[c] = plan_chunks((double)n, tiles, nw, s->n_cu, resident, xdl ? s->class_tile_us_xdl[c] : s->class_tile_us[c],
-                                         opts->launch_blocks_per_cu, s->even_cost);
+                                         s->heavy_tile_us_xdl, opts->launch_blocks_per_cu, how);
             }
             const Plan pl = s->plan[c];
             if ((uint64_t)n * pl.chunks > 0x7FFFFFFFull) return RINR_E_SIZE;
@@ -574,7 +609,7 @@ extern "C" int rinr_decode_batch_ex(rinr_store *s, const int64_t *image_ids, int
             a.cls = c;
             a.lds_bytes = lds_bytes;
             if (int rc = before_launch()) return rc;
-            hipLaunchKernelGGL(xdl ? im.stream_xdl[all16 ? 2 : (act16 ? 1 : (ints ? 3 : 0))] : im.stream, dim3((uint32_t)n * a.chunks),
+            hipLaunchKernelGGL(!xdl ? im.stream : (n_classes > 1 ? xdl_stream_any_fn(ints, act16, all16) : im.stream_xdl[all16 ? 2 : (act16 ? 1 : (ints ? 3 : 0))]), dim3((uint32_t)n * a.chunks),
                                dim3((uint32_t)kStreamThreads), lds_bytes, (hipStream_t)stream, a);
             RINR_HIP(hipGetLastError());
             ++launches;

@@ -986,8 +986,8 @@ __global__ __launch_bounds__(NTHREADS) void decode_xdl_any_kernel(const DecodeAr
         case 4: xdl_body<xdl_tile_rows(32, MODE), 32, MODE>(a, w, lds_f); break;
         case 5: xdl_body<xdl_tile_rows(40, MODE), 40, MODE>(a, w, lds_f); break;
         case 6: xdl_body<xdl_tile_rows(48, MODE), 48, MODE>(a, w, lds_f); break;
-        case 7: xdl_body<32, 56, MODE>(a, w, lds_f); break;     // 32-row tiles: measured faster here, slower in the one-class kernel;
-        default: xdl_body<32, 64, MODE>(a, w, lds_f); break;    // the layout is smaller than the 16-row one the host sizes LDS for
+        case 7: xdl_body<32, 56, MODE>(a, w, lds_f); break;     // 32-row tiles: 122 registers leave room for 16 wavefronts a CU; with 16-row
+        default: xdl_body<32, 64, MODE>(a, w, lds_f); break;    // ones 64 ragged images of 300 x 300 take 236 us instead of 209
     }
 }
 
@@ -999,6 +999,24 @@ __global__ __launch_bounds__(kStreamThreads) void decode_xdl_stream_kernel(const
     Work w;
     if (!decode_prologue(a, w)) return;
     xdl_stream_body<xdl_tile_rows(WQ, MODE), WQ, MODE>(a, w, lds_f);
+}
+
+// ... in a store of several width classes: the bodies of the all-class kernel, for the same bytes (a launch still serves one class)
+template <int MODE>
+__global__ __launch_bounds__(kStreamThreads) void decode_xdl_stream_any_kernel(const DecodeArgs a) {
+    extern __shared__ __attribute__((aligned(16))) float lds_f[];
+    Work w;
+    if (!decode_prologue(a, w)) return;
+    switch ((w.e.width + 7u) >> 3) {
+        case 0: case 1: xdl_stream_body<xdl_tile_rows(8, MODE), 8, MODE>(a, w, lds_f); break;
+        case 2: xdl_stream_body<xdl_tile_rows(16, MODE), 16, MODE>(a, w, lds_f); break;
+        case 3: xdl_stream_body<xdl_tile_rows(24, MODE), 24, MODE>(a, w, lds_f); break;
+        case 4: xdl_stream_body<xdl_tile_rows(32, MODE), 32, MODE>(a, w, lds_f); break;
+        case 5: xdl_stream_body<xdl_tile_rows(40, MODE), 40, MODE>(a, w, lds_f); break;
+        case 6: xdl_stream_body<xdl_tile_rows(48, MODE), 48, MODE>(a, w, lds_f); break;
+        case 7: xdl_stream_body<32, 56, MODE>(a, w, lds_f); break;
+        default: xdl_stream_body<32, 64, MODE>(a, w, lds_f); break;
+    }
 }
 
 // ---- debug export of the split-precision operand blocks (see rinr_debug_dequant_split) ----------------------------
