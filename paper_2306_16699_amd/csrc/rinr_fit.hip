@@ -648,29 +648,51 @@ extern "C" int rinr_fit_destroy(rinr_fit *f) {
 extern "C" int64_t rinr_fit_n_params(const rinr_fit *f) { return f ? f->n_params : -1; }
 
 namespace {
-// masked parameters are zero: done on the host copy before upload, or by a download/upload round trip
-int apply_keep_to_device_params(rinr_fit *f, const uint8_t *keep_host) {
-    const size_t np = (size_t)f->n_images * (size_t)f->n_params;
-    if (np == 0) return RINR_OK;
-    std::vector<float> p;
-    try { p.resize(np); } catch (const std::bad_alloc &) { return RINR_E_SIZE; }
-    FIT_HIP(hipMemcpy(p.data(), f->params, np * 4, hipMemcpyDeviceToHost));
-    for (size_t i = 0; i < np; ++i)
-        if (!keep_host[i]) p[i] = 0.0f;
-    FIT_HIP(hipMemcpy(f->params, p.data(), np * 4, hipMemcpyHostToDevice));
+// Start of a fit or of a round of it: pruned parameters are zero (`keep`, may be null), the moments (`m`, `v`, may be null) and the
+// error's history are cleared.  One pass over the handle's state where there were three fills and, with a mask, a way to the host and
+// back for mask and parameters (8 images, 10 layers x 32, masked: 8 steps with their upload and read-back 1019 -> 942 us).
+__global__ __launch_bounds__(256) void fit_start_kernel(float *params, float *m, float *v, float *emag, const uint8_t *keep, int64_t np, int64_t n_images) {
+    const int64_t stride = (int64_t)gridDim.x * 256, first = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    const float4 none = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    for (int64_t q = first; q < np / 4; q += stride) {              // the arrays are whole allocations: aligned
+        if (m) {
+            ((float4 *)m)[q] = none;
+            ((float4 *)v)[q] = none;
+        }
+        if (keep) {
+            const uchar4 k = ((const uchar4 *)keep)[q];
+            float4 p = ((float4 *)params)[q];
+            p.x = k.x ? p.x : 0.0f;
+            p.y = k.y ? p.y : 0.0f;
+            p.z = k.z ? p.z : 0.0f;
+            p.w = k.w ? p.w : 0.0f;
+            ((float4 *)params)[q] = p;
+        }
+    }
+    for (int64_t i = np / 4 * 4 + first; i < np; i += stride) {
+        if (m) m[i] = v[i] = 0.0f;
+        if (keep && !keep[i]) params[i] = 0.0f;
+    }
+    for (int64_t i = first; i < n_images; i += stride) emag[i] = 0.0f;
+}
+// Complete when it returns, whatever stream the next call is given.
+int fit_start(rinr_fit *f, bool moments, bool mask) {
+    const int64_t np = f->n_images * f->n_params;
+    if (f->n_images == 0) return RINR_OK;
+    const uint32_t blocks = (uint32_t)std::min<int64_t>((np / 4 + 255) / 256 + 1, 2048);
+    hipLaunchKernelGGL(fit_start_kernel, dim3(blocks), dim3(256), 0, (hipStream_t) nullptr, f->params, moments ? f->m : nullptr,
+                       moments ? f->v : nullptr, f->emag, mask ? f->keep : nullptr, np, f->n_images);
+    FIT_HIP(hipGetLastError());
+    FIT_HIP(hipStreamSynchronize(nullptr));
     return RINR_OK;
 }
 }  // namespace
 
 extern "C" int rinr_fit_reset_optimizer(rinr_fit *f) {
     if (!f) return RINR_E_NULL;
-    const size_t np = (size_t)f->n_images * (size_t)f->n_params;
     FIT_HIP(hipDeviceSynchronize());
-    if (np) {
-        FIT_HIP(hipMemset(f->m, 0, np * 4));
-        FIT_HIP(hipMemset(f->v, 0, np * 4));
-    }
-    if (f->n_images) FIT_HIP(hipMemset(f->emag, 0, (size_t)f->n_images * 4));      // a new round: no error history
+    const int rc = fit_start(f, true, false);      // a new round: no moments, no error history
+    if (rc) return rc;
     f->t = 0;
     return RINR_OK;
 }
@@ -680,14 +702,9 @@ extern "C" int rinr_fit_set_params(rinr_fit *f, const float *params) {
     const size_t np = (size_t)f->n_images * (size_t)f->n_params;
     FIT_HIP(hipDeviceSynchronize());
     if (np) FIT_HIP(hipMemcpy(f->params, params, np * 4, hipMemcpyHostToDevice));
-    int rc = rinr_fit_reset_optimizer(f);
+    const int rc = fit_start(f, true, f->has_keep);
     if (rc) return rc;
-    if (f->has_keep && np) {
-        std::vector<uint8_t> k;
-        try { k.resize(np); } catch (const std::bad_alloc &) { return RINR_E_SIZE; }
-        FIT_HIP(hipMemcpy(k.data(), f->keep, np, hipMemcpyDeviceToHost));
-        return apply_keep_to_device_params(f, k.data());
-    }
+    f->t = 0;
     return RINR_OK;
 }
 
@@ -695,11 +712,9 @@ extern "C" int rinr_fit_set_keep(rinr_fit *f, const uint8_t *keep) {
     if (!f) return RINR_E_NULL;
     const size_t np = (size_t)f->n_images * (size_t)f->n_params;
     FIT_HIP(hipDeviceSynchronize());
-    if (f->n_images) FIT_HIP(hipMemset(f->emag, 0, (size_t)f->n_images * 4));
-    if (!keep) { f->has_keep = false; return RINR_OK; }
-    if (np) FIT_HIP(hipMemcpy(f->keep, keep, np, hipMemcpyHostToDevice));
-    f->has_keep = true;
-    return np ? apply_keep_to_device_params(f, keep) : RINR_OK;
+    if (np && keep) FIT_HIP(hipMemcpy(f->keep, keep, np, hipMemcpyHostToDevice));
+    f->has_keep = keep != nullptr;
+    return fit_start(f, false, f->has_keep);
 }
 
 extern "C" int rinr_fit_get_params(const rinr_fit *f, float *params, void *stream) {
