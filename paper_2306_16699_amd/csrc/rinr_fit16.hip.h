@@ -78,19 +78,20 @@ constexpr int fit16_waves_per_simd(int wp, int ml, int nt) {
 }
 
 // Shapes and the LDS layout (bytes) for hidden widths <= WP (a multiple of 16).
-// HALF (an odd number of tiles): the widths are at most WP - 8, so half of the last tile is padding.  A lane then holds two real units of it
+// HALF: the widths are at most WP - 8, so half of the last tile is padding.  A lane then holds two real units of it
 // instead of four (units 16 t + 2 g + v sit in rows 4 g + v, v < 2), which takes half the sines, cosines and splits, and the two
-// halfs of both go into one quad (h0 h1 l0 l1).  As an operand that quad twice meets (W0 W1 W0 W1 | w0 w1 0 0), w the weights' low parts: all three terms in one
-// matrix step instead of two.  Turned in one step, its rows are the units' hi and lo parts side by side, and the gradient tile
-// that it makes as either operand takes all terms likewise; the parts' rows and columns are added up at the end of the step.
+// halfs of both go into one quad (h0 h1 l0 l1).  As an operand that quad meets (W0 W1 W0 W1) and (w0 w1 0 0), w the weights' low parts: an odd last
+// tile has both side by side and takes all three terms in one matrix step instead of two; in a pair of tiles they are the halves of its two
+// planes.  Turned in one step instead of two, its rows are the units' hi and lo parts side by side, and a gradient tile that it makes as
+// either operand takes fewer steps likewise; the parts' rows and columns are added up at the end of the step.
 // A hidden layer of 40 units takes 52 matrix steps per 16 pixels instead of 63, and 10 sines instead of 12 each way.  us a step, before ->
-// now: 256 images of 224 x 224, 10 x 40: 6230 -> 5120; of 96 x 96, 3 x 40: 190 -> 166, 7 x 40: 709 -> 584; 1024 of 64 x 64, 3 x 8: 114 -> 79, 10 x 8: 394 ->
-// 244.  Against fp64 the gradient is as far off as before (10 x 40: 2.73e-6, 3 x 8: 7.8e-7).
+// now: 256 images of 224 x 224, 10 x 40: 6230 -> 5120; of 96 x 96, 3 x 40: 190 -> 166, 7 x 40: 709 -> 584, 4 x 56: 506 -> 467; 1024 of 64 x 64, 3 x 8: 114 -> 79,
+// 10 x 8: 394 -> 244; 512 of 96 x 96, 3 x 24: 237 -> 198, 6 x 24: 541 -> 502, 10 x 24: 1149 -> 968.  Against fp64 the gradient is as far off as before
+// (10 x 40: 2.73e-6, 10 x 24: 1.94e-6 and 1.92e-6, 3 x 8: 7.8e-7).
 template <int WP, bool HALF> struct Shape {
     static constexpr int MT = WP / 16;                  // 16-unit tiles of a hidden layer
     static constexpr int NP = MT / 2, TAIL = MT % 2;    // pairs of them, and an odd last one
     static constexpr int NPL = 2 * NP + TAIL;           // planes of one operand matrix
-    static_assert(!HALF || TAIL, "half tiles only where there is an odd one");
     static __device__ __forceinline__ bool mixed(int t) { return HALF && t == MT - 1; }          // tile t's quads hold hi and lo
     static __device__ __forceinline__ int row(int unit) {
         const int j = unit & 15;
@@ -188,12 +189,20 @@ __device__ __forceinline__ f32x4 cos4(f32x4 z) {
 
 // A quad of tile t: the sines, split; the error, split
 template <class S> __device__ __forceinline__ void sine_split(f32x4 z, int t, float neg1, h4v &hi, h4v &lo) {
-    if (S::mixed(t)) hi = lo = split2_rne(__builtin_amdgcn_sinf(z[0]), __builtin_amdgcn_sinf(z[1]), neg1);
-    else split_rne(sin4(z), neg1, hi, lo);
+    if (S::mixed(t)) {
+        hi = split2_rne(__builtin_amdgcn_sinf(z[0]), __builtin_amdgcn_sinf(z[1]), neg1);
+        lo = S::TAIL ? hi : (h4v)((_Float16)0.0f);              // in a pair, the second term's step takes nothing more of this tile
+    } else {
+        split_rne(sin4(z), neg1, hi, lo);
+    }
 }
 template <class S> __device__ __forceinline__ void error_split(f32x4 e, int t, float neg1, h4v &hi, h4v &lo) {
-    if (S::mixed(t)) hi = lo = split2_rtz(e[0], e[1], neg1);
-    else split_rtz(e, neg1, hi, lo);
+    if (S::mixed(t)) {
+        hi = split2_rtz(e[0], e[1], neg1);
+        lo = S::TAIL ? hi : (h4v)((_Float16)0.0f);
+    } else {
+        split_rtz(e, neg1, hi, lo);
+    }
 }
 
 // Entry (row r, contraction index k) of an operand matrix whose planes have `plane` bytes, as a hi/lo pair
@@ -205,9 +214,9 @@ template <int WP, bool HALF> __device__ __forceinline__ void put_operand(char *m
     const int q = (k >> 2) & 3;
     const uint32_t at = (uint32_t)r * 64 + 16 * (q ^ ((r >> 1) & 2)) + 2 * (k & 3);
     if (HALF && t == S::MT - 1) {
-        _Float16 *p = (_Float16 *)(m + 2 * S::NP * plane + at);
+        _Float16 *p = (_Float16 *)(m + (S::TAIL ? 2 * S::NP : 2 * (S::NP - 1)) * plane + at + (S::TAIL ? 0 : 8));
         p[0] = p[2] = h;
-        p[4] = l;
+        p[S::TAIL ? 4 : plane / 2] = l;             // beside them, or in the pair's plane of low parts
     } else if (S::TAIL && t == S::MT - 1) {
         _Float16 *p = (_Float16 *)(m + 2 * S::NP * plane + at);
         p[0] = h;
@@ -397,7 +406,9 @@ template <int WP, bool HALF, int L, int NT, bool kBelow> __device__ __forceinlin
     // P -> U: tile t of a hi/lo pair of quads.  An odd last tile's quads go side by side into one operand, of which either unit
     // matrix takes one half.
     auto turn = [&](const h4v (&Xh)[MT], const h4v (&Xl)[MT], int t, h4v &hi, h4v &lo) {
-        if (t < 2 * S::NP) {
+        if (HALF && !S::TAIL && t == MT - 1) {
+            hi = lo = to_h4(mfma32(cat(Xh[t & ~1], Xh[t | 1]), I1, zero4));
+        } else if (t < 2 * S::NP) {
             hi = to_h4(mfma32(cat(Xh[t & ~1], Xh[t | 1]), (t & 1) ? I1 : I0, zero4));
             lo = to_h4(mfma32(cat(Xl[t & ~1], Xl[t | 1]), (t & 1) ? I1 : I0, zero4));
         } else {

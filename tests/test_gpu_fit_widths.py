@@ -1,4 +1,4 @@
-"""Split-precision fit kernels of models that leave half of their last 16-unit tile empty (up to 8, and 33 to 40 units), and layers' inputs
+"""Split-precision fit kernels of models that leave half of their last 16-unit tile empty (widths 8 below a multiple of 16), and layers' inputs
 that wait in LDS, against the fp64 oracle: every depth there is a kernel for, widths at either end, ragged and masked models."""
 import numpy as np
 import pytest
@@ -32,24 +32,24 @@ def check(widths, n=2, H=9, W=15, keep=None, gain=1.0):
 
 @pytest.mark.parametrize("L", range(2, 13))
 def test_every_depth_of_half_filled_tiles(L):
-    for width in (8, 5, 1) + ((40, 33, 37) if L <= 10 else ()):
+    for width in (8, 5, 1, 24, 17, 21) + ((40, 33, 37) if L <= 10 else ()) + ((56, 49, 51) if L <= 6 else ()):
         check([2] + [width] * (L - 1) + [3])
 
 
-@pytest.mark.parametrize("widths", [[2, 40, 3, 40, 3], [2, 7, 39, 16, 3], [2, 33, 32, 31, 34, 3], [2, 1, 40, 3], [2, 8, 1, 7, 3], [2, 3, 8, 3]], ids=str)
+@pytest.mark.parametrize("widths", [[2, 40, 3, 40, 3], [2, 7, 39, 16, 3], [2, 33, 32, 31, 34, 3], [2, 1, 40, 3], [2, 8, 1, 7, 3], [2, 3, 8, 3], [2, 24, 5, 20, 3], [2, 56, 24, 50, 3], [2, 17, 16, 18, 3]], ids=str)
 @pytest.mark.parametrize("masked", [False, True])
 def test_layers_of_unequal_width(widths, masked):
     keep = keep_flags(np.random.default_rng(5), widths, 3, 0.6) if masked else None
     check(widths, n=3, H=17, W=13, keep=keep)
 
 
-@pytest.mark.parametrize("width,L", [(40, 3), (36, 5), (8, 4)])
+@pytest.mark.parametrize("width,L", [(40, 3), (36, 5), (8, 4), (24, 5), (56, 4)])
 def test_large_weights_take_the_form_that_scales_the_cosine(width, L):
     """A layer whose estimated gain is above 1.4 applies its factor of the error to the cosine: the second form of the kernels."""
     check([2] + [width] * (L - 1) + [3], gain=2.0)
 
 
-@pytest.mark.parametrize("width,L", [(15, 3), (16, 4), (12, 9), (24, 5), (32, 4), (30, 7), (46, 3), (40, 4), (8, 10)])
+@pytest.mark.parametrize("width,L", [(15, 3), (16, 4), (12, 9), (24, 5), (32, 4), (30, 7), (46, 3), (40, 4), (8, 10), (20, 6), (24, 8), (56, 3)])
 def test_many_chunks_of_pixels(width, L):
     """Layers' inputs wait in LDS from the forward to the backward pass: many chunks one after the other, the last one ragged."""
     check([2] + [width] * (L - 1) + [3], n=2, H=61, W=47)
