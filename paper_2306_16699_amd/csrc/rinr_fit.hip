@@ -536,6 +536,7 @@ struct rinr_fit {
     uint8_t *keep;            // null until set
     bool has_keep;
     int64_t t;                // Adam steps taken
+    int device;               // where all of it is
 };
 
 namespace {
@@ -581,6 +582,7 @@ extern "C" int rinr_fit_create_ex(const rinr_fit_arch *arch, int64_t n_images, i
     rinr_fit *f = new (std::nothrow) rinr_fit();
     if (!f) return RINR_E_SIZE;
     f->arch = *arch;
+    if (hip_fail(hipGetDevice(&f->device))) f->device = 0;       // no GPU: the allocations below say so
     f->n_images = n_images;
     f->H = H;
     f->W = W;
@@ -676,10 +678,21 @@ __global__ __launch_bounds__(256) void fit_start_kernel(float *params, float *m,
     }
     for (int64_t i = first; i < n_images; i += stride) emag[i] = 0.0f;
 }
-// Complete when it returns, whatever stream the next call is given.
+// Complete when it returns, whatever stream the next call is given, and on the handle's GPU, whatever GPU is current: a caller that
+// holds handles on several need not switch to upload.
 int fit_start(rinr_fit *f, bool moments, bool mask) {
     const int64_t np = f->n_images * f->n_params;
     if (f->n_images == 0) return RINR_OK;
+    struct OnDevice {
+        int was = -1;
+        bool switched = false;
+        ~OnDevice() { if (switched) (void)hipSetDevice(was); }
+    } on;
+    FIT_HIP(hipGetDevice(&on.was));
+    if (on.was != f->device) {
+        FIT_HIP(hipSetDevice(f->device));
+        on.switched = true;
+    }
     const uint32_t blocks = (uint32_t)std::min<int64_t>((np / 4 + 255) / 256 + 1, 2048);
     hipLaunchKernelGGL(fit_start_kernel, dim3(blocks), dim3(256), 0, (hipStream_t) nullptr, f->params, moments ? f->m : nullptr,
                        moments ? f->v : nullptr, f->emag, mask ? f->keep : nullptr, np, f->n_images);

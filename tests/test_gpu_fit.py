@@ -169,6 +169,37 @@ def test_adam_steps_follow_the_oracle(name, family):
     f.close()
 
 
+@pytest.mark.parametrize("widths,n", [([2, 1, 3], 1), ([2, 15, 15, 3], 1), ([2, 15, 15, 3], 3), ([2] + [40] * 9 + [3], 173)])
+def test_start_of_a_fit_under_a_mask(widths, n):
+    """Pruned parameters are zero and all others keep their bits, whichever of mask and parameters comes first, whatever the count
+    leaves behind its last four (and beyond one pass of the grid); a new mask leaves the moments, new parameters clear them."""
+    rng = np.random.default_rng(6)
+    p0 = synth.init_params(8, widths, n)
+    keep, other = keep_flags(rng, widths, n, 0.7), keep_flags(rng, widths, n, 0.5)
+    _, tgt = targets_of(9, n, 4, 3)
+    f = rinr_fit.Fit(widths, n, 4, 3)
+    f.set_params(p0)
+    np.testing.assert_array_equal(f.get_params(), p0)
+    f.set_keep(keep)
+    np.testing.assert_array_equal(f.get_params(), np.where(keep, p0, np.float32(0)))
+    f.set_params(p0)
+    np.testing.assert_array_equal(f.get_params(), np.where(keep, p0, np.float32(0)))
+    f.steps(tgt, 2, 1e-3, t0=0, T=8)
+    moved = f.get_params()
+    f.set_keep(other)
+    np.testing.assert_array_equal(f.get_params(), np.where(other, moved, np.float32(0)))
+    f.set_keep(None)
+    f.set_params(p0)
+    f.steps(tgt, 2, 1e-3, t0=0, T=8)
+    again = f.get_params()
+    g = rinr_fit.Fit(widths, n, 4, 3)
+    g.set_params(p0)
+    g.steps(tgt, 2, 1e-3, t0=0, T=8)
+    np.testing.assert_array_equal(again, g.get_params())       # nothing is left of the first fit: moments, error history
+    f.close()
+    g.close()
+
+
 def test_split_kernels_carry_the_error_at_any_size():
     """The split-precision kernels carry the back-propagated error in fp16 times a power of two chosen from the size of
     the error (the last step's, once there is one) and from the weights' gains.  Parity of the gradient must not depend on
