@@ -64,6 +64,33 @@ def test_all_widths_in_one_grid(torch):  # noqa: F811
     st.close()
 
 
+def test_streamed_layers_of_a_store_of_all_widths(torch):  # noqa: F811
+    """Deep models of every width: streamed by the bodies of the one grid, for the bytes of the resident kernels."""
+    ms = sum((synth.make_models(90 + w, np.arange(1), w, 14, [0] + [8] * 13 + [0], 0.8) for w in (8, 16, 24, 32, 40, 48, 56, 64)), [])
+    blob = rinr.pack(ms)
+    big, small = rinr.Store(blob), rinr.Store(blob, lds_budget=20 * 1024)
+    ids = ids_dev(torch, np.arange(len(ms))[::-1].copy())
+    for flags in (0, rinr.FLAG_FP16_ACT | rinr.FLAG_FP16_UNCHECKED, rinr.FLAG_FP16_ALL | rinr.FLAG_FP16_UNCHECKED):
+        a, b = (s.decode_batch_ex(ids, 31, 17, rinr.OUT_F32, flags) for s in (big, small))
+        assert torch.equal(a, b) and small.last_launch_info()["streamed"], flags
+    big.close()
+    small.close()
+
+
+@pytest.mark.parametrize("n,H,W", [(1, 1, 1), (1, 65, 129), (3, 8, 8), (40, 64, 63), (255, 16, 17), (257, 9, 23)])
+def test_splits_of_ragged_batches(torch, n, H, W):  # noqa: F811
+    """However a ragged batch is split over workgroups, with the order's scratch and without: the bytes of one workgroup an image."""
+    ms = image_like(synth.ragged_pool(5, 48))
+    st = rinr.Store(rinr.pack(ms))
+    sel = (np.arange(n) * 7) % len(ms)
+    ids, ws = ids_dev(torch, sel), torch.empty(rinr.workspace_bytes(n), dtype=torch.uint8, device="cuda")
+    got = st.decode_batch_ex(ids, H, W, rinr.OUT_F32)
+    assert torch.equal(got, st.decode_batch_ex(ids, H, W, rinr.OUT_F32, workspace=ws))
+    assert torch.equal(got, st.decode_batch_ex(ids, H, W, rinr.OUT_F32, blocks_per_cu=1))
+    assert np.abs(got[:5].cpu().numpy() - oracle.decode(ms, sel[:5], H, W)).max() <= TIGHT
+    st.close()
+
+
 @pytest.mark.parametrize("W", [1, 2, 3, 7, 31, 33, 62, 63, 64, 65, 66, 127, 128, 129, 1000])
 def test_rows_and_columns_of_every_pixel(torch, W):  # noqa: F811
     """A lane's row and column follow from those of its tile's first pixel: rows shorter than a tile, as long, a little longer."""
