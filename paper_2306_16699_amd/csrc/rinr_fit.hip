@@ -511,9 +511,17 @@ template <int WP, bool HALF, int L = 2> Fit16 kernel16_of(int n) {
 }
 // width: of the widest hidden layer.  Half of the last tile empty: the kernels that do not compute it (fit16::Shape), but for one that spills and is
 // the slower for it (256 images of 96 x 96, 3 layers x 56: 318 us a step instead of 310).
-Fit16 kernel16_for(int width, int L) {
+bool half_filled(int width, int L) {
     const int wp = (width + 15) / 16 * 16;
-    const bool half = width <= wp - 8 && !(wp == 64 && L <= 3);
+    return width <= wp - 8 && !(wp == 64 && L <= 3);
+}
+// Pixels of a workgroup's share from which they pay: a step's start and end, the same for any share, are longer in them.  us a step of one image
+// of 25 x 17, all units of the last tile -> the half-filled tile's kernel: 10 layers x 24 29.3 -> 32.4, 4 x 40 19.2 -> 21.3, 6 x 49 39.5 -> 45.0,
+// and of 300 of 32 x 32 (512 pixels a share): 163 -> 161, 92.9 -> 90.0, 259 -> 273; 8 of 171 x 219 (1216), 4 x 56: 97.9 -> 94.1, 6 x 56:
+// 162.8 -> 165.8.  Up to 8 units they are the faster ones from 8 x 8 pixels.
+int64_t half_pays_from(int width, int L) { return width <= 8 ? 0 : (width <= 40 ? 256 : 832 * (L - 3)); }
+Fit16 kernel16_for(int width, int L, bool half) {
+    const int wp = (width + 15) / 16 * 16;
     const Fit16 k = half ? (wp == 16 ? kernel16_of<16, true>(L) : (wp == 32 ? kernel16_of<32, true>(L) : (wp == 48 ? kernel16_of<48, true>(L) : kernel16_of<64, true>(L))))
                          : (wp == 16 ? kernel16_of<16, false>(L) : (wp == 32 ? kernel16_of<32, false>(L) : (wp == 48 ? kernel16_of<48, false>(L) : kernel16_of<64, false>(L))));
     return k.lds <= kLdsLimit - 256 ? k : Fit16{nullptr, 0, 0};
@@ -591,7 +599,8 @@ extern "C" int rinr_fit_create_ex(const rinr_fit_arch *arch, int64_t n_images, i
     f->wq = (wmax + 7) / 8 * 8;
     f->lds_floats = lds_floats(f->wq, arch->n_layers);
     if ((size_t)f->lds_floats * 4 + 256 > kLdsLimit) f->lds_floats = 0;
-    f->k16 = kernel16_for(wmax, arch->n_layers);
+    const bool half = half_filled(wmax, arch->n_layers);
+    f->k16 = kernel16_for(wmax, arch->n_layers, half);
     // the split-precision kernels where they are built for the shape, the fp32 ones otherwise or on request
     f->family = (f->k16.fn && !(flags & RINR_FIT_FLAG_FP32_MFMA)) ? RINR_FIT_KERNEL_SPLIT16 : RINR_FIT_KERNEL_FP32;
     if (f->family == RINR_FIT_KERNEL_FP32 && f->lds_floats == 0) { delete f; return RINR_E_UNSUPPORTED; }
@@ -618,6 +627,13 @@ extern "C" int rinr_fit_create_ex(const rinr_fit_arch *arch, int64_t n_images, i
         return RINR_E_HIP;
     }
     f->splits = plan_splits(f, fn);
+    if (half && f->family == RINR_FIT_KERNEL_SPLIT16 && ((int64_t)H * W + f->splits - 1) / f->splits < half_pays_from(wmax, arch->n_layers)) {
+        const Fit16 k = kernel16_for(wmax, arch->n_layers, false);
+        if (k.fn && !hip_fail(hipFuncSetAttribute((const void *)k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit - 256))) {
+            f->k16 = k;
+            f->splits = plan_splits(f, (const void *)k.fn);
+        }
+    }
     // no memory for the partial gradients: a workgroup takes a whole image, and the refusal is not left for the first launch's check
     if (f->splits > 1 && hip_fail(hipMalloc((void **)&f->part, ni * (size_t)f->splits * (size_t)(f->n_params + 1) * 4))) {
         f->part = nullptr;

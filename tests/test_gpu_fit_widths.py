@@ -12,9 +12,13 @@ pytestmark = pytest.mark.gpu
 BAR = 2e-5            # of the largest gradient entry, as in the suite's other gradient tests
 
 
-def check(widths, n=2, H=9, W=15, keep=None, gain=1.0):
-    p0 = (synth.init_params(41, widths, n) * gain).astype(np.float32)
+def check(widths, n=2, H=9, W=15, keep=None, gain=1.0, copies=1):
+    p0 = np.tile((synth.init_params(41, widths, n) * gain).astype(np.float32), (copies, 1))
     tgt, tgt_d = targets_of(43, n, H, W)
+    tgt_d = tgt_d.repeat(copies, 1, 1, 1)
+    n, first = n * copies, n
+    if keep is not None:
+        keep = np.tile(keep, (copies, 1))
     f = rinr_fit.Fit(widths, n, H, W)
     assert f.kernel_family == rinr_fit.KERNEL_SPLIT16
     if keep is not None:
@@ -22,10 +26,10 @@ def check(widths, n=2, H=9, W=15, keep=None, gain=1.0):
     f.set_params(p0)
     loss, grad = f.loss_grad(tgt_d)
     f.close()
-    for i in range(n):
+    for i in list(range(first)) + list(range(n - first if copies > 1 else n, n)):
         k = None if keep is None else keep[i]
         p = p0[i].astype(np.float64) if k is None else p0[i].astype(np.float64) * k
-        want_loss, want_g = fo.loss_grad(widths, p, tgt[i], k)
+        want_loss, want_g = fo.loss_grad(widths, p, tgt[i % first], k)
         assert abs(loss[i] - want_loss) <= BAR * want_loss
         assert np.abs(grad[i] - want_g).max() <= BAR * np.abs(want_g).max(), widths
 
@@ -34,6 +38,28 @@ def check(widths, n=2, H=9, W=15, keep=None, gain=1.0):
 def test_every_depth_of_half_filled_tiles(L):
     for width in (8, 5, 1, 24, 17, 21) + ((40, 33, 37) if L <= 10 else ()) + ((56, 49, 51) if L <= 6 else ()):
         check([2] + [width] * (L - 1) + [3])
+
+
+@pytest.mark.parametrize("L", range(2, 13))
+def test_every_depth_where_a_workgroup_takes_many_pixels(L):
+    """With many images a workgroup takes a whole one, and the kernels of half-filled tiles run from 256 pixels a share (49 to 56 units:
+    832 times the depth less 3) on: just below that and at it."""
+    for width in (8, 24, 17) + ((40, 33) if L <= 10 else ()):
+        for H, W in ((15, 17), (16, 16), (17, 17)):
+            check([2] + [width] * (L - 1) + [3], H=H, W=W, copies=600)
+    if 4 <= L <= 6:
+        for width, H in ((56, 26 * (L - 3)), (49, 26 * (L - 3)), (51, 26 * (L - 3) - 1)):
+            check([2] + [width] * (L - 1) + [3], n=1, H=H, W=32, copies=1024)
+
+
+def test_masks_and_large_weights_where_a_workgroup_takes_many_pixels():
+    """The other forms of the same kernels."""
+    for widths in ([2, 40, 3, 40, 3], [2, 7, 39, 16, 3], [2, 24, 5, 20, 3], [2, 17, 16, 18, 3]):
+        check(widths, n=3, H=17, W=16, keep=keep_flags(np.random.default_rng(5), widths, 3, 0.6), copies=400)
+        check(widths, n=3, H=17, W=16, gain=2.0, copies=400)
+    for gain in (1.0, 2.0):
+        widths = [2, 56, 24, 50, 3]
+        check(widths, n=1, H=32, W=27, keep=keep_flags(np.random.default_rng(6), widths, 1, 0.6), gain=gain, copies=1024)
 
 
 @pytest.mark.parametrize("widths", [[2, 40, 3, 40, 3], [2, 7, 39, 16, 3], [2, 33, 32, 31, 34, 3], [2, 1, 40, 3], [2, 8, 1, 7, 3], [2, 3, 8, 3], [2, 24, 5, 20, 3], [2, 56, 24, 50, 3], [2, 17, 16, 18, 3]], ids=str)
