@@ -694,21 +694,23 @@ __global__ __launch_bounds__(256) void fit_start_kernel(float *params, float *m,
     }
     for (int64_t i = first; i < n_images; i += stride) emag[i] = 0.0f;
 }
-// Complete when it returns, whatever stream the next call is given, and on the handle's GPU, whatever GPU is current: a caller that
-// holds handles on several need not switch to upload.
+// Makes a GPU the current one for the calls that follow, and the one before it again at the end
+struct OnDevice {
+    int was = -1;
+    bool switched = false;
+    int to(int device) {
+        FIT_HIP(hipGetDevice(&was));
+        if (was == device) return RINR_OK;
+        FIT_HIP(hipSetDevice(device));
+        switched = true;
+        return RINR_OK;
+    }
+    ~OnDevice() { if (switched) (void)hipSetDevice(was); }
+};
+// Called with the handle's GPU current, as its uploads are; complete when it returns, whatever stream the next call is given.
 int fit_start(rinr_fit *f, bool moments, bool mask) {
     const int64_t np = f->n_images * f->n_params;
     if (f->n_images == 0) return RINR_OK;
-    struct OnDevice {
-        int was = -1;
-        bool switched = false;
-        ~OnDevice() { if (switched) (void)hipSetDevice(was); }
-    } on;
-    FIT_HIP(hipGetDevice(&on.was));
-    if (on.was != f->device) {
-        FIT_HIP(hipSetDevice(f->device));
-        on.switched = true;
-    }
     const uint32_t blocks = (uint32_t)std::min<int64_t>((np / 4 + 255) / 256 + 1, 2048);
     hipLaunchKernelGGL(fit_start_kernel, dim3(blocks), dim3(256), 0, (hipStream_t) nullptr, f->params, moments ? f->m : nullptr,
                        moments ? f->v : nullptr, f->emag, mask ? f->keep : nullptr, np, f->n_images);
@@ -718,8 +720,12 @@ int fit_start(rinr_fit *f, bool moments, bool mask) {
 }
 }  // namespace
 
+// The three calls that overwrite a handle's state wait for all work on its GPU first, whatever GPU is current: a caller that holds handles
+// on several need not switch to upload.
 extern "C" int rinr_fit_reset_optimizer(rinr_fit *f) {
     if (!f) return RINR_E_NULL;
+    OnDevice on;
+    if (const int rc = on.to(f->device)) return rc;
     FIT_HIP(hipDeviceSynchronize());
     const int rc = fit_start(f, true, false);      // a new round: no moments, no error history
     if (rc) return rc;
@@ -730,6 +736,8 @@ extern "C" int rinr_fit_reset_optimizer(rinr_fit *f) {
 extern "C" int rinr_fit_set_params(rinr_fit *f, const float *params) {
     if (!f || (!params && f->n_images > 0)) return RINR_E_NULL;
     const size_t np = (size_t)f->n_images * (size_t)f->n_params;
+    OnDevice on;
+    if (const int rc = on.to(f->device)) return rc;
     FIT_HIP(hipDeviceSynchronize());
     if (np) FIT_HIP(hipMemcpy(f->params, params, np * 4, hipMemcpyHostToDevice));
     const int rc = fit_start(f, true, f->has_keep);
@@ -741,6 +749,8 @@ extern "C" int rinr_fit_set_params(rinr_fit *f, const float *params) {
 extern "C" int rinr_fit_set_keep(rinr_fit *f, const uint8_t *keep) {
     if (!f) return RINR_E_NULL;
     const size_t np = (size_t)f->n_images * (size_t)f->n_params;
+    OnDevice on;
+    if (const int rc = on.to(f->device)) return rc;
     FIT_HIP(hipDeviceSynchronize());
     if (np && keep) FIT_HIP(hipMemcpy(f->keep, keep, np, hipMemcpyHostToDevice));
     f->has_keep = keep != nullptr;

@@ -2,6 +2,7 @@
  * kernel launches are only written down.  For tests of the library's host side without a GPU; loaded before librinr.so. */
 #include <stddef.h>
 #include <stdint.h>
+#include <stdio.h>
 #include <stdlib.h>
 #include <string.h>
 
@@ -11,6 +12,9 @@ enum { OK = 0, OUT_OF_MEMORY = 2, N_LAUNCHES = 1024 };
 static int last_error;
 static size_t malloc_limit = SIZE_MAX;
 static int cus = 256, resident = 1;
+static int device;                      /* the current GPU */
+static char *done;                      /* what touches a GPU's work, with the GPU that was current: "sync 0, copy 0, " */
+static size_t done_room;
 static int64_t live;                    /* allocations not freed */
 static int n_launches;
 static uint32_t launches[N_LAUNCHES][4];       /* grid x, y; threads; dynamic LDS */
@@ -18,6 +22,11 @@ static uint32_t launches[N_LAUNCHES][4];       /* grid x, y; threads; dynamic LD
 void fake_set(size_t limit, int n_cus, int n_resident) { malloc_limit = limit; cus = n_cus; resident = n_resident; n_launches = 0; }
 int fake_launches(uint32_t *out) { memcpy(out, launches, (size_t)n_launches * sizeof launches[0]); return n_launches; }
 int64_t fake_live(void) { return live; }
+void fake_log(char *to, size_t room) { done = to; done_room = room; if (room) to[0] = 0; }
+static void note(const char *what) {
+    const size_t at = done ? strlen(done) : 0;
+    if (done) snprintf(done + at, done_room - at, "%s %d, ", what, device);
+}
 
 int hipMalloc(void **p, size_t n) {
     *p = n <= malloc_limit ? calloc(1, n ? n : 1) : NULL;
@@ -27,11 +36,12 @@ int hipMalloc(void **p, size_t n) {
 }
 int hipFree(void *p) { if (p) --live; free(p); return OK; }
 int hipMemset(void *p, int v, size_t n) { memset(p, v, n); return OK; }
-int hipMemcpy(void *d, const void *s, size_t n, int kind) { (void)kind; memcpy(d, s, n); return OK; }
+int hipMemcpy(void *d, const void *s, size_t n, int kind) { (void)kind; note("copy"); memcpy(d, s, n); return OK; }
 int hipGetLastError(void) { const int e = last_error; last_error = OK; return e; }      /* reported once, as the runtime does */
-int hipDeviceSynchronize(void) { return OK; }
+int hipDeviceSynchronize(void) { note("sync"); return OK; }
 int hipStreamSynchronize(void *s) { (void)s; return OK; }
-int hipGetDevice(int *d) { *d = 0; return OK; }
+int hipGetDevice(int *d) { *d = device; return OK; }
+int hipSetDevice(int d) { device = d; return OK; }
 int hipDeviceGetAttribute(int *v, int attr, int d) { (void)attr; (void)d; *v = cus; return OK; }
 int hipFuncSetAttribute(const void *f, int attr, int v) { (void)f; (void)attr; (void)v; return OK; }
 int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *f, int threads, size_t lds) {
@@ -51,6 +61,7 @@ int __hipPopCallConfiguration(dim3 *grid, dim3 *block, size_t *lds, void **strea
 }
 int hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t lds, void *stream) {
     (void)f; (void)args; (void)stream;
+    note("launch");
     if (n_launches < N_LAUNCHES) {
         uint32_t *l = launches[n_launches++];
         l[0] = grid.x; l[1] = grid.y; l[2] = block.x; l[3] = (uint32_t)lds;

@@ -25,6 +25,7 @@ def child(stub, cases):
     fake.fake_live.restype = C.c_int64
     out = []
     for c in cases:
+        log = C.create_string_buffer(1)
         arch = rinr_fit.FitArch(len(c["widths"]) - 1, (C.c_int32 * 13)(*c["widths"]), 30.0, -1.0, 1.0)
         h = C.c_void_p()
         fake.fake_set(c.get("limit", 2 ** 62), CUS, c["resident"])
@@ -35,8 +36,19 @@ def child(stub, cases):
             o = rinr_fit.FitOpts(1e-3, 0, 0, 0.0, 0.0, 0.0, 0.0)
             rc.append(L.rinr_fit_steps(h, 16, 1, C.byref(o), None))          # the targets' address is never followed here
             n = fake.fake_launches(grids)
+            log = C.create_string_buffer(4096)
+            if "current" in c:                   # the calls that overwrite the state, with another GPU current
+                n_params, keep = L.rinr_fit_n_params(h), (C.c_uint8 * (c["n"] * L.rinr_fit_n_params(h)))()
+                fake.hipSetDevice(c["current"])
+                fake.fake_log(log, C.c_size_t(len(log)))
+                rc += [L.rinr_fit_set_params(h, (C.c_float * (c["n"] * n_params))()), L.rinr_fit_set_keep(h, keep), L.rinr_fit_reset_optimizer(h)]
+                fake.fake_log(None, C.c_size_t(0))
+                now = C.c_int()
+                fake.hipGetDevice(C.byref(now))
+                log.value += b"now %d" % now.value
+                fake.hipSetDevice(0)
             rc.append(L.rinr_fit_destroy(h))
-        out.append(dict(rc=rc, launches=[list(grids[4 * k:4 * k + 4]) for k in range(n)], live=fake.fake_live()))
+        out.append(dict(rc=rc, launches=[list(grids[4 * k:4 * k + 4]) for k in range(n)], live=fake.fake_live(), log=log.value.decode()))
     print(json.dumps(out))
 
 
@@ -100,6 +112,15 @@ def test_workgroups_per_image(tmp_path):
         n_params = sum((i + 1) * o for i, o in zip(c["widths"], c["widths"][1:]))
         second = [[n_params // 64 + 1, n, 256 if s <= 16 else 1024]] if s > 1 else []
         assert [l[:3] for l in g["launches"][1:]] == second, name
+
+
+def test_state_is_overwritten_on_the_handles_gpu(tmp_path):
+    """Steps in flight on the handle's GPU are waited for, and its memory is written from there, whatever GPU is current; that one is
+    current again afterwards."""
+    for current in (0, 3):
+        g, = on_fake_runtime(tmp_path, [case(3, 8, 8, 15, 3, current=current)])
+        assert g["rc"] == [0] * 6
+        assert g["log"] == "sync 0, copy 0, launch 0, " * 2 + "sync 0, launch 0, now %d" % current
 
 
 if __name__ == "__main__":
