@@ -193,9 +193,11 @@ int scratch_for_device(int device, uint32_t **out) {
     return RINR_OK;
 }
 
-// The three ways a model's resident size is reckoned (see resident_fits): fp32 kernels, split-precision kernels
-// with the store's own kinds of hidden layer, split-precision kernels with fp16 weights.
-enum { kSizeFp32 = 0, kSizeXdl = 1, kSizeXdl16 = 2, kSizes = 3 };
+// The ways a model's resident size is reckoned (see resident_fits): fp32 kernels; split-precision kernels of the default mode, with fp16
+// activations, all in fp16 (kSizeXdl + 0, 1, 2), a class at a time, and (+ kSizeAny) in the one grid.  Each by its own kernel's layout: charged
+// the largest of the class's, 300 images of 32 x 32, 3 x 48, had four workgroups a CU instead of five in the reduced modes (us, charged alike
+// -> exactly: 17.7 -> 15.7 with fp16 activations, 23.7 -> 19.6 all in fp16).
+enum { kSizeFp32 = 0, kSizeXdl = 1, kSizeAny = 3, kSizes = 7 };
 
 }  // namespace
 
@@ -218,7 +220,7 @@ struct rinr_store {
     int hidden_kind;                          // kHiddenAllInt / AllRaw / Mixed over all hidden layers of all models
     bool narrow[kMaxClass + 1];               // no model of the class is wider than 8 less than its padded width
     bool even_cost;                           // every model has the same width class and depth: slot order does not matter
-    uint32_t fit_form[kSizes];                // resident_fits form per way of sizing
+    uint32_t fit_form[kSizes];                // resident_fits form per way of sizing (kFit...)
     uint32_t res_lds[kSizes][kMaxClass + 1];  // LDS of a resident launch: largest expanded model + its record, over the models that fit
     uint64_t n_res[kSizes][kMaxClass + 1];    // models decoded from a resident copy
     uint64_t n_str[kSizes][kMaxClass + 1];    // models whose layers are streamed
@@ -321,8 +323,13 @@ extern "C" int rinr_store_open_ex(const void *device_blob, const void *host_blob
     }
     // which models each kernel family decodes from a resident copy, and the LDS that takes
     s->fit_form[kSizeFp32] = kFitFp32;
-    s->fit_form[kSizeXdl] = s->hidden_kind == kHiddenAllInt ? kFitXdlOne : kFitXdlTwo;
-    s->fit_form[kSizeXdl16] = kFitXdlOne;
+    for (int m = 0; m < 3; ++m) {
+        const bool ints = s->hidden_kind == kHiddenAllInt;
+        uint32_t f = (m == 2 || ints ? kFitXdlOne : kFitXdlTwo) | (m > 0 ? kFitOneTerm : (ints ? kFitPairs : 0));
+        s->fit_form[kSizeXdl + kSizeAny + m] = f | kFitAny;
+        for (uint32_t c = 1; c <= kMaxClass; ++c) f |= s->narrow[c] ? (uint32_t)kFitNarrow << (c - 1) : 0u;
+        s->fit_form[kSizeXdl + m] = f;
+    }
     std::memset(s->res_lds, 0, sizeof s->res_lds);
     std::memset(s->n_res, 0, sizeof s->n_res);
     std::memset(s->n_str, 0, sizeof s->n_str);
@@ -330,10 +337,10 @@ extern "C" int rinr_store_open_ex(const void *device_blob, const void *host_blob
     for (const IndexEntry &e : s->index) {
         const uint32_t c = e.width == 0 ? 1u : (e.width + 15u) >> 4;
         for (int z = 0; z < kSizes; ++z) {
-            if (resident_fits(s->fit_form[z], c, e.n_layers, e.nbytes, (uint32_t)tile_rows, budget - 16u)) {
+            if (resident_fits(s->fit_form[z], e.width, e.n_layers, e.nbytes, (uint32_t)tile_rows, budget - 16u)) {
                 ++s->n_res[z][c];
                 // with the packed record staged behind the expanded weights where the budget holds both, and the tile counter
-                const uint32_t need = resident_bytes(s->fit_form[z], c, e.n_layers, (uint32_t)tile_rows) + 16u;
+                const uint32_t need = resident_bytes(s->fit_form[z], e.width, e.n_layers, (uint32_t)tile_rows) + 16u;
                 s->res_lds[z][c] = std::max(s->res_lds[z][c], need + e.nbytes <= budget ? need + e.nbytes : need);
             } else {
                 ++s->n_str[z][c];
@@ -361,7 +368,7 @@ extern "C" int rinr_store_open_ex(const void *device_blob, const void *host_blob
     if (!ok) { delete s; return RINR_E_HIP; }
     for (int m = 0; m < 3; ++m) {
         uint32_t lds_bytes = 16;
-        for (uint32_t c = 1; c <= kMaxClass; ++c) lds_bytes = std::max(lds_bytes, s->res_lds[m == 2 ? kSizeXdl16 : kSizeXdl][c]);
+        for (uint32_t c = 1; c <= kMaxClass; ++c) lds_bytes = std::max(lds_bytes, s->res_lds[kSizeXdl + kSizeAny + m][c]);
         int resident = 0;
         s->two_of_512[m] = !hip_fail(hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, xdl_any_fn(s->hidden_kind, m == 1, m == 2), 512, lds_bytes)) &&
                            resident >= 2;
@@ -488,23 +495,23 @@ extern "C" int rinr_decode_batch_ex(rinr_store *s, const int64_t *image_ids, int
                        (all16 || unchecked || s->bounds[0] <= kBoundLimit);
     const int family = !xdl ? kFamFp32 : (all16 ? kFamAll16 : (act16 ? kFamAct16 : kFamSplit));
     const int xk = all16 ? 6 : s->hidden_kind + (act16 ? 3 : 0);      // index into ClassImpl::decode_xdl
-    const int z = !xdl ? kSizeFp32 : (all16 ? kSizeXdl16 : kSizeXdl);
-    a.fit_form = s->fit_form[z];
 
     const uint32_t tiles = (uint32_t)((HW + 63) >> 6);
     int n_classes = 0;
-    uint64_t any_streamed = 0, any_resident = 0;
-    for (uint32_t c = 1; c <= kMaxClass; ++c) {
-        n_classes += s->sum.class_count[c] ? 1 : 0;
-        any_streamed += s->n_str[z][c];
-        any_resident += s->n_res[z][c];
-    }
+    for (uint32_t c = 1; c <= kMaxClass; ++c) n_classes += s->sum.class_count[c] ? 1 : 0;
     // a store that mixes width classes: one grid whose workgroups run the body of their slot's class, in two workgroups of 512 threads a
     // CU where they fit (us, class by class in workgroups by tiles -> so: 4000 ragged images of 32 x 32 216 -> 187, of 16 x 16 100 -> 88, 500
     // of 32 x 32 80 -> 38).  The fp32 kernels take images of few tiles class by class, with that class's LDS size (workgroups of other
     // classes return at once).  An empty store also takes the one grid: every id is out of range and its slot is zero-filled.
     const int64_t any_min_tiles = opts->one_grid_min_tiles ? opts->one_grid_min_tiles : (xdl ? 1 : 64);
     const bool one_grid = n_classes == 0 || (n_classes > 1 && (int64_t)tiles >= any_min_tiles);
+    const int z = !xdl ? kSizeFp32 : kSizeXdl + (all16 ? 2 : (act16 ? 1 : 0)) + (one_grid ? kSizeAny : 0);
+    a.fit_form = s->fit_form[z];
+    uint64_t any_streamed = 0, any_resident = 0;
+    for (uint32_t c = 1; c <= kMaxClass; ++c) {
+        any_streamed += s->n_str[z][c];
+        any_resident += s->n_res[z][c];
+    }
     // slots of unequal cost are taken heaviest first when the caller gives the scratch for the order
     const bool order = opts->workspace && !s->even_cost;
     // threads by tiles, and the smaller workgroups where the others would not give half the CUs one (one image of 224 x 224, 9 x 40: 24.4 -> 19.1 us)

@@ -271,23 +271,28 @@ __device__ __forceinline__ void expand_model(float *lds, const uint32_t *rec, co
 constexpr uint32_t kLdsLimit = 160 * 1024;   // LDS per workgroup on gfx950
 enum { kFitFp32 = 0,        // fp32 kernels: 4 bytes per padded weight
        kFitXdlOne = 1,      // split-precision kernels, one fp16 block per hidden layer (2..8-bit layers, or fp16 weights)
-       kFitXdlTwo = 2 };    // ... two blocks per hidden layer (a store with fp32 or 16-bit hidden layers)
+       kFitXdlTwo = 2,      // ... two blocks per hidden layer (a store with fp32 or 16-bit hidden layers)
+       kFitKind = 3,
+       // which of them, for the layout: a model counts in that of the kernel the launch serves it with
+       kFitPairs = 4,       // all hidden layers integer-coded, activations hi/lo pairs
+       kFitOneTerm = 8,     // activations single halfs
+       kFitAny = 16,        // the one grid's kernel, whose layouts are by the model's own width
+       kFitNarrow = 32 };   // << class - 1: the class's kernel is the one for 8 units less than its padded width
 __host__ __device__ inline uint32_t fp32_model_bytes(uint32_t cls, uint32_t tile_rows_wide, uint32_t L) {
     const uint32_t wp = 16u * cls, tm = (cls == 2 || cls == 4) ? tile_rows_wide : 16u, g = 64u / tm;
     const uint32_t mt = wp / tm, mts = mt == 3 ? 4u : mt, ksteps = wp / g;
     const uint32_t first = 64u * mts, hidden = ksteps * 64u * mts;
     return 4u * (first + (L - 1) * wp + (L - 2) * hidden + 4u * wp + 4u);
 }
-__host__ __device__ inline uint32_t xdl_model_bytes(int cls, int n_layers, int n_int, int n_raw);
-__host__ __device__ inline uint32_t resident_bytes(uint32_t form, uint32_t cls, uint32_t L, uint32_t tile_rows_wide) {
-    const uint32_t b = form == kFitFp32 ? fp32_model_bytes(cls, tile_rows_wide, L)
-                                        : xdl_model_bytes((int)cls, (int)L, form == kFitXdlOne ? (int)L - 2 : 0,
-                                                          form == kFitXdlTwo ? (int)L - 2 : 0);
+__host__ __device__ inline uint32_t xdl_model_bytes(uint32_t form, uint32_t width, uint32_t L);
+__host__ __device__ inline uint32_t resident_bytes(uint32_t form, uint32_t width, uint32_t L, uint32_t tile_rows_wide) {
+    const uint32_t cls = width == 0u ? 1u : (width + 15u) >> 4;
+    const uint32_t b = (form & kFitKind) == kFitFp32 ? fp32_model_bytes(cls, tile_rows_wide, L) : xdl_model_bytes(form, width, L);
     return (b + 15u) & ~15u;
 }
-__host__ __device__ inline bool resident_fits(uint32_t form, uint32_t cls, uint32_t L, uint32_t rec_bytes, uint32_t tile_rows_wide,
+__host__ __device__ inline bool resident_fits(uint32_t form, uint32_t width, uint32_t L, uint32_t rec_bytes, uint32_t tile_rows_wide,
                                               uint32_t budget) {
-    return (uint64_t)resident_bytes(form, cls, L, tile_rows_wide) + (form == kFitXdlTwo ? 0u : rec_bytes) <= budget;
+    return (uint64_t)resident_bytes(form, width, L, tile_rows_wide) + ((form & kFitKind) == kFitXdlTwo ? 0u : rec_bytes) <= budget;
 }
 
 // ---- decode kernel ---------------------------------------------------------------------------
@@ -418,7 +423,7 @@ __device__ __forceinline__ bool decode_prologue(const DecodeArgs &a, Work &w) {
     w.cls = w.e.width == 0 ? 1u : (w.e.width + 15u) >> 4;
     if (a.cls != 0 && w.cls != a.cls) return false;
     if (a.stream_mode) {
-        const bool fits = resident_fits(a.fit_form, w.cls, w.e.n_layers, w.e.nbytes, a.tile_rows_wide, a.lds_budget);
+        const bool fits = resident_fits(a.fit_form, w.e.width, w.e.n_layers, w.e.nbytes, a.tile_rows_wide, a.lds_budget);
         if (fits != (a.stream_mode == 1u)) return false;
     }
     return true;

@@ -64,6 +64,9 @@ enum { kWeight16 = 8 };
 __host__ __device__ constexpr int xdl_tile_rows(int wq, int mode) {
     return wq == 24 || (wq == 32 && (mode & (kAct16 | kWeight16))) ? 32 : 16;
 }
+// ... and the one grid's: with 32-row tiles above 48 units 122 registers leave room for 16 wavefronts a CU; with 16-row ones 64 ragged images
+// of 300 x 300 take 236 us instead of 209
+__host__ __device__ constexpr int xdl_any_tile_rows(int wq, int mode) { return wq > 48 ? 32 : xdl_tile_rows(wq, mode); }
 
 struct XLayer {            // one entry per linear layer, built in LDS by the workgroup
     uint32_t off_hi;       // byte offset of the fp16 operand block
@@ -152,18 +155,30 @@ template <int TM, int WQ_, bool INT> struct XLayout {
     static __device__ __forceinline__ int idx_bias(int o) { return idx_bias_row(row(o)); }
 };
 
-// Bytes of LDS the expanded model of width class `cls` needs at most (without the staging copy of the
-// record), whatever kernel takes it.  n_int = hidden layers in integer form, n_raw = hidden layers split hi/lo.
-__host__ __device__ inline uint32_t xdl_model_bytes(int cls, int n_layers, int n_int, int n_raw) {
-    const uint32_t wp = 16u * cls, nq = (uint32_t)cls;              // 16-row tiles; layouts of 32-row tiles are smaller
-    const uint32_t out = (nq / 2 + nq % 2) * 1024u, one = wp * wp * 2u + (nq % 2) * nq * 512u;
-    return 16u * 16u + 16u * 4u + ((uint32_t)(n_layers - 1) * wp + 16u) * 4u + 4u * nq * 1024u +
-           one * (uint32_t)n_int + 2u * wp * wp * 2u * (uint32_t)n_raw + 2u * out;
+// Bytes of LDS of an expanded model (without the staging copy of the record): base + (L - 2) * layer, in layout XLayout<tm, wq, ints>
+struct XBytes { uint32_t base, layer; };
+__host__ __device__ constexpr XBytes xdl_bytes(uint32_t tm, uint32_t wq, bool ints, bool two_blocks) {
+    const uint32_t wp = (wq + 15u) / 16u * 16u, g = 64u / tm, mt = wp / tm, nq = tm == 16u ? wp / 16u : wq / 8u, kj = nq / 2u;
+    const bool odd = nq % 2u != 0u, two_rows = odd && tm == 16u && wq != wp;                              // kTailTwo
+    const uint32_t tail = !odd ? 0u : (two_rows || tm == 32u || ints ? 1024u : 512u), low = two_rows ? 0u : tail;
+    const uint32_t hidden = mt * (kj * 1024u + tail), hidden_low = mt * (kj * 1024u + low);
+    return XBytes{16u * 16u + 16u * 4u + 4u * wp + 4u * tm + g * mt * 1024u + 2u * kj * 1024u + tail + low,
+                  4u * wp + hidden + (two_blocks ? hidden_low : 0u)};
 }
-// Whether that holds for layout LY: for the parts every model has, and per hidden layer of either kind
-template <class LY> constexpr bool xdl_within_bound() {
-    constexpr int nq = LY::WP / 16, out = (nq / 2 + nq % 2) * 1024, two = 4 * LY::WP * LY::WP, one = two / 2 + nq % 2 * nq * 512;
-    return LY::OUTB + LY::FIRST + LY::OUT + LY::OUTLO <= 64 + 4 * nq * 1024 + 2 * out && LY::HID <= one && (LY::INTS || LY::HID + LY::HIDLO <= two);
+// ... of one of `width` units and L linear layers in the layout that `form` (kFit...) names
+__host__ __device__ inline uint32_t xdl_model_bytes(uint32_t form, uint32_t width, uint32_t L) {
+    const uint32_t cls = width == 0u ? 1u : (width + 15u) >> 4, own = width == 0u ? 8u : (width + 7u) & ~7u;
+    const uint32_t wq = form & kFitAny ? own : 16u * cls - (form & (uint32_t)kFitNarrow << (cls - 1u) ? 8u : 0u);
+    const uint32_t tm = form & kFitAny ? (uint32_t)xdl_any_tile_rows((int)wq, form & kFitOneTerm ? kAct16 : 0)
+                                       : (uint32_t)xdl_tile_rows((int)wq, form & kFitOneTerm ? kAct16 : 0);
+    const XBytes b = xdl_bytes(tm, wq, (form & kFitPairs) != 0u, (form & kFitKind) == kFitXdlTwo);
+    return b.base + (L - 2u) * b.layer;
+}
+// Whether xdl_bytes has layout LY's
+template <int TM, class LY> constexpr bool xdl_bytes_hold() {
+    constexpr XBytes one = xdl_bytes(TM, LY::WQ, LY::INTS, false), two = xdl_bytes(TM, LY::WQ, LY::INTS, true);
+    return one.base == LY::TABLE + 4 * LY::WP + LY::OUTB + LY::FIRST + LY::OUT + LY::OUTLO && two.base == one.base &&
+           one.layer == 4 * LY::WP + LY::HID && two.layer == one.layer + LY::HIDLO;
 }
 
 // Builds the operand blocks of layers [l0, l1) in LDS and their XLayer entries tab[l].  `rec` is the model record:
@@ -433,7 +448,6 @@ template <> struct XTile<16> {
 template <> struct XTile<32> {
     typedef f32x16 acc_t;
     static __device__ __forceinline__ acc_t mfma(h8v a, h8v b, acc_t c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
-    static __device__ __forceinline__ acc_t mfma_half(h4v, h4v, acc_t c) { return c; }     // never used: no odd quad at TM = 32
 };
 
 // sine of four accumulator values (one quad), then the exact hi/lo split of the results: hi = fp16(h), lo = fp16(h - hi).
@@ -816,7 +830,7 @@ __device__ __forceinline__ void xdl_body(const DecodeArgs &a, const Work &w, flo
     typedef XLayout<TM, WQ, MODE_ == kHiddenAllInt> LY;
     typedef XHalf<TM, LY> Half;
     constexpr int WP = LY::WP;
-    static_assert(xdl_within_bound<LY>(), "what the host sizes LDS for");
+    static_assert(xdl_bytes_hold<TM, LY>(), "what the host sizes LDS for");
     char *lds = (char *)lds_f;
     const int tid = threadIdx.x, nthreads = blockDim.x;
     const uint32_t tile0 = w.tile0, tile1 = w.tile1;
@@ -833,7 +847,8 @@ __device__ __forceinline__ void xdl_body(const DecodeArgs &a, const Work &w, flo
     if (tid == 0) *next_tile = tile0 + (nthreads >> 6);
     {
         const LaneLayers t = lane_layers<XExpand<LY::WP>::PASSES>(record, L, 0, L, tid & 63, __builtin_amdgcn_readfirstlane(tid >> 6), nthreads >> 6);
-        const uint32_t need = resident_bytes(a.fit_form, w.cls, L, 0);
+        constexpr XBytes bytes = xdl_bytes(TM, WQ, LY::INTS, true);
+        const uint32_t need = bytes.base + (uint32_t)(L - 2) * bytes.layer;
         if (MODE == kHiddenAllInt || W16 || need + e.nbytes <= room) {     // (in one-block form a model fits with its record)
             uint32_t *stage = (uint32_t *)(lds + (room - e.nbytes));
             for (uint32_t q = tid; q < (e.nbytes >> 4); q += nthreads) ((uint4 *)stage)[q] = ((const uint4 *)record)[q];
@@ -980,14 +995,14 @@ __global__ __launch_bounds__(NTHREADS) void decode_xdl_any_kernel(const DecodeAr
     Work w;
     if (!decode_prologue(a, w)) return;
     switch ((w.e.width + 7u) >> 3) {
-        case 0: case 1: xdl_body<xdl_tile_rows(8, MODE), 8, MODE>(a, w, lds_f); break;
-        case 2: xdl_body<xdl_tile_rows(16, MODE), 16, MODE>(a, w, lds_f); break;
-        case 3: xdl_body<xdl_tile_rows(24, MODE), 24, MODE>(a, w, lds_f); break;
-        case 4: xdl_body<xdl_tile_rows(32, MODE), 32, MODE>(a, w, lds_f); break;
-        case 5: xdl_body<xdl_tile_rows(40, MODE), 40, MODE>(a, w, lds_f); break;
-        case 6: xdl_body<xdl_tile_rows(48, MODE), 48, MODE>(a, w, lds_f); break;
-        case 7: xdl_body<32, 56, MODE>(a, w, lds_f); break;     // 32-row tiles: 122 registers leave room for 16 wavefronts a CU; with 16-row
-        default: xdl_body<32, 64, MODE>(a, w, lds_f); break;    // ones 64 ragged images of 300 x 300 take 236 us instead of 209
+        case 0: case 1: xdl_body<xdl_any_tile_rows(8, MODE), 8, MODE>(a, w, lds_f); break;
+        case 2: xdl_body<xdl_any_tile_rows(16, MODE), 16, MODE>(a, w, lds_f); break;
+        case 3: xdl_body<xdl_any_tile_rows(24, MODE), 24, MODE>(a, w, lds_f); break;
+        case 4: xdl_body<xdl_any_tile_rows(32, MODE), 32, MODE>(a, w, lds_f); break;
+        case 5: xdl_body<xdl_any_tile_rows(40, MODE), 40, MODE>(a, w, lds_f); break;
+        case 6: xdl_body<xdl_any_tile_rows(48, MODE), 48, MODE>(a, w, lds_f); break;
+        case 7: xdl_body<xdl_any_tile_rows(56, MODE), 56, MODE>(a, w, lds_f); break;
+        default: xdl_body<xdl_any_tile_rows(64, MODE), 64, MODE>(a, w, lds_f); break;
     }
 }
 
@@ -1008,14 +1023,14 @@ __global__ __launch_bounds__(kStreamThreads) void decode_xdl_stream_any_kernel(c
     Work w;
     if (!decode_prologue(a, w)) return;
     switch ((w.e.width + 7u) >> 3) {
-        case 0: case 1: xdl_stream_body<xdl_tile_rows(8, MODE), 8, MODE>(a, w, lds_f); break;
-        case 2: xdl_stream_body<xdl_tile_rows(16, MODE), 16, MODE>(a, w, lds_f); break;
-        case 3: xdl_stream_body<xdl_tile_rows(24, MODE), 24, MODE>(a, w, lds_f); break;
-        case 4: xdl_stream_body<xdl_tile_rows(32, MODE), 32, MODE>(a, w, lds_f); break;
-        case 5: xdl_stream_body<xdl_tile_rows(40, MODE), 40, MODE>(a, w, lds_f); break;
-        case 6: xdl_stream_body<xdl_tile_rows(48, MODE), 48, MODE>(a, w, lds_f); break;
-        case 7: xdl_stream_body<32, 56, MODE>(a, w, lds_f); break;
-        default: xdl_stream_body<32, 64, MODE>(a, w, lds_f); break;
+        case 0: case 1: xdl_stream_body<xdl_any_tile_rows(8, MODE), 8, MODE>(a, w, lds_f); break;
+        case 2: xdl_stream_body<xdl_any_tile_rows(16, MODE), 16, MODE>(a, w, lds_f); break;
+        case 3: xdl_stream_body<xdl_any_tile_rows(24, MODE), 24, MODE>(a, w, lds_f); break;
+        case 4: xdl_stream_body<xdl_any_tile_rows(32, MODE), 32, MODE>(a, w, lds_f); break;
+        case 5: xdl_stream_body<xdl_any_tile_rows(40, MODE), 40, MODE>(a, w, lds_f); break;
+        case 6: xdl_stream_body<xdl_any_tile_rows(48, MODE), 48, MODE>(a, w, lds_f); break;
+        case 7: xdl_stream_body<xdl_any_tile_rows(56, MODE), 56, MODE>(a, w, lds_f); break;
+        default: xdl_stream_body<xdl_any_tile_rows(64, MODE), 64, MODE>(a, w, lds_f); break;
     }
 }
 

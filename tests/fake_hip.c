@@ -12,6 +12,7 @@ enum { OK = 0, OUT_OF_MEMORY = 2, N_LAUNCHES = 1024 };
 static int last_error;
 static size_t malloc_limit = SIZE_MAX;
 static int cus = 256, resident = 1;
+static size_t cu_lds;                   /* not 0: a CU's LDS, which bounds the workgroups side by side as well */
 static int device;                      /* the current GPU */
 static char *done;                      /* what touches a GPU's work, with the GPU that was current: "sync 0, copy 0, " */
 static size_t done_room;
@@ -20,6 +21,7 @@ static int n_launches;
 static uint32_t launches[N_LAUNCHES][4];       /* grid x, y; threads; dynamic LDS */
 
 void fake_set(size_t limit, int n_cus, int n_resident) { malloc_limit = limit; cus = n_cus; resident = n_resident; n_launches = 0; }
+void fake_cu_lds(size_t bytes) { cu_lds = bytes; }
 int fake_launches(uint32_t *out) { memcpy(out, launches, (size_t)n_launches * sizeof launches[0]); return n_launches; }
 int64_t fake_live(void) { return live; }
 void fake_log(char *to, size_t room) { done = to; done_room = room; if (room) to[0] = 0; }
@@ -43,10 +45,12 @@ int hipStreamSynchronize(void *s) { (void)s; return OK; }
 int hipGetDevice(int *d) { *d = device; return OK; }
 int hipSetDevice(int d) { device = d; return OK; }
 int hipDeviceGetAttribute(int *v, int attr, int d) { (void)attr; (void)d; *v = cus; return OK; }
+int hipGetDevicePropertiesR0600(void *p, int d) { (void)d; memset(p, 0, 1024); return OK; }     /* no number of CUs: the library takes 256 */
+int hipGetSymbolAddress(void **p, const void *symbol) { *p = (void *)(uintptr_t)symbol; return OK; }
 int hipFuncSetAttribute(const void *f, int attr, int v) { (void)f; (void)attr; (void)v; return OK; }
 int hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *f, int threads, size_t lds) {
-    (void)f; (void)threads; (void)lds;
-    *n = resident;
+    (void)f; (void)threads;
+    *n = cu_lds && lds && cu_lds / lds < (size_t)resident ? (int)(cu_lds / lds) : resident;
     return OK;
 }
 
