@@ -133,7 +133,12 @@ template <int TM, int WQ_, bool INT> struct XLayout {
         return KJ * mts * 512 + (mt * 64 + g * TM + m) * (TAIL == kTailHalf ? 4 : 8) + b;
     }
     static __device__ __forceinline__ bool in_tail(int i) { return TAIL != kTailNone && i >= (TM == 16 ? 32 * KJ : 16 * KJ); }
-    // hidden weight (o, i); i's quad position 0 where four inputs go out together
+    static __device__ __forceinline__ int idx_input(int i) {      // input i of row 0 in a hidden layer's block
+        int q, g, b;
+        locate(i, q, g, b);
+        return idx(MT, 0, 0, q, g, b);
+    }
+    // hidden weight (o, i)
     static __device__ __forceinline__ int idx_hidden(int o, int i) {
         const int r = row(o);
         int q, g, b;
@@ -193,17 +198,18 @@ template <class LY> struct XSlot {
     static constexpr int BYTES = BIAS + BLOCKS;
 };
 
-// This wavefront's part of a hidden layer, four consecutive inputs of one output per lane: exactly one 8-byte word of the operand block,
-// written whole, pruned weights and the padding up to WP x WP included, so nothing has to be cleared first.  A lane has a nibble
+// This wavefront's part of a hidden layer, four consecutive inputs of one output per lane: one 8-byte word of the operand block (PutFour: in
+// a last quad more),
+// written whole, pruned weights and the padding of a row included, so only rows of padding have to be cleared first.  A lane has a nibble
 // of the mask; the ranks of all lanes' first kept weights come from the counts' three bits (ballots and masked bit counts), and
 // the codes of a lane's kept weights follow each other, so two words of the stream hold them.  For 2..8-bit codes the four bytes
 // go to their places by one byte permute, whose selector is a table's (pruned: the zero point), and to halfs by another:
 // 1024 + code is a half with the code as its low byte, and subtracting 1024 + zp is exact.
 // About 35 vector instructions for up to 256 weights, where one weight per lane took 30 for up to 64 (10 layers x 40: from the
 // workgroup's start to the end of this phase 25 -> 14.5 thousand clocks).
-template <int WP> struct XExpand {
-    static constexpr int LANES = WP <= 16 ? 4 : (WP <= 32 ? 8 : 16), ROWS = 64 / LANES;      // lanes per row, rows per pass
-    static constexpr int PASSES = WP / ROWS;
+template <int WQ> struct XExpand {
+    static constexpr int LANES = WQ <= 16 ? 4 : (WQ <= 32 ? 8 : 16), ROWS = 64 / LANES;      // lanes per row, rows per pass
+    static constexpr int PASSES = (WQ + ROWS - 1) / ROWS;
 };
 // Byte selector of a nibble of keep bits: byte b is the rank of weight b among the kept ones, or 4 (the zero point) if pruned.
 __device__ __forceinline__ uint32_t nibble_selector(uint32_t bits) {
@@ -212,31 +218,60 @@ __device__ __forceinline__ uint32_t nibble_selector(uint32_t bits) {
     for (int b = 0; b < 4; ++b) s |= ((bits >> b & 1u) ? (uint32_t)__popc(bits & ((1u << b) - 1u)) : 4u) << (8 * b);
     return s;
 }
-// Four consecutive inputs of one output into an operand block: one word of it, or, where they are in a last tile with two rows a lane,
-// half of the words of two lane groups.
-template <class LY> __device__ __forceinline__ void put_four(char *block, int o, int i, h4v w, h4v low) {
-    const h4v none = (h4v)((_Float16)0.0f);
-    char *const p = block + 2 * LY::idx_hidden(o, i);
-    if (LY::HALF && i >= 16 * (LY::MT - 1)) {
-        constexpr int NEXT = 16 * 16;                       // bytes to the next lane group's word
-        const h4v w01 = __builtin_shufflevector(w, none, 0, 1, 4, 5), w23 = __builtin_shufflevector(w, none, 2, 3, 4, 5);
-        if (LY::TAIL == kTailTwo) {
-            *(h8v *)p = __builtin_shufflevector(__builtin_shufflevector(w, w, 0, 1, 0, 1), __builtin_shufflevector(low, none, 0, 1, 4, 5), 0, 1, 2, 3, 4, 5, 6, 7);
-            *(h8v *)(p + NEXT) = __builtin_shufflevector(__builtin_shufflevector(w, w, 2, 3, 2, 3), __builtin_shufflevector(low, none, 2, 3, 4, 5), 0, 1, 2, 3, 4, 5, 6, 7);
-        } else {
-            *(h4v *)p = w01;
-            *(h4v *)(p + NEXT) = w23;
-        }
-    } else if (LY::TAIL == kTailFull && LY::in_tail(i)) {
-        *(h8v *)p = __builtin_shufflevector(w, w, 0, 1, 2, 3, 4, 5, 6, 7);
-    } else {
-        *(h4v *)p = w;
+// Where a lane's four consecutive inputs of one output go in an operand block: one word of it, two where the step has it twice (kTailFull),
+// or, in a last tile with two rows a lane, half of the words of two lane groups.  A pass's rows are in one row tile, so what
+// depends on the pass is the scalar unit's, and what depends on the lane is known before the first pass; the half tile's inputs take no branch
+// of their own but for the second word.  Expansion of 8 x 40 and 8 x 56, us a call with nothing decoded behind it: 515 images of 146 x 17 (2575
+// workgroups) 61.4 -> 53.7 and 59.1 -> 53.3 against two branches that find their places in every pass (and passes for rows of padding),
+// 57 of 23 x 38 (228) 11.6 -> 10.1 and 13.2 -> 12.0; whole calls, 515 of 146 x 17 149.0 -> 140.6, 57 of 23 x 38 17.3 -> 15.8 and 21.1 -> 19.9.
+template <class LY, int TM> struct PutFour {
+    static constexpr int LANES = XExpand<LY::WQ>::LANES, ROWS = XExpand<LY::WQ>::ROWS;
+    static constexpr int NEXT = 16 * 16;            // bytes to the next lane group's word
+    uint32_t at, at_half;                           // bytes: the word of the lane's row in a pass that begins a row tile; ... the half tile
+    uint32_t narrow;                                // 1: rows are 8 bytes apart (kTailHalf), not 16
+    bool tail, split, has;                          // in the last quad; ... shared with the next lane group; there is such an input
+    __device__ __forceinline__ PutFour(uint32_t lane) {
+        const uint32_t i = 4u * (lane % LANES), r = lane / LANES;
+        const bool last = LY::in_tail((int)i);
+        tail = last;
+        narrow = LY::TAIL == kTailHalf && last ? 1u : 0u;
+        split = LY::HALF && i >= 16u * (LY::MT - 1);
+        has = i < (uint32_t)LY::WQ;
+        const uint32_t word = 2u * (uint32_t)LY::idx_input((int)i);
+        at = word + (16u * r >> narrow);
+        at_half = word + 16u * ((r & 7u) + (r & 6u) + (r >> 3) * 2u);     // row(16 t + j); j above 7 are rows of padding
     }
-}
-template <class LY, bool W16, int KIND, int U>
+    // bytes of the lane's word in pass p
+    __device__ __forceinline__ uint32_t place(uint32_t p) const {
+        const uint32_t row = p * ROWS, t = row / TM, in = row % TM;
+        const bool half = LY::HALF && t == (uint32_t)LY::MT - 1u;
+        const uint32_t pass = t * 1024u + 16u * in * (half ? 2u : 1u);
+        return (half ? at_half : at) + (LY::TAIL == kTailHalf ? pass >> narrow : pass);
+    }
+    __device__ __forceinline__ void put(char *block, uint32_t place, h4v w, h4v low) const {
+        typedef uint32_t u2v __attribute__((ext_vector_type(2)));
+        typedef uint32_t u4v __attribute__((ext_vector_type(4)));
+        char *const p = block + place;
+        const u2v x = __builtin_bit_cast(u2v, w), y = __builtin_bit_cast(u2v, low);
+        if (LY::HALF && LY::TAIL == kTailTwo) {
+            *(u2v *)p = (u2v){x[0], split ? x[0] : x[1]};
+            if (split) {
+                *(u2v *)(p + 8) = (u2v){y[0], 0u};
+                *(u4v *)(p + NEXT) = (u4v){x[1], x[1], y[1], 0u};
+            }
+        } else if (LY::HALF) {
+            *(u2v *)p = (u2v){x[0], split ? 0u : x[1]};
+            if (split) *(u2v *)(p + NEXT) = (u2v){x[1], 0u};
+        } else {
+            *(u2v *)p = x;
+            if (LY::TAIL == kTailFull && tail) *(u2v *)(p + 8) = x;
+        }
+    }
+};
+template <class LY, int TM, bool W16, int KIND, int U>
 __device__ __forceinline__ void expand_hidden(const uint32_t *rec, const LaneLayers &t, int l, int lane, char *lds, char *hi, char *lo, float *bt,
                                               float bias_factor, bool whole, float pre) {
-    typedef XExpand<LY::WP> X;
+    typedef XExpand<LY::WQ> X;
     const uint32_t last = lane_value(t.upto, l), first = last - lane_value(t.passes, l);
     if (t.g1 <= first || t.g0 >= last) return;
     const uint32_t io = lane_value(t.io, l), kind = lane_value(t.kind, l), n_in = io & 0xFFFFu, n_out = io >> 16;
@@ -251,6 +286,7 @@ __device__ __forceinline__ void expand_hidden(const uint32_t *rec, const LaneLay
     const uint32_t real = i >= n_in ? 0u : (n_in - i >= 4u ? 15u : (1u << (n_in - i)) - 1u);    // the lane's inputs that exist
     const uint32_t last_word = (n_in * n_out - 1u) >> 5;
     const uint32_t *select = (const uint32_t *)(lds + LY::SELECT);
+    const PutFour<LY, TM> to((uint32_t)lane);
     const uint32_t zp4 = (uint32_t)zp * 0x01010101u;
     const h2v less = {(_Float16)(float)(-1024 - zp), (_Float16)(float)(-1024 - zp)};
     const uint32_t k0 = min(p0 * X::ROWS, n_out) * n_in;                        // weights before the wavefront's first pass
@@ -309,7 +345,7 @@ __device__ __forceinline__ void expand_hidden(const uint32_t *rec, const LaneLay
                 const uint32_t y = __builtin_amdgcn_perm(zp4, x[j], sel[j]);
                 const h2v h01 = __builtin_bit_cast(h2v, __builtin_amdgcn_perm(0x64646464u, y, 0x04010400u)) + less;
                 const h2v h23 = __builtin_bit_cast(h2v, __builtin_amdgcn_perm(0x64646464u, y, 0x04030402u)) + less;
-                if ((int)i < LY::WQ && p + j < p1) put_four<LY>(hi, (int)o[j], (int)i, (h4v){h01[0], h01[1], h23[0], h23[1]}, (h4v)((_Float16)0.0f));
+                if (to.has && p + j < p1) to.put(hi, to.place(p + j), (h4v){h01[0], h01[1], h23[0], h23[1]}, (h4v)((_Float16)0.0f));
             }
         } else {
 #pragma unroll
@@ -330,9 +366,10 @@ __device__ __forceinline__ void expand_hidden(const uint32_t *rec, const LaneLay
                     wh[b] = (_Float16)w;
                     wl[b] = (_Float16)(w - (float)wh[b]);
                 }
-                if ((int)i < LY::WQ && p + j < p1) {
-                    put_four<LY>(hi, (int)o[j], (int)i, wh, W16 ? (h4v)((_Float16)0.0f) : wl);
-                    if (!W16 && !(LY::TAIL == kTailTwo && LY::in_tail((int)i))) put_four<LY>(lo, (int)o[j], (int)i, wl, wl);
+                if (to.has && p + j < p1) {
+                    const uint32_t place = to.place(p + j);
+                    to.put(hi, place, wh, W16 ? (h4v)((_Float16)0.0f) : wl);
+                    if (!W16 && !(LY::TAIL == kTailTwo && to.tail)) to.put(lo, place, wl, wl);
                 }
             }
         }
@@ -344,7 +381,7 @@ __device__ __forceinline__ void expand_hidden(const uint32_t *rec, const LaneLay
 }
 
 // KIND says which kinds of hidden layer there can be (kHidden...), U how many passes of a hidden layer a wavefront has under way.
-template <class LY, bool W16, bool SLOTTED, int KIND, int U>
+template <class LY, int TM, bool W16, bool SLOTTED, int KIND, int U>
 __device__ __forceinline__ void xdl_expand_layers(char *lds, const uint32_t *rec, const LaneLayers &t, int L, int l0, int l1, float pre, int tid,
                                                   int nthreads) {
     constexpr int WP = LY::WP;
@@ -379,6 +416,21 @@ __device__ __forceinline__ void xdl_expand_layers(char *lds, const uint32_t *rec
         const uint32_t out = lane_value(mine.off_hi, L - 1);
         clear(LY::TABLE, lane_value(mine.off_hi, 0) + LY::FIRST);
         clear(out, out + LY::OUT + LY::OUTLO);
+    }
+    // Rows of hidden layers' last tiles that are only padding: nothing reads what they make, but with whatever LDS held before in them the
+    // matrix unit takes more energy (256 images of 160 x 160, 4 x 40 of 16-bit weights, fp16 activations: 172.3 us instead of 166.6).
+    if (XExpand<LY::WQ>::PASSES * XExpand<LY::WQ>::ROWS < WP) {
+        constexpr int STEPS = LY::KJ + (LY::TAIL != kTailNone ? 1 : 0), LOW = LY::KJ + (LY::TAIL == kTailFull ? 1 : 0), PER = 8 * LY::G;       // words of 16 bytes a step
+        const int nwaves = nthreads >> 6;
+        for (int l = max(l0, 1) + __builtin_amdgcn_readfirstlane(tid >> 6); l < min(l1, L - 1); l += nwaves) {
+            const uint32_t hi = lane_value(mine.off_hi, l), lo = lane_value(mine.off_lo, l);
+            for (int e = lane; e < STEPS * PER; e += 64) {
+                const int j = e / PER, g = e / 8 % LY::G, m = LY::HALF ? (e & 6) * 2 + 2 + (e & 1) : TM - 8 + (e & 7);
+                const uint32_t at = (uint32_t)(((j + 1) * LY::MT - 1) * 64 + g * TM + m) * 16u;
+                *(uint4 *)(lds + hi + at) = make_uint4(0u, 0u, 0u, 0u);
+                if (lo && j < LOW) *(uint4 *)(lds + lo + at) = make_uint4(0u, 0u, 0u, 0u);
+            }
+        }
     }
     __syncthreads();
     // only the layers that have passes of this wavefront (from the lanes: those whose passes end behind its first, and begin before its end)
@@ -421,7 +473,7 @@ __device__ __forceinline__ void xdl_expand_layers(char *lds, const uint32_t *rec
         } else {
             const bool whole = !W16 && off_lo == 0;
             const float s = whole ? __uint_as_float(lane_value(__float_as_uint(mine.scale), l)) : 1.0f;
-            expand_hidden<LY, W16, KIND, U>(rec, t, l, lane, lds, (char *)hi, (char *)lo, bt, whole ? 1.0f / s : 1.0f, whole, pre);
+            expand_hidden<LY, TM, W16, KIND, U>(rec, t, l, lane, lds, (char *)hi, (char *)lo, bt, whole ? 1.0f / s : 1.0f, whole, pre);
         }
     }
     __syncthreads();
@@ -846,15 +898,15 @@ __device__ __forceinline__ void xdl_body(const DecodeArgs &a, const Work &w, flo
     uint32_t *next_tile = (uint32_t *)(lds + room);
     if (tid == 0) *next_tile = tile0 + (nthreads >> 6);
     {
-        const LaneLayers t = lane_layers<XExpand<LY::WP>::PASSES>(record, L, 0, L, tid & 63, __builtin_amdgcn_readfirstlane(tid >> 6), nthreads >> 6);
+        const LaneLayers t = lane_layers<XExpand<LY::WQ>::PASSES>(record, L, 0, L, tid & 63, __builtin_amdgcn_readfirstlane(tid >> 6), nthreads >> 6);
         constexpr XBytes bytes = xdl_bytes(TM, WQ, LY::INTS, true);
         const uint32_t need = bytes.base + (uint32_t)(L - 2) * bytes.layer;
         if (MODE == kHiddenAllInt || W16 || need + e.nbytes <= room) {     // (in one-block form a model fits with its record)
             uint32_t *stage = (uint32_t *)(lds + (room - e.nbytes));
             for (uint32_t q = tid; q < (e.nbytes >> 4); q += nthreads) ((uint4 *)stage)[q] = ((const uint4 *)record)[q];
-            xdl_expand_layers<LY, W16, false, MODE, (WP <= 32 ? 1 : 2)>(lds, stage, t, L, 0, L, a.pre, tid, nthreads);
+            xdl_expand_layers<LY, TM, W16, false, MODE, (WP <= 32 ? 1 : 2)>(lds, stage, t, L, 0, L, a.pre, tid, nthreads);
         } else {
-            xdl_expand_layers<LY, W16, false, MODE, 1>(lds, (const uint32_t *)record, t, L, 0, L, a.pre, tid, nthreads);
+            xdl_expand_layers<LY, TM, W16, false, MODE, 1>(lds, (const uint32_t *)record, t, L, 0, L, a.pre, tid, nthreads);
         }
     }
 
@@ -955,8 +1007,8 @@ __device__ __forceinline__ void xdl_stream_body(const DecodeArgs &a, const Work 
         for (int l0 = 0; l0 < L; l0 += K) {
             const int l1 = l0 + K < L ? l0 + K : L;
             __syncthreads();                                           // every wavefront is done with the previous group
-            const LaneLayers t = lane_layers<XExpand<LY::WP>::PASSES>((const uint8_t *)rec, L, l0, l1, lane, wave, nwaves);
-            xdl_expand_layers<LY, W16, true, kHiddenMixed, 1>(lds, rec, t, L, l0, l1, a.pre, tid, nthreads);
+            const LaneLayers t = lane_layers<XExpand<LY::WQ>::PASSES>((const uint8_t *)rec, L, l0, l1, lane, wave, nwaves);
+            xdl_expand_layers<LY, TM, W16, true, kHiddenMixed, 1>(lds, rec, t, L, l0, l1, a.pre, tid, nthreads);
             if (!active) continue;
             for (int l = l0; l < l1; ++l) {
                 const XLayer el = uniform_layer(tab[l]);
@@ -1046,8 +1098,8 @@ __global__ __launch_bounds__(256) void xdl_debug_kernel(const uint8_t *blob, int
     const int L = e.n_layers;
     const uint32_t *rec = (const uint32_t *)(blob + e.off);
     // one layer at a time in the slotted layout, straight from global memory: any depth fits
-    const LaneLayers t = lane_layers<XExpand<LY::WP>::PASSES>((const uint8_t *)rec, L, layer, layer + 1, tid & 63, __builtin_amdgcn_readfirstlane(tid >> 6), nthreads >> 6);
-    xdl_expand_layers<LY, W16, true, kHiddenMixed, 1>(lds, rec, t, L, layer, layer + 1, 1.0f, tid, nthreads);
+    const LaneLayers t = lane_layers<XExpand<LY::WQ>::PASSES>((const uint8_t *)rec, L, layer, layer + 1, tid & 63, __builtin_amdgcn_readfirstlane(tid >> 6), nthreads >> 6);
+    xdl_expand_layers<LY, TM, W16, true, kHiddenMixed, 1>(lds, rec, t, L, layer, layer + 1, 1.0f, tid, nthreads);
     const XLayer el = ((const XLayer *)lds)[layer];
     const LayerRec r = *(const LayerRec *)(rec + layer * (sizeof(LayerRec) / 4));
     const _Float16 *hi = (const _Float16 *)(lds + el.off_hi), *lo = (const _Float16 *)(lds + el.off_lo);
