@@ -111,26 +111,33 @@ bool allow_full_lds(const void *fn) {
 // cost, 100 images of 200 x 200, 7 x 32, took 262 us (now 170), 150 of 150 x 150, 3 x 64, 223 (155), two pictures of 1021 x 1363,
 // 9 x 32, 173 (158); of 25 shapes none lost more than 1 %.
 struct Plan { uint32_t chunks, tiles_per_chunk; };
+double rate_of(double waves) {          // ... that `waves` wavefronts a SIMD reach
+    return std::max(waves >= 3.0 ? 1.0 : (waves >= 2.0 ? 0.75 + 0.25 * (waves - 2.0) : 0.5 + 0.25 * (waves - 1.0)), 0.25);
+}
 double even_slots_us(double n_slots, uint32_t chunks, uint32_t tpc, uint32_t nw, int n_cu, int resident, double tile_us) {
     const double per_cu = std::ceil(n_slots * chunks / n_cu), at_once = std::min<double>(resident, per_cu);
-    const double waves = at_once * nw / 4.0;                         // per SIMD
-    const double rate = waves >= 3.0 ? 1.0 : (waves >= 2.0 ? 0.75 + 0.25 * (waves - 2.0) : 0.5 + 0.25 * (waves - 1.0));
     const double work = per_cu * (tpc * tile_us / 4.0 + 0.13 * tile_us + 0.3);
-    return work / std::max(rate, 0.25) + (0.26 * tile_us + 1.0) * (at_once < 1.5 ? per_cu : 1.0);
+    return work / rate_of(at_once * nw / 4.0) + (0.26 * tile_us + 1.0) * (at_once < 1.5 ? per_cu : 1.0);
 }
 // Slots of unequal cost in the split-precision kernels, heaviest first where `ordered`: while every workgroup has a place at once, the
-// heaviest model's decides, and what shares its CU; else the work there is and a part of the heaviest workgroup for the end.  Against
-// 17 ragged batches of 4 to 4000 images of 16 x 16 to 700 x 700 with up to 32 workgroups per CU it picks the best split or one within 5 %.  With
-// a workgroup per image where the other model left them, 256 images of 160 x 160 took 418 us (now 245), 64 of 300 x 300 373 (205).
-double uneven_slots_us(double n_slots, uint32_t chunks, uint32_t tpc, int n_cu, int resident, double tile_us, double heavy_us, bool ordered) {
-    const double own_us = 1.8, blocks = n_slots * chunks;             // what a workgroup costs its CU beside its tiles
-    const double mean = tpc * tile_us / 4.0 + own_us, heavy = tpc * heavy_us / 4.0 + own_us;
+// heaviest model's decides, and what shares its CU (two heavy ones may, where they are not ordered); else the work there is and a part of the
+// heaviest workgroup for the end.  Against 60 ragged batches of three stores, 1 to 1000 images of 16 x 16 to 512 x 512 with and without
+// the order, it picks the best split of its workgroup size or one within 5 % in all but three (8 %).  Without the rate of a CU's wavefronts, one
+// workgroup a CU with two tiles for each of its wavefronts looked as good as two with one: 4 images of 224 x 224 took 26.2 us (now 18.9),
+// 40 of 64 x 64 17.7 (12.4).
+double uneven_slots_us(double n_slots, uint32_t chunks, uint32_t tpc, uint32_t nw, int n_cu, int resident, double tile_us, double heavy_us, double own_us, bool ordered) {
+    const double blocks = n_slots * chunks;
+    const bool fills = resident > 1 && nw < 12;                       // a second workgroup on a CU takes issue slots that one leaves empty
+    const double rate = fills ? rate_of(std::min<double>(resident, std::ceil(blocks / n_cu)) * nw / 4.0) : 1.0;
+    const double mean = tpc * tile_us / 4.0 / rate + own_us, heavy = tpc * heavy_us / 4.0 / rate + own_us;
     if (blocks <= n_cu) return heavy;
-    if (blocks <= (double)n_cu * resident) return ordered ? heavy + mean * (blocks / n_cu - 1.0) : heavy * resident;     // unordered: two heavy ones may meet
+    if (blocks <= (double)n_cu * resident) return ordered ? heavy + mean * (blocks / n_cu - 1.0) : heavy * (fills ? blocks / n_cu + 0.1 : resident);
     return mean * blocks / n_cu + (ordered ? 0.15 : 0.6) * heavy;
 }
 enum { kEven = 0, kUneven = 1, kUnevenOrdered = 2, kUnevenFp32 = 3 };       // how a plan's time is reckoned
-Plan plan_chunks(double n_slots, uint32_t tiles, uint32_t nw, int n_cu, int resident, double tile_us, double heavy_us, int blocks_per_cu, int how) {
+// What a workgroup costs its CU beside its tiles, where slots are of unequal cost: its expansion, of twice the weights where hidden layers have low parts
+double own_us(double tile_us, bool ints) { return ints ? std::min(1.8, 0.5 + 0.6 * tile_us) : 1.8; }
+Plan plan_chunks(double n_slots, uint32_t tiles, uint32_t nw, int n_cu, int resident, double tile_us, double heavy_us, double own_us, int blocks_per_cu, int how) {
     const double expand_us = 15.0;
     if (n_slots < 1.0) n_slots = 1.0;
     Plan best{1, ((tiles + nw - 1) / nw) * nw};
@@ -150,7 +157,7 @@ Plan plan_chunks(double n_slots, uint32_t tiles, uint32_t nw, int n_cu, int resi
         const uint32_t cc = (tiles + tpc - 1) / tpc;
         if (how != kUnevenFp32) {
             const double t = how == kEven ? even_slots_us(n_slots, cc, tpc, nw, n_cu, resident, tile_us)
-                                          : uneven_slots_us(n_slots, cc, tpc, n_cu, resident, tile_us, heavy_us, how == kUnevenOrdered);
+                                          : uneven_slots_us(n_slots, cc, tpc, nw, n_cu, resident, tile_us, heavy_us, own_us, how == kUnevenOrdered);
             if (t < best_t * (how == kEven ? 0.98 : 0.99)) { best_t = t; best = Plan{cc, tpc}; }
             if (tpc <= nw) break;
             continue;
@@ -518,9 +525,14 @@ extern "C" int rinr_decode_batch_ex(rinr_store *s, const int64_t *image_ids, int
     const uint32_t full = tiles >= 96 ? 768 : (tiles >= 64 ? 512 : 256);
     const bool few = (int64_t)n * ((tiles + full / 64 - 1) / (full / 64)) * 2 <= s->n_cu;
     const bool pairs = one_grid && xdl && s->two_of_512[all16 ? 2 : (act16 ? 1 : 0)];
-    const int threads = opts->launch_threads ? opts->launch_threads : (int)(pairs ? 512 : (few ? 256 : full));
+    // in the one grid, where it is few images' tiles at one for each wavefront: workgroups of 256 while they have a CU each (16 ragged images of
+    // 64 x 64 17.0 -> 15.8 us, 64 of 32 x 32 15.1 -> 13.4; up to four tiles expanding in eight wavefronts counts more, 16 of 16 x 16 15.5
+    // and 12.7), or of 768 where 512 would put two heavy ones on a CU for want of an order (16 of 100 x 100 25.9 -> 20.8)
+    const auto side_by_side = [&](uint32_t waves) { return (int64_t)n * ((tiles + waves - 1) / waves) <= s->n_cu; };
+    const uint32_t paired = tiles > 4 && side_by_side(4) ? 256 : (!order && side_by_side(12) && !side_by_side(8) ? 768 : 512);
+    const int threads = opts->launch_threads ? opts->launch_threads : (int)(pairs ? paired : (few ? 256 : full));
     const uint32_t nw = (uint32_t)threads / 64;
-    const int how = s->even_cost ? kEven : (!xdl ? kUnevenFp32 : (order ? kUnevenOrdered : kUneven));
+    const int how = s->even_cost || (xdl && n == 1) ? kEven : (!xdl ? kUnevenFp32 : (order ? kUnevenOrdered : kUneven));
     const int knob = opts->launch_blocks_per_cu * 16 + family + (one_grid ? 8 : 0) + (order ? 4 : 0);
     const bool replan = !(s->plan_hw == HW && s->plan_n == n && s->plan_threads == threads && s->plan_knob == knob);
 
@@ -555,7 +567,7 @@ extern "C" int rinr_decode_batch_ex(rinr_store *s, const int64_t *image_ids, int
             int resident = 1;
             if (hip_fail(hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, fn, threads, lds_bytes)) || resident < 1)
                 resident = 1;
-            s->plan[0] = plan_chunks((double)n, tiles, nw, s->n_cu, resident, tile_us, s->heavy_tile_us_xdl, opts->launch_blocks_per_cu, how == kEven ? kUnevenFp32 : how);
+            s->plan[0] = plan_chunks((double)n, tiles, nw, s->n_cu, resident, tile_us, s->heavy_tile_us_xdl, own_us(tile_us, s->hidden_kind == kHiddenAllInt), opts->launch_blocks_per_cu, n_classes ? how : kUnevenFp32);
         }
         const Plan pl = s->plan[0];
         if ((uint64_t)n * pl.chunks > 0x7FFFFFFFull) return RINR_E_SIZE;
@@ -581,7 +593,7 @@ extern "C" int rinr_decode_batch_ex(rinr_store *s, const int64_t *image_ids, int
                                                                           threads, lds_bytes)) || resident < 1)
                     resident = 1;
                 s->plan[c] = plan_chunks((double)n, tiles, nw, s->n_cu, resident, xdl ? s->class_tile_us_xdl[c] : s->class_tile_us[c],
-                                         s->heavy_tile_us_xdl, opts->launch_blocks_per_cu, how);
+                                         s->heavy_tile_us_xdl, own_us(s->class_tile_us_xdl[c], s->hidden_kind == kHiddenAllInt), opts->launch_blocks_per_cu, how);
             }
             const Plan pl = s->plan[c];
             if ((uint64_t)n * pl.chunks > 0x7FFFFFFFull) return RINR_E_SIZE;

@@ -95,5 +95,19 @@ def test_a_launch_takes_the_lds_of_its_own_layout(tmp_path, flags):
         assert g["lds"] == w, (c, g["lds"], w)
 
 
+RAGGED = [(w, d, 8) for w in (24, 40, 64) for d in (3, 6)]
+# images, side, ordered -> threads, workgroups: a tile for each wavefront in as many workgroups as can run at once without sharing a CU in vain
+SPLITS = [((1, 100, False), (256, 40)), ((4, 64, False), (256, 64)), ((16, 64, False), (256, 256)), ((16, 64, True), (256, 256)), ((64, 32, False), (256, 256)),
+          ((17, 64, False), (512, 136)), ((16, 16, False), (512, 16)), ((16, 100, False), (768, 224)), ((16, 100, True), (512, 320)),
+          ((4, 224, False), (512, 392)), ((4, 224, True), (512, 392)), ((64, 64, False), (512, 512)), ((64, 64, True), (512, 512)),
+          ((256, 32, False), (512, 512)), ((256, 32, True), (512, 512))]
+
+
+def test_few_ragged_images_are_split_into_what_runs_at_once(tmp_path):
+    got = on_fake_runtime(tmp_path, [dict(groups=RAGGED, n=n, H=side, W=side, order=order, resident=2) for (n, side, order), _ in SPLITS])
+    for (c, want), g in zip(SPLITS, got):
+        assert g["rc"] == [0] * 4 and (g["threads"], g["blocks"]) == want, (c, g)
+
+
 if __name__ == "__main__":
     child(sys.argv[1], json.loads(sys.argv[2]))
