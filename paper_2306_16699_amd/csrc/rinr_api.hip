@@ -134,6 +134,9 @@ double uneven_slots_us(double n_slots, uint32_t chunks, uint32_t tpc, uint32_t n
     if (blocks <= (double)n_cu * resident) return ordered ? heavy + mean * (blocks / n_cu - 1.0) : heavy * (fills ? blocks / n_cu + 0.1 : resident);
     return mean * blocks / n_cu + (ordered ? 0.15 : 0.6) * heavy;
 }
+// Modelled time of a 64-pixel tile of a model of so many activations a pixel on one SIMD, split-precision kernels: bound by vector issue, ~20 clocks
+// an activation and lane (sine and split)
+double xdl_tile_us(double acts) { return (acts * 20.0 + 600.0) / 2400.0; }
 enum { kEven = 0, kUneven = 1, kUnevenOrdered = 2, kUnevenFp32 = 3 };       // how a plan's time is reckoned
 // What a workgroup costs its CU beside its tiles, where slots are of unequal cost: its expansion, of twice the weights where hidden layers have low parts
 double own_us(double tile_us, bool ints) { return ints ? std::min(1.8, 0.5 + 0.6 * tile_us) : 1.8; }
@@ -221,7 +224,7 @@ struct rinr_store {
     std::vector<IndexEntry> index;            // host copy of the index (debug export, diagnostics)
     double class_tile_us[kMaxClass + 1];      // modelled time of one 64-pixel tile on one SIMD
     double class_tile_us_xdl[kMaxClass + 1];
-    double heavy_tile_us_xdl;                 // ... of the heaviest model
+    double heavy_tile_us_xdl[kSizes][kMaxClass + 1];   // ... of the heaviest model that is decoded from a resident copy, per way of sizing; [0]: of all classes
     bool two_of_512[3];                       // two workgroups of 512 threads of the all-class kernel fit a CU: default, fp16 activations, all fp16
     bool xdl_ok;                              // every operand fits fp16 range after pre-scaling
     int hidden_kind;                          // kHiddenAllInt / AllRaw / Mixed over all hidden layers of all models
@@ -294,7 +297,7 @@ extern "C" int rinr_store_open_ex(const void *device_blob, const void *host_blob
     {   // split-precision kernels: kinds of hidden layer, fp16 range of every operand they would build
         const uint8_t *hb = (const uint8_t *)host_blob;
         const float pre = (float)((double)sum.header.w0 / (2.0 * M_PI));
-        double acts[kMaxClass + 1] = {0, 0, 0, 0, 0}, most = 0.0;
+        double acts[kMaxClass + 1] = {0, 0, 0, 0, 0};
         s->xdl_ok = std::fabs(sum.header.coord_lo) < 60000.0f && std::fabs(sum.header.coord_hi) < 60000.0f;   // coordinates travel as fp16 hi+lo
         int64_t tot_int = 0, tot_raw = 0;
         for (const IndexEntry &e : s->index) {
@@ -317,15 +320,12 @@ extern "C" int rinr_store_open_ex(const void *device_blob, const void *host_blob
                 if (!(wmax * std::fabs(k) < 60000.0f)) s->xdl_ok = false;
             }
             acts[c] += (e.n_layers - 1) * 16.0 * c;
-            most = std::max(most, (e.n_layers - 1) * 16.0 * c);
         }
         s->hidden_kind = tot_raw == 0 ? kHiddenAllInt : (tot_int == 0 ? kHiddenAllRaw : kHiddenMixed);
         for (uint32_t c = 1; c <= kMaxClass; ++c) {
-            // vector-ALU bound: ~20 clocks per activation per lane (sine + hi/lo split), 64 lanes = 64 pixels
             const double mean = sum.class_count[c] ? acts[c] / (double)sum.class_count[c] : 0.0;
-            s->class_tile_us_xdl[c] = (mean * 20.0 + 600.0) / 2400.0;
+            s->class_tile_us_xdl[c] = xdl_tile_us(mean);
         }
-        s->heavy_tile_us_xdl = (most * 20.0 + 600.0) / 2400.0;
         store_error_bounds(host_blob, sum, s->bounds);
     }
     // which models each kernel family decodes from a resident copy, and the LDS that takes
@@ -341,11 +341,14 @@ extern "C" int rinr_store_open_ex(const void *device_blob, const void *host_blob
     std::memset(s->n_res, 0, sizeof s->n_res);
     std::memset(s->n_str, 0, sizeof s->n_str);
     std::memset(s->str_layers, 0, sizeof s->str_layers);
+    for (auto &z : s->heavy_tile_us_xdl) std::fill(z, z + kMaxClass + 1, 0.0);
     for (const IndexEntry &e : s->index) {
         const uint32_t c = e.width == 0 ? 1u : (e.width + 15u) >> 4;
         for (int z = 0; z < kSizes; ++z) {
             if (resident_fits(s->fit_form[z], e.width, e.n_layers, e.nbytes, (uint32_t)tile_rows, budget - 16u)) {
                 ++s->n_res[z][c];
+                const double us = xdl_tile_us((e.n_layers - 1) * 16.0 * c);
+                for (const uint32_t k : {0u, c}) s->heavy_tile_us_xdl[z][k] = std::max(s->heavy_tile_us_xdl[z][k], us);
                 // with the packed record staged behind the expanded weights where the budget holds both, and the tile counter
                 const uint32_t need = resident_bytes(s->fit_form[z], e.width, e.n_layers, (uint32_t)tile_rows) + 16u;
                 s->res_lds[z][c] = std::max(s->res_lds[z][c], need + e.nbytes <= budget ? need + e.nbytes : need);
@@ -567,7 +570,7 @@ extern "C" int rinr_decode_batch_ex(rinr_store *s, const int64_t *image_ids, int
             int resident = 1;
             if (hip_fail(hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, fn, threads, lds_bytes)) || resident < 1)
                 resident = 1;
-            s->plan[0] = plan_chunks((double)n, tiles, nw, s->n_cu, resident, tile_us, s->heavy_tile_us_xdl, own_us(tile_us, s->hidden_kind == kHiddenAllInt), opts->launch_blocks_per_cu, n_classes ? how : kUnevenFp32);
+            s->plan[0] = plan_chunks((double)n, tiles, nw, s->n_cu, resident, tile_us, s->heavy_tile_us_xdl[z][0], own_us(tile_us, s->hidden_kind == kHiddenAllInt), opts->launch_blocks_per_cu, n_classes ? how : kUnevenFp32);
         }
         const Plan pl = s->plan[0];
         if ((uint64_t)n * pl.chunks > 0x7FFFFFFFull) return RINR_E_SIZE;
@@ -593,7 +596,7 @@ extern "C" int rinr_decode_batch_ex(rinr_store *s, const int64_t *image_ids, int
                                                                           threads, lds_bytes)) || resident < 1)
                     resident = 1;
                 s->plan[c] = plan_chunks((double)n, tiles, nw, s->n_cu, resident, xdl ? s->class_tile_us_xdl[c] : s->class_tile_us[c],
-                                         s->heavy_tile_us_xdl, own_us(s->class_tile_us_xdl[c], s->hidden_kind == kHiddenAllInt), opts->launch_blocks_per_cu, how);
+                                         s->heavy_tile_us_xdl[z][c], own_us(s->class_tile_us_xdl[c], s->hidden_kind == kHiddenAllInt), opts->launch_blocks_per_cu, how);
             }
             const Plan pl = s->plan[c];
             if ((uint64_t)n * pl.chunks > 0x7FFFFFFFull) return RINR_E_SIZE;

@@ -109,5 +109,16 @@ def test_few_ragged_images_are_split_into_what_runs_at_once(tmp_path):
         assert g["rc"] == [0] * 4 and (g["threads"], g["blocks"]) == want, (c, g)
 
 
+def test_a_class_is_split_by_its_own_heaviest_model(tmp_path):
+    """Class by class, the models of another class do not count: 64 units are split as in a store without the deep 16-unit model."""
+    alone = [(64, d, 8) for d in (2, 3)]
+    cases = [dict(groups=g, n=n, H=side, W=side, order=order, resident=2, one_grid_min_tiles=1 << 30)
+             for n in (4, 16, 64, 300) for side in (32, 64, 100, 224) for order in (False, True) for g in (alone, [(16, 15, 8)] * 2 + alone)]
+    got = on_fake_runtime(tmp_path, cases)
+    for c, a, b in zip(cases[::2], got[::2], got[1::2]):
+        assert a["rc"] == b["rc"] == [0] * 4 and b["launches"] == a["launches"] + 1, c
+        assert (a["threads"], a["blocks"]) == (b["threads"], b["blocks"]), (c, a, b)
+
+
 if __name__ == "__main__":
     child(sys.argv[1], json.loads(sys.argv[2]))
