@@ -99,6 +99,9 @@ int rinr_fit_create_ex(const rinr_fit_arch *arch, int64_t n_images, int32_t H, i
 /* Which kernels this handle's steps run: RINR_FIT_KERNEL_*; RINR_E_NULL on NULL.  (Sec. VI-A fixes the method, not the
  * arithmetic; both families meet the same parity bar against the fp64 reference.) */
 int rinr_fit_kernel_family(const rinr_fit *fit);
+/* Units of a hidden layer that they compute: the widest layer's rounded up to 16, to 8 in the fp32 kernels and in the split-precision ones that
+ * leave half of a last tile out; RINR_E_NULL on NULL. */
+int rinr_fit_kernel_units(const rinr_fit *fit);
 int rinr_fit_destroy(rinr_fit *fit);
 int64_t rinr_fit_n_params(const rinr_fit *fit);        /* per image; < 0 on NULL */
 

@@ -536,6 +536,7 @@ struct rinr_fit {
     int wq, lds_floats;         // wq: widest hidden layer rounded up to a multiple of 8 (fp32 kernels); lds_floats 0 = no fp32 kernel fits
     int family;                 // RINR_FIT_KERNEL_FP32 or RINR_FIT_KERNEL_SPLIT16: the kernels this handle's steps run
     Fit16 k16;                  // their kernel; null = none is built for the shape
+    int units;                  // of a hidden layer that the handle's kernel computes (rinr_fit_kernel_units)
     float *emag;                // [n_images] error size seen by the last step (split kernels' error scale); 0 = none yet
     int32_t p_off[kMaxL];
     float *params, *m, *v, *loss, *scratch_grad;
@@ -604,6 +605,7 @@ extern "C" int rinr_fit_create_ex(const rinr_fit_arch *arch, int64_t n_images, i
     // the split-precision kernels where they are built for the shape, the fp32 ones otherwise or on request
     f->family = (f->k16.fn && !(flags & RINR_FIT_FLAG_FP32_MFMA)) ? RINR_FIT_KERNEL_SPLIT16 : RINR_FIT_KERNEL_FP32;
     if (f->family == RINR_FIT_KERNEL_FP32 && f->lds_floats == 0) { delete f; return RINR_E_UNSUPPORTED; }
+    f->units = f->family == RINR_FIT_KERNEL_FP32 || half ? f->wq : (wmax + 15) / 16 * 16;
     f->n_params = 0;
     for (int l = 0; l < arch->n_layers; ++l) {
         f->p_off[l] = (int32_t)f->n_params;
@@ -631,6 +633,7 @@ extern "C" int rinr_fit_create_ex(const rinr_fit_arch *arch, int64_t n_images, i
         const Fit16 k = kernel16_for(wmax, arch->n_layers, false);
         if (k.fn && !hip_fail(hipFuncSetAttribute((const void *)k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit - 256))) {
             f->k16 = k;
+            f->units = (wmax + 15) / 16 * 16;
             f->splits = plan_splits(f, (const void *)k.fn);
         }
     }
@@ -649,6 +652,7 @@ extern "C" int rinr_fit_create(const rinr_fit_arch *arch, int64_t n_images, int3
 }
 
 extern "C" int rinr_fit_kernel_family(const rinr_fit *f) { return f ? f->family : RINR_E_NULL; }
+extern "C" int rinr_fit_kernel_units(const rinr_fit *f) { return f ? f->units : RINR_E_NULL; }
 
 extern "C" int rinr_fit_destroy(rinr_fit *f) {
     if (!f) return RINR_OK;

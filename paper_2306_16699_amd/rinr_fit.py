@@ -17,7 +17,7 @@ MAX_LAYERS = 12
 FIT_FLAG_FP32_MFMA = 1
 KERNEL_FP32, KERNEL_SPLIT16 = 0, 1
 EXPORTS = ["rinr_prune_ratio", "rinr_l1_mask", "rinr_quantize_layer", "rinr_fit_create", "rinr_fit_create_ex", "rinr_fit_kernel_family",
-           "rinr_fit_destroy",
+           "rinr_fit_kernel_units", "rinr_fit_destroy",
            "rinr_fit_n_params", "rinr_fit_set_params", "rinr_fit_set_keep", "rinr_fit_reset_optimizer",
            "rinr_fit_get_params", "rinr_fit_steps", "rinr_fit_loss_grad", "rinr_fit_last_loss", "rinr_psnr_batch", "rinr_encode_blob_bound",
            "rinr_encode_images"]
@@ -53,6 +53,7 @@ def lib():
         L.rinr_fit_create.argtypes = [C.POINTER(FitArch), i64, i32, i32, C.POINTER(vp)]
         L.rinr_fit_create_ex.argtypes = [C.POINTER(FitArch), i64, i32, i32, C.c_uint32, C.POINTER(vp)]
         L.rinr_fit_kernel_family.argtypes = [vp]
+        L.rinr_fit_kernel_units.argtypes = [vp]
         L.rinr_fit_destroy.argtypes = [vp]
         L.rinr_fit_n_params.argtypes = [vp]
         L.rinr_fit_n_params.restype = i64
@@ -127,6 +128,7 @@ class Fit:
                     "rinr_fit_create_ex")
         self._h = h
         self.kernel_family = int(lib().rinr_fit_kernel_family(h))      # KERNEL_FP32 or KERNEL_SPLIT16
+        self.kernel_units = int(lib().rinr_fit_kernel_units(h))        # of a hidden layer, with padding
         self.n_params = int(lib().rinr_fit_n_params(h))
 
     def close(self):
