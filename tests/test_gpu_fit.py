@@ -196,6 +196,13 @@ def test_start_of_a_fit_under_a_mask(widths, n):
     g.set_params(p0)
     g.steps(tgt, 2, 1e-3, t0=0, T=8)
     np.testing.assert_array_equal(again, g.get_params())       # nothing is left of the first fit: moments, error history
+    # a mask that prunes nothing, set in the middle: the moments and the count of steps go on (without them this step would be 0.64 lr where it is
+    # near lr); only the error's scale starts anew, which moves no more than rounding
+    f.set_keep(np.ones_like(keep))
+    f.steps(tgt, 1, 1e-3, t0=2, T=8)
+    g.steps(tgt, 1, 1e-3, t0=2, T=8)
+    off = np.abs(f.get_params() - g.get_params())
+    assert np.mean(off > 0.02e-3) < 0.01 and off.max() <= 2e-3
     f.close()
     g.close()
 

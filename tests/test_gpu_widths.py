@@ -85,9 +85,16 @@ def test_splits_of_ragged_batches(torch, n, H, W):  # noqa: F811
     sel = (np.arange(n) * 7) % len(ms)
     ids, ws = ids_dev(torch, sel), torch.empty(rinr.workspace_bytes(n), dtype=torch.uint8, device="cuda")
     got = st.decode_batch_ex(ids, H, W, rinr.OUT_F32)
+    tiles = -(-H * W // 64)
+    assert st.last_launch_info()["workgroups"] > n or tiles <= 8
+    copies = -(-torch.cuda.get_device_properties(0).multi_processor_count // n)            # a workgroup a CU is then one for each image, or less
+    whole = st.decode_batch_ex(ids.repeat(copies), H, W, rinr.OUT_F32, blocks_per_cu=1)
+    assert st.last_launch_info()["workgroups"] == n * copies
+    for k in range(copies):
+        assert torch.equal(got, whole[k * n:k * n + n]), k
     assert torch.equal(got, st.decode_batch_ex(ids, H, W, rinr.OUT_F32, workspace=ws))
-    assert torch.equal(got, st.decode_batch_ex(ids, H, W, rinr.OUT_F32, blocks_per_cu=1))
-    assert np.abs(got[:5].cpu().numpy() - oracle.decode(ms, sel[:5], H, W)).max() <= TIGHT
+    some = np.unique(np.linspace(0, n - 1, 13).astype(int))
+    assert np.abs(got.cpu().numpy()[some] - oracle.decode(ms, sel[some], H, W)).max() <= TIGHT
     st.close()
 
 
