@@ -518,8 +518,15 @@ bool half_filled(int width, int L) {
 // Pixels of a workgroup's share from which they pay: a step's start and end, the same for any share, are longer in them.  us a step of one image
 // of 25 x 17, all units of the last tile -> the half-filled tile's kernel: 10 layers x 24 29.3 -> 32.4, 4 x 40 19.2 -> 21.3, 6 x 49 39.5 -> 45.0,
 // and of 300 of 32 x 32 (512 pixels a share): 163 -> 161, 92.9 -> 90.0, 259 -> 273; 8 of 171 x 219 (1216), 4 x 56: 97.9 -> 94.1, 6 x 56:
-// 162.8 -> 165.8.  Up to 8 units they are the faster ones from 8 x 8 pixels.
-int64_t half_pays_from(int width, int L) { return width <= 8 ? 0 : (width <= 40 ? 256 : 832 * (L - 3)); }
+// 162.8 -> 165.8.  Up to 8 units they are the faster ones from 8 x 8 pixels.  1024 images, one share each, of 256 pixels: 2 layers x 40 26.1 -> 24.4, 4 x 40
+// 85.6 -> 83.4, 10 x 40 446 -> 405, 3 x 24 34.4 -> 31.9, 7 x 24 90.0 -> 85.5.  Models of 17 to 24 units and 8 layers or more leave no registers for
+// a wavefront more than whole tiles do, and gain later: 8 x 24 at 256, 384, 448, 512 pixels 103.3 -> 104.3, 122.8 -> 123.5, 133.1 -> 132.3, 143.6 -> 141.7;
+// 9, 10 and 11 layers at 256 171.5 -> 173.3, 192.3 -> 195.6, 211.9 -> 214.1, at 320 198.7 -> 195.7, 221.9 -> 220.3, 245.0 -> 242.2.
+int64_t half_pays_from(int width, int L) {
+    if (width <= 8) return 0;
+    if (width <= 24 && L >= 8) return L == 8 ? 448 : 257;
+    return width <= 40 ? 256 : 832 * (L - 3);
+}
 Fit16 kernel16_for(int width, int L, bool half) {
     const int wp = (width + 15) / 16 * 16;
     const Fit16 k = half ? (wp == 16 ? kernel16_of<16, true>(L) : (wp == 32 ? kernel16_of<32, true>(L) : (wp == 48 ? kernel16_of<48, true>(L) : kernel16_of<64, true>(L))))

@@ -18,6 +18,15 @@ def units(widths, half):
     return -(-max(widths[1:-1]) // step) * step
 
 
+def half_from(width, L):
+    """Pixels of a workgroup's share from which a handle takes the half-filled kernel."""
+    if width <= 8:
+        return 0
+    if width <= 24 and L >= 8:
+        return 448 if L == 8 else 257
+    return 256 if width <= 40 else 832 * (L - 3)
+
+
 def error_factors(widths, p, w0=30.0):
     """The power of two each layer but the first multiplies the error by on the way down: the nearest to the inverse of its estimated gain."""
     out = []
@@ -94,11 +103,11 @@ def test_every_depth_where_a_workgroup_takes_few_pixels(L):
 
 @pytest.mark.parametrize("L", range(2, 13))
 def test_every_depth_where_a_workgroup_takes_many_pixels(L):
-    """With many images a workgroup takes a whole one, and the kernels of half-filled tiles run from 256 pixels a share (49 to 56 units:
-    832 times the depth less 3) on: just below that and at it."""
+    """With many images a workgroup takes a whole one, and the kernels of half-filled tiles run from 256 pixels a share on (8 layers of 17 to 24
+    units 448, more of them 257; 49 to 56 units 832 times the depth less 3): just below that and at it."""
     for width in (8, 24, 17) + ((40, 33) if L <= 10 else ()):
-        for H, W in ((15, 17), (16, 16), (17, 17)):
-            check([2] + [width] * (L - 1) + [3], H=H, W=W, copies=600, half=width <= 8 or H * W >= 256)
+        for H, W in ((15, 17), (16, 16), (17, 17)) if (width > 24 or L != 8) else ((17, 17), (21, 21), (16, 28)):
+            check([2] + [width] * (L - 1) + [3], H=H, W=W, copies=600, half=H * W >= half_from(width, L))
     if 4 <= L <= 6:
         for width, H in ((56, 26 * (L - 3)), (49, 26 * (L - 3)), (51, 26 * (L - 3) - 1)):
             check([2] + [width] * (L - 1) + [3], n=1, H=H, W=32, copies=1024, half=width != 51)
@@ -117,7 +126,7 @@ def test_large_layers_take_the_form_that_scales_the_cosine(L):
     layer of a model in turn."""
     copies = -(-1200 // (L - 1))
     for width in (8, 5, 24, 17) + ((40, 33) if L <= 10 else ()):
-        check([2] + [width] * (L - 1) + [3], H=17, W=16, copies=copies, half=True, large=True)
+        check([2] + [width] * (L - 1) + [3], H=28 if half_from(width, L) > 257 else 17, W=16, copies=copies, half=True, large=True)
     if 4 <= L <= 6:
         for width in (56, 49):
             check([2] + [width] * (L - 1) + [3], H=26 * (L - 3), W=32, copies=1024 // (L - 1), half=True, large=True)
