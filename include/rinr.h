@@ -197,8 +197,8 @@ typedef struct {
     int32_t launch_blocks_per_cu;  /* fixed grid target in workgroups per compute unit (1..1024) instead of
                                       the built-in cost model's split of each slot's pixels              */
     int32_t one_grid_min_tiles;    /* stores that mix width classes decode images of at least this many
-                                      64-pixel tiles in one grid, smaller ones class by class (0: the
-                                      library's choice)                                                  */
+                                      64-pixel tiles in one grid, smaller ones class by class (0: 1 in the
+                                      split-precision kernels, 64 in the fp32 ones)                      */
 } rinr_decode_opts;
 
 /* Bytes of rinr_decode_opts.workspace a batch of n slots needs (4 per slot). */

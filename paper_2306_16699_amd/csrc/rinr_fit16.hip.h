@@ -13,11 +13,12 @@
 //
 // What bounds it is instruction issue: a matrix instruction takes two issue slots of 4.1 clocks, a sine or cosine two, other
 // vector instructions one (measured; matrix and vector instructions of one wavefront overlap where they alternate).  A hidden
-// layer of 48 units takes 48 matrix and 169 vector slots per 16 pixels backward, 15 and 52 forward.  At 10 layers x 40, padded to 48, the matrix
-// unit was busy 46 % of the time and vector issue 53 % (the matrix instructions' included), but only 27 % of the matrix time had
-// vector instructions beside it, and a wavefront waited 24 % of its time for loads and barriers and 15 % to issue.
-// Measured, ms a step, gradient tiles shared -> a wavefront's own -> layers interleaved (see the kernel): 256 images of 224 x 224,
-// 10 layers x 40: 8.91 -> 6.83 -> 6.29; 10 x 32: 4.54 -> 3.50 -> 3.00; 2048 of 32 x 32, 3 x 15: 0.0934 -> 0.0738 -> 0.0675.
+// layer of 48 units takes 48 matrix and 169 vector slots per 16 pixels backward, 15 and 52 forward.  At 10 layers x 40, with a half-filled last tile, the
+// matrix unit is busy 47 % of the time and vector issue 56 % (the matrix instructions' included), but only 27 % of the matrix time has
+// vector instructions beside it, and a wavefront waits 20 % of its time for loads and barriers and 15 % to issue.
+// Measured, ms a step, gradient tiles shared -> a wavefront's own -> layers interleaved (see the kernel) -> half-filled tiles, inputs in LDS
+// (Shape): 256 images of 224 x 224, 10 layers x 40: 8.91 -> 6.83 -> 6.29 -> 5.00; 10 x 32: 4.54 -> 3.50 -> 3.00, and no more; 2048 of
+// 32 x 32, 3 x 15: 0.0934 -> 0.0738 -> 0.0675 -> 0.0655.
 //
 // Two orientations.  P: lane (n, g) holds pixel n and, per 16-row tile of a layer's units, the quad of units 4 g + v.  That is
 // what a matrix instruction leaves with the units as its rows, and two tiles' quads side by side are exactly the B operand
@@ -46,9 +47,11 @@
 // gradient is multiplied by at the end.
 // A layer's factor above 1 (the usual case) is in its transposed weights: times a power of two both halves stay exact.  Below 1
 // (an estimated gain above 1.4) the low half would go into fp16's subnormals, 1.1e-7 of the weights' size instead of 4.6e-8
-// (64 units, factor 1/64), so such a factor multiplies the cosine in fp32.  One more multiply per unit costs every model
-// 2 to 6 % (10 layers x 40: 6.26 -> 6.65 ms a step); so the code over the pixels is there twice, and a model takes the form with the
-// multiply only if one of its factors is below 1.  The other form's times stay (10 x 40: 6.27 -> 6.24 ms, 3 x 15: 0.0677 -> 0.0679).
+// (64 units, factor 1/64), so such a factor multiplies the cosine in fp32.  One more multiply per unit, and where registers are scarce the
+// slower order, cost up to 12 %; so the code over the pixels is there twice, and a model takes the form with the multiply only if one
+// of its factors is below 1.  us a step, without and with: 256 images of 224 x 224, 10 layers x 40 5000 and 5530; 512, 10 x 32 6020 and 6540; of 96 x 96,
+// 5 x 24 364 and 366; 256, 5 x 56 717 and 802; 1024 of 64 x 64, 3 x 8 79 and 82; 2048 of 32 x 32, 3 x 15 66.0 and 68.2.  Having both costs the other form
+// nothing (10 x 40, whole last tile: 6.27 -> 6.24 ms).
 #pragma once
 
 namespace fit16 {
@@ -66,12 +69,14 @@ constexpr int fit16_registers(int wp, int ml, int nt) {
     const int mt = wp / 16;
     return 4 * (2 * mt + (ml - 2) * mt * mt) + 4 * nt * mt * (ml - 1) + 40 + 16 * nt * mt;
 }
-// Wavefronts per SIMD a kernel is compiled for: as many as its estimate leaves without a spill, but for one shape, which spills
-// at three and is the better for it.  Measured, us a step, spilled -> as chosen:
+// Wavefronts per SIMD a kernel is compiled for: as many as its estimate leaves.  The estimate does not count the addresses and operands of
+// the inputs in LDS, and so four kernels spill: 7 layers x 16 at three wavefronts (33 registers), 5 x 32 (8), 8 x 32 (28) and 8 x 24 (15) at two.  With
+// the inputs in LDS and these spills against the kernels before (of them 7 x 16 alone spilled, 24): 512 images of 96 x 96, 5 x 32 500 -> 459, 256 of 96 x 96, 8 x 32 475 -> 478 and 8 x 24 (half-filled
+// tile) 441 -> 396, 1024 of 64 x 64, 7 x 16 343 -> 312.  Measured, us a step, spilled -> as chosen:
 //   four instead of three, 48 x 48, width 16, 2048 images: 4 layers 198 -> 189, 5 layers 249 -> 241; 6144 images: 561 -> 555, 692 -> 691;
 //     against it only where four make whole rounds (1024 images of 64 x 64, width 15): 175 -> 180, 219 -> 227
 //   two instead of three: 8 layers x 16: 243 -> 232; 3 x 32: 150 -> 144
-//   three (spills 24) instead of two at 7 layers x 16, 48 x 48: 6144 images 1063 -> 1001; against it 1024 of 64 x 64: 319 -> 328
+//   three (spilling) instead of two at 7 layers x 16, 48 x 48: 6144 images 1063 -> 1001; against it 1024 of 64 x 64: 319 -> 328
 constexpr int fit16_waves_per_simd(int wp, int ml, int nt) {
     const int r = fit16_registers(wp, ml, nt);
     return r <= 100 ? 4 : (r <= 156 ? 3 : (r <= 256 ? 2 : 1));

@@ -58,8 +58,9 @@ enum { kWeight16 = 8 };
 // beside it by a clock per operand register, so a 32-row step, which does twice the work of a 16-row one on as many, delays
 // less; but it takes more energy for it, and these kernels run at the card's power limit (a stream of 32-row steps on random operands runs at
 // 1.73 GHz, of 16-row ones at 1.9, on zeros both at 2.4), and its accumulators are harder to place.  us, 32 -> 16 rows, on two cards: 256 images
-// of 160 x 160, 4 x 32: 154.5 -> 147.7 and 148.6 -> 144.7, of fp32 weights 171 -> 159 and 161 -> 152, the reduced
-// modes (one term, the lightest on the matrix unit) 110 -> 104 and 103.0 -> 103.5, 114 -> 114 and 111.8 -> 113.5; 4 x 64: 349.5 -> 337.5.  At 24 units a 32-row tile has three
+// of 160 x 160, 4 x 32: 154.5 -> 147.7 and 148.6 -> 144.7, of fp32 weights 171 -> 159 and 161 -> 152; 4 x 64: 349.5 -> 337.5.  The reduced modes (one
+// term, the lightest on the matrix unit) keep 32 rows there: all in fp16 16 are no better on either card (114 -> 114, 111.8 -> 113.5), with fp16
+// activations on one of them only (110 -> 104, 103.0 -> 103.5).  At 24 units a 32-row tile has three
 // quads a lane and the odd one's terms take one step, while 16-row ones make a pair of a full and a half-filled tile: 126.9 against 128.2.
 __host__ __device__ constexpr int xdl_tile_rows(int wq, int mode) {
     return wq == 24 || (wq == 32 && (mode & (kAct16 | kWeight16))) ? 32 : 16;
@@ -511,8 +512,9 @@ template <> struct XTile<32> {
 // sine of four accumulator values (one quad), then the exact hi/lo split of the results: hi = fp16(h), lo = fp16(h - hi).
 // The four differences come from one small matrix step, v_mfma_f32_4x4x4_16b_f16, C operand h, B operand hi, A operand minus the
 // unit matrix (`neg_unit`): its 16 blocks are four lanes each, and with that A a lane gets its own C less its own B back.
-// One product per sum and a difference that 32 bits hold: exact, and the outputs are those of the
-// four mixed-precision subtractions (v_fma_mix_f32) that it replaces, byte for byte.  Those took 4.9 clocks each beside matrix work,
+// One product per sum and a difference that 32 bits hold: exact, and for finite activations the outputs are those of the
+// four mixed-precision subtractions (v_fma_mix_f32) that it replaces, byte for byte.  (A sine is NaN only for a pre-activation that is no finite
+// number; the step's products by zero then make the low parts of its whole quad NaN, which in a half-filled last tile is two pixels'.)  Those took 4.9 clocks each beside matrix work,
 // this step takes about 4.2 (a matrix step delays vector instructions by a clock per operand register of A and B, and has two
 // of each here, against four of each in a 16x16x32 step).  us before -> now: 256 images of 224 x 224, 6 x 64: 986 -> 955; 4096 of
 // 32 x 32, 4 x 32: 109.3 -> 104.0; 64 of 224 x 224, 9 x 40: 283 -> 268; 256 of 160 x 160, 4 x 16: 88.2 -> 83.1, 4 x 64 of fp32 weights: 415 -> 408.
