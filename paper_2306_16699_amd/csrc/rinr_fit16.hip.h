@@ -11,14 +11,16 @@
 // in LDS, and after the last, when the wavefronts' gradients are added up.  The version before this shared the gradient tiles
 // among eight wavefronts: fewer registers, but every layer's errors and inputs went through LDS between two barriers.
 //
-// What bounds it is instruction issue: a matrix instruction takes two issue slots of 4.1 clocks, a sine or cosine two, other
-// vector instructions one (measured; matrix and vector instructions of one wavefront overlap where they alternate).  A hidden
-// layer of 48 units takes 48 matrix and 169 vector slots per 16 pixels backward, 15 and 52 forward.  At 10 layers x 40, with a half-filled last tile, the
+// What bounds it is instruction issue: a matrix instruction takes 8 clocks of it (and 16 of the matrix unit), a sine or cosine 8, any other
+// instruction 4, s_nop 4 a wait state; an LDS read is back after 64 (measured in streams of them and on pieces of this kernel, one wavefront
+// per SIMD; a sum over the instructions of a piece in order, with those latencies, gives its measured time to 3 %).  A hidden
+// layer of 48 units takes 48 matrix and 169 vector slots per 16 pixels backward, 15 and 52 forward.  So a lone wavefront loses what it waits
+// in order: for operand words from LDS and for matrix results (see kDownFirst).  At 10 layers x 40, with a half-filled last tile, the
 // matrix unit is busy 47 % of the time and vector issue 56 % (the matrix instructions' included), but only 27 % of the matrix time has
 // vector instructions beside it, and a wavefront waits 20 % of its time for loads and barriers and 15 % to issue.
 // Measured, ms a step, gradient tiles shared -> a wavefront's own -> layers interleaved (see the kernel) -> half-filled tiles, inputs in LDS
-// (Shape): 256 images of 224 x 224, 10 layers x 40: 8.91 -> 6.83 -> 6.29 -> 5.00; 10 x 32: 4.54 -> 3.50 -> 3.00, and no more; 2048 of
-// 32 x 32, 3 x 15: 0.0934 -> 0.0738 -> 0.0675 -> 0.0655.
+// (Shape) -> words loaded ahead (kDownFirst): 256 images of 224 x 224, 10 layers x 40: 8.91 -> 6.83 -> 6.29 -> 5.00 -> 4.69; 10 x 32: 4.54 -> 3.50 ->
+// 3.00, no more from the half-filled tiles, -> 2.88; 2048 of 32 x 32, 3 x 15: 0.0934 -> 0.0738 -> 0.0675 -> 0.0655.
 //
 // Two orientations.  P: lane (n, g) holds pixel n and, per 16-row tile of a layer's units, the quad of units 4 g + v.  That is
 // what a matrix instruction leaves with the units as its rows, and two tiles' quads side by side are exactly the B operand
@@ -47,10 +49,10 @@
 // gradient is multiplied by at the end.
 // A layer's factor above 1 (the usual case) is in its transposed weights: times a power of two both halves stay exact.  Below 1
 // (an estimated gain above 1.4) the low half would go into fp16's subnormals, 1.1e-7 of the weights' size instead of 4.6e-8
-// (64 units, factor 1/64), so such a factor multiplies the cosine in fp32.  One more multiply per unit, and where registers are scarce the
-// slower order, cost up to 12 %; so the code over the pixels is there twice, and a model takes the form with the multiply only if one
-// of its factors is below 1.  us a step, without and with: 256 images of 224 x 224, 10 layers x 40 5000 and 5530; 512, 10 x 32 6020 and 6540; of 96 x 96,
-// 5 x 24 364 and 366; 256, 5 x 56 717 and 802; 1024 of 64 x 64, 3 x 8 79 and 82; 2048 of 32 x 32, 3 x 15 66.0 and 68.2.  Having both costs the other form
+// (64 units, factor 1/64), so such a factor multiplies the cosine in fp32.  One more multiply per unit costs up to 5 %,
+// so the code over the pixels is there twice, and a model takes the form with the multiply only if one
+// of its factors is below 1.  us a step, without and with: 256 images of 224 x 224, 10 layers x 40 4690 and 4900; 512, 10 x 32 5730 and 5890; of 96 x 96,
+// 5 x 24 364 and 366; 256, 4 x 56 430 and 445; 1024 of 64 x 64, 3 x 8 79 and 82; 2048 of 32 x 32, 3 x 15 66.0 and 68.2.  Having both costs the other form
 // nothing (10 x 40, whole last tile: 6.27 -> 6.24 ms).
 #pragma once
 
@@ -379,6 +381,22 @@ template <int WP, bool HALF, int L, int NT, bool kBelow> __device__ __forceinlin
     typedef Shape<WP, HALF> S;
     constexpr int MT = S::MT, NH = L - 2, kPC = kWaves * 16 * NT;
     constexpr int kColOut = 11, kColFirst = 12;         // columns of acc_b: step u's biases in column u, the output layer's, the first layer's bias, x and y
+    constexpr int kRegisters = fit16_registers(WP, L, NT);
+    // The order of a lone wavefront's work, which nothing else hides the waits of.  Everywhere: the first layer's words are loaded before the
+    // coordinates are formed, the output layer's before its last contraction, and the way down's (kAhead tiles of them) at the layer's start, where
+    // the split of the error covers them.  kDownFirst: all of the way down's words at once, the contraction with nothing else beside it, and the output
+    // layer's input is turned before the output is there.  That is the faster one with four tiles, and with three where registers are
+    // scarcest and a half tile spares some; else two tiles' words ahead and the compiler's own order are.  Clocks per 16 NT
+    // pixels of a wavefront as the compiler orders them, before -> two tiles ahead, kDownFirst: 10 layers x 32 16500 -> 15600, 19900; 10 x 40 14540 ->
+    // 14140 with spills, 13090; 8 x 40 11610 -> 10460, 11020; 8 x 48 13530 -> 12020, 12990; 6 x 56 13500 -> 13390, 12680; 6 x 64 13740 -> 13950, 13340.  us a step,
+    // 256 images of 96 x 96, before -> now: 5 x 40 389 -> 372, 8 x 40 793 -> 722, 6 x 48 564 -> 554, 8 x 48 908 -> 822, 10 x 48 1221 -> 1128, 4 x 56 458 -> 430, 6 x 56 892 ->
+    // 848, 4 x 64 510 -> 469, 6 x 64 932 -> 898, 10 x 24 488 -> 474, 12 x 32 726 -> 687; against it 12 x 24 589 -> 593.  The form with the multiply (kBelow): 10 x 24 570 ->
+    // 494, 10 x 48 1320 -> 1121, 6 x 64 1019 -> 921.
+    // kTight: the one kernel (10 layers x 48) that spills (see FIT16_EDGE) where the first layer's words are ahead or the contraction is not first.
+    constexpr bool kAlone = fit16_waves_per_simd(WP, L, NT) == 1, kTight = !HALF && kRegisters > 500;
+    constexpr bool kDownFirst = kAlone && !kTight && (MT == 4 || (MT == 3 && (kBelow ? HALF || kRegisters <= 480 : HALF && kRegisters > 480)));
+    constexpr bool kFirstAhead = kAlone && !kTight;
+    constexpr int kAhead = !kAlone ? 1 : (kDownFirst || MT < 2 ? MT : 2);          // row tiles whose operand words the way down loads ahead
     const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
     const h4v zh = {(_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f};
     Misc *const misc = (Misc *)(lds + S::MISC);
@@ -474,27 +492,20 @@ template <int WP, bool HALF, int L, int NT, bool kBelow> __device__ __forceinlin
 
     for (uint32_t c = share.c0; c < share.c1; ++c) {
         int stop = 0;                      // see FIT16_EDGE
-        float x[NT], y[NT], want[NT];
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt) {
-            const uint32_t p = min(pixel(c, nt), a.HW - 1);
-            const uint32_t row = a.wmagic ? (__umulhi(p, a.wmagic) >> a.wshift) : p, col = p - row * a.W;
-            x[nt] = fmaf(a.span, (float)(2 * col + 1) * a.inv2W, a.lo);
-            y[nt] = fmaf(a.span, (float)(2 * row + 1) * a.inv2H, a.lo);
-            want[nt] = tgt[nt];
-            tgt[nt] = target(c + 1 < share.c1 ? c + 1 : c, nt);             // the next pixels' targets are under way during this chunk
-        }
 
         // ---- forward.  First layer on the vector ALU (two inputs); hidden layers: Z = W H + b
         h4v Bh[NT][MT], Bl[NT][MT];
-        auto first = [&](f32x4 (&z)[NT][MT]) {
+        float x[NT], y[NT], want[NT];
+        float4 w0[MT][4];
+        auto first_word = [&](int t, int v) { w0[t][v] = ((const float4 *)(lds + S::W0))[16 * t + (S::mixed(t) ? 2 : 4) * g + v]; };
+        auto first = [&](f32x4 (&z)[NT][MT], bool ahead) {             // ahead: its words are loaded
 #pragma unroll
             for (int t = 0; t < MT; ++t)
 #pragma unroll
                 for (int v = 0; v < (S::mixed(t) ? 2 : 4); ++v) {
-                    const float4 w = ((const float4 *)(lds + S::W0))[16 * t + (S::mixed(t) ? 2 : 4) * g + v];
+                    if (!ahead) first_word(t, v);
 #pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) z[nt][t][v] = fmaf(w.x, x[nt], fmaf(w.y, y[nt], w.z));
+                    for (int nt = 0; nt < NT; ++nt) z[nt][t][v] = fmaf(w0[t][v].x, x[nt], fmaf(w0[t][v].y, y[nt], w0[t][v].z));
                 }
         };
         Words<WP, HALF, MT> W;
@@ -525,8 +536,25 @@ template <int WP, bool HALF, int L, int NT, bool kBelow> __device__ __forceinlin
         };
         {
             f32x4 z0[NT][MT];
-            first(z0);
+            if (kFirstAhead) {
+#pragma unroll
+                for (int t = 0; t < MT; ++t)
+#pragma unroll
+                    for (int v = 0; v < (S::mixed(t) ? 2 : 4); ++v) first_word(t, v);
+            }
+            if (kDownFirst) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int nt = 0; nt < NT; ++nt) {
+                const uint32_t p = min(pixel(c, nt), a.HW - 1);
+                const uint32_t row = a.wmagic ? (__umulhi(p, a.wmagic) >> a.wshift) : p, col = p - row * a.W;
+                x[nt] = fmaf(a.span, (float)(2 * col + 1) * a.inv2W, a.lo);
+                y[nt] = fmaf(a.span, (float)(2 * row + 1) * a.inv2H, a.lo);
+                want[nt] = tgt[nt];
+                tgt[nt] = target(c + 1 < share.c1 ? c + 1 : c, nt);             // the next pixels' targets are under way during this chunk
+            }
+            first(z0, kFirstAhead);
             begin(0);
+            if (kDownFirst) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -550,16 +578,26 @@ template <int WP, bool HALF, int L, int NT, bool kBelow> __device__ __forceinlin
             blocks(u + 1, 0, kBlocks - 1);
         }
         FIT16_EDGE;
+        h8v out_words[MT];
+        h4v inh[NT][MT], inl[NT][MT];      // the output layer's input, turned
+        if (kAlone) {
+#pragma unroll
+            for (int t = 0; t < MT; ++t) out_words[t] = *(const h8v *)(base + S::LASTT + t * 1024);
+        }
         blocks(NH, kBlocks - 1, kBlocks);
+        if (kDownFirst) {
+#pragma unroll
+            for (int i = 0; i < MT; ++i)
+#pragma unroll
+                for (int nt = 0; nt < NT; ++nt) turn(Bh[nt], Bl[nt], i, inh[nt][i], inl[nt][i]);
+        }
 
         // ---- output layer
         f32x4 E[NT][MT];                   // the error at hand, scaled (see the file header)
         h4v Eh[NT][MT], El[NT][MT];
         // Its split belongs to the end of the layer that leaves it, beside that layer's weight gradient (10 layers x 32: 6.08 ->
-        // 6.00 ms a step); where registers are scarce, to the start of the next; and where they are scarcest (one kernel: padded width
-        // 48, 10 layers), the contraction comes before the turning: nothing may be spilled there (see FIT16_EDGE), and the
-        // faster order, 6.08 ms against 6.29, spills 20.  So it does in the rarer of the two forms, at every shape.
-        constexpr bool kLate = fit16_registers(WP, L, NT) > 480, kScarce = kBelow || (!HALF && fit16_registers(WP, L, NT) > 500);
+        // 6.00 ms a step); where registers are scarce, to the start of the next.
+        constexpr bool kLate = kRegisters > 480;
         auto slope = [&](f32x4 z, int l) { return kBelow ? cos4(z) * fminf(misc->scale[l], 1.0f) : cos4(z); };
         auto leave = [&](int nt, int t, f32x4 e, f32x4 z, int l) {
             if (HALF) {
@@ -586,7 +624,7 @@ template <int WP, bool HALF, int L, int NT, bool kBelow> __device__ __forceinlin
                     for (int t = 0; t < MT; ++t) error_split<S>(E[nt][t], t, neg1, Eh[nt][t], El[nt][t]);
         };
         {
-            FIT16_EDGE;
+            if (!kAlone || kDownFirst) FIT16_EDGE;
             const float eo = misc->out;
             h4v eh[NT], el[NT];
 #pragma unroll
@@ -597,7 +635,7 @@ template <int WP, bool HALF, int L, int NT, bool kBelow> __device__ __forceinlin
             }
 #pragma unroll
             for (int t = 0; t < MT; ++t) {
-                const h8v at = *(const h8v *)(base + S::LASTT + t * 1024);
+                const h8v at = kAlone ? out_words[t] : *(const h8v *)(base + S::LASTT + t * 1024);
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) E[nt][t] = mfma32(at, cat(el[nt], el[nt]), mfma32(at, cat(eh[nt], eh[nt]), zero4));
             }
@@ -613,8 +651,10 @@ template <int WP, bool HALF, int L, int NT, bool kBelow> __device__ __forceinlin
 #pragma unroll
             for (int i = 0; i < MT; ++i) {
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) turn(Bh[nt], Bl[nt], i, uh[nt], ul[nt]);
-                const h8v b0 = cat(uh[0], uh[NT - 1]), b1 = cat(ul[0], ul[NT - 1]);
+                for (int nt = 0; nt < NT; ++nt) {
+                    if (!kDownFirst) turn(Bh[nt], Bl[nt], i, inh[nt][i], inl[nt][i]);
+                }
+                const h8v b0 = cat(inh[0][i], inh[NT - 1][i]), b1 = cat(inl[0][i], inl[NT - 1][i]);
                 acc_last[i] = mfma32(A0, b0, acc_last[i]);
                 if (!S::mixed(i)) acc_last[i] = mfma32(A0, b1, acc_last[i]);
                 if (NT == 2) acc_last[i] = mfma32(A1, b0, acc_last[i]);
@@ -646,34 +686,44 @@ template <int WP, bool HALF, int L, int NT, bool kBelow> __device__ __forceinlin
         for (int u = NH - 1; u >= 0; --u) {
             if (u == 0) {                              // not kept from the forward pass: cheaper to form again than to hold
                 FIT16_EDGE;
-                first(zst[0]);
+                first(zst[0], false);
             }
             h4v Hh[NT][MT], Hl[NT][MT];
             FIT16_EDGE;
+            Words<WP, HALF, 1> V[kAhead];
+            const char *const down_at = step(u, c, S::HID);
+            if (kAlone) {
+#pragma unroll
+                for (int t = 0; t < kAhead; ++t) V[t].load(down_at + t * 1024, S::PLANE);
+                if (kDownFirst || kTight) __builtin_amdgcn_sched_barrier(0);
+            }
             take();
             f32x4 down[NT][MT];
             auto contract = [&] {
 #pragma unroll
                 for (int t = 0; t < MT; ++t) {
-                    Words<WP, HALF, 1> V;
-                    V.load(step(u, c, S::HID + t * 1024), S::PLANE);
+                    if (!kAlone) V[0].load(step(u, c, S::HID + t * 1024), S::PLANE);
+                    else if (t > 0 && t + kAhead - 1 < MT) V[(t + kAhead - 1) % kAhead].load(down_at + (t + kAhead - 1) * 1024, S::PLANE);
                     f32x4 d[NT][1];
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt) d[nt][0] = zero4;
 #pragma unroll
-                    for (int k = 0; k < kBlocks; ++k) V.template block<NT>(k, Eh, El, d);
+                    for (int k = 0; k < kBlocks; ++k) V[t % kAhead].template block<NT>(k, Eh, El, d);
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt) down[nt][t] = d[nt][0];
                 }
             };
-            if (kScarce) contract();
+            // (the contraction first: fewer registers; with the multiply, kBelow, where they are scarce, and where several wavefronts share a SIMD)
+            constexpr bool kContractFirst = kDownFirst || kTight || (kBelow && (!kAlone || kLate));
+            if (kContractFirst) contract();
+            if (kDownFirst) __builtin_amdgcn_sched_barrier(0);
             turn_error(Eh, El);
             if (u >= kKept)
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
                     for (int t = 0; t < MT; ++t) sine_split<S>(zst[u][nt][t], t, neg1, Hh[nt][t], Hl[nt][t]);
-            if (!kScarce) contract();
+            if (!kContractFirst) contract();
             const h8v ones = column(u, c);
 #pragma unroll
             for (int t = 0; t < MT; ++t) {
