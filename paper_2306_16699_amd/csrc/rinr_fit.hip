@@ -104,6 +104,10 @@ template <int WQ> struct Shape {
     static __host__ __device__ constexpr int total(int L) { return buf(PIPE ? 4 : 3, L); }
 };
 
+// Adam steps one launch takes at most, and chunks of pixels a workgroup has in it if there is more than one step (a step of more is long enough by itself)
+constexpr int kStepsAtOnce = 32, kChunksAtOnce = 1024;
+struct FitStep { float lr, c1inv, c2inv; };
+
 struct FitArgs {
     float *params, *m, *v;        // [n_images][n_params]
     const uint8_t *keep;          // [n_images][n_params] or null
@@ -119,16 +123,18 @@ struct FitArgs {
     float inv2W, inv2H, lo, span, w0rev;        // w0rev = w0 / 2pi
     float loss_scale;
     float neg1;                   // -1, as data: keeps x - float(half) a single mixed-precision fma in the split kernels
-    float lr, c1inv, c2inv, b1, b2, eps;
+    float b1, b2, eps;
     int32_t L;
     int32_t d[kMaxL + 1];         // true widths
     int32_t p_off[kMaxL];         // offset of W_l in the parameter vector
     float gscale[kMaxL];          // what the accumulated weight gradient of layer l is multiplied by (see the kernel)
+    int32_t steps;                // Adam steps of this launch: 1 but in split-precision kernels that say so (fit16_many_steps)
+    FitStep step[kStepsAtOnce];
 };
 
 // The chunks of an image's pixels that this workgroup takes: all of them, or its share where `splits` workgroups have one image.
 struct FitShare { size_t img; uint32_t c0, c1; float *part; };
-__device__ __forceinline__ FitShare fit_share(const FitArgs &a, uint32_t nchunks) {
+template <class Args> __device__ __forceinline__ FitShare fit_share(const Args &a, uint32_t nchunks) {
     const uint32_t img = blockIdx.x / (uint32_t)a.splits, sp = blockIdx.x - img * (uint32_t)a.splits;
     FitShare w;
     w.img = img;
@@ -139,7 +145,7 @@ __device__ __forceinline__ FitShare fit_share(const FitArgs &a, uint32_t nchunks
 }
 
 // Squared error of the workgroup's pixels (`s`, one thread): the image's loss and error size, or this share's part of them.
-__device__ __forceinline__ void fit_put_loss(const FitArgs &a, const FitShare &w, float s) {
+template <class Args> __device__ __forceinline__ void fit_put_loss(const Args &a, const FitShare &w, float s) {
     if (w.part) {
         w.part[a.n_params] = s;
     } else {
@@ -149,7 +155,7 @@ __device__ __forceinline__ void fit_put_loss(const FitArgs &a, const FitShare &w
 }
 
 // One gradient entry of an image: handed out, or Adam on the parameter in place (a pruned one stays 0).
-__device__ __forceinline__ void fit_apply(const FitArgs &a, size_t img, int at, float gr) {
+template <class Args> __device__ __forceinline__ void fit_apply(const Args &a, size_t img, int at, float gr, int step) {
     const size_t q = img * (size_t)a.n_params + (size_t)at;
     const bool kept = !a.keep || a.keep[q];
     if (a.grad_out) {
@@ -159,14 +165,14 @@ __device__ __forceinline__ void fit_apply(const FitArgs &a, size_t img, int at, 
         const float vv = a.b2 * a.v[q] + (1.0f - a.b2) * gr * gr;
         a.m[q] = mm;
         a.v[q] = vv;
-        a.params[q] -= a.lr * (mm * a.c1inv) / (sqrtf(vv * a.c2inv) + a.eps);
+        a.params[q] -= a.step[step].lr * (mm * a.step[step].c1inv) / (sqrtf(vv * a.step[step].c2inv) + a.eps);
     } else {
         a.params[q] = 0.0f;
     }
 }
-__device__ __forceinline__ void fit_put_grad(const FitArgs &a, const FitShare &w, int at, float gr) {
+template <class Args> __device__ __forceinline__ void fit_put_grad(const Args &a, const FitShare &w, int at, float gr, int step) {
     if (w.part) w.part[at] = gr;
-    else fit_apply(a, w.img, at, gr);
+    else fit_apply(a, w.img, at, gr, step);
 }
 
 __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
@@ -413,7 +419,7 @@ __global__ __launch_bounds__(Shape<WQ>::NTHREADS, fit_waves_per_simd(WQ)) void f
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const int at = param_index(a, l, ot * 16 + 4 * kq + v, it * 16 + m);
-                        if (at >= 0) fit_put_grad(a, share, at, acc[l][s][v] * a.gscale[l]);
+                        if (at >= 0) fit_put_grad(a, share, at, acc[l][s][v] * a.gscale[l], 0);
                     }
                 }
             }
@@ -448,7 +454,7 @@ __global__ __launch_bounds__(kReduceParams *GROUPS) void fit_reduce_kernel(const
 #pragma unroll
         for (int w = 0; w < GROUPS; ++w) g += red[w][lane];
         if (at < a.n_params) {
-            fit_apply(a, img, (int)at, g);
+            fit_apply(a, img, (int)at, g, 0);
         } else {
             a.loss[img] = a.loss_scale * g;
             if (!a.grad_out) a.emag[img] = sqrtf(g / (3.0f * (float)a.HW));
@@ -499,14 +505,14 @@ constexpr int fit16_tiles(int wp, int ml) {
     const int one = fit16::fit16_waves_per_simd(wp, ml, 1), two = fit16::fit16_waves_per_simd(wp, ml, 2);
     return (one > 1 && two == 1) || fit16::fit16_registers(wp, ml, 2) > 512 ? 1 : 2;
 }
-struct Fit16 { fit_fn fn; uint32_t lds; int pixels; };      // kernel, LDS bytes, pixels a workgroup takes at a time
+struct Fit16 { fit_fn fn; uint32_t lds; int pixels; bool many_steps; };      // kernel, LDS bytes, pixels a workgroup takes at a time, several steps a launch
 template <int WP, bool HALF, int L = 2> Fit16 kernel16_of(int n) {
     if constexpr (L > fit16_depth(WP)) {
-        return Fit16{nullptr, 0, 0};
+        return Fit16{nullptr, 0, 0, false};
     } else {
         constexpr int nt = fit16_tiles(WP, L);
         if constexpr (WP == 64 && HALF && L <= 3) return kernel16_of<WP, HALF, L + 1>(n);
-        else return n == L ? Fit16{fit16::fit16_step_kernel<WP, HALF, L, nt>, fit16::Shape<WP, HALF>::total(L, nt), fit16::kThreads / 4 * nt} : kernel16_of<WP, HALF, L + 1>(n);
+        else return n == L ? Fit16{fit16::fit16_step_kernel<WP, HALF, L, nt>, fit16::Shape<WP, HALF>::total(L, nt), fit16::kThreads / 4 * nt, fit16::fit16_many_steps(WP, L, nt)} : kernel16_of<WP, HALF, L + 1>(n);
     }
 }
 // width: of the widest hidden layer.  Half of the last tile empty: the kernels that do not compute it (fit16::Shape), but for one that spills and is
@@ -531,7 +537,7 @@ Fit16 kernel16_for(int width, int L, bool half) {
     const int wp = (width + 15) / 16 * 16;
     const Fit16 k = half ? (wp == 16 ? kernel16_of<16, true>(L) : (wp == 32 ? kernel16_of<32, true>(L) : (wp == 48 ? kernel16_of<48, true>(L) : kernel16_of<64, true>(L))))
                          : (wp == 16 ? kernel16_of<16, false>(L) : (wp == 32 ? kernel16_of<32, false>(L) : (wp == 48 ? kernel16_of<48, false>(L) : kernel16_of<64, false>(L))));
-    return k.lds <= kLdsLimit - 256 ? k : Fit16{nullptr, 0, 0};
+    return k.lds <= kLdsLimit - 256 ? k : Fit16{nullptr, 0, 0, false};
 }
 
 }  // namespace
@@ -777,7 +783,8 @@ extern "C" int rinr_fit_get_params(const rinr_fit *f, float *params, void *strea
 }
 
 namespace {
-int launch(rinr_fit *f, const float *targets, float loss_scale, float lr, int64_t t, float b1, float b2, float eps,
+// The steps `steps` at rates lr[0 ..], the first of them the handle's `t`-th
+int launch(rinr_fit *f, const float *targets, float loss_scale, const float *lr, int steps, int64_t t, float b1, float b2, float eps,
            float *grad_out, hipStream_t stream) {
     FitArgs a;
     a.params = f->params; a.m = f->m; a.v = f->v;
@@ -810,9 +817,9 @@ int launch(rinr_fit *f, const float *targets, float loss_scale, float lr, int64_
             c = l == L - 1 ? (double)f->arch.w0 : c * 2.0 * 3.14159265358979323846;
         }
     }
-    a.lr = lr;
-    a.c1inv = (float)(1.0 / (1.0 - std::pow((double)b1, (double)t)));
-    a.c2inv = (float)(1.0 / (1.0 - std::pow((double)b2, (double)t)));
+    a.steps = steps;
+    for (int k = 0; k < steps; ++k)
+        a.step[k] = FitStep{lr[k], (float)(1.0 / (1.0 - std::pow((double)b1, (double)(t + k)))), (float)(1.0 / (1.0 - std::pow((double)b2, (double)(t + k))))};
     a.b1 = b1; a.b2 = b2; a.eps = eps;
     a.L = f->arch.n_layers;
     for (int l = 0; l <= a.L; ++l) a.d[l] = f->arch.widths[l];
@@ -841,12 +848,24 @@ extern "C" int rinr_fit_steps(rinr_fit *f, const float *targets, int32_t n_steps
     if (!(b1 > 0.0f && b1 < 1.0f && b2 > 0.0f && b2 < 1.0f && eps > 0.0f) || !(o->loss_scale >= 0.0f)) return RINR_E_ARG;
     const float ls = o->loss_scale != 0.0f ? o->loss_scale : (float)(1.0 / (3.0 * (double)f->H * (double)f->W));
     if (f->n_images == 0) { f->t += n_steps; return RINR_OK; }
-    for (int32_t i = 0; i < n_steps; ++i) {
-        double lr = o->lr;
-        if (o->T > 0) lr = 0.5 * lr * (1.0 + std::cos(3.14159265358979323846 * (double)(o->t0 + i) / (double)o->T));
-        f->t += 1;
-        const int rc = launch(f, targets, ls, (float)lr, f->t, b1, b2, eps, nullptr, (hipStream_t)stream);
+    // an image that one workgroup takes goes through several steps in one launch, where the kernel is built for it
+    int32_t most = 1;
+    if (f->family == RINR_FIT_KERNEL_SPLIT16 && f->k16.many_steps && f->splits == 1) {
+        const int64_t chunks = ((int64_t)f->H * f->W + f->k16.pixels - 1) / f->k16.pixels;
+        most = (int32_t)std::max<int64_t>(1, std::min<int64_t>(kStepsAtOnce, kChunksAtOnce / chunks));
+    }
+    for (int32_t i = 0; i < n_steps;) {
+        float rates[kStepsAtOnce];
+        int32_t k = 0;
+        for (; k < most && i + k < n_steps; ++k) {
+            double lr = o->lr;
+            if (o->T > 0) lr = 0.5 * lr * (1.0 + std::cos(3.14159265358979323846 * (double)(o->t0 + i + k) / (double)o->T));
+            rates[k] = (float)lr;
+        }
+        const int rc = launch(f, targets, ls, rates, k, f->t + 1, b1, b2, eps, nullptr, (hipStream_t)stream);
+        f->t += rc ? 1 : k;
         if (rc) return rc;
+        i += k;
     }
     return RINR_OK;
 }
@@ -859,7 +878,8 @@ extern "C" int rinr_fit_loss_grad(rinr_fit *f, const float *targets, float loss_
     const size_t np = (size_t)f->n_images * (size_t)f->n_params;
     if (!f->scratch_grad) FIT_HIP(hipMalloc((void **)&f->scratch_grad, np * 4));
     const float ls = loss_scale != 0.0f ? loss_scale : (float)(1.0 / (3.0 * (double)f->H * (double)f->W));
-    const int rc = launch(f, targets, ls, 0.0f, 1, 0.9f, 0.999f, 1e-8f, f->scratch_grad, (hipStream_t)stream);
+    const float none = 0.0f;
+    const int rc = launch(f, targets, ls, &none, 1, 1, 0.9f, 0.999f, 1e-8f, f->scratch_grad, (hipStream_t)stream);
     if (rc) return rc;
     FIT_HIP(hipStreamSynchronize((hipStream_t)stream));
     FIT_HIP(hipMemcpy(loss, f->loss, (size_t)f->n_images * 4, hipMemcpyDeviceToHost));

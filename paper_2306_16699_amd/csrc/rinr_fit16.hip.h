@@ -72,17 +72,24 @@ constexpr int fit16_registers(int wp, int ml, int nt) {
     return 4 * (2 * mt + (ml - 2) * mt * mt) + 4 * nt * mt * (ml - 1) + 40 + 16 * nt * mt;
 }
 // Wavefronts per SIMD a kernel is compiled for: as many as its estimate leaves.  The estimate does not count the addresses and operands of
-// the inputs in LDS, and so four kernels spill: 7 layers x 16 at three wavefronts (33 registers), 5 x 32 (8), 8 x 32 (28) and 8 x 24 (15) at two.  With
+// the inputs in LDS, and so some kernels spill: 4 layers x 16 at four wavefronts (23 registers; half-filled 16), 7 x 16 at three (20; 9), 5 x 32 (8), 8 x 32 (28)
+// and 8 x 24 (15) at two.  With
 // the inputs in LDS and these spills against the kernels before (of them 7 x 16 alone spilled, 24): 512 images of 96 x 96, 5 x 32 500 -> 459, 256 of 96 x 96, 8 x 32 475 -> 478 and 8 x 24 (half-filled
 // tile) 441 -> 396, 1024 of 64 x 64, 7 x 16 343 -> 312.  Measured, us a step, spilled -> as chosen:
-//   four instead of three, 48 x 48, width 16, 2048 images: 4 layers 198 -> 189, 5 layers 249 -> 241; 6144 images: 561 -> 555, 692 -> 691;
-//     against it only where four make whole rounds (1024 images of 64 x 64, width 15): 175 -> 180, 219 -> 227
+//   four instead of three, 48 x 48, width 16, 2048 images: 4 layers 198 -> 189, 5 layers 249 -> 241; 6144 images: 561 -> 555, 692 -> 691
+//   three instead of four at 4 layers, which with several steps a launch take more registers: 1024 images of 64 x 64, width 8: 94.1 -> 110
 //   two instead of three: 8 layers x 16: 243 -> 232; 3 x 32: 150 -> 144
 //   three (spilling) instead of two at 7 layers x 16, 48 x 48: 6144 images 1063 -> 1001; against it 1024 of 64 x 64: 319 -> 328
 constexpr int fit16_waves_per_simd(int wp, int ml, int nt) {
     const int r = fit16_registers(wp, ml, nt);
-    return r <= 100 ? 4 : (r <= 156 ? 3 : (r <= 256 ? 2 : 1));
+    return r <= 112 ? 4 : (r <= 156 ? 3 : (r <= 256 ? 2 : 1));
 }
+
+// Whether a launch takes several steps of an image that one workgroup has.  A launch of its own costs a step its gap, the last round's idle part and
+// instructions that are fetched again; a kernel that loops takes more registers, which small ones have.  us a step, a launch each -> 32
+// steps a launch, 2048 images of 32 x 32: 2 layers x 15 43.0 -> 39.6, 3 x 15 64.8 -> 60.5, 5 x 15 107.7 -> 104.6, 8 x 15 187.9 -> 181.3, 8 x 8 129.1 -> 122.5, 2 x 32 71.2 -> 69.1,
+// 3 x 32 132.3 -> 127.8; 1024 of 64 x 64: 4 x 15 158.1 -> 146.7, 5 x 15 194.3 -> 195.7, 3 x 32 214.2 -> 209.5.  Beyond: 512 of 96 x 96, 4 x 32 322 -> 331, 5 x 24 338 -> 352.
+constexpr bool fit16_many_steps(int wp, int ml, int nt) { return fit16_registers(wp, ml, nt) <= 168; }
 
 // Shapes and the LDS layout (bytes) for hidden widths <= WP (a multiple of 16).
 // HALF: the widths are at most WP - 8, so half of the last tile is padding.  A lane then holds two real units of it
@@ -271,11 +278,10 @@ template <int WP, bool HALF, int R> struct Words {
     } while (0)
 
 // Weights and tables of image `img` into LDS.  Returns whether some layer's factor of the error is below 1 (the same in every lane).
-template <int WP, bool HALF, int L> __device__ __forceinline__ bool fit16_set_up(const FitArgs &a, char *lds, size_t img, int wave) {
+template <int WP, bool HALF, int L, class Args> __device__ __forceinline__ bool fit16_set_up(const Args &a, char *lds, size_t img, int tid, int wave) {
     typedef Shape<WP, HALF> S;
     constexpr int MT = S::MT;
     Misc *const misc = (Misc *)(lds + S::MISC);
-    const int tid = threadIdx.x;
     const int lane = tid & 63;
     const float *P = a.params + img * a.n_params;
 
@@ -377,7 +383,7 @@ template <int WP, bool HALF, int L> __device__ __forceinline__ bool fit16_set_up
 // 224 x 224, 10 x 32: 6.98 -> 6.00; 512 of 96 x 96, 5 x 24: 0.532 -> 0.457; 64 of 128 x 128, 6 x 64: 0.500 -> 0.450.  Forcing one
 // matrix step per two to four vector instructions backward (scheduling groups) was slower: 7.8 ms at 10 x 40.
 // kBelow: some layer's factor of the error is below 1 and is applied here, on the cosine (see the file header).
-template <int WP, bool HALF, int L, int NT, bool kBelow> __device__ __forceinline__ void fit16_pixels(const FitArgs &a, char *lds, const FitShare &share, int wave) {
+template <int WP, bool HALF, int L, int NT, bool kBelow, class Args> __device__ __forceinline__ void fit16_pixels(const Args &a, char *lds, const FitShare &share, int number, int tid, int wave) {
     typedef Shape<WP, HALF> S;
     constexpr int MT = S::MT, NH = L - 2, kPC = kWaves * 16 * NT;
     constexpr int kColOut = 11, kColFirst = 12;         // columns of acc_b: step u's biases in column u, the output layer's, the first layer's bias, x and y
@@ -400,7 +406,7 @@ template <int WP, bool HALF, int L, int NT, bool kBelow> __device__ __forceinlin
     const f32x4 zero4 = {0.0f, 0.0f, 0.0f, 0.0f};
     const h4v zh = {(_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f, (_Float16)0.0f};
     Misc *const misc = (Misc *)(lds + S::MISC);
-    const int tid = threadIdx.x, lane = tid & 63, n = lane & 15, g = lane >> 4;
+    const int lane = tid & 63, n = lane & 15, g = lane >> 4;
     const size_t img = share.img;
     const float neg1 = a.neg1;
 
@@ -836,7 +842,7 @@ template <int WP, bool HALF, int L, int NT, bool kBelow> __device__ __forceinlin
                 for (int v = 0; v < 4; ++v) {
                     if (half_rows && v >= 2) continue;
                     const int row = ot * 16 + (half_rows ? 2 : 4) * g + v, o = l == L - 1 ? (ot == 0 && v == 0 ? g : dout) : row;
-                    if (col >= 0 && o < dout) fit_put_grad(a, share, off + (col == din ? dout * din + o : o * din + col), s[v] * gs);
+                    if (col >= 0 && o < dout) fit_put_grad(a, share, off + (col == din ? dout * din + o : o * din + col), s[v] * gs, number);
                 }
             }
             __syncthreads();
@@ -848,10 +854,25 @@ template <int WP, bool HALF, int L, int NT>
 __global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, L, NT)) void fit16_step_kernel(const FitArgs a) {
     extern __shared__ __attribute__((aligned(16))) char lds16[];
     const uint32_t pixels = kWaves * 16 * NT;
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const FitShare share = fit_share(a, (a.HW + pixels - 1) / pixels);
-    if (!fit16_set_up<WP, HALF, L>(a, lds16, share.img, wave)) fit16_pixels<WP, HALF, L, NT, false>(a, lds16, share, wave);
-    else fit16_pixels<WP, HALF, L, NT, true>(a, lds16, share, wave);
+    auto step = [&](const auto &args, int s, int tid) {
+        const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+        const uint32_t nchunks = (args.HW + pixels - 1) / pixels;
+        const FitShare share = fit16_many_steps(WP, L, NT) && args.splits == 1 ? FitShare{blockIdx.x, 0u, nchunks, nullptr} : fit_share(args, nchunks);      // (a 64-bit division)
+        if (!fit16_set_up<WP, HALF, L>(args, lds16, share.img, tid, wave)) fit16_pixels<WP, HALF, L, NT, false>(args, lds16, share, s, tid, wave);
+        else fit16_pixels<WP, HALF, L, NT, true>(args, lds16, share, s, tid, wave);
+    };
+    if constexpr (fit16_many_steps(WP, L, NT)) {
+        // The arguments and the lane are made unknown again for every step: what a step derives from them would be held across the loop, and spill.
+        typedef const __attribute__((address_space(4))) FitArgs *ConstArgs;
+        for (int s = 0; s < a.steps; ++s) {
+            ConstArgs args = (ConstArgs)__builtin_amdgcn_kernarg_segment_ptr();
+            int tid = threadIdx.x;
+            asm volatile("" : "+s"(args), "+v"(tid));
+            step(*args, s, tid & (kThreads - 1));       // (its range is known again)
+        }
+    } else {
+        step(a, 0, threadIdx.x);
+    }
 }
 
 }  // namespace fit16
