@@ -565,7 +565,8 @@ namespace {
 // Workgroups per image.  One workgroup per image updates it in the same launch; where the images alone leave the machine
 // idle (few of them, or a last round that is nearly empty), an image's pixels are shared by several, and a second kernel
 // adds their partial gradients up.  The model: rounds of workgroups x (a share's chunks + what a workgroup costs before its
-// first chunk, about two chunks' time), and for more than one share the second launch (about one chunk more).  Measured
+// first chunk, about two chunks' time), and for more than one share the second launch (about one chunk more; five against several steps a launch, us
+// a step in shares -> so, images of 32 x 32: 300, 2 layers x 8 13.9 -> 11.1; 600, 3 x 32 59.3 -> 52.6, 8 x 15 85.7 -> 77.8).  Measured
 // (8 images of 171 x 219, 10 layers x 32): 3241 us a step with one workgroup per image, 106 with 30 and the kernels of today.
 int plan_splits(const rinr_fit *f, const void *fn) {
     const bool split16 = f->family == RINR_FIT_KERNEL_SPLIT16;
@@ -578,10 +579,11 @@ int plan_splits(const rinr_fit *f, const void *fn) {
     // workgroups that run side by side without slowing each other much: four wavefronts per SIMD
     const int64_t slots = (int64_t)cus * std::min(resident, std::max(1, 16 / waves));
     if (f->n_images >= 16 * slots) return 1;           // many rounds: the last one's idle part does not matter
+    const int64_t second = split16 && f->k16.many_steps && chunks * 2 <= kChunksAtOnce ? 5 : 1;
     int64_t best = 1, best_t = INT64_MAX;
     for (int64_t s = 1; s <= chunks && s <= 1024; ++s) {
         const int64_t rounds = (f->n_images * s + slots - 1) / slots;
-        const int64_t t = rounds * ((chunks + s - 1) / s + 2) + (s > 1 ? 1 : 0);
+        const int64_t t = rounds * ((chunks + s - 1) / s + 2) + (s > 1 ? second : 0);
         if (t < best_t) { best_t = t; best = s; }
         if (f->n_images * s > 8 * slots) break;
     }
