@@ -144,6 +144,12 @@ int rinr_fit_last_loss(const rinr_fit *fit, float *loss, void *stream);
  * RINR_E_NULL / RINR_E_ARG (negative sizes, peak <= 0) / RINR_E_ALIGN / RINR_E_HIP. */
 int rinr_psnr_batch(const float *a, const float *b, int64_t n_images, int64_t elems, float peak, float *psnr,
                     void *stream);
+/* The same (Sec. IV-A) with scratch memory on the device for the few images that several workgroups share: workspace is 8-byte
+ * aligned, of at least rinr_psnr_workspace_bytes bytes (0: none is used), and in use until the call's two kernels have run.
+ * NULL, or fewer bytes: as rinr_psnr_batch.  The sums are in 64 bits either way. */
+size_t rinr_psnr_workspace_bytes(int64_t n_images, int64_t elems);
+int rinr_psnr_batch_ex(const float *a, const float *b, int64_t n_images, int64_t elems, float peak, float *psnr,
+                       void *workspace, size_t workspace_bytes, void *stream);
 
 /* ---- the whole encode procedure of Sec. IV in one call ----------------------------------- */
 

@@ -896,49 +896,129 @@ extern "C" int rinr_fit_last_loss(const rinr_fit *f, float *loss, void *stream) 
     return RINR_OK;
 }
 
-// ---- PSNR per image: a streaming reduction, bound by HBM (8 bytes read per element)
+// ---- PSNR per image: a streaming reduction, bound by HBM (8 bytes read per element) where there are images enough to fill the GPU.  A workgroup
+// reads about 0.1 TB/s, so fewer than 256 images are shared by several workgroups each, which leave their sums in the caller's workspace, where
+// there is one, and a second small kernel adds them up.  us a call, before -> now, images of 224 x 224: 1 14.8 -> 12.2, 64 26.8 -> 16.9, 300 82.0 ->
+// 74.2; of 512 x 512: 1 67.6 -> 12.1, 8 117 -> 16.0; rows that begin anywhere in a 16-byte word: 100 of 333 x 211 105.8 -> 34.2, 2000 of 73 x 73 50.3 -> 43.7;
+// 4096 of 16 x 16 15.8 -> 7.7.  Sharing takes the host 12 us for a call instead of 7: below 131072 elements, or from 128 images on (200 of 224 x 224: 41.1 alone,
+// 45.3 shared), it does not pay.
 namespace {
-__global__ __launch_bounds__(1024) void psnr_kernel(const float *a, const float *b, int64_t elems, float peak, float *out) {
-    __shared__ double red[16];
-    const float *pa = a + (size_t)blockIdx.x * (size_t)elems, *pb = b + (size_t)blockIdx.x * (size_t)elems;
+constexpr int kPsnrThreads = 1024;
+constexpr int64_t kPsnrSmall = 4096, kPsnrShared = 131072, kPsnrShare = 16384;      // elements of an image for 256 threads; to share; of a share, at least
+// workgroups per image, with a workspace
+int64_t psnr_splits(int64_t n_images, int64_t elems) {
+    if (n_images < 1 || n_images >= 128 || elems < kPsnrShared) return 1;
+    return std::min((512 + n_images - 1) / n_images, elems / kPsnrShare);
+}
+
+// Sum of squared differences of `elems` elements over the workgroup; thread 0 has it.  AHEAD pairs of loads are under way in a thread: one where each
+// workgroup has a CU to itself (256 images of 224 x 224: 51.4 us, with two 52.3), else two (300: 82.0 and 74.2; 512 of 128 x 128: 37.0 and 35.2).
+template <int THREADS, int AHEAD> __device__ __forceinline__ double psnr_sum(const float *pa, const float *pb, int64_t elems) {
+    __shared__ double red[THREADS / 64];
     const int tid = threadIdx.x;
     double acc = 0.0;
-    // groups of 4 floats where both rows are 16-byte aligned, singly otherwise
-    const bool vec = ((((uintptr_t)pa) | ((uintptr_t)pb)) & 15) == 0;
-    const int64_t nv = vec ? elems / 4 : 0;
     float part = 0.0f;
     int since = 0;
-    for (int64_t q = tid; q < nv; q += 1024) {
-        const float4 x = ((const float4 *)pa)[q], y = ((const float4 *)pb)[q];
+    auto flush = [&] { acc += (double)part; part = 0.0f; since = 0; };         // keeps the fp32 partial sums short
+    // groups of 4 floats where both have the same place in a 16-byte word (but for the elements before the first whole one), singly otherwise
+    const bool vec = ((((uintptr_t)pa) ^ ((uintptr_t)pb)) & 15) == 0;
+    const int64_t head = vec ? min((int64_t)(-(((uintptr_t)pa) >> 2) & 3), elems) : 0, nv = vec ? (elems - head) / 4 : 0;
+    const float4 *const va = (const float4 *)(pa + head), *const vb = (const float4 *)(pb + head);
+    auto add = [&](float4 x, float4 y) {
         const float d0 = x.x - y.x, d1 = x.y - y.y, d2 = x.z - y.z, d3 = x.w - y.w;
         part += d0 * d0 + d1 * d1 + d2 * d2 + d3 * d3;
-        if (++since == 64) { acc += (double)part; part = 0.0f; since = 0; }     // keep the fp32 partial sums short
+        if (++since == 64) flush();
+    };
+    int64_t q = tid;
+    if (AHEAD > 1) {
+        for (; q + (AHEAD - 1) * THREADS < nv; q += AHEAD * THREADS) {
+            float4 x[AHEAD], y[AHEAD];
+#pragma unroll
+            for (int k = 0; k < AHEAD; ++k) {
+                x[k] = va[q + k * THREADS];
+                y[k] = vb[q + k * THREADS];
+            }
+#pragma unroll
+            for (int k = 0; k < AHEAD; ++k) add(x[k], y[k]);
+        }
     }
-    for (int64_t k = nv * 4 + tid; k < elems; k += 1024) {
-        const float d = pa[k] - pb[k];
+    for (; q < nv; q += THREADS) add(va[q], vb[q]);
+    flush();
+    if (tid < head) {
+        const float d = pa[tid] - pb[tid];
         part += d * d;
     }
-    acc += (double)part;
+    for (int64_t k = head + nv * 4 + tid; k < elems; k += THREADS) {
+        const float d = pa[k] - pb[k];
+        part += d * d;
+        if (++since == 256) flush();
+    }
+    flush();
     for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
     if ((tid & 63) == 0) red[tid >> 6] = acc;
     __syncthreads();
-    if (tid == 0) {
-        double s = 0.0;
-        for (int w = 0; w < 16; ++w) s += red[w];
-        out[blockIdx.x] = s > 0.0 ? (float)(10.0 * log10((double)peak * (double)peak * (double)elems / s)) : INFINITY;
-    }
+    double s = 0.0;
+    if (tid == 0)
+        for (int w = 0; w < THREADS / 64; ++w) s += red[w];
+    return s;
+}
+__device__ __forceinline__ float psnr_of(double s, int64_t elems, float peak) {
+    return s > 0.0 ? (float)(10.0 * log10((double)peak * (double)peak * (double)elems / s)) : INFINITY;
+}
+template <int THREADS, int AHEAD>
+__global__ __launch_bounds__(THREADS) void psnr_kernel(const float *a, const float *b, int64_t elems, float peak, float *out) {
+    const size_t at = (size_t)blockIdx.x * (size_t)elems;
+    const double s = psnr_sum<THREADS, AHEAD>(a + at, b + at, elems);
+    if (threadIdx.x == 0) out[blockIdx.x] = psnr_of(s, elems, peak);
+}
+// One share of an image: `share` elements, the last one's to the image's end
+__global__ __launch_bounds__(kPsnrThreads) void psnr_share_kernel(const float *a, const float *b, int64_t elems, int64_t share, double *sums) {
+    const int64_t from = (int64_t)blockIdx.x * share;
+    const size_t at = (size_t)blockIdx.y * (size_t)elems + (size_t)from;
+    const double s = psnr_sum<kPsnrThreads, 2>(a + at, b + at, blockIdx.x + 1 == gridDim.x ? elems - from : share);
+    if (threadIdx.x == 0) sums[(size_t)blockIdx.y * gridDim.x + blockIdx.x] = s;
+}
+__global__ __launch_bounds__(256) void psnr_finish_kernel(const double *sums, int32_t splits, int64_t elems, float peak, float *out, int32_t n) {
+    const int i = threadIdx.x;
+    if (i >= n) return;
+    double s = 0.0;
+    for (int k = 0; k < splits; ++k) s += sums[(size_t)i * splits + k];
+    out[i] = psnr_of(s, elems, peak);
 }
 }  // namespace
 
-extern "C" int rinr_psnr_batch(const float *a, const float *b, int64_t n_images, int64_t elems, float peak, float *psnr,
-                               void *stream) {
+extern "C" size_t rinr_psnr_workspace_bytes(int64_t n_images, int64_t elems) {
+    const int64_t s = psnr_splits(n_images, elems);
+    return s > 1 ? (size_t)(n_images * s) * sizeof(double) : 0;
+}
+
+extern "C" int rinr_psnr_batch_ex(const float *a, const float *b, int64_t n_images, int64_t elems, float peak, float *psnr, void *workspace,
+                                  size_t workspace_bytes, void *stream) {
     if (n_images < 0 || elems < 0 || !(peak > 0.0f) || n_images > ((int64_t)1 << 31) - 1) return RINR_E_ARG;
     if (n_images == 0) return RINR_OK;
     if (!psnr || (elems > 0 && (!a || !b))) return RINR_E_NULL;
     if ((((uintptr_t)a) | ((uintptr_t)b) | ((uintptr_t)psnr)) & 3) return RINR_E_ALIGN;
-    hipLaunchKernelGGL(psnr_kernel, dim3((uint32_t)n_images), dim3(1024), 0, (hipStream_t)stream, a, b, elems, peak, psnr);
+    if (workspace && ((uintptr_t)workspace & 7)) return RINR_E_ALIGN;
+    const hipStream_t st = (hipStream_t)stream;
+    const int64_t splits = psnr_splits(n_images, elems);
+    if (splits > 1 && workspace && workspace_bytes >= rinr_psnr_workspace_bytes(n_images, elems)) {
+        const int64_t share = elems / splits / 4 * 4;
+        hipLaunchKernelGGL(psnr_share_kernel, dim3((uint32_t)splits, (uint32_t)n_images), dim3(kPsnrThreads), 0, st, a, b, elems, share, (double *)workspace);
+        FIT_HIP(hipGetLastError());
+        hipLaunchKernelGGL(psnr_finish_kernel, dim3(1), dim3(256), 0, st, (const double *)workspace, (int32_t)splits, elems, peak, psnr, (int32_t)n_images);
+    } else if (elems <= kPsnrSmall) {           // a small image leaves most of 1024 threads idle
+        hipLaunchKernelGGL((psnr_kernel<256, 2>), dim3((uint32_t)n_images), dim3(256), 0, st, a, b, elems, peak, psnr);
+    } else if (n_images <= 256) {
+        hipLaunchKernelGGL((psnr_kernel<kPsnrThreads, 1>), dim3((uint32_t)n_images), dim3(kPsnrThreads), 0, st, a, b, elems, peak, psnr);
+    } else {
+        hipLaunchKernelGGL((psnr_kernel<kPsnrThreads, 2>), dim3((uint32_t)n_images), dim3(kPsnrThreads), 0, st, a, b, elems, peak, psnr);
+    }
     FIT_HIP(hipGetLastError());
     return RINR_OK;
+}
+
+extern "C" int rinr_psnr_batch(const float *a, const float *b, int64_t n_images, int64_t elems, float peak, float *psnr, void *stream) {
+    return rinr_psnr_batch_ex(a, b, n_images, elems, peak, psnr, nullptr, 0, stream);
 }
 
 // ---- Sec. IV as one call: fit, prune (fixed round, then the PSNR-driven one), re-fit, quantise, pack -------------

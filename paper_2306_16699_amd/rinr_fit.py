@@ -65,6 +65,9 @@ def lib():
         L.rinr_fit_loss_grad.argtypes = [vp, vp, C.c_float, vp, vp, vp]
         L.rinr_fit_last_loss.argtypes = [vp, vp, vp]
         L.rinr_psnr_batch.argtypes = [vp, vp, i64, i64, C.c_float, vp, vp]
+        L.rinr_psnr_workspace_bytes.argtypes = [i64, i64]
+        L.rinr_psnr_workspace_bytes.restype = C.c_size_t
+        L.rinr_psnr_batch_ex.argtypes = [vp, vp, i64, i64, C.c_float, vp, vp, C.c_size_t, vp]
         L.rinr_encode_blob_bound.argtypes = [vp, i32, C.POINTER(C.c_size_t)]
         L.rinr_encode_images.argtypes = [vp, vp, C.POINTER(EncodeOpts), vp, vp, C.c_size_t, C.POINTER(C.c_size_t), vp]
         _ready = True
@@ -103,8 +106,16 @@ def psnr_batch(a, b, peak: float = 1.0, stream=None):
     n = a.shape[0]
     out = torch.empty((n,), dtype=torch.float32, device=a.device)
     elems = a.numel() // n if n else 0
-    rinr._check(lib().rinr_psnr_batch(a.data_ptr(), b.data_ptr(), n, elems, peak, out.data_ptr(), rinr._stream_ptr(stream)),
-                "rinr_psnr_batch")
+    L = lib()
+    need = L.rinr_psnr_workspace_bytes(n, elems) if n < 128 and elems >= 131072 else 0       # (0 beyond, without asking)
+    if not need:
+        rinr._check(L.rinr_psnr_batch(a.data_ptr(), b.data_ptr(), n, elems, peak, out.data_ptr(), rinr._stream_ptr(stream)), "rinr_psnr_batch")
+    else:                                                              # few images: several workgroups share one
+        work = torch.empty((need,), dtype=torch.uint8, device=a.device)
+        if stream is not None:                                         # the allocator must not hand it on while the other stream uses it
+            work.record_stream(torch.cuda.ExternalStream(stream) if isinstance(stream, int) else stream)
+        rinr._check(L.rinr_psnr_batch_ex(a.data_ptr(), b.data_ptr(), n, elems, peak, out.data_ptr(), work.data_ptr(), need, rinr._stream_ptr(stream)),
+                    "rinr_psnr_batch_ex")
     return out
 
 

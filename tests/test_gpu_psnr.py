@@ -1,0 +1,68 @@
+"""PSNR per image on the GPU against its definition in 64 bits: few images that several workgroups share, small images, rows that do not
+begin on 16 bytes, with and without a workspace."""
+import numpy as np
+import pytest
+
+from paper_2306_16699_amd import rinr, rinr_fit
+
+pytestmark = pytest.mark.gpu
+
+# fp32 differences (half an ulp each) and partial sums of at most 256 squares: below 256 * 2^-24 of the sum, which is 6.6e-5 dB
+BOUND_DB = 10.0 / np.log(10.0) * 256 * 2.0 ** -24
+
+
+def reference(a, b, peak):
+    d = (a.double() - b.double()).flatten(1)
+    return 10.0 * np.log10(peak * peak / (d * d).mean(1).cpu().numpy())
+
+
+@pytest.mark.parametrize("n,H,W", [(1, 1, 1), (1, 74, 74), (1, 103, 107), (1, 512, 512), (2, 257, 171), (7, 333, 211), (127, 210, 209), (128, 210, 209), (256, 64, 64),
+                                   (300, 13, 53), (1000, 26, 26), (1001, 7, 9), (3, 1021, 5)])
+@pytest.mark.parametrize("skew", [0, 1])
+def test_psnr_is_its_definition(n, H, W, skew):
+    import torch
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n * 7 + H)
+    size = n * 3 * H * W
+    # skew: b begins one float later in its 16-byte word than a, so no vector of both is aligned
+    a = torch.rand(size + 4, generator=g, device="cuda")[:size].view(n, 3, H, W)
+    b = torch.rand(size + 4, generator=g, device="cuda")[skew:size + skew].view(n, 3, H, W)
+    for peak in (1.0, 255.0):
+        want = reference(a, b, peak)
+        got = rinr_fit.psnr_batch(a, b, peak).cpu().numpy()
+        plain = torch.empty(n, device="cuda")                                 # one workgroup per image
+        assert rinr_fit.lib().rinr_psnr_batch(a.data_ptr(), b.data_ptr(), n, 3 * H * W, peak, plain.data_ptr(), rinr._stream_ptr(None)) == rinr.OK
+        # and what rounding the result to 32 bits leaves
+        assert np.abs(got - want).max() <= BOUND_DB + 2e-6 * np.abs(want).max()
+        assert np.abs(plain.cpu().numpy() - want).max() <= BOUND_DB + 2e-6 * np.abs(want).max()
+
+
+def test_shares_of_few_images():
+    import torch
+    L = rinr_fit.lib()
+    assert L.rinr_psnr_workspace_bytes(128, 10 ** 6) == 0 and L.rinr_psnr_workspace_bytes(1, 131071) == 0
+    assert L.rinr_psnr_workspace_bytes(1, 131072) == 8 * 8 and L.rinr_psnr_workspace_bytes(127, 10 ** 6) == 127 * 5 * 8
+    a = torch.rand(5, 3, 210, 210, device="cuda")
+    b = a.clone()
+    b[1, 2, 209, 209] += 0.5                                                  # the last element of an image, alone
+    b[3, 0, 0, 0] = float("nan")
+    side = torch.cuda.Stream()
+    side.wait_stream(torch.cuda.current_stream())
+    for stream in (None, side, side.cuda_stream):
+        got = rinr_fit.psnr_batch(a, b, stream=stream)
+        torch.cuda.synchronize()
+        got = got.cpu().numpy()
+        assert np.isinf(got[[0, 2, 4]]).all() and (got[[0, 2, 4]] > 0).all()
+        d = float(b[1, 2, 209, 209] - a[1, 2, 209, 209])
+        assert abs(got[1] - 10.0 * np.log10(3 * 210 * 210 / d ** 2)) <= 1e-4
+        plain = torch.empty(5, device="cuda")
+        assert L.rinr_psnr_batch(a.data_ptr(), b.data_ptr(), 5, 3 * 210 * 210, 1.0, plain.data_ptr(), rinr._stream_ptr(None)) == rinr.OK
+        np.testing.assert_array_equal(plain.cpu().numpy()[3], got[3])         # not a number: as without shares
+    # a workspace that is too small is not used; one that is not aligned is refused
+    ws = torch.zeros(64, dtype=torch.uint8, device="cuda")
+    out = torch.empty(5, device="cuda")
+    args = (a.data_ptr(), b.data_ptr(), 5, 3 * 210 * 210, 1.0, out.data_ptr())
+    assert L.rinr_psnr_batch_ex(*args, ws.data_ptr(), 64, rinr._stream_ptr(None)) == rinr.OK
+    assert L.rinr_psnr_batch_ex(*args, ws.data_ptr() + 4, 60, rinr._stream_ptr(None)) == rinr.E_ALIGN
+    torch.cuda.synchronize()
+    assert int(ws.sum()) == 0 and np.isinf(out.cpu().numpy()[0])
