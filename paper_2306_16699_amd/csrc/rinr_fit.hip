@@ -175,6 +175,42 @@ template <class Args> __device__ __forceinline__ void fit_put_grad(const Args &a
     else fit_apply(a, w.img, at, gr, step);
 }
 
+// Four entries of an image at once (at < 0: none): what Adam reads of all of them is under way together.  An entry at a time waits for memory twice
+// for each, since the stores may be to what the next one loads.
+template <class Args> __device__ __forceinline__ void fit_put_grads(const Args &a, const FitShare &w, const int (&at)[4], const float (&gr)[4], int step) {
+    if (w.part || a.grad_out) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (at[v] >= 0) fit_put_grad(a, w, at[v], gr[v], step);
+        return;
+    }
+    const size_t first = w.img * (size_t)a.n_params;
+    float m[4], s[4], p[4];
+    bool kept[4];
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        const size_t q = first + (size_t)(at[v] < 0 ? 0 : at[v]);
+        kept[v] = !a.keep || a.keep[q];
+        m[v] = a.m[q];
+        s[v] = a.v[q];
+        p[v] = a.params[q];
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        if (at[v] < 0) continue;
+        const size_t q = first + (size_t)at[v];
+        if (kept[v]) {
+            const float mm = a.b1 * m[v] + (1.0f - a.b1) * gr[v];
+            const float vv = a.b2 * s[v] + (1.0f - a.b2) * gr[v] * gr[v];
+            a.m[q] = mm;
+            a.v[q] = vv;
+            a.params[q] = p[v] - a.step[step].lr * (mm * a.step[step].c1inv) / (sqrtf(vv * a.step[step].c2inv) + a.eps);
+        } else {
+            a.params[q] = 0.0f;
+        }
+    }
+}
+
 __device__ __forceinline__ f32x4 mfma4(float a, float b, f32x4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
 
 // acc += sum over KSTEPS k-steps of A(ks) x B(ks): one float per lane from LDS at ap[ks * AS], bp[ks * BS].

@@ -791,62 +791,77 @@ template <int WP, bool HALF, int L, int NT, bool kBelow, class Args> __device__ 
         fit_put_loss(a, share, s);
     }
 
-    // ---- the wavefronts' gradients are added up, GT tiles at a time through LDS (in a fixed order), and each entry handed out
+    // ---- the wavefronts' gradients are added up, GT tiles at a time through LDS (in a fixed order), and each entry handed out.  Where
+    //      wavefronts share a SIMD, what comes after the tiles are written is one piece of code for all of them: instructions that a launch meets for the
+    //      first time cost it more than their issue (with a lone wavefront's registers that makes the pixels' code the worse one: 10 layers x 40 4690 -> 5060).
+    //      us a step with that and four entries of Adam at once (fit_put_grads), before -> now: 256 images of 96 x 96, 4 x 64 469 -> 449, 7 x 40 560 -> 546, 6 x 56 843 -> 824,
+    //      10 x 24 478 -> 465; 512 of 96 x 96, 6 x 30 558 -> 552; of 224 x 224, 10 x 40 4690 -> 4650.
     f32x4 *const R = (f32x4 *)(lds + S::W0);
     constexpr int kTiles = 2 * MT + NH * MT * MT;
-#pragma unroll
+#pragma unroll (kAlone ? kTiles : 1)
     for (int b0 = 0; b0 < kTiles; b0 += S::GT) {
-        {
 #pragma unroll
-            for (int q = 0; q < S::GT; ++q) {
-                const int at = b0 + q, h = at - 2 * MT;
-                if (at < kTiles)
-                    R[(wave * S::GT + q) * 64 + lane] = at < MT ? acc_b[at] : (at < 2 * MT ? acc_last[at - MT] : acc[h / (MT * MT)][h / MT % MT][h % MT]);
-            }
-            __syncthreads();
-            for (int q = wave; q < S::GT && b0 + q < kTiles; q += kWaves) {
-                const int at = b0 + q, h = at - 2 * MT;
-                f32x4 s = R[q * 64 + lane];
+        for (int c = 0; c < kTiles; c += S::GT)
+            if (b0 == c) {
 #pragma unroll
-                for (int w = 1; w < kWaves; ++w) s += R[(w * S::GT + q) * 64 + lane];
-                // layer, row tile, and which column of its matrix this lane's column is (din: the bias, -1: none)
-                int l = L - 1, ot = 0, col;
-                if (at < MT) {
-                    ot = at;
-                    l = n < NH ? n + 1 : (n == kColOut ? L - 1 : 0);
-                    col = n < NH ? misc->d[l] : (n == kColOut ? misc->d[l] : (n >= kColFirst && n < kColFirst + 3 ? (n + 2 - kColFirst) % 3 : -1));
-                    if (col < 0) l = 0;
-                } else if (at < 2 * MT) {
-                    col = (at - MT) * 16 + n;
-                } else {
-                    l = h / (MT * MT) + 1;
-                    ot = h / MT % MT;
-                    col = h % MT * 16 + n;
-                }
-                const int din = misc->d[l], dout = misc->d[l + 1], off = misc->p_off[l];
-                float gs = misc->grad[l];
-                // a half tile's hi and lo parts: columns n and n + 2, rows v and v + 2; those rows came in twice where a step has 16 pixels
-                if (HALF && at >= MT && (at < 2 * MT ? at - MT : h % MT) == MT - 1) {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) s[v] += __shfl_xor(s[v], 2, 64);
-                    col = (n & 2) ? -1 : (MT - 1) * 16 + 2 * (n >> 2) + (n & 1);
-                }
-                const bool half_rows = HALF && (at < MT || at >= 2 * MT) && l < L - 1 && ot == MT - 1;
-                if (half_rows) {
-                    s[0] += s[2];
-                    s[1] += s[3];
-                    gs *= NT == 1 ? 0.5f : 1.0f;
-                }
-                if (at >= MT && col >= din) col = -1;
-#pragma unroll
-                for (int v = 0; v < 4; ++v) {
-                    if (half_rows && v >= 2) continue;
-                    const int row = ot * 16 + (half_rows ? 2 : 4) * g + v, o = l == L - 1 ? (ot == 0 && v == 0 ? g : dout) : row;
-                    if (col >= 0 && o < dout) fit_put_grad(a, share, off + (col == din ? dout * din + o : o * din + col), s[v] * gs, number);
+                for (int q = 0; q < S::GT; ++q) {
+                    const int at = c + q, h = at - 2 * MT;
+                    if (at < kTiles)
+                        R[(wave * S::GT + q) * 64 + lane] = at < MT ? acc_b[at] : (at < 2 * MT ? acc_last[at - MT] : acc[h / (MT * MT)][h / MT % MT][h % MT]);
                 }
             }
-            __syncthreads();
+        __syncthreads();
+        for (int q = wave; q < S::GT && b0 + q < kTiles; q += kWaves) {
+            const int at = b0 + q, h = at - 2 * MT;
+            f32x4 s = R[q * 64 + lane];
+#pragma unroll
+            for (int w = 1; w < kWaves; ++w) s += R[(w * S::GT + q) * 64 + lane];
+            // layer, row tile, and which column of its matrix this lane's column is (din: the bias, -1: none)
+            int l = L - 1, ot = 0, col;
+            if (at < MT) {
+                ot = at;
+                l = n < NH ? n + 1 : (n == kColOut ? L - 1 : 0);
+                col = n < NH ? misc->d[l] : (n == kColOut ? misc->d[l] : (n >= kColFirst && n < kColFirst + 3 ? (n + 2 - kColFirst) % 3 : -1));
+                if (col < 0) l = 0;
+            } else if (at < 2 * MT) {
+                col = (at - MT) * 16 + n;
+            } else {
+                l = h / (MT * MT) + 1;
+                ot = h / MT % MT;
+                col = h % MT * 16 + n;
+            }
+            const int din = misc->d[l], dout = misc->d[l + 1], off = misc->p_off[l];
+            float gs = misc->grad[l];
+            // a half tile's hi and lo parts: columns n and n + 2, rows v and v + 2; those rows came in twice where a step has 16 pixels
+            if (HALF && at >= MT && (at < 2 * MT ? at - MT : h % MT) == MT - 1) {
+#pragma unroll
+                for (int v = 0; v < 4; ++v) s[v] += __shfl_xor(s[v], 2, 64);
+                col = (n & 2) ? -1 : (MT - 1) * 16 + 2 * (n >> 2) + (n & 1);
+            }
+            const bool half_rows = HALF && (at < MT || at >= 2 * MT) && l < L - 1 && ot == MT - 1;
+            if (half_rows) {
+                s[0] += s[2];
+                s[1] += s[3];
+                gs *= NT == 1 ? 0.5f : 1.0f;
+            }
+            if (at >= MT && col >= din) col = -1;
+            int to[4];
+            float gr[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = ot * 16 + (half_rows ? 2 : 4) * g + v, o = l == L - 1 ? (ot == 0 && v == 0 ? g : dout) : row;
+                to[v] = col >= 0 && o < dout && !(half_rows && v >= 2) ? off + (col == din ? dout * din + o : o * din + col) : -1;
+                gr[v] = s[v] * gs;
+            }
+            if (!kTight) {
+                fit_put_grads(a, share, to, gr, number);
+            } else {
+#pragma unroll
+                for (int v = 0; v < 4; ++v)
+                    if (to[v] >= 0) fit_put_grad(a, share, to[v], gr[v], number);
+            }
         }
+        __syncthreads();
     }
 }
 
