@@ -326,7 +326,8 @@ struct DecodeArgs {
     uint32_t normalize;
     const uint32_t *order;        // workgroups take the slots in this order (heaviest model first), or NULL = 0, 1, 2, ...
     uint32_t vec_store;           // H * W is a multiple of 4, the fp32 output 16-byte and the uint8 output 4-byte aligned:
-                                  // a lane's consecutive pixels go out as one vector
+                                  // a lane's consecutive pixels go out as one vector (in the split-precision kernels wherever they begin, and without
+                                  // it the last pixels of an image may be fewer)
 };
 
 // sin(2 pi r): the hardware sine takes its argument in revolutions and reduces the range
