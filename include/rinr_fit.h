@@ -117,8 +117,8 @@ int rinr_fit_reset_optimizer(rinr_fit *fit);
 int rinr_fit_get_params(const rinr_fit *fit, float *params, void *stream);
 
 /* n_steps full-batch steps (every pixel of every image each step) on `stream`: one kernel per
- * step, one workgroup per image (few images: several per image and a second, small kernel that adds their gradients up
- * in a fixed order), nothing allocated, no synchronisation.  targets: device,
+ * step, or per 32 steps of small models and images, one workgroup per image (few images: several per image and a second, small
+ * kernel that adds their gradients up in a fixed order), nothing allocated, no synchronisation.  targets: device,
  * float[n_images][3][H][W], 4-byte aligned, values on the 0..1 scale of the decoded image.
  * The same calls on handles of one shape give the same bits.  But how an image's pixels are cut into partial sums
  * is chosen when the handle is created, from n_images, H, W, the architecture and the GPU's number of compute units; so the

@@ -16,8 +16,8 @@
 // per SIMD; a sum over the instructions of a piece in order, with those latencies, gives its measured time to 3 %).  A hidden
 // layer of 48 units takes 48 matrix and 169 vector slots per 16 pixels backward, 15 and 52 forward.  So a lone wavefront loses what it waits
 // in order: for operand words from LDS and for matrix results (see kDownFirst).  At 10 layers x 40, with a half-filled last tile, the
-// matrix unit is busy 47 % of the time and vector issue 56 % (the matrix instructions' included), but only 27 % of the matrix time has
-// vector instructions beside it, and a wavefront waits 20 % of its time for loads and barriers and 15 % to issue.
+// matrix unit is busy 51 % of the time and vector issue 60 % (the matrix instructions' included), 29 % of the matrix time has
+// vector instructions beside it, and a wavefront waits 11 % of its time for loads and barriers and 20 % to issue.
 // Measured, ms a step, gradient tiles shared -> a wavefront's own -> layers interleaved (see the kernel) -> half-filled tiles, inputs in LDS
 // (Shape) -> words loaded ahead (kDownFirst): 256 images of 224 x 224, 10 layers x 40: 8.91 -> 6.83 -> 6.29 -> 5.00 -> 4.69; 10 x 32: 4.54 -> 3.50 ->
 // 3.00, no more from the half-filled tiles, -> 2.88; 2048 of 32 x 32, 3 x 15: 0.0934 -> 0.0738 -> 0.0675 -> 0.0655.

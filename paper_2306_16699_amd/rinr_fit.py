@@ -19,7 +19,8 @@ KERNEL_FP32, KERNEL_SPLIT16 = 0, 1
 EXPORTS = ["rinr_prune_ratio", "rinr_l1_mask", "rinr_quantize_layer", "rinr_fit_create", "rinr_fit_create_ex", "rinr_fit_kernel_family",
            "rinr_fit_kernel_units", "rinr_fit_destroy",
            "rinr_fit_n_params", "rinr_fit_set_params", "rinr_fit_set_keep", "rinr_fit_reset_optimizer",
-           "rinr_fit_get_params", "rinr_fit_steps", "rinr_fit_loss_grad", "rinr_fit_last_loss", "rinr_psnr_batch", "rinr_encode_blob_bound",
+           "rinr_fit_get_params", "rinr_fit_steps", "rinr_fit_loss_grad", "rinr_fit_last_loss", "rinr_psnr_batch",
+           "rinr_psnr_workspace_bytes", "rinr_psnr_batch_ex", "rinr_encode_blob_bound",
            "rinr_encode_images"]
 
 
