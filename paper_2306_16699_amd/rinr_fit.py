@@ -105,16 +105,27 @@ def psnr_batch(a, b, peak: float = 1.0, stream=None):
     assert a.is_cuda and b.is_cuda and a.dtype == torch.float32 and b.dtype == torch.float32
     assert a.shape == b.shape and a.is_contiguous() and b.is_contiguous()
     n = a.shape[0]
-    out = torch.empty((n,), dtype=torch.float32, device=a.device)
     elems = a.numel() // n if n else 0
     L = lib()
     need = L.rinr_psnr_workspace_bytes(n, elems) if n < 128 and elems >= 131072 else 0       # (0 beyond, without asking)
-    if not need:
+
+    def memory():                                                      # few images: several workgroups share one, with scratch memory
+        return (torch.empty((n,), dtype=torch.float32, device=a.device),
+                torch.empty((need,), dtype=torch.uint8, device=a.device) if need else None)
+
+    if stream is None:
+        out, work = memory()
+    else:
+        # Memory of the stream that works on it: what the current stream has freed it may still be using, and nothing makes `stream` wait for
+        # that.  An integer is a stream of the tensors' GPU, 0 its default stream (ExternalStream(0) would be another stream of PyTorch's own).
+        s = stream if isinstance(stream, torch.cuda.Stream) else \
+            (torch.cuda.ExternalStream(rinr._stream_ptr(stream), device=a.device) if rinr._stream_ptr(stream) else torch.cuda.default_stream(a.device))
+        with torch.cuda.stream(s):
+            out, work = memory()
+        out.record_stream(torch.cuda.current_stream(a.device))         # where the caller goes on with it
+    if work is None:
         rinr._check(L.rinr_psnr_batch(a.data_ptr(), b.data_ptr(), n, elems, peak, out.data_ptr(), rinr._stream_ptr(stream)), "rinr_psnr_batch")
-    else:                                                              # few images: several workgroups share one
-        work = torch.empty((need,), dtype=torch.uint8, device=a.device)
-        if stream is not None:                                         # the allocator must not hand it on while the other stream uses it
-            work.record_stream(torch.cuda.ExternalStream(stream) if isinstance(stream, int) else stream)
+    else:
         rinr._check(L.rinr_psnr_batch_ex(a.data_ptr(), b.data_ptr(), n, elems, peak, out.data_ptr(), work.data_ptr(), need, rinr._stream_ptr(stream)),
                     "rinr_psnr_batch_ex")
     return out

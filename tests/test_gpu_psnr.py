@@ -66,3 +66,32 @@ def test_shares_of_few_images():
     assert L.rinr_psnr_batch_ex(*args, ws.data_ptr() + 4, 60, rinr._stream_ptr(None)) == rinr.E_ALIGN
     torch.cuda.synchronize()
     assert int(ws.sum()) == 0 and np.isinf(out.cpu().numpy()[0])
+
+
+@pytest.mark.parametrize("H", [64, 210])                                      # without and with scratch memory
+def test_memory_belongs_to_the_stream_that_uses_it(H, monkeypatch):
+    """The output and the scratch memory come from the stream that writes them, whatever stream is current: PyTorch hands on what a stream
+    has freed without waiting for that stream's kernels."""
+    import torch
+    side, other = torch.cuda.Stream(), torch.cuda.Stream()
+    at, plain = [], torch.empty
+
+    def empty(*args, **kw):
+        at.append(torch.cuda.current_stream(kw["device"]).cuda_stream)
+        return plain(*args, **kw)
+    for stream, handle in ((side, side.cuda_stream), (side.cuda_stream, side.cuda_stream), (torch.cuda.default_stream(), 0), (0, 0), (None, other.cuda_stream)):
+        writer = other if stream is None else (side if handle else torch.cuda.default_stream())
+        with torch.cuda.stream(writer):
+            a = torch.rand(5, 3, H, H, device="cuda")
+            b = torch.rand(5, 3, H, H, device="cuda")
+            want = reference(a, b, 1.0)
+        with torch.cuda.stream(other):
+            monkeypatch.setattr(torch, "empty", empty)
+            got = rinr_fit.psnr_batch(a, b, stream=stream)
+            monkeypatch.setattr(torch, "empty", plain)
+            other.wait_stream(writer)
+            got = got.cpu().numpy()
+            assert torch.cuda.current_stream().cuda_stream == other.cuda_stream
+        assert at == [handle] * (2 if H == 210 else 1), (stream, at)
+        at.clear()
+        assert np.abs(got - want).max() <= BOUND_DB + 2e-6 * np.abs(want).max()
