@@ -137,7 +137,8 @@ int rinr_fit_last_loss(const rinr_fit *fit, float *loss, void *stream);
 /* ---- reconstruction quality on the GPU --------------------------------------------------- */
 
 /* Peak signal-to-noise ratio per image, the quantity the pruning ratio is chosen from (Sec. IV-A):
- * psnr[s] = 10 log10(peak^2 * elems / sum_k (a[s][k] - b[s][k])^2) in dB, +inf where the two are equal.
+ * psnr[s] = 10 log10(peak^2 * elems / sum_k (a[s][k] - b[s][k])^2) in dB, +inf where the two are equal
+ * (and not a number where the sum is none).
  * a, b: device float[n_images][elems] (e.g. a decoded batch and the original images, elems = 3 H W),
  * 4-byte aligned; psnr: device float[n_images]; peak: the value range (1 for 0..1 images).  One kernel on
  * `stream`, one workgroup per image, no synchronisation, nothing allocated.

@@ -999,7 +999,7 @@ template <int THREADS, int AHEAD> __device__ __forceinline__ double psnr_sum(con
     return s;
 }
 __device__ __forceinline__ float psnr_of(double s, int64_t elems, float peak) {
-    return s > 0.0 ? (float)(10.0 * log10((double)peak * (double)peak * (double)elems / s)) : INFINITY;
+    return s == 0.0 ? INFINITY : (float)(10.0 * log10((double)peak * (double)peak * (double)elems / s));         // (not a number stays one)
 }
 template <int THREADS, int AHEAD>
 __global__ __launch_bounds__(THREADS) void psnr_kernel(const float *a, const float *b, int64_t elems, float peak, float *out) {
@@ -1093,7 +1093,7 @@ int psnr_now(rinr_fit *f, const float *targets, std::vector<double> &psnr, void 
     const int rc = rinr_fit_loss_grad(f, targets, 0.0f, loss.data(), nullptr, stream);      // mean squared error
     if (rc) return rc;
     psnr.resize(loss.size());
-    for (size_t i = 0; i < loss.size(); ++i) psnr[i] = loss[i] > 0.0f ? -10.0 * std::log10((double)loss[i]) : INFINITY;
+    for (size_t i = 0; i < loss.size(); ++i) psnr[i] = loss[i] == 0.0f ? INFINITY : -10.0 * std::log10((double)loss[i]);
     return RINR_OK;
 }
 
@@ -1205,7 +1205,8 @@ extern "C" int rinr_encode_images(rinr_fit *f, const float *targets, const rinr_
                 std::fill(ratio.begin(), ratio.end(), (double)o->first_ratio);
             } else {
                 if ((rc = psnr_now(f, targets, psnr, stream))) return rc;
-                for (int64_t i = 0; i < n; ++i) ratio[(size_t)i] = rinr_prune_ratio(o->schedule, psnr[(size_t)i]);
+                // (an image whose error is no number does not end the others' encoding)
+                for (int64_t i = 0; i < n; ++i) ratio[(size_t)i] = rinr_prune_ratio(o->schedule, std::isnan(psnr[(size_t)i]) ? INFINITY : psnr[(size_t)i]);
             }
             if ((rc = rinr_fit_get_params(f, e.params.data(), stream))) return rc;
             if ((rc = prune_round(f, e.params, ratio, e.keep, have_keep))) return rc;

@@ -3,7 +3,7 @@ begin on 16 bytes, with and without a workspace."""
 import numpy as np
 import pytest
 
-from paper_2306_16699_amd import rinr, rinr_fit
+from paper_2306_16699_amd import rinr, rinr_fit, synth
 
 pytestmark = pytest.mark.gpu
 
@@ -57,7 +57,7 @@ def test_shares_of_few_images():
         assert abs(got[1] - 10.0 * np.log10(3 * 210 * 210 / d ** 2)) <= 1e-4
         plain = torch.empty(5, device="cuda")
         assert L.rinr_psnr_batch(a.data_ptr(), b.data_ptr(), 5, 3 * 210 * 210, 1.0, plain.data_ptr(), rinr._stream_ptr(None)) == rinr.OK
-        np.testing.assert_array_equal(plain.cpu().numpy()[3], got[3])         # not a number: as without shares
+        assert np.isnan(got[3]) and np.isnan(plain.cpu().numpy()[3])          # not a number, and no perfect match
     # a workspace that is too small is not used; one that is not aligned is refused
     ws = torch.zeros(64, dtype=torch.uint8, device="cuda")
     out = torch.empty(5, device="cuda")
@@ -95,3 +95,16 @@ def test_memory_belongs_to_the_stream_that_uses_it(H, monkeypatch):
         assert at == [handle] * (2 if H == 210 else 1), (stream, at)
         at.clear()
         assert np.abs(got - want).max() <= BOUND_DB + 2e-6 * np.abs(want).max()
+
+
+def test_an_encoded_image_whose_error_is_no_number():
+    """The whole procedure reports it as such, and encodes the others."""
+    import torch
+    widths = [2, 8, 8, 3]
+    f = rinr_fit.Fit(widths, 3, 8, 8)
+    f.set_params(synth.init_params(3, widths, 3))
+    targets = torch.rand(3, 3, 8, 8, device="cuda")
+    targets[1, 2, 7, 7] = float("nan")
+    _, psnr = f.encode(targets, 0, 0.0, 0, 0, 1e-3, 1e-3)
+    assert np.isnan(psnr[1]) and np.isfinite(psnr[[0, 2]]).all()
+    f.close()
