@@ -154,6 +154,10 @@ template <class Args> __device__ __forceinline__ void fit_put_loss(const Args &a
     }
 }
 
+// Adam's two moments.  Which product of a sum goes unrounded is written out: the compiler's choice differs from kernel to kernel, and with it a fit's bits.
+template <class Args> __device__ __forceinline__ float adam_m(const Args &a, float m, float gr) { return fmaf(1.0f - a.b1, gr, a.b1 * m); }
+template <class Args> __device__ __forceinline__ float adam_v(const Args &a, float v, float gr) { return fmaf((1.0f - a.b2) * gr, gr, a.b2 * v); }
+
 // One gradient entry of an image: handed out, or Adam on the parameter in place (a pruned one stays 0).
 template <class Args> __device__ __forceinline__ void fit_apply(const Args &a, size_t img, int at, float gr, int step) {
     const size_t q = img * (size_t)a.n_params + (size_t)at;
@@ -161,8 +165,8 @@ template <class Args> __device__ __forceinline__ void fit_apply(const Args &a, s
     if (a.grad_out) {
         a.grad_out[q] = kept ? gr : 0.0f;
     } else if (kept) {
-        const float mm = a.b1 * a.m[q] + (1.0f - a.b1) * gr;
-        const float vv = a.b2 * a.v[q] + (1.0f - a.b2) * gr * gr;
+        const float mm = adam_m(a, a.m[q], gr);
+        const float vv = adam_v(a, a.v[q], gr);
         a.m[q] = mm;
         a.v[q] = vv;
         a.params[q] -= a.step[step].lr * (mm * a.step[step].c1inv) / (sqrtf(vv * a.step[step].c2inv) + a.eps);
@@ -200,8 +204,8 @@ template <class Args> __device__ __forceinline__ void fit_put_grads(const Args &
         if (at[v] < 0) continue;
         const size_t q = first + (size_t)at[v];
         if (kept[v]) {
-            const float mm = a.b1 * m[v] + (1.0f - a.b1) * gr[v];
-            const float vv = a.b2 * s[v] + (1.0f - a.b2) * gr[v] * gr[v];
+            const float mm = adam_m(a, m[v], gr[v]);
+            const float vv = adam_v(a, s[v], gr[v]);
             a.m[q] = mm;
             a.v[q] = vv;
             a.params[q] = p[v] - a.step[step].lr * (mm * a.step[step].c1inv) / (sqrtf(vv * a.step[step].c2inv) + a.eps);
