@@ -179,16 +179,27 @@ template <class Args> __device__ __forceinline__ void fit_put_grad(const Args &a
     else fit_apply(a, w.img, at, gr, step);
 }
 
-// Four entries of an image at once (at < 0: none): what Adam reads of all of them is under way together.  An entry at a time waits for memory twice
-// for each, since the stores may be to what the next one loads.
+// Four entries of an image at once (at < 0: none).  A share's part goes out first and waits for nothing.  For Adam, what it reads of all four is under
+// way together (an entry at a time waits for memory twice for each, since the stores may be to what the next one loads), and all of it is used
+// whether an entry is there or not: a load that some lanes leave unused is still under way where the ways meet again, and the wait for it there
+// was a wait for the last tile's stores on every way, the share's too.  With that, and Adam's code five times behind every tile, us a step, before -> now:
+// 4 images of 32 x 32, 5 x 64 39.1 -> 37.2, 30 of 64 x 64, 6 x 40 59.4 -> 57.6, one of 224 x 224, 10 x 32 43.5 -> 42.1, 2 of 128 x 128, 5 x 56 46.9 -> 45.0; 8 of
+// 171 x 219, 10 x 40 170.2 -> 168.0, 10 x 32 102.6 -> 100.9; unshared, 256 of 96 x 96: 9 x 48 974 -> 935, 8 x 40 736 -> 720, 7 x 24 523 -> 523, 10 x 40 909 -> 914,
+// 9 x 24 417 -> 423, 12 x 32 668 -> 676 and, where the compiler orders the code over the pixels the worse way for it, 9 x 40 810 -> 822, 5 x 64 705 -> 726.
 template <class Args> __device__ __forceinline__ void fit_put_grads(const Args &a, const FitShare &w, const int (&at)[4], const float (&gr)[4], int step) {
-    if (w.part || a.grad_out) {
+    if (w.part) {
 #pragma unroll
         for (int v = 0; v < 4; ++v)
-            if (at[v] >= 0) fit_put_grad(a, w, at[v], gr[v], step);
+            if (at[v] >= 0) w.part[at[v]] = gr[v];
         return;
     }
     const size_t first = w.img * (size_t)a.n_params;
+    if (a.grad_out) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            if (at[v] >= 0) a.grad_out[first + (size_t)at[v]] = !a.keep || a.keep[first + (size_t)at[v]] ? gr[v] : 0.0f;
+        return;
+    }
     float m[4], s[4], p[4];
     bool kept[4];
 #pragma unroll
@@ -201,17 +212,19 @@ template <class Args> __device__ __forceinline__ void fit_put_grads(const Args &
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
+        m[v] = adam_m(a, m[v], gr[v]);
+        s[v] = adam_v(a, s[v], gr[v]);
+        p[v] -= a.step[step].lr * (m[v] * a.step[step].c1inv) / (sqrtf(s[v] * a.step[step].c2inv) + a.eps);
+    }
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
         if (at[v] < 0) continue;
         const size_t q = first + (size_t)at[v];
         if (kept[v]) {
-            const float mm = adam_m(a, m[v], gr[v]);
-            const float vv = adam_v(a, s[v], gr[v]);
-            a.m[q] = mm;
-            a.v[q] = vv;
-            a.params[q] = p[v] - a.step[step].lr * (mm * a.step[step].c1inv) / (sqrtf(vv * a.step[step].c2inv) + a.eps);
-        } else {
-            a.params[q] = 0.0f;
+            a.m[q] = m[v];
+            a.v[q] = s[v];
         }
+        a.params[q] = kept[v] ? p[v] : 0.0f;
     }
 }
 

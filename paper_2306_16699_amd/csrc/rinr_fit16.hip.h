@@ -770,6 +770,7 @@ template <int WP, bool HALF, int L, int NT, bool kBelow, class Args> __device__ 
                 split_rne((f32x4){1.0f, x[nt], y[nt], 0.0f}, neg1, xh, xl);
                 turn1(g == kColFirst / 4 ? xh : zh, g == kColFirst / 4 ? xl : zh, h[nt], lo[nt]);
             }
+            if (MT == 4 && NT == 2) __builtin_amdgcn_sched_barrier(0);          // (256 images of 96 x 96, 4 x 64 461 -> 455 us a step, 4 x 56 423 -> 420)
             turn_error(Eh, El);
             const h8v b0 = cat(h[0], h[NT - 1]), b1 = cat(lo[0], lo[NT - 1]);
 #pragma unroll
@@ -845,12 +846,14 @@ template <int WP, bool HALF, int L, int NT, bool kBelow, class Args> __device__ 
                 gs *= NT == 1 ? 0.5f : 1.0f;
             }
             if (at >= MT && col >= din) col = -1;
+            const bool bias = col == din;                               // entry (o, col) of the layer is at from + o * by
+            const int from = off + (bias ? dout * din : col), by = bias ? 1 : din;
             int to[4];
             float gr[4];
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const int row = ot * 16 + (half_rows ? 2 : 4) * g + v, o = l == L - 1 ? (ot == 0 && v == 0 ? g : dout) : row;
-                to[v] = col >= 0 && o < dout && !(half_rows && v >= 2) ? off + (col == din ? dout * din + o : o * din + col) : -1;
+                to[v] = col >= 0 && o < dout && !(half_rows && v >= 2) ? from + o * by : -1;
                 gr[v] = s[v] * gs;
             }
             if (!kTight) {
