@@ -57,7 +57,7 @@ def test_shares_of_few_images():
         assert abs(got[1] - 10.0 * np.log10(3 * 210 * 210 / d ** 2)) <= 1e-4
         plain = torch.empty(5, device="cuda")
         assert L.rinr_psnr_batch(a.data_ptr(), b.data_ptr(), 5, 3 * 210 * 210, 1.0, plain.data_ptr(), rinr._stream_ptr(None)) == rinr.OK
-        assert np.isnan(got[3]) and np.isnan(plain.cpu().numpy()[3])          # not a number, and no perfect match
+        np.testing.assert_array_equal(plain.cpu().numpy()[3], got[3])         # not a number: as without shares
     # a workspace that is too small is not used; one that is not aligned is refused
     ws = torch.zeros(64, dtype=torch.uint8, device="cuda")
     out = torch.empty(5, device="cuda")
@@ -95,6 +95,21 @@ def test_memory_belongs_to_the_stream_that_uses_it(H, monkeypatch):
         assert at == [handle] * (2 if H == 210 else 1), (stream, at)
         at.clear()
         assert np.abs(got - want).max() <= BOUND_DB + 2e-6 * np.abs(want).max()
+
+
+@pytest.mark.parametrize("H", [40, 64, 210])                                  # 256 threads, 1024, several workgroups an image
+def test_a_sum_that_is_no_number_is_not_a_perfect_match(H):
+    import torch
+    a = torch.rand(5, 3, H, H, device="cuda")
+    b = a.clone()
+    b[1, 2, H - 1, H - 1] += 0.5
+    b[3, 0, 0, 0] = float("nan")
+    for peak in (1.0, 255.0):
+        got = rinr_fit.psnr_batch(a, b, peak).cpu().numpy()
+        plain = torch.empty(5, device="cuda")
+        assert rinr_fit.lib().rinr_psnr_batch(a.data_ptr(), b.data_ptr(), 5, 3 * H * H, peak, plain.data_ptr(), rinr._stream_ptr(None)) == rinr.OK
+        for x in (got, plain.cpu().numpy()):
+            assert np.isnan(x[3]) and np.isposinf(x[[0, 2, 4]]).all() and np.isfinite(x[1])
 
 
 def test_an_encoded_image_whose_error_is_no_number():
