@@ -16,6 +16,9 @@ from .synth import Layer, Model
 MAX_LAYERS = 12
 FIT_FLAG_FP32_MFMA = 1
 KERNEL_FP32, KERNEL_SPLIT16 = 0, 1
+# rinr_psnr_workspace_bytes is 0 from that many images on, and below that many elements of each: it is not asked then (0.8 us of a 7 us call).  A
+# test holds the library to it.
+PSNR_SHARED_IMAGES, PSNR_SHARED_ELEMS = 128, 131072
 EXPORTS = ["rinr_prune_ratio", "rinr_l1_mask", "rinr_quantize_layer", "rinr_fit_create", "rinr_fit_create_ex", "rinr_fit_kernel_family",
            "rinr_fit_kernel_units", "rinr_fit_destroy",
            "rinr_fit_n_params", "rinr_fit_set_params", "rinr_fit_set_keep", "rinr_fit_reset_optimizer",
@@ -107,7 +110,7 @@ def psnr_batch(a, b, peak: float = 1.0, stream=None):
     n = a.shape[0]
     elems = a.numel() // n if n else 0
     L = lib()
-    need = L.rinr_psnr_workspace_bytes(n, elems) if n < 128 and elems >= 131072 else 0       # (0 beyond, without asking)
+    need = L.rinr_psnr_workspace_bytes(n, elems) if n < PSNR_SHARED_IMAGES and elems >= PSNR_SHARED_ELEMS else 0
 
     def memory():                                                      # few images: several workgroups share one, with scratch memory
         return (torch.empty((n,), dtype=torch.float32, device=a.device),

@@ -97,7 +97,7 @@ def test_memory_belongs_to_the_stream_that_uses_it(H, monkeypatch):
         assert np.abs(got - want).max() <= BOUND_DB + 2e-6 * np.abs(want).max()
 
 
-@pytest.mark.parametrize("H", [40, 64, 210])                                  # 256 threads, 1024, several workgroups an image
+@pytest.mark.parametrize("H", [36, 64, 210])                                  # 256 threads, 1024, several workgroups an image
 def test_a_sum_that_is_no_number_is_not_a_perfect_match(H):
     import torch
     a = torch.rand(5, 3, H, H, device="cuda")
