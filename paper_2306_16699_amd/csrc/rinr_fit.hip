@@ -128,7 +128,7 @@ struct FitArgs {
     int32_t d[kMaxL + 1];         // true widths
     int32_t p_off[kMaxL];         // offset of W_l in the parameter vector
     float gscale[kMaxL];          // what the accumulated weight gradient of layer l is multiplied by (see the kernel)
-    int32_t steps;                // Adam steps of this launch: 1 but in split-precision kernels that say so (fit16_many_steps)
+    int32_t steps;                // Adam steps of this launch: one, or more of a kernel that takes several (fit16_many_steps)
     FitStep step[kStepsAtOnce];
 };
 
@@ -558,14 +558,20 @@ constexpr int fit16_tiles(int wp, int ml) {
     const int one = fit16::fit16_waves_per_simd(wp, ml, 1), two = fit16::fit16_waves_per_simd(wp, ml, 2);
     return (one > 1 && two == 1) || fit16::fit16_registers(wp, ml, 2) > 512 ? 1 : 2;
 }
-struct Fit16 { fit_fn fn; uint32_t lds; int pixels; bool many_steps; };      // kernel, LDS bytes, pixels a workgroup takes at a time, several steps a launch
+// The kernel, and the one that takes several steps a launch (or null); LDS bytes and pixels a workgroup takes at a time of either
+struct Fit16 { fit_fn fn, many; uint32_t lds; int pixels; };
+template <int WP, bool HALF, int L, int NT> constexpr fit_fn many_of() {
+    if constexpr (fit16::fit16_many_steps(WP, L, NT)) return fit16::fit16_step_kernel<WP, HALF, L, NT, true>;
+    else return nullptr;
+}
 template <int WP, bool HALF, int L = 2> Fit16 kernel16_of(int n) {
     if constexpr (L > fit16_depth(WP)) {
-        return Fit16{nullptr, 0, 0, false};
+        return Fit16{nullptr, nullptr, 0, 0};
     } else {
         constexpr int nt = fit16_tiles(WP, L);
         if constexpr (WP == 64 && HALF && L <= 3) return kernel16_of<WP, HALF, L + 1>(n);
-        else return n == L ? Fit16{fit16::fit16_step_kernel<WP, HALF, L, nt>, fit16::Shape<WP, HALF>::total(L, nt), fit16::kThreads / 4 * nt, fit16::fit16_many_steps(WP, L, nt)} : kernel16_of<WP, HALF, L + 1>(n);
+        else return n == L ? Fit16{fit16::fit16_step_kernel<WP, HALF, L, nt, false>, many_of<WP, HALF, L, nt>(), fit16::Shape<WP, HALF>::total(L, nt), fit16::kThreads / 4 * nt}
+                           : kernel16_of<WP, HALF, L + 1>(n);
     }
 }
 // width: of the widest hidden layer.  Half of the last tile empty: the kernels that do not compute it (fit16::Shape), but for one that spills and is
@@ -590,7 +596,7 @@ Fit16 kernel16_for(int width, int L, bool half) {
     const int wp = (width + 15) / 16 * 16;
     const Fit16 k = half ? (wp == 16 ? kernel16_of<16, true>(L) : (wp == 32 ? kernel16_of<32, true>(L) : (wp == 48 ? kernel16_of<48, true>(L) : kernel16_of<64, true>(L))))
                          : (wp == 16 ? kernel16_of<16, false>(L) : (wp == 32 ? kernel16_of<32, false>(L) : (wp == 48 ? kernel16_of<48, false>(L) : kernel16_of<64, false>(L))));
-    return k.lds <= kLdsLimit - 256 ? k : Fit16{nullptr, 0, 0, false};
+    return k.lds <= kLdsLimit - 256 ? k : Fit16{nullptr, nullptr, 0, 0};
 }
 
 }  // namespace
@@ -601,7 +607,8 @@ struct rinr_fit {
     int32_t H, W;
     int wq, lds_floats;         // wq: widest hidden layer rounded up to a multiple of 8 (fp32 kernels); lds_floats 0 = no fp32 kernel fits
     int family;                 // RINR_FIT_KERNEL_FP32 or RINR_FIT_KERNEL_SPLIT16: the kernels this handle's steps run
-    Fit16 k16;                  // their kernel; null = none is built for the shape
+    Fit16 k16;                  // their kernels; null = none is built for the shape
+    int most;                   // Adam steps that a launch takes; more than one: of k16.many
     int units;                  // of a hidden layer that the handle's kernel computes (rinr_fit_kernel_units)
     float *emag;                // [n_images] error size seen by the last step (split kernels' error scale); 0 = none yet
     int32_t p_off[kMaxL];
@@ -615,27 +622,45 @@ struct rinr_fit {
 };
 
 namespace {
+// Adam steps that a launch takes of an image that one workgroup has
+int most_steps(const rinr_fit *f) {
+    if (f->family != RINR_FIT_KERNEL_SPLIT16 || !f->k16.many) return 1;
+    const int64_t chunks = ((int64_t)f->H * f->W + f->k16.pixels - 1) / f->k16.pixels;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(kStepsAtOnce, kChunksAtOnce / chunks));
+}
+// Dynamic LDS beyond the default for a handle's kernels
+bool may_use_lds(const Fit16 &k) {
+    const int most = (int)kLdsLimit - 256;
+    return !hip_fail(hipFuncSetAttribute((const void *)k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, most)) &&
+           (!k.many || !hip_fail(hipFuncSetAttribute((const void *)k.many, hipFuncAttributeMaxDynamicSharedMemorySize, most)));
+}
 // Workgroups per image.  One workgroup per image updates it in the same launch; where the images alone leave the machine
 // idle (few of them, or a last round that is nearly empty), an image's pixels are shared by several, and a second kernel
 // adds their partial gradients up.  The model: rounds of workgroups x (a share's chunks + what a workgroup costs before its
 // first chunk, about two chunks' time), and for more than one share the second launch (about one chunk more; five against several steps a launch, us
 // a step in shares -> so, images of 32 x 32: 300, 2 layers x 8 13.9 -> 11.1; 600, 3 x 32 59.3 -> 52.6, 8 x 15 85.7 -> 77.8).  Measured
 // (8 images of 171 x 219, 10 layers x 32): 3241 us a step with one workgroup per image, 106 with 30 and the kernels of today.
-int plan_splits(const rinr_fit *f, const void *fn) {
+int plan_splits(const rinr_fit *f) {
     const bool split16 = f->family == RINR_FIT_KERNEL_SPLIT16;
     const int waves = split16 ? fit16::kWaves : fit_waves(f->wq);
     const size_t lds = split16 ? (size_t)f->k16.lds : (size_t)f->lds_floats * 4;
     const int64_t pc = split16 ? f->k16.pixels : 64, chunks = ((int64_t)f->H * f->W + pc - 1) / pc;
-    int device = 0, cus = 256, resident = 1;
+    int device = 0, cus = 256;
     if (hip_fail(hipGetDevice(&device)) || hip_fail(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, device)) || cus < 1) cus = 256;
-    if (hip_fail(hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, fn, 64 * waves, lds)) || resident < 1) resident = 1;
     // workgroups that run side by side without slowing each other much: four wavefronts per SIMD
-    const int64_t slots = (int64_t)cus * std::min(resident, std::max(1, 16 / waves));
-    if (f->n_images >= 16 * slots) return 1;           // many rounds: the last one's idle part does not matter
-    const int64_t second = split16 && f->k16.many_steps && chunks * 2 <= kChunksAtOnce ? 5 : 1;
+    auto side_by_side = [&](const void *fn) {
+        int resident = 1;
+        if (hip_fail(hipOccupancyMaxActiveBlocksPerMultiprocessor(&resident, fn, 64 * waves, lds)) || resident < 1) resident = 1;
+        return (int64_t)cus * std::min(resident, std::max(1, 16 / waves));
+    };
+    const bool many = most_steps(f) > 1;
+    const int64_t shared = side_by_side(split16 ? (const void *)f->k16.fn : (const void *)kernel_for(f->wq, f->arch.n_layers));
+    const int64_t alone = many ? side_by_side((const void *)f->k16.many) : shared;
+    const int64_t second = many ? 5 : 1;
+    if (f->n_images >= 16 * alone) return 1;           // many rounds: the last one's idle part does not matter
     int64_t best = 1, best_t = INT64_MAX;
     for (int64_t s = 1; s <= chunks && s <= 1024; ++s) {
-        const int64_t rounds = (f->n_images * s + slots - 1) / slots;
+        const int64_t slots = s > 1 ? shared : alone, rounds = (f->n_images * s + slots - 1) / slots;
         const int64_t t = rounds * ((chunks + s - 1) / s + 2) + (s > 1 ? second : 0);
         if (t < best_t) { best_t = t; best = s; }
         if (f->n_images * s > 8 * slots) break;
@@ -685,24 +710,22 @@ extern "C" int rinr_fit_create_ex(const rinr_fit_arch *arch, int64_t n_images, i
     f->keep = nullptr;
     f->has_keep = false;
     f->t = 0;
-    const void *fn = f->family == RINR_FIT_KERNEL_SPLIT16 ? (const void *)f->k16.fn
-                                                         : (const void *)kernel_for(f->wq, arch->n_layers);
     if (hip_fail(hipMalloc((void **)&f->params, np * 4)) || hip_fail(hipMalloc((void **)&f->m, np * 4)) ||
         hip_fail(hipMalloc((void **)&f->v, np * 4)) || hip_fail(hipMalloc((void **)&f->keep, np)) ||
         hip_fail(hipMalloc((void **)&f->loss, ni * 4)) || hip_fail(hipMalloc((void **)&f->emag, ni * 4)) ||
         hip_fail(hipMemset(f->params, 0, np * 4)) || hip_fail(hipMemset(f->m, 0, np * 4)) ||
         hip_fail(hipMemset(f->v, 0, np * 4)) || hip_fail(hipMemset(f->loss, 0, ni * 4)) || hip_fail(hipMemset(f->emag, 0, ni * 4)) ||
-        hip_fail(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit - 256))) {
+        !may_use_lds(f->family == RINR_FIT_KERNEL_SPLIT16 ? f->k16 : Fit16{kernel_for(f->wq, arch->n_layers), nullptr, 0, 0})) {
         rinr_fit_destroy(f);
         return RINR_E_HIP;
     }
-    f->splits = plan_splits(f, fn);
+    f->splits = plan_splits(f);
     if (half && f->family == RINR_FIT_KERNEL_SPLIT16 && ((int64_t)H * W + f->splits - 1) / f->splits < half_pays_from(wmax, arch->n_layers)) {
         const Fit16 k = kernel16_for(wmax, arch->n_layers, false);
-        if (k.fn && !hip_fail(hipFuncSetAttribute((const void *)k.fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLdsLimit - 256))) {
+        if (k.fn && may_use_lds(k)) {
             f->k16 = k;
             f->units = (wmax + 15) / 16 * 16;
-            f->splits = plan_splits(f, (const void *)k.fn);
+            f->splits = plan_splits(f);
         }
     }
     // no memory for the partial gradients: a workgroup takes a whole image, and the refusal is not left for the first launch's check
@@ -711,6 +734,7 @@ extern "C" int rinr_fit_create_ex(const rinr_fit_arch *arch, int64_t n_images, i
         f->splits = 1;
         (void)hipGetLastError();
     }
+    f->most = f->splits == 1 ? most_steps(f) : 1;
     *out = f;
     return RINR_OK;
 }
@@ -880,7 +904,7 @@ int launch(rinr_fit *f, const float *targets, float loss_scale, const float *lr,
     for (int l = 0; l <= a.L; ++l) a.d[l] = f->arch.widths[l];
     for (int l = 0; l < a.L; ++l) a.p_off[l] = f->p_off[l];
     if (f->family == RINR_FIT_KERNEL_SPLIT16)
-        hipLaunchKernelGGL(f->k16.fn, dim3((uint32_t)(f->n_images * f->splits)), dim3(fit16::kThreads), (size_t)f->k16.lds, stream, a);
+        hipLaunchKernelGGL(f->most > 1 ? f->k16.many : f->k16.fn, dim3((uint32_t)(f->n_images * f->splits)), dim3(fit16::kThreads), (size_t)f->k16.lds, stream, a);
     else
         hipLaunchKernelGGL(kernel_for(f->wq, f->arch.n_layers), dim3((uint32_t)(f->n_images * f->splits)), dim3(64 * fit_waves(f->wq)), (size_t)f->lds_floats * 4, stream, a);
     FIT_HIP(hipGetLastError());
@@ -903,16 +927,10 @@ extern "C" int rinr_fit_steps(rinr_fit *f, const float *targets, int32_t n_steps
     if (!(b1 > 0.0f && b1 < 1.0f && b2 > 0.0f && b2 < 1.0f && eps > 0.0f) || !(o->loss_scale >= 0.0f)) return RINR_E_ARG;
     const float ls = o->loss_scale != 0.0f ? o->loss_scale : (float)(1.0 / (3.0 * (double)f->H * (double)f->W));
     if (f->n_images == 0) { f->t += n_steps; return RINR_OK; }
-    // an image that one workgroup takes goes through several steps in one launch, where the kernel is built for it
-    int32_t most = 1;
-    if (f->family == RINR_FIT_KERNEL_SPLIT16 && f->k16.many_steps && f->splits == 1) {
-        const int64_t chunks = ((int64_t)f->H * f->W + f->k16.pixels - 1) / f->k16.pixels;
-        most = (int32_t)std::max<int64_t>(1, std::min<int64_t>(kStepsAtOnce, kChunksAtOnce / chunks));
-    }
     for (int32_t i = 0; i < n_steps;) {
         float rates[kStepsAtOnce];
         int32_t k = 0;
-        for (; k < most && i + k < n_steps; ++k) {
+        for (; k < f->most && i + k < n_steps; ++k) {
             double lr = o->lr;
             if (o->T > 0) lr = 0.5 * lr * (1.0 + std::cos(3.14159265358979323846 * (double)(o->t0 + i + k) / (double)o->T));
             rates[k] = (float)lr;

@@ -72,21 +72,24 @@ constexpr int fit16_registers(int wp, int ml, int nt) {
     return 4 * (2 * mt + (ml - 2) * mt * mt) + 4 * nt * mt * (ml - 1) + 40 + 16 * nt * mt;
 }
 // Wavefronts per SIMD a kernel is compiled for: as many as its estimate leaves.  The estimate does not count the addresses and operands of
-// the inputs in LDS, and so some kernels spill: 4 layers x 16 at four wavefronts (23 registers; half-filled 16), 7 x 16 at three (20; 9), 5 x 32 (8), 8 x 32 (28)
+// the inputs in LDS, and so some kernels spill: 4 layers x 16 at four wavefronts (23 registers; half-filled 8), 7 x 16 at three (17; 1), 5 x 32 (4), 8 x 32 (16)
 // and 8 x 24 (15) at two.  With
 // the inputs in LDS and these spills against the kernels before (of them 7 x 16 alone spilled, 24): 512 images of 96 x 96, 5 x 32 500 -> 459, 256 of 96 x 96, 8 x 32 475 -> 478 and 8 x 24 (half-filled
 // tile) 441 -> 396, 1024 of 64 x 64, 7 x 16 343 -> 312.  Measured, us a step, spilled -> as chosen:
 //   four instead of three, 48 x 48, width 16, 2048 images: 4 layers 198 -> 189, 5 layers 249 -> 241; 6144 images: 561 -> 555, 692 -> 691
-//   three instead of four at 4 layers, which with several steps a launch take more registers: 1024 images of 64 x 64, width 8: 94.1 -> 110
 //   two instead of three: 8 layers x 16: 243 -> 232; 3 x 32: 150 -> 144
 //   three (spilling) instead of two at 7 layers x 16, 48 x 48: 6144 images 1063 -> 1001; against it 1024 of 64 x 64: 319 -> 328
-constexpr int fit16_waves_per_simd(int wp, int ml, int nt) {
+// Four (spilling) is as chosen too at 4 layers x 16 where a launch takes several steps: 1024 images of 64 x 64, width 8, three 110, four 94.1.  Where images are shared, three:
+// 20 of 128 x 128, 4 x 15 24.2, four 26.3.
+// many: of the kernel that takes several steps a launch, where there is one
+constexpr int fit16_waves_per_simd(int wp, int ml, int nt, bool many = true) {
     const int r = fit16_registers(wp, ml, nt);
-    return r <= 112 ? 4 : (r <= 156 ? 3 : (r <= 256 ? 2 : 1));
+    return r <= (many ? 112 : 100) ? 4 : (r <= 156 ? 3 : (r <= 256 ? 2 : 1));
 }
 
 // Whether a launch takes several steps of an image that one workgroup has.  A launch of its own costs a step its gap, the last round's idle part and
-// instructions that are fetched again; a kernel that loops takes more registers, which small ones have.  us a step, a launch each -> 32
+// instructions that are fetched again; a kernel that loops takes more registers, which small ones have.  Images that are shared, or so large that a launch takes one step,
+// have the kernel without the loop (with it -> without: 8 images of 128 x 128, 3 x 24 18.1 -> 17.4; 20, 4 x 15 26.3 -> 24.2; 256 of 362 x 362, 2 x 15 556 -> 545).  us a step, a launch each -> 32
 // steps a launch, 2048 images of 32 x 32: 2 layers x 15 43.0 -> 39.6, 3 x 15 64.8 -> 60.5, 5 x 15 107.7 -> 104.6, 8 x 15 187.9 -> 181.3, 8 x 8 129.1 -> 122.5, 2 x 32 71.2 -> 69.1,
 // 3 x 32 132.3 -> 127.8; 1024 of 64 x 64: 4 x 15 158.1 -> 146.7, 5 x 15 194.3 -> 195.7, 3 x 32 214.2 -> 209.5.  Beyond: 512 of 96 x 96, 4 x 32 322 -> 331, 5 x 24 338 -> 352.
 constexpr bool fit16_many_steps(int wp, int ml, int nt) { return fit16_registers(wp, ml, nt) <= 168; }
@@ -868,18 +871,19 @@ template <int WP, bool HALF, int L, int NT, bool kBelow, class Args> __device__ 
     }
 }
 
-template <int WP, bool HALF, int L, int NT>
-__global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, L, NT)) void fit16_step_kernel(const FitArgs a) {
+// kMany: several steps of an image that one workgroup has
+template <int WP, bool HALF, int L, int NT, bool kMany>
+__global__ __launch_bounds__(kThreads, fit16_waves_per_simd(WP, L, NT, kMany)) void fit16_step_kernel(const FitArgs a) {
     extern __shared__ __attribute__((aligned(16))) char lds16[];
     const uint32_t pixels = kWaves * 16 * NT;
     auto step = [&](const auto &args, int s, int tid) {
         const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
         const uint32_t nchunks = (args.HW + pixels - 1) / pixels;
-        const FitShare share = fit16_many_steps(WP, L, NT) && args.splits == 1 ? FitShare{blockIdx.x, 0u, nchunks, nullptr} : fit_share(args, nchunks);      // (a 64-bit division)
+        const FitShare share = kMany ? FitShare{blockIdx.x, 0u, nchunks, nullptr} : fit_share(args, nchunks);
         if (!fit16_set_up<WP, HALF, L>(args, lds16, share.img, tid, wave)) fit16_pixels<WP, HALF, L, NT, false>(args, lds16, share, s, tid, wave);
         else fit16_pixels<WP, HALF, L, NT, true>(args, lds16, share, s, tid, wave);
     };
-    if constexpr (fit16_many_steps(WP, L, NT)) {
+    if constexpr (kMany) {
         // The arguments and the lane are made unknown again for every step: what a step derives from them would be held across the loop, and spill.
         typedef const __attribute__((address_space(4))) FitArgs *ConstArgs;
         for (int s = 0; s < a.steps; ++s) {
