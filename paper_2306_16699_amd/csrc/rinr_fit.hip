@@ -637,9 +637,16 @@ bool may_use_lds(const Fit16 &k) {
 // Workgroups per image.  One workgroup per image updates it in the same launch; where the images alone leave the machine
 // idle (few of them, or a last round that is nearly empty), an image's pixels are shared by several, and a second kernel
 // adds their partial gradients up.  The model: rounds of workgroups x (a share's chunks + what a workgroup costs before its
-// first chunk, about two chunks' time), and for more than one share the second launch (about one chunk more; five against several steps a launch, us
-// a step in shares -> so, images of 32 x 32: 300, 2 layers x 8 13.9 -> 11.1; 600, 3 x 32 59.3 -> 52.6, 8 x 15 85.7 -> 77.8).  Measured
-// (8 images of 171 x 219, 10 layers x 32): 3241 us a step with one workgroup per image, 106 with 30 and the kernels of today.
+// first chunk, about two chunks' time), and for more than one share the second launch, about one chunk more.  Measured
+// (8 images of 171 x 219, 10 layers x 32): 3241 us a step with one workgroup per image, 101 with 30.
+// Where a launch takes several steps of an unshared image, and no second launch, the second launch of a shared one weighs more: it takes 5 to 11 us, and a
+// chunk of 128 pixels 1.1 us at 2 layers x 15, 1.6 at 3 x 15, 1.8 at 2 x 32, 2.3 at 3 x 32, 2.5 at 4 and 5 x 15, 3.6 at 8 x 15.  That gives what it weighs in
+// chunks.  us a step, shared -> a workgroup an image in launches of 32 steps, and one step a call: 300 images of 32 x 32, 2 x 8 13.6 -> 10.8, 13.4; 64 of 24 x 24,
+// 2 x 15 10.7 -> 7.7, 10.0; 1000 of 40 x 40, 7 x 15 147 -> 120, 123; 700, 3 x 32 92.5 -> 72.9, 75.0; 600 of 32 x 32, 8 x 15 83.7 -> 74.0, 76.7.  Five
+// chunks for all of them are too much for deeper models: 64 of 24 x 24, 4 x 15 13.8 -> 14.2, 16.5, 5 x 15 15.5 -> 17.1, 19.5, 8 x 15 20.8 -> 24.9, 27.4; 128 of 28 x 28,
+// 6 x 15 21.8 -> 24.5, 27.1, 3 x 32 19.5 -> 20.6, 22.8; 800 of 64 x 64, 8 x 15 288 -> 312, 307.  The plan is the handle's, whatever the steps of a call, so that a
+// fit's bits do not depend on how its steps are cut into calls; one step a call loses most at 700 of 64 x 64, 2 x 15: 57.0 -> 58.9, in launches of 32 56.5.  What the rule
+// leaves shared although launches of 32 are the faster: 1100 of 48 x 48, 3 x 32 160 -> 155, 154; 300 of 32 x 32, 5 x 8 23.0 -> 22.2, 25.3.
 int plan_splits(const rinr_fit *f) {
     const bool split16 = f->family == RINR_FIT_KERNEL_SPLIT16;
     const int waves = split16 ? fit16::kWaves : fit_waves(f->wq);
@@ -656,7 +663,8 @@ int plan_splits(const rinr_fit *f) {
     const bool many = most_steps(f) > 1;
     const int64_t shared = side_by_side(split16 ? (const void *)f->k16.fn : (const void *)kernel_for(f->wq, f->arch.n_layers));
     const int64_t alone = many ? side_by_side((const void *)f->k16.many) : shared;
-    const int64_t second = many ? 5 : 1;
+    const int L = f->arch.n_layers;
+    const int64_t second = !many ? 1 : (L >= 8 ? 2 : (L >= 4 ? 3 : (L == 3 && f->wq > 16 ? 4 : 5)));
     if (f->n_images >= 16 * alone) return 1;           // many rounds: the last one's idle part does not matter
     int64_t best = 1, best_t = INT64_MAX;
     for (int64_t s = 1; s <= chunks && s <= 1024; ++s) {

@@ -48,6 +48,17 @@ PLANS = [
     # images that are shared only where a step is a launch anyway
     ((600, 32, 32, 32, 3, 2, 70), 3, False),
     ((600, 32, 32, 32, 4, 2, 2), 4, True),
+    # the second launch weighs less the deeper the model: measured on either side
+    ((64, 24, 24, 15, 2, 4, 32), 1, False),
+    ((64, 24, 24, 15, 5, 3, 1), 2, True),
+    ((64, 24, 24, 15, 8, 2, 1), 2, True),
+    ((128, 28, 28, 15, 6, 3, 1), 2, True),
+    ((128, 28, 28, 32, 3, 2, 1), 2, True),
+    ((800, 64, 64, 15, 8, 2, 1), 2, True),
+    ((64, 24, 24, 15, 4, 3, 1), 2, True),
+    ((400, 32, 32, 15, 4, 3, 32), 1, False),
+    ((1000, 40, 40, 15, 7, 3, 32), 1, False),
+    ((600, 32, 32, 15, 8, 2, 32), 1, False),
 ]
 
 
