@@ -16,9 +16,9 @@ from .synth import Layer, Model
 MAX_LAYERS = 12
 FIT_FLAG_FP32_MFMA = 1
 KERNEL_FP32, KERNEL_SPLIT16 = 0, 1
-# rinr_psnr_workspace_bytes is 0 from that many images on, and below that many elements of each: it is not asked then (0.8 us of a 7 us call).  A
-# test holds the library to it.
-PSNR_SHARED_IMAGES, PSNR_SHARED_ELEMS = 128, 131072
+# rinr_psnr_workspace_bytes is 0 from that many images on, and below that many elements of each, and nowhere more than that many bytes: it is not asked
+# (0.8 us of a call of 7 to 12).  A test holds the library to all three.
+PSNR_SHARED_IMAGES, PSNR_SHARED_ELEMS, PSNR_WORK_BYTES = 128, 131072, 5080
 EXPORTS = ["rinr_prune_ratio", "rinr_l1_mask", "rinr_quantize_layer", "rinr_fit_create", "rinr_fit_create_ex", "rinr_fit_kernel_family",
            "rinr_fit_kernel_units", "rinr_fit_destroy",
            "rinr_fit_n_params", "rinr_fit_set_params", "rinr_fit_set_keep", "rinr_fit_reset_optimizer",
@@ -110,25 +110,22 @@ def psnr_batch(a, b, peak: float = 1.0, stream=None):
     n = a.shape[0]
     elems = a.numel() // n if n else 0
     L = lib()
-    need = L.rinr_psnr_workspace_bytes(n, elems) if n < PSNR_SHARED_IMAGES and elems >= PSNR_SHARED_ELEMS else 0
-
-    def memory():                                                      # few images: several workgroups share one, with scratch memory
-        return (torch.empty((n,), dtype=torch.float32, device=a.device),
-                torch.empty((need,), dtype=torch.uint8, device=a.device) if need else None)
-
+    need = PSNR_WORK_BYTES if n < PSNR_SHARED_IMAGES and elems >= PSNR_SHARED_ELEMS else 0
     if stream is None:
-        out, work = memory()
+        out = torch.empty((n,), dtype=torch.float32, device=a.device)
+        work = torch.empty((need,), dtype=torch.uint8, device=a.device) if need else None
     else:
         # Memory of the stream that works on it: what the current stream has freed it may still be using, and nothing makes `stream` wait for
         # that.  An integer is a stream of the tensors' GPU, 0 its default stream (ExternalStream(0) would be another stream of PyTorch's own).
         s = stream if isinstance(stream, torch.cuda.Stream) else \
             (torch.cuda.ExternalStream(rinr._stream_ptr(stream), device=a.device) if rinr._stream_ptr(stream) else torch.cuda.default_stream(a.device))
         with torch.cuda.stream(s):
-            out, work = memory()
+            out = torch.empty((n,), dtype=torch.float32, device=a.device)
+            work = torch.empty((need,), dtype=torch.uint8, device=a.device) if need else None
         out.record_stream(torch.cuda.current_stream(a.device))         # where the caller goes on with it
     if work is None:
         rinr._check(L.rinr_psnr_batch(a.data_ptr(), b.data_ptr(), n, elems, peak, out.data_ptr(), rinr._stream_ptr(stream)), "rinr_psnr_batch")
-    else:
+    else:                                                              # few images: several workgroups share one
         rinr._check(L.rinr_psnr_batch_ex(a.data_ptr(), b.data_ptr(), n, elems, peak, out.data_ptr(), work.data_ptr(), need, rinr._stream_ptr(stream)),
                     "rinr_psnr_batch_ex")
     return out
