@@ -179,13 +179,14 @@ template <class Args> __device__ __forceinline__ void fit_put_grad(const Args &a
     else fit_apply(a, w.img, at, gr, step);
 }
 
-// Four entries of an image at once (at < 0: none).  A share's part goes out first and waits for nothing.  For Adam, what it reads of all four is under
-// way together (an entry at a time waits for memory twice for each, since the stores may be to what the next one loads), and all of it is used
-// whether an entry is there or not: a load that some lanes leave unused is still under way where the ways meet again, and the wait for it there
-// was a wait for the last tile's stores on every way, the share's too.  With that, and Adam's code five times behind every tile, us a step, before -> now:
-// 4 images of 32 x 32, 5 x 64 39.1 -> 37.2, 30 of 64 x 64, 6 x 40 59.4 -> 57.6, one of 224 x 224, 10 x 32 43.5 -> 42.1, 2 of 128 x 128, 5 x 56 46.9 -> 45.0; 8 of
-// 171 x 219, 10 x 40 170.2 -> 168.0, 10 x 32 102.6 -> 100.9; unshared, 256 of 96 x 96: 9 x 48 974 -> 935, 8 x 40 736 -> 720, 7 x 24 523 -> 523, 10 x 40 909 -> 914,
-// 9 x 24 417 -> 423, 12 x 32 668 -> 676 and, where the compiler orders the code over the pixels the worse way for it, 9 x 40 810 -> 822, 5 x 64 705 -> 726.
+// Four entries of an image at once (at < 0: none).  A share's part goes out first and waits for nothing.  For Adam, what it reads of all four is
+// under way together (an entry at a time waits for memory twice for each, since the stores may be to what the next one loads), and all of it is used
+// whether an entry is there or not: a load that some lanes leave unused is still under way where the ways meet again, and the wait for it there was a
+// wait for the last tile's stores on every way, the share's too.  With that, and Adam's code five times behind every tile, us a step, before -> now:
+// 4 images of 32 x 32, 5 x 64 39.1 -> 37.2, 30 of 64 x 64, 6 x 40 59.4 -> 57.6, one of 224 x 224, 10 x 32 43.5 -> 42.1, 2 of 128 x 128, 5 x 56 46.9
+// -> 45.0; 8 of 171 x 219, 10 x 40 170.2 -> 168.0, 10 x 32 102.6 -> 100.9; unshared, 256 of 96 x 96: 9 x 48 974 -> 935, 8 x 40 736 -> 720, 7 x 24 523
+// -> 523, 10 x 40 909 -> 914, 9 x 24 417 -> 423, 12 x 32 668 -> 676 and, where the compiler orders the code over the pixels the worse way for it, 9 x
+// 40 810 -> 822, 5 x 64 705 -> 726.
 template <class Args> __device__ __forceinline__ void fit_put_grads(const Args &a, const FitShare &w, const int (&at)[4], const float (&gr)[4], int step) {
     if (w.part) {
 #pragma unroll
@@ -570,8 +571,8 @@ template <int WP, bool HALF, int L = 2> Fit16 kernel16_of(int n) {
     } else {
         constexpr int nt = fit16_tiles(WP, L);
         if constexpr (WP == 64 && HALF && L <= 3) return kernel16_of<WP, HALF, L + 1>(n);
-        else return n == L ? Fit16{fit16::fit16_step_kernel<WP, HALF, L, nt, false>, many_of<WP, HALF, L, nt>(), fit16::Shape<WP, HALF>::total(L, nt), fit16::kThreads / 4 * nt}
-                           : kernel16_of<WP, HALF, L + 1>(n);
+        else if (n != L) return kernel16_of<WP, HALF, L + 1>(n);
+        else return Fit16{fit16::fit16_step_kernel<WP, HALF, L, nt, false>, many_of<WP, HALF, L, nt>(), fit16::Shape<WP, HALF>::total(L, nt), fit16::kThreads / 4 * nt};
     }
 }
 // width: of the widest hidden layer.  Half of the last tile empty: the kernels that do not compute it (fit16::Shape), but for one that spills and is
@@ -639,14 +640,15 @@ bool may_use_lds(const Fit16 &k) {
 // adds their partial gradients up.  The model: rounds of workgroups x (a share's chunks + what a workgroup costs before its
 // first chunk, about two chunks' time), and for more than one share the second launch, about one chunk more.  Measured
 // (8 images of 171 x 219, 10 layers x 32): 3241 us a step with one workgroup per image, 101 with 30.
-// Where a launch takes several steps of an unshared image, and no second launch, the second launch of a shared one weighs more: it takes 5 to 11 us, and a
-// chunk of 128 pixels 1.1 us at 2 layers x 15, 1.6 at 3 x 15, 1.8 at 2 x 32, 2.3 at 3 x 32, 2.5 at 4 and 5 x 15, 3.6 at 8 x 15.  That gives what it weighs in
-// chunks.  us a step, shared -> a workgroup an image in launches of 32 steps, and one step a call: 300 images of 32 x 32, 2 x 8 13.6 -> 10.8, 13.4; 64 of 24 x 24,
-// 2 x 15 10.7 -> 7.7, 10.0; 1000 of 40 x 40, 7 x 15 147 -> 120, 123; 700, 3 x 32 92.5 -> 72.9, 75.0; 600 of 32 x 32, 8 x 15 83.7 -> 74.0, 76.7.  Five
-// chunks for all of them are too much for deeper models: 64 of 24 x 24, 4 x 15 13.8 -> 14.2, 16.5, 5 x 15 15.5 -> 17.1, 19.5, 8 x 15 20.8 -> 24.9, 27.4; 128 of 28 x 28,
-// 6 x 15 21.8 -> 24.5, 27.1, 3 x 32 19.5 -> 20.6, 22.8; 800 of 64 x 64, 8 x 15 288 -> 312, 307.  The plan is the handle's, whatever the steps of a call, so that a
-// fit's bits do not depend on how its steps are cut into calls; one step a call loses most at 700 of 64 x 64, 2 x 15: 57.0 -> 58.9, in launches of 32 56.5.  What the rule
-// leaves shared although launches of 32 are the faster: 1100 of 48 x 48, 3 x 32 160 -> 155, 154; 300 of 32 x 32, 5 x 8 23.0 -> 22.2, 25.3.
+// Where a launch takes several steps of an unshared image, and no second launch, the second launch of a shared one weighs more: it takes 5 to 11 us,
+// and a chunk of 128 pixels 1.1 us at 2 layers x 15, 1.6 at 3 x 15, 1.8 at 2 x 32, 2.3 at 3 x 32, 2.5 at 4 and 5 x 15, 3.6 at 8 x 15.  That gives
+// what it weighs in chunks.  us a step, shared -> a workgroup an image in launches of 32 steps, and one step a call: 300 images of 32 x 32, 2 x 8
+// 13.6 -> 10.8, 13.4; 64 of 24 x 24, 2 x 15 10.7 -> 7.7, 10.0; 1000 of 40 x 40, 7 x 15 147 -> 120, 123; 700, 3 x 32 92.5 -> 72.9, 75.0; 600 of 32 x
+// 32, 8 x 15 83.7 -> 74.0, 76.7.  Five chunks for all of them are too much for deeper models: 64 of 24 x 24, 4 x 15 13.8 -> 14.2, 16.5, 5 x 15 15.5
+// -> 17.1, 19.5, 8 x 15 20.8 -> 24.9, 27.4; 128 of 28 x 28, 6 x 15 21.8 -> 24.5, 27.1, 3 x 32 19.5 -> 20.6, 22.8; 800 of 64 x 64, 8 x 15 288 -> 312,
+// 307.  The plan is the handle's, whatever the steps of a call, so that a fit's bits do not depend on how its steps are cut into calls; one step a
+// call loses most at 700 of 64 x 64, 2 x 15: 57.0 -> 58.9, in launches of 32 56.5.  What the rule leaves shared although launches of 32 are the
+// faster: 1100 of 48 x 48, 3 x 32 160 -> 155, 154; 300 of 32 x 32, 5 x 8 23.0 -> 22.2, 25.3.
 int plan_splits(const rinr_fit *f) {
     const bool split16 = f->family == RINR_FIT_KERNEL_SPLIT16;
     const int waves = split16 ? fit16::kWaves : fit_waves(f->wq);
@@ -976,11 +978,15 @@ extern "C" int rinr_fit_last_loss(const rinr_fit *f, float *loss, void *stream) 
 }
 
 // ---- PSNR per image: a streaming reduction, bound by HBM (8 bytes read per element) where there are images enough to fill the GPU.  A workgroup
-// reads about 0.1 TB/s, so fewer than 256 images are shared by several workgroups each, which leave their sums in the caller's workspace, where
-// there is one, and a second small kernel adds them up.  us a call, before -> now, images of 224 x 224: 1 14.8 -> 12.2, 64 26.8 -> 16.9, 300 82.0 ->
-// 74.2; of 512 x 512: 1 67.6 -> 12.1, 8 117 -> 16.0; rows that begin anywhere in a 16-byte word: 100 of 333 x 211 105.8 -> 34.2, 2000 of 73 x 73 50.3 -> 43.7;
-// 4096 of 16 x 16 15.8 -> 7.7.  Sharing takes the host 12 us for a call instead of 7: below 131072 elements, or from 128 images on (200 of 224 x 224: 41.1 alone,
-// 45.3 shared), it does not pay.
+// reads about 0.1 TB/s, so fewer than 128 images of 131072 elements or more are shared by several workgroups each, which leave their sums in the
+// caller's workspace, where there is one, and a second small kernel adds them up.  us a call, before -> now, images of 224 x 224: 1 14.8 -> 12.2, 64
+// 26.8 -> 16.9, 300 82.0 -> 74.2; of 512 x 512: 1 67.6 -> 12.1, 8 117 -> 16.0; rows that begin anywhere in a 16-byte word: 100 of 333 x 211 105.8 ->
+// 34.2, 2000 of 73 x 73 50.3 -> 43.7; 4096 of 16 x 16 15.8 -> 7.7.  Sharing takes the host 12 us for a call instead of 7: below 131072 elements, or
+// from 128 images on (200 of 224 x 224: 41.1 alone, 45.3 shared), it does not pay.  Inside that it always does for images that no cache holds; the
+// same images again, one call after the other, are up to 3 us slower for it where they are small and few, or 80 and more.  One workgroup each
+// -> shared, new images, and the same again: 1 of 210 x 210 13.6 -> 12.5, 9.3 -> 12.5; of 224 x 224 15.2 -> 12.5, 10.3 -> 12.4; 16 25.8 -> 12.8, 10.6 -> 12.6; 1 of 256 x 256 19.2 ->
+// 12.6, 12.6 -> 12.6; 64 37.3 -> 21.1, 21.6 -> 18.1; 100 37.3 -> 32.0, 23.5 -> 25.5; 110 38.1 -> 36.2, 25.2 -> 28.5; 127 of 512 x 512 152 -> 144, 152
+// -> 143.
 namespace {
 constexpr int kPsnrThreads = 1024;
 constexpr int64_t kPsnrSmall = 4096, kPsnrShared = 131072, kPsnrShare = 16384;      // elements of an image for 256 threads; to share; of a share, at least

@@ -16,8 +16,8 @@
 // per SIMD; a sum over the instructions of a piece in order, with those latencies, gives its measured time to 3 %).  A hidden
 // layer of 48 units takes 48 matrix and 169 vector slots per 16 pixels backward, 15 and 52 forward.  So a lone wavefront loses what it waits
 // in order: for operand words from LDS and for matrix results (see kDownFirst).  At 10 layers x 40, with a half-filled last tile, the
-// matrix unit is busy 51 % of the time and vector issue 60 % (the matrix instructions' included), 29 % of the matrix time has
-// vector instructions beside it, and a wavefront waits 11 % of its time for loads and barriers and 20 % to issue.
+// matrix unit is busy 50 % of the time and vector issue 59 % (the matrix instructions' included), 31 % of the matrix time has
+// vector instructions beside it, and a wavefront waits 12 % of its time for loads and barriers and 19 % to issue.
 // Measured, ms a step, gradient tiles shared -> a wavefront's own -> layers interleaved (see the kernel) -> half-filled tiles, inputs in LDS
 // (Shape) -> words loaded ahead (kDownFirst): 256 images of 224 x 224, 10 layers x 40: 8.91 -> 6.83 -> 6.29 -> 5.00 -> 4.69; 10 x 32: 4.54 -> 3.50 ->
 // 3.00, no more from the half-filled tiles, -> 2.88; 2048 of 32 x 32, 3 x 15: 0.0934 -> 0.0738 -> 0.0675 -> 0.0655.
@@ -79,8 +79,8 @@ constexpr int fit16_registers(int wp, int ml, int nt) {
 //   four instead of three, 48 x 48, width 16, 2048 images: 4 layers 198 -> 189, 5 layers 249 -> 241; 6144 images: 561 -> 555, 692 -> 691
 //   two instead of three: 8 layers x 16: 243 -> 232; 3 x 32: 150 -> 144
 //   three (spilling) instead of two at 7 layers x 16, 48 x 48: 6144 images 1063 -> 1001; against it 1024 of 64 x 64: 319 -> 328
-// Four (spilling) is as chosen too at 4 layers x 16 where a launch takes several steps: 1024 images of 64 x 64, width 8, three 110, four 94.1.  Where images are shared, three:
-// 20 of 128 x 128, 4 x 15 24.2, four 26.3.
+// Four (spilling) is as chosen too at 4 layers x 16 where a launch takes several steps: 1024 images of 64 x 64, width 8, three 110, four 94.1.  Where
+// images are shared, three: 20 of 128 x 128, 4 x 15 24.2, four 26.3.
 // many: of the kernel that takes several steps a launch, where there is one
 constexpr int fit16_waves_per_simd(int wp, int ml, int nt, bool many = true) {
     const int r = fit16_registers(wp, ml, nt);
@@ -88,10 +88,11 @@ constexpr int fit16_waves_per_simd(int wp, int ml, int nt, bool many = true) {
 }
 
 // Whether a launch takes several steps of an image that one workgroup has.  A launch of its own costs a step its gap, the last round's idle part and
-// instructions that are fetched again; a kernel that loops takes more registers, which small ones have.  Images that are shared, or so large that a launch takes one step,
-// have the kernel without the loop (with it -> without: 8 images of 128 x 128, 3 x 24 18.1 -> 17.4; 20, 4 x 15 26.3 -> 24.2; 256 of 362 x 362, 2 x 15 556 -> 545).  us a step, a launch each -> 32
-// steps a launch, 2048 images of 32 x 32: 2 layers x 15 43.0 -> 39.6, 3 x 15 64.8 -> 60.5, 5 x 15 107.7 -> 104.6, 8 x 15 187.9 -> 181.3, 8 x 8 129.1 -> 122.5, 2 x 32 71.2 -> 69.1,
-// 3 x 32 132.3 -> 127.8; 1024 of 64 x 64: 4 x 15 158.1 -> 146.7, 5 x 15 194.3 -> 195.7, 3 x 32 214.2 -> 209.5.  Beyond: 512 of 96 x 96, 4 x 32 322 -> 331, 5 x 24 338 -> 352.
+// instructions that are fetched again; a kernel that loops takes more registers, which small ones have.  Images that are shared, or so large that a
+// launch takes one step, have the kernel without the loop (with it -> without: 8 images of 128 x 128, 3 x 24 18.1 -> 17.4; 20, 4 x 15 26.3 -> 24.2;
+// 256 of 362 x 362, 2 x 15 556 -> 545).  us a step, a launch each -> 32 steps a launch, 2048 images of 32 x 32: 2 layers x 15 43.0 -> 39.6, 3 x 15
+// 64.8 -> 60.5, 5 x 15 107.7 -> 104.6, 8 x 15 187.9 -> 181.3, 8 x 8 129.1 -> 122.5, 2 x 32 71.2 -> 69.1, 3 x 32 132.3 -> 127.8; 1024 of 64 x 64: 4 x
+// 15 158.1 -> 146.7, 5 x 15 194.3 -> 195.7, 3 x 32 214.2 -> 209.5.  Beyond: 512 of 96 x 96, 4 x 32 322 -> 331, 5 x 24 338 -> 352.
 constexpr bool fit16_many_steps(int wp, int ml, int nt) { return fit16_registers(wp, ml, nt) <= 168; }
 
 // Shapes and the LDS layout (bytes) for hidden widths <= WP (a multiple of 16).
@@ -399,7 +400,7 @@ template <int WP, bool HALF, int L, int NT, bool kBelow, class Args> __device__ 
     // pixels of a wavefront as the compiler orders them, before -> two tiles ahead, kDownFirst: 10 layers x 32 16500 -> 15600, 19900; 10 x 40 14540 ->
     // 14140 with spills, 13090; 8 x 40 11610 -> 10460, 11020; 8 x 48 13530 -> 12020, 12990; 6 x 56 13500 -> 13390, 12680; 6 x 64 13740 -> 13950, 13340.  us a step,
     // 256 images of 96 x 96, before -> now: 5 x 40 389 -> 372, 8 x 40 793 -> 722, 6 x 48 564 -> 554, 8 x 48 908 -> 822, 10 x 48 1221 -> 1128, 4 x 56 458 -> 430, 6 x 56 892 ->
-    // 848, 4 x 64 510 -> 469, 6 x 64 932 -> 898, 10 x 24 488 -> 474, 12 x 32 726 -> 687; against it 12 x 24 589 -> 593.  The form with the multiply (kBelow): 10 x 24 570 ->
+    // 848, 4 x 64 510 -> 469, 6 x 64 932 -> 898, 10 x 24 488 -> 474, 12 x 32 726 -> 687; against it 12 x 24 589 -> 593 (since the end of a step is another, 583).  The form with the multiply (kBelow): 10 x 24 570 ->
     // 494, 10 x 48 1320 -> 1121, 6 x 64 1019 -> 921.
     // kTight: the one kernel (10 layers x 48) that spills (see FIT16_EDGE) where the first layer's words are ahead or the contraction is not first.
     constexpr bool kAlone = fit16_waves_per_simd(WP, L, NT) == 1, kTight = !HALF && kRegisters > 500;
